@@ -107,12 +107,8 @@ struct AttnWorkspace {
   size_t partials_off, lists_off, counts_off, total;
 };
 
-// Per-block token lists are built for a pruned sequence and for a complete grid that the list
-// kernel serves (bf16, head_dim 64, and either a block side other than 8 and 16 or a grid that the
-// block side does not divide).
-bool wants_lists(const ns_attn_desc &d) {
-  return d.coords != nullptr || (!mfma_attn_supported(d) && ragged_attn_supported(d));
-}
+// Per-block token lists are built for a pruned sequence.
+bool wants_lists(const ns_attn_desc &d) { return d.coords != nullptr; }
 
 AttnWorkspace attn_workspace_layout(const ns_attn_desc &d) {
   AttnWorkspace w;
@@ -203,8 +199,8 @@ static ns_status launch_patch_attention(const AttnArgs &a) {
     case PK_BLOCK16: return launch_attn_block16(a);
     case PK_PERSIST: return launch_attn_persist(a);
     case PK_MFMA: return launch_attn_mfma(a);
-    case PK_RAGGED: return launch_attn_ragged(a);
-    default: return launch_attn_generic(a);
+    case PK_RAGGED: return launch_attn_ragged(a, nullptr, nullptr);
+    default: return launch_attn_generic(a, nullptr, nullptr);
   }
 }
 
@@ -227,19 +223,13 @@ static ns_status prepare_attn(const ns_attn_desc *desc, const void *q, const voi
   partials = reinterpret_cast<float *>(ws + w.partials_off);
   a.d = d; a.q = q; a.k = k; a.v = v; a.out = out; a.stream = s;
   BlockGeom &g = a.geom;
-  g.grid_h = d.grid_h; g.grid_w = d.grid_w; g.block = d.block;
-  g.nbh = (d.grid_h + d.block - 1) / d.block;
-  g.nbw = (d.grid_w + d.block - 1) / d.block;
-  g.n_global = d.n_global; g.tokens = d.tokens; g.cap = d.block * d.block;
   g.lists = nullptr; g.counts = nullptr;
-  // (the workspace has room for lists whenever wants_lists(); a complete grid that the sweep serves
-  // does without them)
   a.kernel = choose_patch_kernel(d);
-  if (wants_lists(d) && (d.coords || a.kernel == PK_RAGGED)) {
+  if (wants_lists(d)) {
     int32_t *lists = reinterpret_cast<int32_t *>(ws + w.lists_off);
     int32_t *counts = reinterpret_cast<int32_t *>(ws + w.counts_off);
     if (!reuse_lists) {
-      st = d.coords ? launch_block_lists(d, lists, counts, s) : launch_grid_lists(d, lists, counts, s);
+      st = launch_block_lists(d, lists, counts, s);
       if (st != NS_OK) return st;
     }
     g.lists = lists; g.counts = counts;
@@ -304,11 +294,17 @@ ns_status ns::attn_forward_impl(const ns_attn_desc *desc, const void *q, const v
     if (scores) return launch_cls_combine_scores(d, partials, out, cls_lse, cls_logits, scores, a.stream, sweep_cls_chunks(d));
     return launch_cls_combine(d, partials, out, cls_lse, true, a.stream, sweep_cls_chunks(d));
   }
-  st = launch_patch_attention(a);
-  if (st != NS_OK) return st;
-  // the global query's row: chunk partials, then the merge that also writes out[:, :, 0, :]
-  st = launch_cls_row(d, q, k, v, cls_logits, partials, true, a.stream);
-  if (st != NS_OK) return st;
+  // the global rows: chunk partials (in the same launch where the kernel takes them along), then the
+  // merge that also writes out[:, :, 0..G-1, :]
+  if (a.kernel == PK_RAGGED || a.kernel == PK_GENERIC) {
+    st = a.kernel == PK_RAGGED ? launch_attn_ragged(a, cls_logits, partials) : launch_attn_generic(a, cls_logits, partials);
+    if (st != NS_OK) return st;
+  } else {
+    st = launch_patch_attention(a);
+    if (st != NS_OK) return st;
+    st = launch_cls_row(d, q, k, v, cls_logits, partials, true, a.stream);
+    if (st != NS_OK) return st;
+  }
   if (scores) return launch_cls_combine_scores(d, partials, out, cls_lse, cls_logits, scores, a.stream);
   return launch_cls_combine(d, partials, out, cls_lse, true, a.stream);
 }

@@ -5,85 +5,70 @@
 // global token's attention weights; here: softmax weight of CLS on each patch key, averaged
 // over heads.
 //
-// One query against T keys is a bandwidth problem, so the row is cut into chunks of 512
+// A few queries against T keys are a bandwidth problem, so the rows are cut into chunks of 512
 // keys: cls_row_kernel streams K (and V) once, writes the raw logits and one softmax
-// partial (max, sum, weighted V sum) per chunk; cls_combine_kernel merges the partials in
+// partial (max, sum, weighted V sum) per row and chunk; cls_combine_kernel merges the partials in
 // chunk order; cls_scores_kernel turns logits + log-sum-exp into head-averaged weights.
-#include "ns_common.h"
+#include "ns_window.h"
 
 namespace ns {
 
 namespace {
 
-template <typename T> struct Row8;   // 8 consecutive elements of a row as floats
-template <> struct Row8<float> {
-  template <bool STREAM = false>
-  __device__ static void load(const float *p, float (&x)[8]) {
-    f32x4 a = *reinterpret_cast<const f32x4 *>(p), b = *reinterpret_cast<const f32x4 *>(p + 4);
+// 8 consecutive elements of a row as floats
+__device__ __forceinline__ void load_row8(const float *p, float (&x)[8]) {
+  const f32x4 a = *reinterpret_cast<const f32x4 *>(p), b = *reinterpret_cast<const f32x4 *>(p + 4);
 #pragma unroll
-    for (int e = 0; e < 4; e++) { x[e] = a[e]; x[4 + e] = b[e]; }
-  }
-};
-template <> struct Row8<uint16_t> {
-  // STREAM: non-temporal load.  Measured: 10 % faster where K and V are both streamed (51 against
-  // 57 us on a 256 x 256 grid), 15 % slower where only K is read, so only the former uses it.
-  template <bool STREAM = false>
-  __device__ static void load(const uint16_t *p, float (&x)[8]) {
-    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-    const u32x4 *pv = reinterpret_cast<const u32x4 *>(p);
-    const u32x4 u = STREAM ? __builtin_nontemporal_load(pv) : *pv;
-    x[0] = bf16_lo(u[0]); x[1] = bf16_hi(u[0]); x[2] = bf16_lo(u[1]); x[3] = bf16_hi(u[1]);
-    x[4] = bf16_lo(u[2]); x[5] = bf16_hi(u[2]); x[6] = bf16_lo(u[3]); x[7] = bf16_hi(u[3]);
-  }
-};
+  for (int e = 0; e < 4; e++) { x[e] = a[e]; x[4 + e] = b[e]; }
+}
+__device__ __forceinline__ void load_row8(const uint16_t *p, float (&x)[8]) {
+  const uint4 u = *reinterpret_cast<const uint4 *>(p);
+  x[0] = bf16_lo(u.x); x[1] = bf16_hi(u.x); x[2] = bf16_lo(u.y); x[3] = bf16_hi(u.y);
+  x[4] = bf16_lo(u.z); x[5] = bf16_hi(u.z); x[6] = bf16_lo(u.w); x[7] = bf16_hi(u.w);
+}
 
-constexpr int kSteps = kClsChunk / (4 * 8);   // 4 waves x 8 keys per wave-step
-
-// grid (chunks, H*G, B), 256 threads.  Lane = (key slot, 8-channel slice): 8 lanes per key row.
-// With G global tokens the rows of one head are G consecutive "rows" hg = h*G + g; logits are
-// [B, H*G, T] and the partial records [B, H*G, chunks].
-template <typename T, bool WITH_V>
-__global__ __launch_bounds__(256) void cls_row_kernel(const T *q, const T *k, const T *v,
-                                                      int64_t sb, int64_t sh, int64_t st, int T_,
-                                                      int H, int G, float scale, float *logits,
-                                                      float *partials, int nchunks) {
-  const int chunk = blockIdx.x, hg = blockIdx.y, b = blockIdx.z;
-  const int h = hg / G, gq = hg - h * G;
+// One global token and K only (scoring without an attention output): grid (chunks, H, B), 256
+// threads, lane = (key slot, 8-channel slice), 8 lanes per key row, every load of a wave's 128 keys
+// in flight at once.  Bound: HBM.  For a single row the matrix instructions of the kernel below
+// are work for 15 or 31 padding columns: 2 x 16384 keys x 16 heads bf16 took 13.9 us here and
+// 16.4 us there, 4 x 9825 x 24 fp32 43 against 57 us.
+template <typename T>
+__global__ __launch_bounds__(256) void cls_scan_kernel(const T *q, const T *k, int64_t sb, int64_t sh, int64_t st,
+                                                       int T_, int H, float scale, float *logits, float *partials,
+                                                       int nchunks) {
+  constexpr int kSteps = kClsChunk / (4 * 8);   // 4 waves x 8 keys per wave-step
+  const int chunk = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int slot = lane >> 3, sub = lane & 7;
-  const T *qb = q + b * sb + h * sh + gq * st;   // global token gq
-  const T *kb = k + b * sb + h * sh;
-  const T *vb = WITH_V ? v + b * sb + h * sh : nullptr;
+  const T *kb = k + b * sb + h * sh + sub * 8;
   __shared__ float red[4];
-  __shared__ float osum[4][64];
 
   float q8[8];
-  Row8<T>::load(qb + sub * 8, q8);
+  load_row8(q + b * sb + h * sh + sub * 8, q8);
 #pragma unroll
   for (int e = 0; e < 8; e++) q8[e] *= scale;
-
   const int key0 = chunk * kClsChunk + wave * (kSteps * 8) + slot;
+  float *lrow = logits + ((size_t)b * H + h) * T_;
   float s[kSteps];
   float mx = -INFINITY;
 #pragma unroll
   for (int i = 0; i < kSteps; i++) {
     const int key = key0 + i * 8;
-    float acc = -INFINITY;
-    if (key < T_) {
-      float k8[8];
-      Row8<T>::template load<WITH_V>(kb + (int64_t)key * st + sub * 8, k8);
-      acc = 0.f;
+    float k8[8];
+    load_row8(kb + (int64_t)min(key, T_ - 1) * st, k8);    // (clamped, not skipped: a branch would wait for each load)
+    float acc = 0.f;
 #pragma unroll
-      for (int e = 0; e < 8; e++) acc = __builtin_fmaf(q8[e], k8[e], acc);
-    }
+    for (int e = 0; e < 8; e++) acc = __builtin_fmaf(q8[e], k8[e], acc);
     // sum the 8 channel slices of the row (all lanes of the slot end up with the logit)
     acc += __shfl_xor(acc, 1);
     acc += __shfl_xor(acc, 2);
     acc += __shfl_xor(acc, 4);
-    s[i] = acc;
-    mx = fmaxf(mx, acc);
-    if (sub == 0 && key < T_ && logits) logits[((size_t)b * H * G + hg) * T_ + key] = acc;
+    s[i] = key < T_ ? acc : -INFINITY;
+    mx = fmaxf(mx, s[i]);
   }
+#pragma unroll
+  for (int i = 0; i < kSteps; i++)
+    if (sub == 0 && key0 + i * 8 < T_) lrow[key0 + i * 8] = s[i];
   mx = fmaxf(mx, __shfl_xor(mx, 8));
   mx = fmaxf(mx, __shfl_xor(mx, 16));
   mx = fmaxf(mx, __shfl_xor(mx, 32));
@@ -91,44 +76,27 @@ __global__ __launch_bounds__(256) void cls_row_kernel(const T *q, const T *k, co
   __syncthreads();
   const float M = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));   // finite: chunk non-empty
   __syncthreads();
-
   float l = 0.f;
-  float o8[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-  for (int i = 0; i < kSteps; i++) {
-    const int key = key0 + i * 8;
-    if (key < T_) {
-      const float pr = __builtin_amdgcn_exp2f((s[i] - M) * kLog2e);
-      l += pr;
-      if (WITH_V) {
-        float v8[8];
-        Row8<T>::template load<WITH_V>(vb + (int64_t)key * st + sub * 8, v8);
+  for (int i = 0; i < kSteps; i++) l += __builtin_amdgcn_exp2f((s[i] - M) * kLog2e);
 #pragma unroll
-        for (int e = 0; e < 8; e++) o8[e] = __builtin_fmaf(pr, v8[e], o8[e]);
-      }
-    }
-  }
-  // across the 8 key slots of the wave (not across channel slices)
-#pragma unroll
-  for (int sft = 8; sft < 64; sft <<= 1) {
-    l += __shfl_xor(l, sft);
-    if (WITH_V) {
-#pragma unroll
-      for (int e = 0; e < 8; e++) o8[e] += __shfl_xor(o8[e], sft);
-    }
-  }
+  for (int sft = 8; sft < 64; sft <<= 1) l += __shfl_xor(l, sft);
   if (lane == 0) red[wave] = l;
-  if (WITH_V && slot == 0) {
-#pragma unroll
-    for (int e = 0; e < 8; e++) osum[wave][sub * 8 + e] = o8[e];
-  }
   __syncthreads();
-  float *rec = partials + (((size_t)b * H * G + hg) * nchunks + chunk) * kClsPartialFloats;
   if (tid == 0) {
+    float *rec = partials + (((size_t)b * H + h) * nchunks + chunk) * kClsPartialFloats;
     rec[0] = M;
     rec[1] = (red[0] + red[1]) + (red[2] + red[3]);
   }
-  if (WITH_V && tid < 64) rec[2 + tid] = (osum[0][tid] + osum[1][tid]) + (osum[2][tid] + osum[3][tid]);
+}
+
+// grid (chunks * groups of global rows * H * B): one workgroup per chunk of 512 keys and group of
+// global rows of a head (ns_window.h).  Bound: HBM, K (and V) are read once.
+template <class S, bool WITH_V, bool LOGITS>
+__global__ __launch_bounds__(256, 2) void cls_row_kernel(GlobalRows p, int heads, int G, int T_, int groups, int nchunks) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  global_rows_chunk<S, WITH_V, LOGITS>(p, heads, G, T_, groups, nchunks, blockIdx.x, smem,
+                                       __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), threadIdx.x & 63);
 }
 
 __device__ __forceinline__ void store_out(float *p, float x) { *p = x; }
@@ -260,19 +228,41 @@ __global__ __launch_bounds__(kCombineThreads) void cls_combine_scores_kernel(con
 
 }  // namespace
 
+template <class S, bool WITH_V, bool LOGITS>
+static ns_status launch_rows(const ns_attn_desc &d, const GlobalRows &p, hipStream_t s) {
+  const int nch = cls_num_chunks(d.tokens), groups = (d.n_global + global_group_rows<S>() - 1) / global_group_rows<S>();
+  const long long wgs = (long long)nch * groups * d.heads * d.batch;
+  if (wgs > 0x7fffffffLL) return fail(NS_ERR_UNSUPPORTED, "launch grid too large");
+  const auto kern = cls_row_kernel<S, WITH_V, LOGITS>;
+  const ns_status rs = reserve_lds_once(reinterpret_cast<const void *>(kern), kWindowLds);
+  if (rs != NS_OK) return rs;
+  hipLaunchKernelGGL(kern, dim3((unsigned)wgs), dim3(256), kWindowLds, s, p, d.heads, d.n_global, d.tokens, groups, nch);
+  return check_launch("cls_row_kernel");
+}
+
 ns_status launch_cls_row(const ns_attn_desc &d, const void *q, const void *k, const void *v,
                          float *logits, float *partials, bool with_v, hipStream_t s) {
-  const int nch = cls_num_chunks(d.tokens);
-  dim3 grid(nch, d.heads * d.n_global, d.batch), blk(256);
-#define NS_ROW(T, WV)                                                                          \
-  hipLaunchKernelGGL((cls_row_kernel<T, WV>), grid, blk, 0, s, static_cast<const T *>(q),      \
-                     static_cast<const T *>(k), static_cast<const T *>(v), d.q_stride_b,       \
-                     d.q_stride_h, d.q_stride_t, d.tokens, d.heads, d.n_global, d.scale, logits, \
-                     partials, nch)
-  if (d.dtype == NS_F32) { if (with_v) NS_ROW(float, true); else NS_ROW(float, false); }
-  else { if (with_v) NS_ROW(uint16_t, true); else NS_ROW(uint16_t, false); }
-#undef NS_ROW
-  return check_launch("cls_row_kernel");
+  const GlobalRows p{q, k, v, d.q_stride_b, d.q_stride_h, d.q_stride_t, d.scale, logits, partials};
+  if (d.n_global == 1 && !with_v && logits && d.heads <= 65535 && d.batch <= 65535) {
+    const int nch = cls_num_chunks(d.tokens);
+    dim3 grid(nch, d.heads, d.batch), blk(256);
+    if (d.dtype == NS_F32)
+      hipLaunchKernelGGL(cls_scan_kernel<float>, grid, blk, 0, s, static_cast<const float *>(q), static_cast<const float *>(k),
+                         d.q_stride_b, d.q_stride_h, d.q_stride_t, d.tokens, d.heads, d.scale, logits, partials, nch);
+    else
+      hipLaunchKernelGGL(cls_scan_kernel<uint16_t>, grid, blk, 0, s, static_cast<const uint16_t *>(q),
+                         static_cast<const uint16_t *>(k), d.q_stride_b, d.q_stride_h, d.q_stride_t, d.tokens, d.heads,
+                         d.scale, logits, partials, nch);
+    return check_launch("cls_scan_kernel");
+  }
+#define NS_ROWS(S)                                                                                      \
+  (with_v ? (logits ? launch_rows<S, true, true>(d, p, s) : launch_rows<S, true, false>(d, p, s))       \
+          : (logits ? launch_rows<S, false, true>(d, p, s) : launch_rows<S, false, false>(d, p, s)))
+  if (d.dtype == NS_F32) return NS_ROWS(StepF32<float>);
+  // (the bf16 step wants a positive scale and 32-bit row offsets)
+  if (d.scale > 0.f && (long long)d.tokens * d.q_stride_t * 2 < 0x7fffffffLL) return NS_ROWS(StepBf16);
+  return NS_ROWS(StepF32<uint16_t>);
+#undef NS_ROWS
 }
 
 ns_status launch_cls_combine(const ns_attn_desc &d, const float *partials, void *out, float *lse,

@@ -96,31 +96,11 @@ __device__ __forceinline__ void gelu_erf8(float (&o)[8]) {
 }
 constexpr float kLn2 = 0.6931471805599453f;
 
-// ---- geometry of the block neighbourhood ----------------------------------
-// Everything a kernel needs to turn (block, slot) into a token index.  With lists == nullptr
-// the sequence is the full raster grid and the mapping is analytic; otherwise (pruned
-// sequence) lists[b][blk][slot] holds the token index and counts[b][blk] the fill.
+// ---- block lists of a pruned sequence: lists[b][blk][slot] is the token, counts[b][blk] the fill
 struct BlockGeom {
-  int grid_h, grid_w, block, nbh, nbw, n_global, tokens;
-  int cap;                 // block*block: slots per block in `lists`
-  const int32_t *lists;    // [B, nbh*nbw, cap] or nullptr
-  const int32_t *counts;   // [B, nbh*nbw]      or nullptr
+  const int32_t *lists;    // [B, nbh*nbw, block*block] or nullptr
+  const int32_t *counts;   // [B, nbh*nbw]              or nullptr
 };
-
-__device__ __forceinline__ int block_count(const BlockGeom &g, int b, int R, int C) {
-  if (g.counts) return g.counts[(size_t)b * g.nbh * g.nbw + R * g.nbw + C];
-  int bh = min(g.block, g.grid_h - R * g.block);
-  int bw = min(g.block, g.grid_w - C * g.block);
-  return bh * bw;
-}
-
-__device__ __forceinline__ int block_token(const BlockGeom &g, int b, int R, int C, int slot) {
-  if (g.lists) return g.lists[((size_t)b * g.nbh * g.nbw + R * g.nbw + C) * g.cap + slot];
-  int bw = min(g.block, g.grid_w - C * g.block);
-  int r = R * g.block + slot / bw;
-  int c = C * g.block + slot % bw;
-  return g.n_global + r * g.grid_w + c;
-}
 
 inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
@@ -199,8 +179,9 @@ ns_status cls_scores_impl(const ns_attn_desc *desc, const void *q, const void *k
                           void *workspace, size_t workspace_bytes, void *stream);
 
 ns_status launch_block_lists(const ns_attn_desc &d, int32_t *lists, int32_t *counts, hipStream_t s);
-ns_status launch_grid_lists(const ns_attn_desc &d, int32_t *lists, int32_t *counts, hipStream_t s);
-ns_status launch_attn_generic(const AttnArgs &a);
+// partials != NULL: the launch also computes the global rows' chunk records [B, H*G, cls_num_chunks, 66] and,
+// with logits, their raw logits [B,H,G,T]
+ns_status launch_attn_generic(const AttnArgs &a, float *logits, float *partials);
 bool mfma_attn_supported(const ns_attn_desc &d);
 ns_status launch_attn_mfma(const AttnArgs &a);
 bool persist_attn_supported(const ns_attn_desc &d);
@@ -212,8 +193,8 @@ ns_status launch_attn_sweep(const AttnArgs &a, float *cls_logits, float *cls_par
 inline int sweep_cls_chunks(const ns_attn_desc &d) { return 4 * ((d.grid_h + 7) / 8); }
 bool block16_attn_supported(const ns_attn_desc &d);  // 16x16 blocks: key tiles shared by a block's four query tiles
 ns_status launch_attn_block16(const AttnArgs &a);
-bool ragged_attn_supported(const ns_attn_desc &d);   // bf16, head_dim 64: anything given per-block token lists
-ns_status launch_attn_ragged(const AttnArgs &a);
+bool ragged_attn_supported(const ns_attn_desc &d);   // bf16, head_dim 64: any complete grid or pruned sequence
+ns_status launch_attn_ragged(const AttnArgs &a, float *logits, float *partials);
 
 // global-query (CLS) row: per-chunk partials, then a combine.
 constexpr int kClsChunk = 512;                      // keys per workgroup of the row kernel

@@ -1,0 +1,750 @@
+// Query tiles and key lists of the kernels that split one query tile's keys over the waves of a
+// workgroup (ns_attn_ragged.hip, ns_attn_generic.hip).
+//
+// A workgroup owns one tile of up to QT queries.  Complete grid: the grid is cut into squares of
+// `side` patches - a block, or for blocks of side <= 4 the largest square of whole blocks that
+// fits 8x8 - and a tile is a run of QT tokens of a square in raster order; its keys are the global
+// tokens followed by the patches of the rectangle that the 3x3 blocks around the square's blocks
+// cover, in raster order, so short edge blocks leave no holes.  Pruned sequence: a tile is a run
+// of a block's token list, its keys the global tokens and the lists of the up to nine neighbouring
+// blocks one after the other.  Either way keys are numbered 0 .. nkeys-1 without gaps and every
+// lane turns the number of its key into a token.
+#pragma once
+#include "ns_common.h"
+
+namespace ns {
+
+struct WindowGeom {
+  int grid_h, grid_w, block, n_global, tokens, heads;
+  int side;                // squares' side: a multiple of block
+  int nbh, nbw;            // squares per grid side
+  int tpb;                 // tiles per square (pruned: per block list capacity)
+  int cap;                 // slots per block in `lists`
+  int tiles_per_image;     // nbh * nbw * tpb
+  int tiles;               // batch * heads * tiles_per_image
+  int per_xcd;             // ceil(tiles / 8)
+  int global_wgs;          // leading workgroups that own chunks of the global rows: a multiple of 8
+  int global_live;         // ... of which this many have work
+  int global_groups;       // groups of global rows per head
+  int nchunks;             // key chunks per head-image
+  const int32_t *lists, *counts;
+};
+
+// a / d for 0 <= a < 2^21 with inv = 1.f / d: the quotient's fraction is at least 0.5 / d away from an
+// integer after adding 0.5, more than the two roundings can move it
+__device__ __forceinline__ int div_small(int a, float inv) { return (int)(((float)a + 0.5f) * inv); }
+
+// Tile of a workgroup: everything is wave-uniform except what the token functions return.
+template <bool LISTS, int QT>
+struct WindowTile {
+  int b, h, R, C;
+  int q0, qcnt;            // first slot of the tile in its square / list, queries in it
+  int nkeys;
+  int bw, kr0, kc0, kw;    // complete grid: columns of the square; key rectangle
+  float inv_bw, inv_kw;
+  int pre[10];             // pruned: first key number of each neighbour block (pre[9]: end)
+  const int32_t *lst;      // pruned: this image's lists
+
+  // false: no such tile
+  __device__ __forceinline__ bool init(const WindowGeom &g, int id, int lane) {
+    const int img = id / g.tiles_per_image, t = id - img * g.tiles_per_image;
+    b = img / g.heads;
+    h = img - b * g.heads;
+    const int sq = t / g.tpb;
+    q0 = (t - sq * g.tpb) * QT;
+    R = sq / g.nbw;
+    C = sq - R * g.nbw;
+    if (LISTS) {
+      const int nblocks = g.nbh * g.nbw;
+      const int32_t *cnts = g.counts + (size_t)b * nblocks;
+      lst = g.lists + (size_t)b * nblocks * g.cap;
+      int fill = 0;
+      if (lane < 9) {
+        const int R2 = R + lane / 3 - 1, C2 = C + lane % 3 - 1;
+        if (R2 >= 0 && R2 < g.nbh && C2 >= 0 && C2 < g.nbw) fill = cnts[R2 * g.nbw + C2];
+      }
+      int n = g.n_global;
+#pragma unroll
+      for (int i = 0; i < 9; i++) {
+        pre[i] = n;
+        n += __builtin_amdgcn_readlane(fill, i);
+      }
+      pre[9] = nkeys = n;
+      qcnt = min(pre[5] - pre[4] - q0, QT);
+    } else {
+      const int bh = min(g.side, g.grid_h - R * g.side);
+      bw = min(g.side, g.grid_w - C * g.side);
+      qcnt = min(bh * bw - q0, QT);
+      kr0 = max(R * g.side - g.block, 0);
+      kc0 = max(C * g.side - g.block, 0);
+      kw = min((C + 1) * g.side + g.block, g.grid_w) - kc0;
+      nkeys = g.n_global + (min((R + 1) * g.side + g.block, g.grid_h) - kr0) * kw;
+      inv_bw = 1.f / (float)bw;
+      inv_kw = 1.f / (float)kw;
+    }
+    return qcnt > 0;
+  }
+  // token of query slot i (slots past the end repeat the last one)
+  __device__ __forceinline__ int query(const WindowGeom &g, int i) const {
+    const int s = q0 + min(i, qcnt - 1);
+    if (LISTS) return lst[(size_t)(R * g.nbw + C) * g.cap + s];
+    const int r = div_small(s, inv_bw);
+    return g.n_global + (R * g.side + r) * g.grid_w + C * g.side + s - r * bw;
+  }
+  // Complete grid: token of key j (numbers past the end repeat the last one).
+  __device__ __forceinline__ int key(const WindowGeom &g, int j) const {
+    j = min(j, nkeys - 1);
+    const int jj = max(j - g.n_global, 0), r = div_small(jj, inv_kw);
+    const int tok = g.n_global + (kr0 + r) * g.grid_w + kc0 + jj - r * kw;
+    return j < g.n_global ? j : tok;
+  }
+  // Pruned: where the token of key j stands (a global token has no entry: its number is its token,
+  // and the address given for it is some valid entry).
+  __device__ __forceinline__ const int32_t *key_entry(const WindowGeom &g, int j) const {
+    j = min(j, nkeys - 1);
+    int i = 4, start = pre[4];
+    if (j >= g.n_global) {
+      i = 0; start = pre[0];
+#pragma unroll
+      for (int n = 1; n < 9; n++) {
+        i = j >= pre[n] ? n : i;
+        start = j >= pre[n] ? pre[n] : start;
+      }
+    }
+    const int dr = (i * 11) >> 5;          // i / 3 for i < 9
+    const int blk = (R + dr - 1) * g.nbw + C + i - 3 * dr - 1;
+    return lst + (size_t)blk * g.cap + max(j - start, 0);
+  }
+  // Squares of several blocks: a key may be seen by a query if every bit of the key's code is set
+  // in the query's.  Bits 0.. are block rows, bits 16.. block columns, both counted from one block
+  // before the square; a global token has no bits, a key past the end one that no query has.
+  __device__ __forceinline__ uint32_t key_code(const WindowGeom &g, int j, float inv_block) const {
+    const int jj = max(j - g.n_global, 0), r = div_small(jj, inv_kw), c = jj - r * kw;
+    // (counted from row R*side - block and column C*side - block, at or before the rectangle's first)
+    const int rb = div_small(kr0 + r - (R * g.side - g.block), inv_block);
+    const int cb = div_small(kc0 + c - (C * g.side - g.block), inv_block);
+    const uint32_t code = (1u << rb) | (0x10000u << cb);
+    return j >= nkeys ? 0x8000u : (j < g.n_global ? 0u : code);
+  }
+  __device__ __forceinline__ uint32_t query_code(const WindowGeom &g, int i, float inv_block) const {
+    const int s = q0 + min(i, qcnt - 1), r = div_small(s, inv_bw), c = s - r * bw;
+    return (7u << div_small(r, inv_block)) | (0x70000u << div_small(c, inv_block));
+  }
+};
+
+// Position of workgroup `bid` (of those behind the leading global ones, whose number is a multiple
+// of 8): workgroups are dealt round-robin to the 8 XCDs, and each XCD gets a contiguous range of
+// tiles, so that the K and V rows which neighbouring tiles share are fetched into one L2.
+__device__ __forceinline__ int window_tile_id(const WindowGeom &g, int bid) {
+  return (bid & 7) * g.per_xcd + (bid >> 3);
+}
+
+// ------------------------------------------------------------------------------------------
+// A step: 32 keys against 32*NT queries by one wave.  S^T = K Q^T and O^T += V^T P^T, so that a
+// query's statistics live in one lane pair (l32, l32 + 32) and the logits' accumulator layout -
+// register e of lane (query l32, half hh) is key 8*(e/4) + 4*hh + e%4 - is the operand layout of
+// the second product: the weights never leave the registers.  K and V rows come global -> LDS by
+// direct 16-byte transfers, whole rows per request, into rings of kDepth slots each that belong
+// to the wave alone (no barriers); the transfer into a slot is requested as soon as the wave has
+// read it.
+// ------------------------------------------------------------------------------------------
+
+// bf16: v_mfma_f32_32x32x16_bf16, weights rounded to bf16 for the second product.
+struct StepBf16 {
+  typedef uint16_t elem;
+  static constexpr int kDepth = 2, kReq = 4, kHalf = 4096;     // slots, requests per 32 rows, bytes of 32 rows
+  struct Q { bf16x8 f[4]; };
+  typedef s16x4 __attribute__((address_space(3))) *tr_ptr;
+  typedef bf16x8 __attribute__((address_space(3))) *frag_ptr;
+  uint32_t kch[2], vch;       // source chunk of this lane's 16 bytes
+  uint32_t krd[4], vrd[2][2];
+  int rrow;                   // row of request 0 this lane moves; request it: + 8 it
+
+  __device__ __forceinline__ void init(int lane) {
+    const int l32 = lane & 31, hh = lane >> 5;
+    rrow = lane >> 3;
+    // LDS chunk c of row r holds chunk c ^ ((r>>1)&7) of K and c ^ 4*((r>>1)&1) of V: conflict-free reads
+    kch[0] = 16u * ((lane & 7) ^ (lane >> 4));
+    kch[1] = 16u * ((lane & 7) ^ (4 + (lane >> 4)));
+    vch = 16u * ((lane & 7) ^ (((lane >> 4) & 1) << 2));
+#pragma unroll
+    for (int s = 0; s < 4; s++) krd[s] = l32 * 128 + 16 * ((4 * hh + s) ^ ((l32 >> 1) & 7));
+    const int g = lane >> 4, s = lane & 15;
+    const int dbyte = (16 * (g & 1) + 4 * (s & 3)) * 2;
+#pragma unroll
+    for (int half = 0; half < 2; half++) {
+      const int key = 8 * half + 4 * hh + (s >> 2);
+      const int off = key * 128 + (dbyte ^ (((key >> 1) & 1) << 6));
+      vrd[0][half] = off;
+      vrd[1][half] = off ^ 64;
+    }
+  }
+  // (rows are addressed with 32-bit byte offsets from the head's first row: checked by the launcher)
+  __device__ __forceinline__ void load_q(Q &q, const char *base, int64_t rowB, int tok, int lane, float) const {
+    const char *row = base + (uint32_t)tok * (uint32_t)rowB + 64 * (lane >> 5);
+#pragma unroll
+    for (int s = 0; s < 4; s++) q.f[s] = *reinterpret_cast<const bf16x8 *>(row + 16 * s);
+  }
+  __device__ __forceinline__ void issue_k(const char *base, int64_t rowB, const int (&tok)[kReq], unsigned char *, uint32_t lds, int) const {
+#pragma unroll
+    for (int it = 0; it < kReq; it++) dma16(base, (uint32_t)tok[it] * (uint32_t)rowB + kch[it & 1], lds + it * 1024);
+  }
+  __device__ __forceinline__ void issue_v(const char *base, int64_t rowB, const int (&tok)[kReq], unsigned char *, uint32_t lds, int) const {
+#pragma unroll
+    for (int it = 0; it < kReq; it++) dma16(base, (uint32_t)tok[it] * (uint32_t)rowB + vch, lds + it * 1024);
+  }
+  template <int NT>
+  __device__ __forceinline__ void logits(const Q (&q)[NT], const unsigned char *slot, f32x16 (&s)[NT]) const {
+    bf16x8 kf[4];
+#pragma unroll
+    for (int t = 0; t < 4; t++) kf[t] = *(frag_ptr)(slot + krd[t]);
+#pragma unroll
+    for (int nt = 0; nt < NT; nt++) {
+      s[nt] = f32x16{0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int t = 0; t < 4; t++) s[nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[t], q[nt].f[t], s[nt], 0, 0, 0);
+    }
+  }
+  // LO: lanes of columns 16..31 take what bf16 rounding leaves of a weight, w - bf16(w)
+  template <int NT, bool LO>
+  __device__ __forceinline__ void weigh(const f32x16 (&w)[NT], const unsigned char *slot, f32x16 (&o)[NT][2], int lane) const {
+    bf16x8 pf[NT][2];
+#pragma unroll
+    for (int nt = 0; nt < NT; nt++)
+#pragma unroll
+      for (int i = 0; i < 16; i += 2) {
+        uint32_t u = pack_bf16(w[nt][i], w[nt][i + 1]);
+        if (LO) {
+          const uint32_t lo = pack_bf16(w[nt][i] - bf16_lo(u), w[nt][i + 1] - bf16_hi(u));
+          u = (lane & 16) ? lo : u;
+        }
+        const bf16x2 pk = __builtin_bit_cast(bf16x2, u);
+        pf[nt][i >> 3][i & 7] = pk[0];
+        pf[nt][i >> 3][(i & 7) + 1] = pk[1];
+      }
+#pragma unroll
+    for (int sp = 0; sp < 2; sp++)
+#pragma unroll
+      for (int dt = 0; dt < 2; dt++) {
+        const s16x4 lo4 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((tr_ptr)(slot + vrd[dt][0] + sp * 2048));
+        const s16x4 hi4 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((tr_ptr)(slot + vrd[dt][1] + sp * 2048));
+        const bf16x4 a = __builtin_bit_cast(bf16x4, lo4), b2 = __builtin_bit_cast(bf16x4, hi4);
+        const bf16x8 vf = {a[0], a[1], a[2], a[3], b2[0], b2[1], b2[2], b2[3]};
+#pragma unroll
+        for (int nt = 0; nt < NT; nt++)
+          o[nt][dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, pf[nt][sp], o[nt][dt], 0, 0, 0);
+      }
+  }
+  static __device__ __forceinline__ void store4out(uint16_t *p, f32x4 v) {
+    *reinterpret_cast<u32x2 *>(p) = u32x2{pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3])};
+  }
+};
+
+// fp32 arithmetic: v_mfma_f32_32x32x2_f32 on rows of 64 floats (T = uint16_t: bf16 rows, converted
+// on the way into LDS).  An operand register holds one k index per half-wave: step s of the
+// logits pairs channels s and 32 + s, step e of the second product keys (e, hh = 0) and (e, hh = 1).
+template <typename T>
+struct StepF32 {
+  typedef T elem;
+  static constexpr int kDepth = 1, kReq = 8, kHalf = 8192;
+  struct Q { float f[32]; };
+  uint32_t kbase, kx, vrd[2];
+  int rrow;
+  __device__ __forceinline__ void init(int lane) {
+    const int l32 = lane & 31, hh = lane >> 5;
+    rrow = lane >> 4;
+    // LDS chunk c of row r holds chunk c ^ (r & 15) of K and c ^ 8*((r>>2)&1) of V
+    kbase = l32 * 256;
+    kx = 16 * ((8 * hh) ^ (l32 & 15));
+    vrd[0] = hh * 1024 + ((l32 * 4) ^ (hh * 128));
+    vrd[1] = hh * 1024 + ((l32 * 4 + 128) ^ (hh * 128));
+  }
+  __device__ static __forceinline__ f32x4 load4(const float *p) { return *reinterpret_cast<const f32x4 *>(p); }
+  __device__ static __forceinline__ f32x4 load4(const uint16_t *p) {
+    const u32x2 u = *reinterpret_cast<const u32x2 *>(p);
+    return f32x4{bf16_lo(u[0]), bf16_hi(u[0]), bf16_lo(u[1]), bf16_hi(u[1])};
+  }
+  __device__ __forceinline__ void load_q(Q &q, const char *base, int64_t rowB, int tok, int lane, float mul) const {
+    const T *row = reinterpret_cast<const T *>(base + (int64_t)tok * rowB) + 32 * (lane >> 5);
+#pragma unroll
+    for (int s = 0; s < 8; s++) {
+      const f32x4 v = load4(row + 4 * s);
+#pragma unroll
+      for (int e = 0; e < 4; e++) q.f[4 * s + e] = v[e] * mul;
+    }
+  }
+  // one request: 4 rows of 256 bytes; chunk = 16-byte chunk of the row (4 elements)
+  __device__ static __forceinline__ void request(const char *row, int chunk, unsigned char *dst, uint32_t lds, int lane) {
+    if (sizeof(T) == 4) {
+      const char *src = row + 16 * chunk;
+      asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off" :: "s"(lds), "v"(src) : "memory", "m0");
+    } else {
+      *reinterpret_cast<f32x4 *>(dst + 16 * lane) = load4(reinterpret_cast<const T *>(row) + 4 * chunk);
+    }
+  }
+  __device__ __forceinline__ void issue_k(const char *base, int64_t rowB, const int (&tok)[kReq], unsigned char *dst, uint32_t lds, int lane) const {
+#pragma unroll
+    for (int it = 0; it < kReq; it++)
+      request(base + (int64_t)tok[it] * rowB, (lane & 15) ^ ((4 * it + rrow) & 15), dst + it * 1024, lds + it * 1024, lane);
+  }
+  __device__ __forceinline__ void issue_v(const char *base, int64_t rowB, const int (&tok)[kReq], unsigned char *dst, uint32_t lds, int lane) const {
+#pragma unroll
+    for (int it = 0; it < kReq; it++)
+      request(base + (int64_t)tok[it] * rowB, (lane & 15) ^ (8 * (it & 1)), dst + it * 1024, lds + it * 1024, lane);
+  }
+  template <int NT>
+  __device__ __forceinline__ void logits(const Q (&q)[NT], const unsigned char *slot, f32x16 (&s)[NT]) const {
+#pragma unroll
+    for (int nt = 0; nt < NT; nt++) s[nt] = f32x16{0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int c = 0; c < 8; c++) {
+      const f32x4 k4 = *reinterpret_cast<const f32x4 *>(slot + kbase + (kx ^ (16 * c)));
+#pragma unroll
+      for (int e = 0; e < 4; e++)
+#pragma unroll
+        for (int nt = 0; nt < NT; nt++) s[nt] = __builtin_amdgcn_mfma_f32_32x32x2f32(k4[e], q[nt].f[4 * c + e], s[nt], 0, 0, 0);
+    }
+  }
+  template <int NT, bool LO>
+  __device__ __forceinline__ void weigh(const f32x16 (&w)[NT], const unsigned char *slot, f32x16 (&o)[NT][2], int) const {
+#pragma unroll
+    for (int e = 0; e < 16; e++)
+#pragma unroll
+      for (int dt = 0; dt < 2; dt++) {
+        const float v = *reinterpret_cast<const float *>(slot + vrd[dt] + (8 * (e >> 2) + (e & 3)) * 256);
+#pragma unroll
+        for (int nt = 0; nt < NT; nt++) o[nt][dt] = __builtin_amdgcn_mfma_f32_32x32x2f32(v, w[nt][e], o[nt][dt], 0, 0, 0);
+      }
+  }
+  static __device__ __forceinline__ void store4out(float *p, f32x4 v) { *reinterpret_cast<f32x4 *>(p) = v; }
+  static __device__ __forceinline__ void store4out(uint16_t *p, f32x4 v) {
+    *reinterpret_cast<u32x2 *>(p) = u32x2{pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3])};
+  }
+};
+
+// LDS of a wave: the K ring, the V ring, then 1 KB for tokens in flight (four steps' worth, 256 bytes
+// each) and 128 bytes of key codes.  After the walk the rings hold the wave's partial output.
+constexpr int kWaveRings = 16384, kWaveAux = 1024 + 128, kWaveLds = kWaveRings + kWaveAux;
+constexpr int kWindowMl = 4 * 2 * 64 * 4;                    // (max, sum) per wave and query
+constexpr int kWindowLds = 4 * kWaveLds + kWindowMl;         // two workgroups per CU
+constexpr float kNoMax = -1e30f;
+
+// State of 32*NT queries: running reference m (log2 units), sum l (this half-wave's keys), output.
+template <class S, int NT>
+struct WaveAcc {
+  typename S::Q q[NT];
+  f32x16 o[NT][2];
+  float m[NT], l[NT];
+  __device__ __forceinline__ void clear() {
+#pragma unroll
+    for (int nt = 0; nt < NT; nt++) {
+      m[nt] = kNoMax;
+      l[nt] = 0.f;
+#pragma unroll
+      for (int e = 0; e < 16; e++) { o[nt][0][e] = 0.f; o[nt][1][e] = 0.f; }
+    }
+  }
+  // logits -> weights.  The reference follows the running maximum in jumps: it is raised (and the
+  // sums rescaled) only when a logit exceeds it by more than 8 in log2 units, so weights stay
+  // below 2^8 and the rescale, a third of the vector work otherwise, is rare after the first step.
+  __device__ __forceinline__ void soften(f32x16 (&s)[NT], float c) {
+    float top[NT];
+    bool up = false;
+#pragma unroll
+    for (int nt = 0; nt < NT; nt++) {
+      float a = fmaxf(s[nt][0], s[nt][1]), b = fmaxf(s[nt][2], s[nt][3]);
+#pragma unroll
+      for (int e = 4; e < 16; e += 4) {
+        a = fmaxf(fmaxf(a, s[nt][e]), s[nt][e + 1]);
+        b = fmaxf(fmaxf(b, s[nt][e + 2]), s[nt][e + 3]);
+      }
+      top[nt] = half_swap_max(fmaxf(a, b)) * c;
+      up = up || top[nt] > m[nt] + 8.f;
+    }
+    if (__any(up)) {
+#pragma unroll
+      for (int nt = 0; nt < NT; nt++) {
+        const float m_new = fmaxf(m[nt], top[nt]);
+        const float alpha = __builtin_amdgcn_exp2f(m[nt] - m_new);
+        m[nt] = m_new;
+        l[nt] *= alpha;
+#pragma unroll
+        for (int e = 0; e < 16; e++) { o[nt][0][e] *= alpha; o[nt][1][e] *= alpha; }
+      }
+    }
+#pragma unroll
+    for (int nt = 0; nt < NT; nt++) {
+      float l0 = 0.f, l1 = 0.f;
+#pragma unroll
+      for (int e = 0; e < 16; e += 2) {
+        s[nt][e] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[nt][e], c, -m[nt]));
+        s[nt][e + 1] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[nt][e + 1], c, -m[nt]));
+        l0 += s[nt][e];
+        l1 += s[nt][e + 1];
+      }
+      l[nt] += l0 + l1;
+    }
+  }
+};
+
+// n steps of a wave.  key_token(i): token of key `lane & 31` of step i; with RING the tokens are
+// read from memory instead: key_entry(i) is where that token stands, fix_token(i, row, tok) the last
+// word on it.  fix(i, s) edits the logits of step i and issues exactly E stores.  Vector memory
+// requests complete in issue order, so the waits count how many younger ones may still be in flight.
+template <class S, int NT, bool WITH_V, bool RING, bool LO, int E, class KeyToken, class KeyEntry, class FixToken, class Fix>
+__device__ __forceinline__ void walk_keys(const S &st, WaveAcc<S, NT> &a, const char *kb, const char *vb, int64_t rowB,
+                                          unsigned char *wsm, int n, float c, int lane, KeyToken key_token,
+                                          KeyEntry key_entry, FixToken fix_token, Fix fix) {
+  // (without V the K ring takes the whole space: twice the slots)
+  constexpr int D = WITH_V ? S::kDepth : 2 * S::kDepth, R = S::kReq, TL = RING ? 1 : 0;
+  if (n <= 0) return;
+  const uint32_t lds = (uint32_t)(size_t)((__attribute__((address_space(3))) unsigned char *)wsm);
+  constexpr int kV = D * S::kHalf;            // V ring behind the K ring
+  int *const ring = reinterpret_cast<int *>(wsm + kWaveRings);
+  auto request_tokens = [&](int i) {
+    const int32_t *src = key_entry(i);
+    asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dword %1, off"
+                 :: "s"(lds + kWaveRings + (uint32_t)(i & 3) * 256u), "v"(src) : "memory", "m0");
+  };
+  constexpr int rpr = 32 / R;                 // rows per request
+  int tok[R];
+  auto tokens = [&](int i) {
+    if (RING) {
+#pragma unroll
+      for (int it = 0; it < R; it++) {
+        const int row = it * rpr + st.rrow;
+        tok[it] = fix_token(i, row, ring[(i & 3) * 64 + row]);
+      }
+    } else {
+      const int t = key_token(i);
+#pragma unroll
+      for (int it = 0; it < R; it++) tok[it] = __shfl(t, it * rpr + st.rrow);
+    }
+  };
+  auto issue_k = [&](int i) { const int o = (i % D) * S::kHalf; st.issue_k(kb, rowB, tok, wsm + o, lds + o, lane); };
+  auto issue_v = [&](int i) { const int o = kV + (i % D) * S::kHalf; if (WITH_V) st.issue_v(vb, rowB, tok, wsm + o, lds + o, lane); };
+
+  if (RING) {
+#pragma unroll
+    for (int i = 0; i <= D; i++) request_tokens(i);
+    wait_vm<1>();
+  }
+#pragma unroll
+  for (int i = 0; i < D; i++)
+    if (i < n) {
+      tokens(i);
+      issue_k(i);
+      if (RING && i == D - 1) request_tokens(D + 1);
+      issue_v(i);
+    }
+  constexpr int kNext = D == 2 ? 2 * R : 0;   // requests of the step behind (two slots)
+  for (int i = 0; i < n; i++) {
+    const int rem = n - 1 - i;                // steps behind this one
+    // K of step i.  Behind it with two slots: V of step i, the stores of the step before, K and V
+    // of the next step and, in the ring, one token request; with one slot: V of step i.  (Without V:
+    // K of up to D - 1 further steps and at least one step's stores.)
+    if (WITH_V) {
+      constexpr int kStored = D == 2 ? E : 0;
+      if (i == 0) {
+        if (rem >= D - 1) wait_vm<R + kNext>();
+        else wait_vm<R>();
+      } else if (rem >= D) wait_vm<R + kNext + kStored + (D - 1) * TL>();
+      else if (D == 2 && rem == 1) wait_vm<R + kNext + kStored>();
+      else wait_vm<R + kStored>();
+    } else {
+      const int behind = rem < D - 1 ? rem : D - 1;
+      if (i == 0) {
+        if (behind == 3) wait_vm<3 * R>();
+        else if (behind == 2) wait_vm<2 * R>();
+        else if (behind == 1) wait_vm<R>();
+        else wait_vm<0>();
+      } else {
+        if (behind == 3) wait_vm<3 * R + E>();
+        else if (behind == 2) wait_vm<2 * R + E>();
+        else if (behind == 1) wait_vm<R + E>();
+        else wait_vm<E>();
+      }
+    }
+    f32x16 s[NT];
+    st.template logits<NT>(a.q, wsm + (i % D) * S::kHalf, s);
+    fix(i, s);
+    if (rem >= D) {
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");     // the slot has been read
+      tokens(i + D);
+      issue_k(i + D);
+      if (RING) request_tokens(i + D + 2);
+    }
+    a.soften(s, c);
+    if (WITH_V) {
+      // V of step i.  Behind it: the next step (two slots), this step's stores, K of step i + D
+      if (rem >= D) wait_vm<kNext + E + R + (D - 1) * TL>();
+      else if (D == 2 && rem == 1) wait_vm<kNext + E>();
+      else wait_vm<E>();
+      st.template weigh<NT, LO>(s, wsm + kV + (i % D) * S::kHalf, a.o, lane);
+      if (rem >= D) {
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        issue_v(i + D);
+      }
+    }
+  }
+  wait_vm<0>();                               // (token requests past the end)
+}
+
+// A wave's state -> LDS: output rows of 64 floats in its rings (16-byte chunk c of row r at c ^ (r & 15)),
+// (max, sum) in ml.
+template <class S, int NT>
+__device__ __forceinline__ void park_state(const WaveAcc<S, NT> &a, unsigned char *wsm, float *ml, int lane) {
+  const int l32 = lane & 31, hh = lane >> 5;
+#pragma unroll
+  for (int nt = 0; nt < NT; nt++) {
+    const int row = 32 * nt + l32;
+#pragma unroll
+    for (int dt = 0; dt < 2; dt++)
+#pragma unroll
+      for (int ig = 0; ig < 4; ig++) {
+        const f32x4 v = {a.o[nt][dt][4 * ig], a.o[nt][dt][4 * ig + 1], a.o[nt][dt][4 * ig + 2], a.o[nt][dt][4 * ig + 3]};
+        *reinterpret_cast<f32x4 *>(wsm + row * 256 + 16 * ((8 * dt + 2 * ig + hh) ^ (row & 15))) = v;
+      }
+    const float l = half_swap_sum(a.l[nt]);
+    if (hh == 0) {
+      ml[2 * row] = a.m[nt];
+      ml[2 * row + 1] = l;
+    }
+  }
+}
+__device__ __forceinline__ f32x4 parked(const unsigned char *smem, int w, int row, int chunk) {
+  return *reinterpret_cast<const f32x4 *>(smem + w * kWaveLds + row * 256 + 16 * (chunk ^ (row & 15)));
+}
+
+// ------------------------------------------------------------------------------------------
+// The global rows: workgroup `id` takes a chunk of kClsChunk keys for a group of global tokens of one
+// head, 32 keys a step and wave, all rows of the group against the same K and V rows (which are
+// read once however many global tokens there are).  Leaves the raw logits and one softmax partial
+// (max, sum, weighted V sum) per row and chunk.  bf16: a group is 16 rows, in the operand's columns
+// twice, so that the second product gets every weight as bf16 head and bf16 rest: 16 bits of it.
+// ------------------------------------------------------------------------------------------
+struct GlobalRows {
+  const void *q, *k, *v;
+  int64_t sb, sh, st;      // strides in elements
+  float scale;
+  float *logits;           // [B, H, G, T] or NULL
+  float *partials;         // [B, H*G, nchunks, 66]
+};
+template <class S> constexpr int global_group_rows() { return S::kDepth == 2 ? 16 : 32; }
+
+template <class S, bool WITH_V, bool LOGITS>
+__device__ __forceinline__ void global_rows_chunk(const GlobalRows &p, int heads, int G, int T, int groups, int nchunks,
+                                                  int id, unsigned char *smem, int wave, int lane) {
+  typedef typename S::elem elem;
+  constexpr bool kBf16 = S::kDepth == 2;
+  constexpr int GR = global_group_rows<S>();
+  const int chunk = id % nchunks, hg = id / nchunks, grp = hg % groups, bh = hg / groups;
+  const int b = bh / heads, h = bh - b * heads;
+  const int l32 = lane & 31, hh = lane >> 5;
+  const char *qb = reinterpret_cast<const char *>(static_cast<const elem *>(p.q) + b * p.sb + h * p.sh);
+  const char *kb = reinterpret_cast<const char *>(static_cast<const elem *>(p.k) + b * p.sb + h * p.sh);
+  const char *vb = WITH_V ? reinterpret_cast<const char *>(static_cast<const elem *>(p.v) + b * p.sb + h * p.sh) : nullptr;
+  const int64_t rowB = p.st * (int64_t)sizeof(elem);
+  unsigned char *wsm = smem + wave * kWaveLds;
+  S st;
+  st.init(lane);
+  WaveAcc<S, 1> a;
+  a.clear();
+  const int col = l32 & (GR - 1), g = grp * GR + col;
+  st.load_q(a.q[0], qb, rowB, min(g, G - 1), lane, p.scale);
+  const float c = kBf16 ? p.scale * kLog2e : kLog2e, lmul = kBf16 ? p.scale : 1.f;
+  const int j0 = chunk * kClsChunk + 32 * wave;
+  const int left = min(T - chunk * kClsChunk, kClsChunk);           // keys of this chunk
+  const int steps = (left + 31) / 32, n = steps > wave ? (steps - wave + 3) / 4 : 0;
+  // (the second set of columns and the rows past G write nothing)
+  const bool writes = LOGITS && l32 < GR && g < G;
+  float *lrow = LOGITS ? p.logits + ((size_t)(b * heads + h) * G + min(g, G - 1)) * T : nullptr;
+  walk_keys<S, 1, WITH_V, false, kBf16, LOGITS ? 16 : 0>(
+      st, a, kb, vb, rowB, wsm, n, c, lane, [&](int i) { return min(j0 + 128 * i + l32, T - 1); },
+      [](int) { return (const int32_t *)nullptr; }, [](int, int, int t) { return t; },
+      [&](int i, f32x16 (&s)[1]) {
+        const int jb = j0 + 128 * i + 4 * hh;
+        // (keys past the end are copies of the last one: their lanes store its logit once more)
+        if (LOGITS && writes)
+#pragma unroll
+          for (int e = 0; e < 16; e++) store4(lrow + min(jb + 8 * (e >> 2) + (e & 3), T - 1), s[0][e] * lmul);
+        if (j0 + 128 * i + 32 > T)
+#pragma unroll
+          for (int e = 0; e < 16; e++) s[0][e] = jb + 8 * (e >> 2) + (e & 3) < T ? s[0][e] : -INFINITY;
+      });
+  float *ml = reinterpret_cast<float *>(smem + 4 * kWaveLds);
+  park_state(a, wsm, ml + wave * 128, lane);
+  __syncthreads();
+  // thread = (row, 16-byte chunk of the output)
+  for (int t = wave * 64 + lane; t < GR * 16; t += 256) {
+    const int row = t >> 4, ch = t & 15, gr = grp * GR + row;
+    if (gr >= G) continue;
+    float M = ml[2 * row], L = 0.f;
+#pragma unroll
+    for (int w = 1; w < 4; w++) M = fmaxf(M, ml[w * 128 + 2 * row]);
+    f32x4 O = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int w = 0; w < 4; w++) {
+      const float f = __builtin_amdgcn_exp2f(ml[w * 128 + 2 * row] - M);
+      L = __builtin_fmaf(f, ml[w * 128 + 2 * row + 1], L);
+      if (WITH_V) {
+        f32x4 v = parked(smem, w, row, ch);
+        if (kBf16) v += parked(smem, w, row + 16, ch);
+#pragma unroll
+        for (int e = 0; e < 4; e++) O[e] = __builtin_fmaf(f, v[e], O[e]);
+      }
+    }
+    float *rec = p.partials + (((size_t)(b * heads + h) * G + gr) * nchunks + chunk) * kClsPartialFloats;
+    if (ch == 0) {
+      rec[0] = M * kLn2;
+      rec[1] = L;
+    }
+    if (WITH_V) {
+      *reinterpret_cast<f32x2 *>(rec + 2 + 4 * ch) = f32x2{O[0], O[1]};
+      *reinterpret_cast<f32x2 *>(rec + 4 + 4 * ch) = f32x2{O[2], O[3]};
+    }
+  }
+}
+
+// ------------------------------------------------------------------------------------------
+// One launch: the leading workgroups own chunks of the global rows, the others a query tile each,
+// whose keys the four waves share out step by step; the waves' partial states are merged through
+// LDS.  Bound at small sizes by the latency of the few steps a wave walks, at larger ones by the
+// instruction issue of the steps.
+// ------------------------------------------------------------------------------------------
+struct WindowParams {
+  GlobalRows r;            // q, k, v, strides, scale; logits and partials for the global rows
+  void *out;
+  int64_t osb, osh, ost;
+  WindowGeom g;
+};
+
+template <class S, int NT, bool LISTS, bool MASK>
+__device__ __forceinline__ void window_attention(const WindowParams &p, unsigned char *smem) {
+  typedef typename S::elem elem;
+  constexpr int QT = 32 * NT;
+  constexpr bool kBf16 = S::kDepth == 2;
+  const WindowGeom &g = p.g;
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+  if ((int)blockIdx.x < g.global_wgs) {
+    if ((int)blockIdx.x >= g.global_live) return;
+    if (p.r.logits)
+      global_rows_chunk<S, true, true>(p.r, g.heads, g.n_global, g.tokens, g.global_groups, g.nchunks, blockIdx.x, smem, wave, lane);
+    else
+      global_rows_chunk<S, true, false>(p.r, g.heads, g.n_global, g.tokens, g.global_groups, g.nchunks, blockIdx.x, smem, wave, lane);
+    return;
+  }
+  const int id = window_tile_id(g, blockIdx.x - g.global_wgs);
+  if (id >= g.tiles) return;
+  WindowTile<LISTS, QT> w;
+  if (!w.init(g, id, lane)) return;
+  const int l32 = lane & 31, hh = lane >> 5;
+  const int64_t head = w.b * p.r.sb + w.h * p.r.sh, rowB = p.r.st * (int64_t)sizeof(elem);
+  const char *qb = reinterpret_cast<const char *>(static_cast<const elem *>(p.r.q) + head);
+  const char *kb = reinterpret_cast<const char *>(static_cast<const elem *>(p.r.k) + head);
+  const char *vb = reinterpret_cast<const char *>(static_cast<const elem *>(p.r.v) + head);
+  unsigned char *wsm = smem + wave * kWaveLds;
+  float *ml = reinterpret_cast<float *>(smem + 4 * kWaveLds);
+  S st;
+  st.init(lane);
+  const int steps = (w.nkeys + 31) / 32, n = steps > wave ? (steps - wave + 3) / 4 : 0;
+  WaveAcc<S, NT> a;
+  a.clear();
+  const float inv_block = 1.f / (float)g.block;
+  uint32_t qcode[NT];
+#pragma unroll
+  for (int nt = 0; nt < NT; nt++) {
+    st.load_q(a.q[nt], qb, rowB, w.query(g, 32 * nt + l32), lane, p.r.scale);
+    if (MASK) qcode[nt] = w.query_code(g, 32 * nt + l32, inv_block);
+  }
+  uint32_t *const codes = reinterpret_cast<uint32_t *>(wsm + kWaveRings + 1024);
+  auto key0 = [&](int i) { return 32 * (4 * i + wave); };       // first key of this wave's step i
+  walk_keys<S, NT, true, LISTS, false, 0>(
+      st, a, kb, vb, rowB, wsm, n, kBf16 ? p.r.scale * kLog2e : kLog2e, lane,
+      [&](int i) { return w.key(g, key0(i) + l32); }, [&](int i) { return w.key_entry(g, key0(i) + l32); },
+      [&](int i, int row, int t) { return key0(i) + row < g.n_global ? key0(i) + row : t; },
+      [&](int i, f32x16 (&s)[NT]) {
+        if (MASK) {
+          codes[l32] = w.key_code(g, key0(i) + l32, inv_block);
+          asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+#pragma unroll
+          for (int q4 = 0; q4 < 4; q4++) {
+            const uint4 kc = *reinterpret_cast<const uint4 *>(codes + 8 * q4 + 4 * hh);
+            const uint32_t k4[4] = {kc.x, kc.y, kc.z, kc.w};
+#pragma unroll
+            for (int e = 0; e < 4; e++)
+#pragma unroll
+              for (int nt = 0; nt < NT; nt++)
+                s[nt][4 * q4 + e] = (k4[e] & ~qcode[nt]) == 0 ? s[nt][4 * q4 + e] : -INFINITY;
+          }
+        } else if (key0(i) + 32 > w.nkeys) {
+          const int jb = key0(i) + 4 * hh;
+#pragma unroll
+          for (int e = 0; e < 16; e++)
+#pragma unroll
+            for (int nt = 0; nt < NT; nt++) s[nt][e] = jb + 8 * (e >> 2) + (e & 3) < w.nkeys ? s[nt][e] : -INFINITY;
+        }
+      });
+  park_state(a, wsm, ml + wave * 128, lane);
+  __syncthreads();
+  // merge in wave order, normalise, store: 16 lanes per row
+  elem *ob = static_cast<elem *>(p.out) + w.b * p.osb + w.h * p.osh;
+#pragma unroll
+  for (int ps = 0; ps < QT / 16; ps++) {
+    const int row = 16 * ps + 4 * wave + (lane >> 4), ch = lane & 15;
+    float M = ml[2 * row], L = 0.f;
+#pragma unroll
+    for (int x = 1; x < 4; x++) M = fmaxf(M, ml[x * 128 + 2 * row]);
+    f32x4 O = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int x = 0; x < 4; x++) {
+      const float f = __builtin_amdgcn_exp2f(ml[x * 128 + 2 * row] - M);     // 0 for a wave without keys
+      L = __builtin_fmaf(f, ml[x * 128 + 2 * row + 1], L);
+      const f32x4 v = parked(smem, x, row, ch);
+#pragma unroll
+      for (int e = 0; e < 4; e++) O[e] = __builtin_fmaf(f, v[e], O[e]);
+    }
+    const float inv = 1.f / L;
+    if (row < w.qcnt) S::store4out(ob + (int64_t)w.query(g, row) * p.ost + 4 * ch, O * inv);
+  }
+}
+
+// The geometry on the host; qt = queries per tile, rows_per_group = global rows that one global
+// workgroup handles (0: no global rows in this launch).  Workgroups to launch, or -1.
+inline long long window_geometry(const AttnArgs &a, int qt, int rows_per_group, int nchunks, WindowGeom &g) {
+  const ns_attn_desc &d = a.d;
+  const bool lists = d.coords != nullptr;
+  g.grid_h = d.grid_h; g.grid_w = d.grid_w; g.block = d.block; g.n_global = d.n_global; g.tokens = d.tokens;
+  g.heads = d.heads;
+  g.side = lists || d.block > 4 ? d.block : d.block * (8 / d.block);
+  g.nbh = (d.grid_h + g.side - 1) / g.side;
+  g.nbw = (d.grid_w + g.side - 1) / g.side;
+  g.cap = d.block * d.block;
+  g.tpb = (g.side * g.side + qt - 1) / qt;
+  g.lists = a.geom.lists; g.counts = a.geom.counts;
+  const long long per_image = (long long)g.nbh * g.nbw * g.tpb, tiles = per_image * d.batch * d.heads;
+  const int groups = rows_per_group ? (d.n_global + rows_per_group - 1) / rows_per_group : 0;
+  const long long live = (long long)d.batch * d.heads * groups * nchunks;
+  if (tiles > 0x7ffffff0LL || live > 0x7ffffff0LL) return -1;
+  g.tiles_per_image = (int)per_image;
+  g.tiles = (int)tiles;
+  g.per_xcd = (int)((tiles + 7) / 8);
+  g.global_groups = groups;
+  g.nchunks = nchunks;
+  g.global_live = (int)live;
+  g.global_wgs = (int)((live + 7) / 8 * 8);
+  const long long wgs = g.global_wgs + 8LL * g.per_xcd;
+  return wgs > 0x7fffffffLL ? -1 : wgs;
+}
+
+// The launch arguments; logits, partials: of the global rows, NULL partials = patch queries only
+template <class S, int NT>
+inline long long window_params(const AttnArgs &a, float *logits, float *partials, WindowParams &p) {
+  const ns_attn_desc &d = a.d;
+  p.r = GlobalRows{a.q, a.k, a.v, d.q_stride_b, d.q_stride_h, d.q_stride_t, d.scale, logits, partials};
+  p.out = a.out;
+  p.osb = d.out_stride_b; p.osh = d.out_stride_h; p.ost = d.out_stride_t;
+  return window_geometry(a, 32 * NT, partials ? global_group_rows<S>() : 0, cls_num_chunks(d.tokens), p.g);
+}
+
+}  // namespace ns
