@@ -1,9 +1,10 @@
-"""ctypes binding of libnsattn.so: argument marshalling only.
+"""Binding of libnsattn.so: argument marshalling only.
 
 Every function here has the name of the C entry point it calls (include/nsattn.h) and does
 nothing but turn torch tensors into device pointers, strides and sizes; all computation runs
-in the HIP kernels.  PyTorch supplies device memory and the current stream.  There is no
-fallback: if the library has not been built, importing this module raises.
+in the HIP kernels.  PyTorch supplies device memory and the current stream.  The calls of a
+forward pass are marshalled in C++ (csrc/ns_bind.cpp), the others with ctypes.  There is no
+fallback: if the libraries have not been built, importing this module raises.
 """
 from __future__ import annotations
 
@@ -127,6 +128,10 @@ def _load() -> ctypes.CDLL:
 
 
 lib = _load()
+from . import _nsbind  # noqa: E402  (after libnsattn.so, which it links to)
+
+
+_nsbind.set_error(NsError)
 
 
 def _check(code: int) -> None:
@@ -149,6 +154,13 @@ def _ptr(t: Optional[torch.Tensor]):
 def _stream(stream) -> ctypes.c_void_p:
     s = torch.cuda.current_stream() if stream is None else stream
     return ctypes.c_void_p(s.cuda_stream)
+
+
+def _raw_stream(stream) -> int:
+    """hipStream_t of `stream`, or of the current device's current stream."""
+    if stream is None:
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    return stream.cuda_stream
 
 
 def _workspace(nbytes: int, device, workspace: Optional[torch.Tensor]) -> Optional[torch.Tensor]:
@@ -186,52 +198,16 @@ def ns_attn_forward(q, k, v, grid_h, grid_w, block, scale=None, coords=None, out
     Returns out [B,H,T,D] (allocated contiguous unless given) and, with want_cls, also the
     global query's logits [B,H,T] and log-sum-exp [B,H] (both fp32; [B,H,G,T] and [B,H,G] when
     n_global = G > 1)."""
-    if not (q.shape == k.shape == v.shape and q.stride() == k.stride() == v.stride()):
-        raise ValueError("q, k, v must have the same shape and strides")
-    if not (q.dtype == k.dtype == v.dtype):
-        raise ValueError("q, k, v must have the same dtype")
-    B, H, T, D = q.shape
-    if out is None:
-        out = torch.empty((B, H, T, D), dtype=q.dtype, device=q.device)
-    if coords is not None and (coords.dtype != torch.int32 or not coords.is_contiguous()):
-        raise ValueError("coords must be a contiguous int32 tensor [B, T - n_global]")
-    desc = make_desc(q, grid_h, grid_w, block, scale, out, coords, radius, n_global)
-    logits = lse = None
-    if want_cls:
-        G = int(n_global)
-        logits = torch.empty((B, H, T) if G == 1 else (B, H, G, T), dtype=torch.float32, device=q.device)
-        lse = torch.empty((B, H) if G == 1 else (B, H, G), dtype=torch.float32, device=q.device)
-    nbytes = lib.ns_attn_workspace_bytes(ctypes.byref(desc))
-    ws = _workspace(nbytes, q.device, workspace)
-    _check(lib.ns_attn_forward(ctypes.byref(desc), _ptr(q), _ptr(k), _ptr(v), _ptr(out), _ptr(logits),
-                               _ptr(lse), _ptr(ws), 0 if ws is None else ws.numel(), _stream(stream)))
-    return (out, logits, lse) if want_cls else out
+    return _nsbind.attn(q, k, v, grid_h, grid_w, block, scale, coords, out, workspace, _raw_stream(stream), radius,
+                        int(n_global), 1 if want_cls else 0)
 
 
 def ns_attn_forward_scores(q, k, v, grid_h, grid_w, block, scale=None, coords=None, out=None,
                            workspace=None, stream=None, n_global=1):
     """ns_attn_forward with the global queries' by-products, and the importance scores of the
     patches from them, in one call.  Returns (out, cls_logits, cls_lse, scores [B, T - n_global])."""
-    if not (q.shape == k.shape == v.shape and q.stride() == k.stride() == v.stride()):
-        raise ValueError("q, k, v must have the same shape and strides")
-    if not (q.dtype == k.dtype == v.dtype):
-        raise ValueError("q, k, v must have the same dtype")
-    B, H, T, D = q.shape
-    G = int(n_global)
-    if out is None:
-        out = torch.empty((B, H, T, D), dtype=q.dtype, device=q.device)
-    if coords is not None and (coords.dtype != torch.int32 or not coords.is_contiguous()):
-        raise ValueError("coords must be a contiguous int32 tensor [B, T - n_global]")
-    desc = make_desc(q, grid_h, grid_w, block, scale, out, coords, 1, n_global)
-    logits = torch.empty((B, H, T) if G == 1 else (B, H, G, T), dtype=torch.float32, device=q.device)
-    lse = torch.empty((B, H) if G == 1 else (B, H, G), dtype=torch.float32, device=q.device)
-    scores = torch.empty((B, T - G), dtype=torch.float32, device=q.device)
-    nbytes = lib.ns_attn_workspace_bytes(ctypes.byref(desc))
-    ws = _workspace(nbytes, q.device, workspace)
-    _check(lib.ns_attn_forward_scores(ctypes.byref(desc), _ptr(q), _ptr(k), _ptr(v), _ptr(out), _ptr(logits),
-                                      _ptr(lse), _ptr(scores), _ptr(ws), 0 if ws is None else ws.numel(),
-                                      _stream(stream)))
-    return out, logits, lse, scores
+    return _nsbind.attn(q, k, v, grid_h, grid_w, block, scale, coords, out, workspace, _raw_stream(stream), 1,
+                        int(n_global), 2)
 
 
 def ns_attn_patch_kernel_time(q, k, v, grid_h, grid_w, block, scale=None, coords=None, out=None,
@@ -261,18 +237,7 @@ def ns_attn_patch_kernel_name(q, grid_h, grid_w, block, scale=None, coords=None,
 
 def cls_scores(q, k, scale=None, n_global=1, scores=None, workspace=None, stream=None):
     """Head-averaged softmax weight of the global query on every patch key: [B, T-G] fp32."""
-    if not (q.shape == k.shape and q.stride() == k.stride() and q.dtype == k.dtype):
-        raise ValueError("q and k must have the same shape, strides and dtype")
-    B, H, T, D = q.shape
-    # the grid fields are not used by scoring; a 1 x (T-G) grid keeps the descriptor valid
-    desc = make_desc(q, 1, T - n_global, 1, scale, None, None, 1, n_global)
-    if scores is None:
-        scores = torch.empty((B, T - n_global), dtype=torch.float32, device=q.device)
-    nbytes = lib.cls_scores_workspace_bytes(ctypes.byref(desc))
-    ws = _workspace(nbytes, q.device, workspace)
-    _check(lib.cls_scores(ctypes.byref(desc), _ptr(q), _ptr(k), _ptr(scores), _ptr(ws),
-                          0 if ws is None else ws.numel(), _stream(stream)))
-    return scores
+    return _nsbind.scores(q, k, scale, n_global, scores, workspace, _raw_stream(stream))
 
 
 def cls_scores_static(q, k, scale=None, n_global=1, scores=None, stream=None):
@@ -308,61 +273,14 @@ def topk_filter(scores, k, x=None, coords=None, kept_idx=None, y=None, coords_ou
     scores [B,N] fp32; x optional [B,G+N,C] (G = n_global leading rows are kept); coords optional
     [B,N] int32.
     Returns (kept_idx [B,k] int32 ascending, y [B,G+k,C] or None, coords_out [B,k] or None)."""
-    G = int(n_global)
-    if scores.dtype != torch.float32 or not scores.is_contiguous():
-        raise ValueError("scores must be a contiguous float32 tensor")
-    B, N = scores.shape
-    dev = scores.device
-    kk = max(int(k), 0)
-    if kept_idx is None:
-        kept_idx = torch.empty((B, kk), dtype=torch.int32, device=dev)
-    C, xdt = 0, NS_BF16
-    if x is not None:
-        if not x.is_contiguous() or x.shape[0] != B or x.shape[1] != G + N:
-            raise ValueError("x must be contiguous [B, n_global+N, C]")
-        C, xdt = x.shape[2], _dtype_code(x)
-        if y is None:
-            y = torch.empty((B, G + kk, C), dtype=x.dtype, device=dev)
-    if coords is not None:
-        if coords.dtype != torch.int32 or not coords.is_contiguous():
-            raise ValueError("coords must be contiguous int32 [B,N]")
-        if coords_out is None:
-            coords_out = torch.empty((B, kk), dtype=torch.int32, device=dev)
-    nbytes = lib.topk_filter_workspace_bytes(B, N, int(k))
-    ws = _workspace(nbytes, dev, workspace)
-    if G == 1:
-        _check(lib.topk_filter(B, N, int(k), _ptr(scores), _ptr(x), C, xdt, _ptr(coords), _ptr(kept_idx),
-                               _ptr(y), _ptr(coords_out), _ptr(ws), 0 if ws is None else ws.numel(),
-                               _stream(stream)))
-    else:
-        _check(lib.topk_filter_global(B, N, int(k), G, _ptr(scores), _ptr(x), C, xdt, _ptr(coords),
-                                      _ptr(kept_idx), _ptr(y), _ptr(coords_out), _ptr(ws),
-                                      0 if ws is None else ws.numel(), _stream(stream)))
-    return kept_idx, y, coords_out
+    return _nsbind.topk(scores, int(k), x, coords, kept_idx, y, coords_out, workspace, _raw_stream(stream), int(n_global))
 
 
 def vit_embed(pixels, w_patch, b_patch, cls_token, pos_embed, patch, out=None, workspace=None, stream=None):
     """Patch embedding: pixels [B,channels,gh*patch,gw*patch] bf16 -> tokens [B, 1+gh*gw, dim] bf16
     (CLS token in front, position embeddings added).  w_patch [dim, channels*patch*patch] bf16,
     b_patch [dim] fp32, cls_token [dim] bf16, pos_embed [1+gh*gw, dim] bf16."""
-    for name, t, dt in (("pixels", pixels, torch.bfloat16), ("w_patch", w_patch, torch.bfloat16),
-                        ("b_patch", b_patch, torch.float32), ("cls_token", cls_token, torch.bfloat16),
-                        ("pos_embed", pos_embed, torch.bfloat16)):
-        if t.dtype != dt or not t.is_contiguous():
-            raise ValueError("%s must be a contiguous %s tensor" % (name, dt))
-    B, ch, hp, wp = pixels.shape
-    if hp % patch or wp % patch:
-        raise ValueError("image sides must be multiples of the patch side")
-    gh, gw, dim = hp // patch, wp // patch, w_patch.shape[0]
-    if w_patch.shape[1] != ch * patch * patch or pos_embed.shape != (1 + gh * gw, dim):
-        raise ValueError("w_patch must be [dim, channels*patch*patch] and pos_embed [1+gh*gw, dim]")
-    if out is None:
-        out = torch.empty((B, 1 + gh * gw, dim), dtype=torch.bfloat16, device=pixels.device)
-    nbytes = lib.vit_embed_workspace_bytes(B, ch, gh, gw, patch, dim)
-    ws = _workspace(max(nbytes, 1), pixels.device, workspace)
-    _check(lib.vit_embed(B, ch, gh, gw, patch, dim, _ptr(pixels), _ptr(w_patch), _ptr(b_patch), _ptr(cls_token),
-                         _ptr(pos_embed), _ptr(out), _ptr(ws), ws.numel(), _stream(stream)))
-    return out
+    return _nsbind.embed(pixels, w_patch, b_patch, cls_token, pos_embed, patch, out, workspace, _raw_stream(stream))
 
 
 WEIGHT_NAMES = ("ln1_g", "ln1_b", "w_qkv", "b_qkv", "w_proj", "b_proj", "ln2_g", "ln2_b",
@@ -375,37 +293,8 @@ def vit_block_forward(x, weights, grid_h, grid_w, block, heads, ln_eps=1e-6, sca
 
     x [B,T,dim] bf16 contiguous; weights: dict of device tensors (matrices bf16 [out,in], vectors
     fp32).  Returns x_out [B,T,dim] (and the importance scores [B,T-n_global] with want_scores)."""
-    if x.dtype != torch.bfloat16 or not x.is_contiguous():
-        raise ValueError("x must be a contiguous bfloat16 tensor [B,T,dim]")
-    B, T, dim = x.shape
-    for n in WEIGHT_NAMES:
-        t = weights[n]
-        want = torch.bfloat16 if n.startswith("w_") else torch.float32
-        if t.dtype != want or not t.is_contiguous() or t.device != x.device:
-            raise ValueError("weight %s must be a contiguous %s tensor on %s" % (n, want, x.device))
-    mlp = weights["w_fc1"].shape[0]
-    d = ns_vit_block_desc()
-    a = d.attn
-    a.batch, a.heads, a.head_dim = B, heads, dim // heads
-    a.grid_h, a.grid_w, a.block, a.radius, a.n_global = grid_h, grid_w, block, 1, int(n_global)
-    a.dtype, a.tokens = NS_BF16, T
-    a.scale = float(dim // heads) ** -0.5 if scale is None else float(scale)
-    if coords is not None:
-        if coords.dtype != torch.int32 or not coords.is_contiguous():
-            raise ValueError("coords must be a contiguous int32 tensor [B, T-1]")
-        a.coords = coords.data_ptr()
-    d.dim, d.mlp_dim, d.ln_eps = dim, mlp, float(ln_eps)
-    w = ns_vit_block_weights()
-    for n in WEIGHT_NAMES:
-        setattr(w, n, weights[n].data_ptr())
-    if out is None:
-        out = torch.empty_like(x)
-    scores = torch.empty((B, T - int(n_global)), dtype=torch.float32, device=x.device) if want_scores else None
-    nbytes = lib.vit_block_workspace_bytes(ctypes.byref(d))
-    ws = _workspace(max(nbytes, 1), x.device, workspace)
-    _check(lib.vit_block_forward(ctypes.byref(d), ctypes.byref(w), _ptr(x), _ptr(out), _ptr(scores), _ptr(ws),
-                                 ws.numel(), _stream(stream)))
-    return (out, scores) if want_scores else out
+    return _nsbind.block(x, weights, grid_h, grid_w, block, heads, ln_eps, scale, coords, want_scores, out, workspace,
+                         _raw_stream(stream), int(n_global))
 
 
 def linear_forward(x, w, bias, residual=None, gelu=False, out=None, stream=None):
@@ -435,41 +324,8 @@ def vit_forward(x, layer_weights, grid_h, grid_w, block, heads, prune_after=0, k
     Returns (x_out [B, n_global+keep_k or T, dim], kept_idx [B,keep_k] or None); with tap_layers
     (ascending 1-based block numbers) also a list of feature maps [B, grid_h*grid_w, dim], the patch
     tokens after those blocks in raster order."""
-    if x.dtype != torch.bfloat16 or not x.is_contiguous():
-        raise ValueError("x must be a contiguous bfloat16 tensor [B,T,dim]")
-    B, T, dim = x.shape
-    d = ns_vit_desc()
-    a = d.block.attn
-    a.batch, a.heads, a.head_dim = B, heads, dim // heads
-    a.grid_h, a.grid_w, a.block, a.radius, a.n_global = grid_h, grid_w, block, 1, int(n_global)
-    a.dtype, a.tokens = NS_BF16, T
-    a.scale = float(dim // heads) ** -0.5 if scale is None else float(scale)
-    d.block.dim, d.block.mlp_dim, d.block.ln_eps = dim, layer_weights[0]["w_fc1"].shape[0], float(ln_eps)
-    d.layers, d.prune_after, d.keep_k = len(layer_weights), int(prune_after), int(keep_k)
-    warr = (ns_vit_block_weights * len(layer_weights))()
-    for i, lw in enumerate(layer_weights):
-        for n in WEIGHT_NAMES:
-            t = lw[n]
-            want = torch.bfloat16 if n.startswith("w_") else torch.float32
-            if t.dtype != want or not t.is_contiguous() or t.device != x.device:
-                raise ValueError("layer %d weight %s must be a contiguous %s tensor on %s" % (i, n, want, x.device))
-            setattr(warr[i], n, t.data_ptr())
-    pruning = prune_after > 0 and keep_k > 0
-    if out is None:
-        out = torch.empty((B, int(n_global) + keep_k if pruning else T, dim), dtype=x.dtype, device=x.device)
-    kept = torch.empty((B, keep_k), dtype=torch.int32, device=x.device) if pruning else None
-    nbytes = lib.vit_workspace_bytes(ctypes.byref(d))
-    ws = _workspace(max(nbytes, 1), x.device, workspace)
-    if tap_layers is None:
-        _check(lib.vit_forward(ctypes.byref(d), warr, _ptr(x), _ptr(out), _ptr(kept), _ptr(ws), ws.numel(),
-                               _stream(stream)))
-        return out, kept
-    taps = [torch.empty((B, grid_h * grid_w, dim), dtype=x.dtype, device=x.device) for _ in tap_layers]
-    tl = (ctypes.c_int32 * len(taps))(*[int(t) for t in tap_layers])
-    tp = (ctypes.c_void_p * len(taps))(*[t.data_ptr() for t in taps])
-    _check(lib.vit_forward_features(ctypes.byref(d), warr, _ptr(x), _ptr(out), _ptr(kept), len(taps), tl, tp,
-                                    _ptr(ws), ws.numel(), _stream(stream)))
-    return out, kept, taps
+    return _nsbind.stack(x, layer_weights, grid_h, grid_w, block, heads, int(prune_after), int(keep_k), ln_eps, scale, out,
+                         workspace, _raw_stream(stream), int(n_global), tap_layers)
 
 
 def vit_forward_stages(x, layer_weights, grid_h, grid_w, block, heads, stage_after, stage_keep, ln_eps=1e-6,
