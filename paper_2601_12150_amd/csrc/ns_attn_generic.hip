@@ -13,10 +13,10 @@ namespace ns {
 
 namespace {
 
-template <typename T, bool LISTS, bool MASK>
+template <typename T, bool LISTS, bool MASK, int KS>
 __global__ __launch_bounds__(256, 2) void attn_generic_kernel(WindowParams p) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  window_attention<StepF32<T>, 1, LISTS, MASK>(p, smem);
+  window_attention<StepF32<T>, 1, LISTS, MASK, KS>(p, smem);
 }
 
 constexpr int kListUnroll = 16;   // coordinates per thread and round
@@ -82,12 +82,16 @@ ns_status launch_block_lists(const ns_attn_desc &d, int32_t *lists, int32_t *cou
 template <typename T>
 static ns_status launch_generic(const AttnArgs &a, float *logits, float *partials) {
   WindowParams p;
-  const long long wgs = window_params<StepF32<T>, 1>(a, logits, partials, p);
+  int ks;
+  const long long wgs = window_params<StepF32<T>, 1>(a, logits, partials, p, ks);
   if (wgs < 0) return fail(NS_ERR_UNSUPPORTED, "launch grid too large");
   const bool lists = a.d.coords != nullptr, mask = p.g.side > p.g.block;
   typedef void (*kern_t)(WindowParams);
-  const kern_t kern = lists ? attn_generic_kernel<T, true, false>
-                            : (mask ? attn_generic_kernel<T, false, true> : attn_generic_kernel<T, false, false>);
+#define NS_KERN(KS)                                                                                     \
+  (lists ? attn_generic_kernel<T, true, false, KS>                                                      \
+         : (mask ? attn_generic_kernel<T, false, true, KS> : attn_generic_kernel<T, false, false, KS>))
+  const kern_t kern = ks == 4 ? NS_KERN(4) : (ks == 2 ? NS_KERN(2) : NS_KERN(1));
+#undef NS_KERN
   const ns_status rs = reserve_lds_once(reinterpret_cast<const void *>(kern), kWindowLds);
   if (rs != NS_OK) return rs;
   hipLaunchKernelGGL(kern, dim3((unsigned)wgs), dim3(256), kWindowLds, a.stream, p);

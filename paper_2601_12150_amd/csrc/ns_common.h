@@ -160,6 +160,7 @@ struct AttnArgs {
   BlockGeom geom;
   hipStream_t stream;
   int kernel;            // the patch-query kernel chosen for this call (ns_api.hip: PatchKernel)
+  int split = 0;         // waves per query tile of the window kernels: 1, 2 or 4, or 0: by size
 };
 
 // ns_attn_forward with one more knob: reuse_lists = the per-block token lists that an earlier call
@@ -195,6 +196,7 @@ bool block16_attn_supported(const ns_attn_desc &d);  // 16x16 blocks: key tiles 
 ns_status launch_attn_block16(const AttnArgs &a);
 bool ragged_attn_supported(const ns_attn_desc &d);   // bf16, head_dim 64: any complete grid or pruned sequence
 ns_status launch_attn_ragged(const AttnArgs &a, float *logits, float *partials);
+double ragged_attn_us(const ns_attn_desc &d);         // what its launch takes on a complete grid, roughly
 
 // global-query (CLS) row: per-chunk partials, then a combine.
 constexpr int kClsChunk = 512;                      // keys per workgroup of the row kernel

@@ -11,6 +11,8 @@
 // lane turns the number of its key into a token.
 #pragma once
 #include "ns_common.h"
+#include <algorithm>
+#include <cmath>
 
 namespace ns {
 
@@ -22,7 +24,7 @@ struct WindowGeom {
   int cap;                 // slots per block in `lists`
   int tiles_per_image;     // nbh * nbw * tpb
   int tiles;               // batch * heads * tiles_per_image
-  int per_xcd;             // ceil(tiles / 8)
+  int per_xcd;             // workgroups per XCD
   int global_wgs;          // leading workgroups that own chunks of the global rows: a multiple of 8
   int global_live;         // ... of which this many have work
   int global_groups;       // groups of global rows per head
@@ -185,27 +187,86 @@ struct StepBf16 {
 #pragma unroll
     for (int s = 0; s < 4; s++) q.f[s] = *reinterpret_cast<const bf16x8 *>(row + 16 * s);
   }
-  __device__ __forceinline__ void issue_k(const char *base, int64_t rowB, const int (&tok)[kReq], unsigned char *, uint32_t lds, int) const {
+  // a row's byte offset, passed from lane to lane instead of its token: one multiplication per key
+  static __device__ __forceinline__ uint32_t place(int tok, int64_t rowB) { return (uint32_t)tok * (uint32_t)rowB; }
+  __device__ __forceinline__ void issue_k(const char *base, int64_t, const uint32_t (&at)[kReq], unsigned char *, uint32_t lds, int) const {
 #pragma unroll
-    for (int it = 0; it < kReq; it++) dma16(base, (uint32_t)tok[it] * (uint32_t)rowB + kch[it & 1], lds + it * 1024);
+    for (int it = 0; it < kReq; it++) dma16(base, at[it] + kch[it & 1], lds + it * 1024);
   }
-  __device__ __forceinline__ void issue_v(const char *base, int64_t rowB, const int (&tok)[kReq], unsigned char *, uint32_t lds, int) const {
+  __device__ __forceinline__ void issue_v(const char *base, int64_t, const uint32_t (&at)[kReq], unsigned char *, uint32_t lds, int) const {
 #pragma unroll
-    for (int it = 0; it < kReq; it++) dma16(base, (uint32_t)tok[it] * (uint32_t)rowB + vch, lds + it * 1024);
+    for (int it = 0; it < kReq; it++) dma16(base, at[it] + vch, lds + it * 1024);
+  }
+  struct K { bf16x8 f[4]; };
+  __device__ __forceinline__ void load_k(K &k, const unsigned char *slot) const {
+#pragma unroll
+    for (int t = 0; t < 4; t++) k.f[t] = *(frag_ptr)(slot + krd[t]);
+  }
+  __device__ __forceinline__ f32x16 product(const K &k, const Q &q) const {
+    f32x16 s = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int t = 0; t < 4; t++) s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k.f[t], q.f[t], s, 0, 0, 0);
+    return s;
+  }
+  struct V { bf16x8 f[2][2]; };      // [keys 16 sp ..][channels 32 dt ..]
+  __device__ __forceinline__ void load_v(V &v, const unsigned char *slot, int sp) const {
+#pragma unroll
+    for (int dt = 0; dt < 2; dt++) {
+      const s16x4 lo4 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((tr_ptr)(slot + vrd[dt][0] + sp * 2048));
+      const s16x4 hi4 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((tr_ptr)(slot + vrd[dt][1] + sp * 2048));
+      const bf16x4 a = __builtin_bit_cast(bf16x4, lo4), b2 = __builtin_bit_cast(bf16x4, hi4);
+      v.f[sp][dt] = bf16x8{a[0], a[1], a[2], a[3], b2[0], b2[1], b2[2], b2[3]};
+    }
   }
   template <int NT>
   __device__ __forceinline__ void logits(const Q (&q)[NT], const unsigned char *slot, f32x16 (&s)[NT]) const {
-    bf16x8 kf[4];
+    K k;
+    load_k(k, slot);
 #pragma unroll
-    for (int t = 0; t < 4; t++) kf[t] = *(frag_ptr)(slot + krd[t]);
-#pragma unroll
-    for (int nt = 0; nt < NT; nt++) {
-      s[nt] = f32x16{0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int t = 0; t < 4; t++) s[nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[t], q[nt].f[t], s[nt], 0, 0, 0);
-    }
+    for (int nt = 0; nt < NT; nt++) s[nt] = product(k, q[nt]);
   }
-  // LO: lanes of columns 16..31 take what bf16 rounding leaves of a weight, w - bf16(w)
+  // Half a pipelined step: the weights of 32 queries from their logits `cur`, interleaved with eight matrix
+  // instructions: the last half's open output product (`open`: the second half of its keys' weights, o_open),
+  // the logits `nxt` of the other queries, the first half of this output product.  One matrix instruction
+  // (32 cycles) to the seven vector instructions of two weights (36 cycles); a weight's three links are a
+  // group apart, so that no result is waited for.  The fences keep this order: left to itself the
+  // scheduler groups the exponentials and then the matrix instructions.
+  // LOADV: load the second half of V once the open product has taken the old one.
+  template <bool LOADV>
+  __device__ __forceinline__ void half_step(f32x16 &cur, float c, float nm, float (&l)[2], f32x16 (&o)[2], f32x16 (&o_open)[2],
+                                            bf16x8 &open, V &v, const unsigned char *vslot, const K &k, const Q &q,
+                                            f32x16 &nxt) const {
+    bf16x8 first, second;
+    nxt = f32x16{0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int e = 0; e < 4; e++) cur[e] = __builtin_fmaf(cur[e], c, nm);
+    cur[0] = __builtin_amdgcn_exp2f(cur[0]);
+    cur[1] = __builtin_amdgcn_exp2f(cur[1]);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int j = 0; j < 8; j++) {
+      if (j < 7) {
+        cur[2 * j + 2] = __builtin_amdgcn_exp2f(cur[2 * j + 2]);
+        cur[2 * j + 3] = __builtin_amdgcn_exp2f(cur[2 * j + 3]);
+      }
+      if (j < 6) {
+        cur[2 * j + 4] = __builtin_fmaf(cur[2 * j + 4], c, nm);
+        cur[2 * j + 5] = __builtin_fmaf(cur[2 * j + 5], c, nm);
+      }
+      l[0] += cur[2 * j];
+      l[1] += cur[2 * j + 1];
+      const bf16x2 pk = __builtin_bit_cast(bf16x2, pack_bf16(cur[2 * j], cur[2 * j + 1]));
+      if (j < 4) { first[2 * j] = pk[0]; first[2 * j + 1] = pk[1]; }
+      else { second[2 * j - 8] = pk[0]; second[2 * j - 7] = pk[1]; }
+      if (j < 2) o_open[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v.f[1][j], open, o_open[j], 0, 0, 0);
+      else if (j < 6) nxt = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k.f[j - 2], q.f[j - 2], nxt, 0, 0, 0);
+      else o[j - 6] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v.f[0][j - 6], first, o[j - 6], 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+      if (LOADV && j == 1) load_v(v, vslot, 1);
+    }
+    open = second;
+  }
+  // O^T += V^T w.  LO: lanes of columns 16..31 take what bf16 rounding leaves of a weight, w - bf16(w)
   template <int NT, bool LO>
   __device__ __forceinline__ void weigh(const f32x16 (&w)[NT], const unsigned char *slot, f32x16 (&o)[NT][2], int lane) const {
     bf16x8 pf[NT][2];
@@ -282,15 +343,16 @@ struct StepF32 {
       *reinterpret_cast<f32x4 *>(dst + 16 * lane) = load4(reinterpret_cast<const T *>(row) + 4 * chunk);
     }
   }
-  __device__ __forceinline__ void issue_k(const char *base, int64_t rowB, const int (&tok)[kReq], unsigned char *dst, uint32_t lds, int lane) const {
+  static __device__ __forceinline__ uint32_t place(int tok, int64_t) { return (uint32_t)tok; }
+  __device__ __forceinline__ void issue_k(const char *base, int64_t rowB, const uint32_t (&at)[kReq], unsigned char *dst, uint32_t lds, int lane) const {
 #pragma unroll
     for (int it = 0; it < kReq; it++)
-      request(base + (int64_t)tok[it] * rowB, (lane & 15) ^ ((4 * it + rrow) & 15), dst + it * 1024, lds + it * 1024, lane);
+      request(base + (int64_t)at[it] * rowB, (lane & 15) ^ ((4 * it + rrow) & 15), dst + it * 1024, lds + it * 1024, lane);
   }
-  __device__ __forceinline__ void issue_v(const char *base, int64_t rowB, const int (&tok)[kReq], unsigned char *dst, uint32_t lds, int lane) const {
+  __device__ __forceinline__ void issue_v(const char *base, int64_t rowB, const uint32_t (&at)[kReq], unsigned char *dst, uint32_t lds, int lane) const {
 #pragma unroll
     for (int it = 0; it < kReq; it++)
-      request(base + (int64_t)tok[it] * rowB, (lane & 15) ^ (8 * (it & 1)), dst + it * 1024, lds + it * 1024, lane);
+      request(base + (int64_t)at[it] * rowB, (lane & 15) ^ (8 * (it & 1)), dst + it * 1024, lds + it * 1024, lane);
   }
   template <int NT>
   __device__ __forceinline__ void logits(const Q (&q)[NT], const unsigned char *slot, f32x16 (&s)[NT]) const {
@@ -344,48 +406,172 @@ struct WaveAcc {
       for (int e = 0; e < 16; e++) { o[nt][0][e] = 0.f; o[nt][1][e] = 0.f; }
     }
   }
-  // logits -> weights.  The reference follows the running maximum in jumps: it is raised (and the
-  // sums rescaled) only when a logit exceeds it by more than 8 in log2 units, so weights stay
-  // below 2^8 and the rescale, a third of the vector work otherwise, is rare after the first step.
-  __device__ __forceinline__ void soften(f32x16 (&s)[NT], float c) {
-    float top[NT];
-    bool up = false;
+  // The reference is the first step's maximum and normally stays: a weight is exp2 of how far a logit
+  // lies above it, and neither fp32 nor bf16 lose anything on weights up to 2^100.  A wave whose sums
+  // then turn out too large (or not finite) walks its keys once more and raises the reference
+  // wherever a logit exceeds it by more than 8.
+  __device__ __forceinline__ bool overflowed() const {
+    float big = 0.f;
 #pragma unroll
     for (int nt = 0; nt < NT; nt++) {
-      float a = fmaxf(s[nt][0], s[nt][1]), b = fmaxf(s[nt][2], s[nt][3]);
+      big = fmaxf(big, fabsf(l[nt]));
 #pragma unroll
-      for (int e = 4; e < 16; e += 4) {
-        a = fmaxf(fmaxf(a, s[nt][e]), s[nt][e + 1]);
-        b = fmaxf(fmaxf(b, s[nt][e + 2]), s[nt][e + 3]);
-      }
-      top[nt] = half_swap_max(fmaxf(a, b)) * c;
-      up = up || top[nt] > m[nt] + 8.f;
+      for (int e = 0; e < 16; e++) big = fmaxf(fmaxf(big, fabsf(o[nt][0][e])), fabsf(o[nt][1][e]));
     }
-    if (__any(up)) {
+    return __any(!(big < 1e30f));
+  }
+  __device__ __forceinline__ void reference(const f32x16 &s, int nt, float c) {
+    float a = fmaxf(s[0], s[1]), b = fmaxf(s[2], s[3]);
 #pragma unroll
-      for (int nt = 0; nt < NT; nt++) {
-        const float m_new = fmaxf(m[nt], top[nt]);
-        const float alpha = __builtin_amdgcn_exp2f(m[nt] - m_new);
-        m[nt] = m_new;
-        l[nt] *= alpha;
-#pragma unroll
-        for (int e = 0; e < 16; e++) { o[nt][0][e] *= alpha; o[nt][1][e] *= alpha; }
-      }
+    for (int e = 4; e < 16; e += 4) {
+      a = fmaxf(fmaxf(a, s[e]), s[e + 1]);
+      b = fmaxf(fmaxf(b, s[e + 2]), s[e + 3]);
     }
+    const float top = half_swap_max(fmaxf(a, b)) * c;
+    if (__any(top > m[nt] + 8.f)) {
+      const float m_new = fmaxf(m[nt], top);
+      const float alpha = __builtin_amdgcn_exp2f(m[nt] - m_new);
+      m[nt] = m_new;
+      l[nt] *= alpha;
 #pragma unroll
-    for (int nt = 0; nt < NT; nt++) {
-      float l0 = 0.f, l1 = 0.f;
-#pragma unroll
-      for (int e = 0; e < 16; e += 2) {
-        s[nt][e] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[nt][e], c, -m[nt]));
-        s[nt][e + 1] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[nt][e + 1], c, -m[nt]));
-        l0 += s[nt][e];
-        l1 += s[nt][e + 1];
-      }
-      l[nt] += l0 + l1;
+      for (int e = 0; e < 16; e++) { o[nt][0][e] *= alpha; o[nt][1][e] *= alpha; }
     }
   }
+  // logits -> weights
+  __device__ __forceinline__ void weights(f32x16 &s, int nt, float c) {
+    float l0 = 0.f, l1 = 0.f;
+#pragma unroll
+    for (int e = 0; e < 16; e += 2) {
+      s[e] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[e], c, -m[nt]));
+      s[e + 1] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[e + 1], c, -m[nt]));
+      l0 += s[e];
+      l1 += s[e + 1];
+    }
+    l[nt] += l0 + l1;
+  }
 };
+
+// n steps of a wave with two ring slots and 64 queries, software-pipelined: while the weights of one half of the
+// queries are taken and multiplied with V, the logits of the other half (of the next step) are formed, a
+// matrix instruction to every seven vector instructions, so that one wave keeps both pipes busy.  (Phase
+// after phase, two waves on a SIMD took the sum of their vector and matrix time: they fall into step.)
+// FIXED: fix() has something to do in every step, not only in the first and the last.  Arguments as for
+// walk_keys below.
+template <class S, bool RING, bool FIXED, class KeyToken, class KeyEntry, class FixToken, class Fix>
+__device__ __forceinline__ void walk_keys_pipelined(const S &st, WaveAcc<S, 2> &a, const char *kb, const char *vb, int64_t rowB,
+                                                    unsigned char *wsm, int n, float c, bool careful, int lane, KeyToken key_token,
+                                                    KeyEntry key_entry, FixToken fix_token, Fix fix) {
+  static_assert(S::kDepth == 2, "two slots per ring");
+  constexpr int R = S::kReq, TL = RING ? 1 : 0;
+  if (n <= 0) return;
+  const uint32_t lds = __builtin_amdgcn_readfirstlane((uint32_t)(size_t)((__attribute__((address_space(3))) unsigned char *)wsm));
+  n = __builtin_amdgcn_readfirstlane(n);
+  constexpr int kV = 2 * S::kHalf;            // V ring behind the K ring
+  int *const ring = reinterpret_cast<int *>(wsm + kWaveRings);
+  auto request_tokens = [&](int i) {
+    const int32_t *src = key_entry(i);
+    asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dword %1, off"
+                 :: "s"(__builtin_amdgcn_readfirstlane(lds + kWaveRings + (uint32_t)(i & 3) * 256u)), "v"(src) : "memory", "m0");
+  };
+  constexpr int rpr = 32 / R;                 // rows per request
+  // places of K's and, one step behind, V's next rows
+  uint32_t tk[R], tv[R];
+  auto tokens = [&](int i) {
+    const uint32_t t = S::place(RING ? fix_token(i, lane & 31, ring[(i & 3) * 64 + (lane & 31)]) : key_token(i), rowB);
+#pragma unroll
+    for (int it = 0; it < R; it++) {
+      tv[it] = tk[it];
+      tk[it] = __shfl(t, it * rpr + st.rrow);
+    }
+  };
+  auto issue_k = [&](int slot) { const int o = slot * S::kHalf; st.issue_k(kb, rowB, tk, wsm + o, lds + o, lane); };
+  auto issue_v = [&](int slot, const uint32_t (&t)[R]) { const int o = kV + slot * S::kHalf; st.issue_v(vb, rowB, t, wsm + o, lds + o, lane); };
+
+  // order of requests: K0; K1 V0; K2 V1; then at the end of step i K(i+3) V(i+2)
+  if (RING) {
+#pragma unroll
+    for (int i = 0; i < 4; i++) request_tokens(i);
+    wait_vm<1>();
+  }
+  tokens(0);
+  issue_k(0);
+  if (n > 1) {
+    tokens(1);
+    issue_k(1);
+    issue_v(0, tv);
+  } else {
+    issue_v(0, tk);
+  }
+  f32x16 s0, s1;                              // logits of queries 0..31 and 32..63
+  typename S::K kf;
+  typename S::V vf;
+  // the output product behind: none yet
+  bf16x8 open = {};
+  vf.f[1][0] = vf.f[1][1] = open;
+  float l0[2] = {0.f, 0.f}, l1[2] = {0.f, 0.f};
+  // the first step's logits; then K2 takes its slot
+  if (n > 1) wait_vm<2 * R>();
+  else wait_vm<R>();
+  st.load_k(kf, wsm);
+  s0 = st.product(kf, a.q[0]);
+  fix(0, 0, s0);
+  a.reference(s0, 0, c);
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  if (n > 2) {
+    tokens(2);
+    issue_k(0);
+    if (RING) request_tokens(4);
+    issue_v(1, tv);
+  } else if (n > 1) {
+    issue_v(1, tk);
+  }
+  // a higher reference for half nt, whose output product is not the open one
+  auto raise = [&](int nt, const f32x16 &s) {
+    a.l[nt] = nt ? l1[0] + l1[1] : l0[0] + l0[1];
+    a.reference(s, nt, c);
+    if (nt) { l1[0] = a.l[1]; l1[1] = 0.f; } else { l0[0] = a.l[0]; l0[1] = 0.f; }
+  };
+  // step i, whose V is in slot `odd`; `odd` = i & 1 is a constant at each place of use
+  auto step = [&](int i, int odd) {
+    const int rem = n - 1 - i;
+    // K of step i + 1 and V of step i.  Behind them: K of step i + 2 (and a token request), V of step i + 1.
+    if (rem >= 2) wait_vm<2 * R + TL>();
+    else if (rem == 1) wait_vm<R>();
+    else wait_vm<0>();
+    const bool special = FIXED || careful || i == 0 || rem <= 1;
+    const unsigned char *vslot = wsm + kV + odd * S::kHalf;
+    st.load_v(vf, vslot, 0);
+    st.template half_step<true>(s0, c, -a.m[0], l0, a.o[0], a.o[1], open, vf, vslot, kf, a.q[1], s1);
+    if (special) {
+      fix(i, 1, s1);
+      if (careful || i == 0) raise(1, s1);
+    }
+    st.load_k(kf, wsm + (odd ^ 1) * S::kHalf);      // (behind the last step: what the slot holds, not used)
+    st.template half_step<false>(s1, c, -a.m[1], l1, a.o[1], a.o[0], open, vf, vslot, kf, a.q[0], s0);
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");       // both slots have been read
+    if (rem >= 3) {
+      tokens(i + 3);
+      issue_k(odd ^ 1);
+      if (RING) request_tokens(i + 5);
+      issue_v(odd, tv);
+    } else if (rem == 2) {
+      issue_v(odd, tk);
+    }
+    if (special && rem > 0) {
+      fix(i + 1, 0, s0);
+      if (careful) raise(0, s0);
+    }
+  };
+  for (int i = 0; i < n; i += 2) {
+    step(i, 0);
+    if (i + 1 < n) step(i + 1, 1);
+  }
+#pragma unroll
+  for (int dt = 0; dt < 2; dt++) a.o[1][dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf.f[1][dt], open, a.o[1][dt], 0, 0, 0);
+  a.l[0] = l0[0] + l0[1];
+  a.l[1] = l1[0] + l1[1];
+  wait_vm<0>();                               // (token requests past the end)
+}
 
 // n steps of a wave.  key_token(i): token of key `lane & 31` of step i; with RING the tokens are
 // read from memory instead: key_entry(i) is where that token stands, fix_token(i, row, tok) the last
@@ -393,36 +579,36 @@ struct WaveAcc {
 // requests complete in issue order, so the waits count how many younger ones may still be in flight.
 template <class S, int NT, bool WITH_V, bool RING, bool LO, int E, class KeyToken, class KeyEntry, class FixToken, class Fix>
 __device__ __forceinline__ void walk_keys(const S &st, WaveAcc<S, NT> &a, const char *kb, const char *vb, int64_t rowB,
-                                          unsigned char *wsm, int n, float c, int lane, KeyToken key_token,
+                                          unsigned char *wsm, int n, float c, bool careful, int lane, KeyToken key_token,
                                           KeyEntry key_entry, FixToken fix_token, Fix fix) {
   // (without V the K ring takes the whole space: twice the slots)
   constexpr int D = WITH_V ? S::kDepth : 2 * S::kDepth, R = S::kReq, TL = RING ? 1 : 0;
   if (n <= 0) return;
-  const uint32_t lds = (uint32_t)(size_t)((__attribute__((address_space(3))) unsigned char *)wsm);
+  const uint32_t lds = __builtin_amdgcn_readfirstlane((uint32_t)(size_t)((__attribute__((address_space(3))) unsigned char *)wsm));
+  n = __builtin_amdgcn_readfirstlane(n);
   constexpr int kV = D * S::kHalf;            // V ring behind the K ring
   int *const ring = reinterpret_cast<int *>(wsm + kWaveRings);
   auto request_tokens = [&](int i) {
     const int32_t *src = key_entry(i);
     asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dword %1, off"
-                 :: "s"(lds + kWaveRings + (uint32_t)(i & 3) * 256u), "v"(src) : "memory", "m0");
+                 :: "s"(__builtin_amdgcn_readfirstlane(lds + kWaveRings + (uint32_t)(i & 3) * 256u)), "v"(src) : "memory", "m0");
   };
   constexpr int rpr = 32 / R;                 // rows per request
-  int tok[R];
+  uint32_t at[R];                             // where the rows of this lane's requests stand
   auto tokens = [&](int i) {
     if (RING) {
+      // (lane l of each half turns the token of key l into its row's place)
+      const uint32_t t = S::place(fix_token(i, lane & 31, ring[(i & 3) * 64 + (lane & 31)]), rowB);
 #pragma unroll
-      for (int it = 0; it < R; it++) {
-        const int row = it * rpr + st.rrow;
-        tok[it] = fix_token(i, row, ring[(i & 3) * 64 + row]);
-      }
+      for (int it = 0; it < R; it++) at[it] = __shfl(t, it * rpr + st.rrow);
     } else {
-      const int t = key_token(i);
+      const uint32_t t = S::place(key_token(i), rowB);
 #pragma unroll
-      for (int it = 0; it < R; it++) tok[it] = __shfl(t, it * rpr + st.rrow);
+      for (int it = 0; it < R; it++) at[it] = __shfl(t, it * rpr + st.rrow);
     }
   };
-  auto issue_k = [&](int i) { const int o = (i % D) * S::kHalf; st.issue_k(kb, rowB, tok, wsm + o, lds + o, lane); };
-  auto issue_v = [&](int i) { const int o = kV + (i % D) * S::kHalf; if (WITH_V) st.issue_v(vb, rowB, tok, wsm + o, lds + o, lane); };
+  auto issue_k = [&](int slot) { const int o = slot * S::kHalf; st.issue_k(kb, rowB, at, wsm + o, lds + o, lane); };
+  auto issue_v = [&](int slot) { const int o = kV + slot * S::kHalf; if (WITH_V) st.issue_v(vb, rowB, at, wsm + o, lds + o, lane); };
 
   if (RING) {
 #pragma unroll
@@ -438,7 +624,8 @@ __device__ __forceinline__ void walk_keys(const S &st, WaveAcc<S, NT> &a, const 
       issue_v(i);
     }
   constexpr int kNext = D == 2 ? 2 * R : 0;   // requests of the step behind (two slots)
-  for (int i = 0; i < n; i++) {
+  // slot: i % D, a constant at each place of use
+  auto step = [&](int i, int slot) {
     const int rem = n - 1 - i;                // steps behind this one
     // K of step i.  Behind it with two slots: V of step i, the stores of the step before, K and V
     // of the next step and, in the ring, one token request; with one slot: V of step i.  (Without V:
@@ -466,28 +653,46 @@ __device__ __forceinline__ void walk_keys(const S &st, WaveAcc<S, NT> &a, const 
       }
     }
     f32x16 s[NT];
-    st.template logits<NT>(a.q, wsm + (i % D) * S::kHalf, s);
-    fix(i, s);
+    st.template logits<NT>(a.q, wsm + slot * S::kHalf, s);
+#pragma unroll
+    for (int nt = 0; nt < NT; nt++) fix(i, nt, s[nt]);
     if (rem >= D) {
       asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");     // the slot has been read
       tokens(i + D);
-      issue_k(i + D);
+      issue_k(slot);
       if (RING) request_tokens(i + D + 2);
     }
-    a.soften(s, c);
+#pragma unroll
+    for (int nt = 0; nt < NT; nt++) {
+      if (careful || i == 0) a.reference(s[nt], nt, c);
+      a.weights(s[nt], nt, c);
+    }
     if (WITH_V) {
       // V of step i.  Behind it: the next step (two slots), this step's stores, K of step i + D
       if (rem >= D) wait_vm<kNext + E + R + (D - 1) * TL>();
       else if (D == 2 && rem == 1) wait_vm<kNext + E>();
       else wait_vm<E>();
-      st.template weigh<NT, LO>(s, wsm + kV + (i % D) * S::kHalf, a.o, lane);
+      st.template weigh<NT, LO>(s, wsm + kV + slot * S::kHalf, a.o, lane);
       if (rem >= D) {
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-        issue_v(i + D);
+        issue_v(slot);
       }
     }
+  };
+  for (int i = 0; i < n; i += D) {
+    step(i, 0);
+    if (D > 1 && i + 1 < n) step(i + 1, 1);
+    if (D > 2 && i + 2 < n) step(i + 2, 2);
+    if (D > 3 && i + 3 < n) step(i + 3, 3);
   }
   wait_vm<0>();                               // (token requests past the end)
+}
+
+// a query tile's walk: pipelined where there are two slots
+template <class S, int NT, bool RING, bool FIXED, class... Args>
+__device__ __forceinline__ void window_walk(const S &st, WaveAcc<S, NT> &a, Args &&...args) {
+  if constexpr (S::kDepth == 2 && NT == 2) walk_keys_pipelined<S, RING, FIXED>(st, a, args...);
+  else walk_keys<S, NT, true, RING, false, 0>(st, a, args...);
 }
 
 // A wave's state -> LDS: output rows of 64 floats in its rings (16-byte chunk c of row r at c ^ (r & 15)),
@@ -559,19 +764,23 @@ __device__ __forceinline__ void global_rows_chunk(const GlobalRows &p, int heads
   // (the second set of columns and the rows past G write nothing)
   const bool writes = LOGITS && l32 < GR && g < G;
   float *lrow = LOGITS ? p.logits + ((size_t)(b * heads + h) * G + min(g, G - 1)) * T : nullptr;
-  walk_keys<S, 1, WITH_V, false, kBf16, LOGITS ? 16 : 0>(
-      st, a, kb, vb, rowB, wsm, n, c, lane, [&](int i) { return min(j0 + 128 * i + l32, T - 1); },
+  for (bool careful = false;; careful = true) {
+    walk_keys<S, 1, WITH_V, false, kBf16, LOGITS ? 16 : 0>(
+      st, a, kb, vb, rowB, wsm, n, c, careful, lane, [&](int i) { return min(j0 + 128 * i + l32, T - 1); },
       [](int) { return (const int32_t *)nullptr; }, [](int, int, int t) { return t; },
-      [&](int i, f32x16 (&s)[1]) {
+      [&](int i, int, f32x16 &s) {
         const int jb = j0 + 128 * i + 4 * hh;
         // (keys past the end are copies of the last one: their lanes store its logit once more)
         if (LOGITS && writes)
 #pragma unroll
-          for (int e = 0; e < 16; e++) store4(lrow + min(jb + 8 * (e >> 2) + (e & 3), T - 1), s[0][e] * lmul);
+          for (int e = 0; e < 16; e++) store4(lrow + min(jb + 8 * (e >> 2) + (e & 3), T - 1), s[e] * lmul);
         if (j0 + 128 * i + 32 > T)
 #pragma unroll
-          for (int e = 0; e < 16; e++) s[0][e] = jb + 8 * (e >> 2) + (e & 3) < T ? s[0][e] : -INFINITY;
+          for (int e = 0; e < 16; e++) s[e] = jb + 8 * (e >> 2) + (e & 3) < T ? s[e] : -INFINITY;
       });
+    if (careful || !a.overflowed()) break;
+    a.clear();
+  }
   float *ml = reinterpret_cast<float *>(smem + 4 * kWaveLds);
   park_state(a, wsm, ml + wave * 128, lane);
   __syncthreads();
@@ -619,7 +828,7 @@ struct WindowParams {
   WindowGeom g;
 };
 
-template <class S, int NT, bool LISTS, bool MASK>
+template <class S, int NT, bool LISTS, bool MASK, int KS>
 __device__ __forceinline__ void window_attention(const WindowParams &p, unsigned char *smem) {
   typedef typename S::elem elem;
   constexpr int QT = 32 * NT;
@@ -634,10 +843,16 @@ __device__ __forceinline__ void window_attention(const WindowParams &p, unsigned
       global_rows_chunk<S, true, false>(p.r, g.heads, g.n_global, g.tokens, g.global_groups, g.nchunks, blockIdx.x, smem, wave, lane);
     return;
   }
-  const int id = window_tile_id(g, blockIdx.x - g.global_wgs);
-  if (id >= g.tiles) return;
+  // waves part, part + 1, .. part + KS - 1 share a tile
+  const int part = wave & (KS - 1), id = window_tile_id(g, blockIdx.x - g.global_wgs) * (4 / KS) + wave / KS;
   WindowTile<LISTS, QT> w;
-  if (!w.init(g, id, lane)) return;
+  // (a wave without a tile takes part in the barrier below and touches no memory: with an empty tile
+  // there is no query slot, hence no token to look up)
+  const bool live = id < g.tiles && w.init(g, id, lane);
+  if (!live) {
+    if (KS == 4 || KS == 1) return;            // (with KS = 4 the whole workgroup returns)
+    w.b = w.h = w.qcnt = 0;
+  }
   const int l32 = lane & 31, hh = lane >> 5;
   const int64_t head = w.b * p.r.sb + w.h * p.r.sh, rowB = p.r.st * (int64_t)sizeof(elem);
   const char *qb = reinterpret_cast<const char *>(static_cast<const elem *>(p.r.q) + head);
@@ -647,9 +862,10 @@ __device__ __forceinline__ void window_attention(const WindowParams &p, unsigned
   float *ml = reinterpret_cast<float *>(smem + 4 * kWaveLds);
   S st;
   st.init(lane);
-  const int steps = (w.nkeys + 31) / 32, n = steps > wave ? (steps - wave + 3) / 4 : 0;
   WaveAcc<S, NT> a;
   a.clear();
+  if (KS != 2 || live) {
+  const int steps = (w.nkeys + 31) / 32, n = steps > part ? (steps - part + KS - 1) / KS : 0;
   const float inv_block = 1.f / (float)g.block;
   uint32_t qcode[NT];
 #pragma unroll
@@ -658,49 +874,70 @@ __device__ __forceinline__ void window_attention(const WindowParams &p, unsigned
     if (MASK) qcode[nt] = w.query_code(g, 32 * nt + l32, inv_block);
   }
   uint32_t *const codes = reinterpret_cast<uint32_t *>(wsm + kWaveRings + 1024);
-  auto key0 = [&](int i) { return 32 * (4 * i + wave); };       // first key of this wave's step i
-  walk_keys<S, NT, true, LISTS, false, 0>(
-      st, a, kb, vb, rowB, wsm, n, kBf16 ? p.r.scale * kLog2e : kLog2e, lane,
+  auto key0 = [&](int i) { return 32 * (KS * i + part); };       // first key of this wave's step i
+  // (squares of several blocks: a query may see none of a step's keys, so only a first step with the
+  // global tokens in it gives a reference)
+  for (bool careful = MASK && part != 0;; careful = true) {
+    window_walk<S, NT, LISTS, MASK>(
+      st, a, kb, vb, rowB, wsm, n, kBf16 ? p.r.scale * kLog2e : kLog2e, careful, lane,
       [&](int i) { return w.key(g, key0(i) + l32); }, [&](int i) { return w.key_entry(g, key0(i) + l32); },
       [&](int i, int row, int t) { return key0(i) + row < g.n_global ? key0(i) + row : t; },
-      [&](int i, f32x16 (&s)[NT]) {
+      [&](int i, int nt, f32x16 &s) {
         if (MASK) {
-          codes[l32] = w.key_code(g, key0(i) + l32, inv_block);
-          asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+          if (nt == 0) {
+            codes[l32] = w.key_code(g, key0(i) + l32, inv_block);
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+          }
 #pragma unroll
           for (int q4 = 0; q4 < 4; q4++) {
             const uint4 kc = *reinterpret_cast<const uint4 *>(codes + 8 * q4 + 4 * hh);
             const uint32_t k4[4] = {kc.x, kc.y, kc.z, kc.w};
 #pragma unroll
-            for (int e = 0; e < 4; e++)
-#pragma unroll
-              for (int nt = 0; nt < NT; nt++)
-                s[nt][4 * q4 + e] = (k4[e] & ~qcode[nt]) == 0 ? s[nt][4 * q4 + e] : -INFINITY;
+            for (int e = 0; e < 4; e++) s[4 * q4 + e] = (k4[e] & ~qcode[nt]) == 0 ? s[4 * q4 + e] : -INFINITY;
           }
         } else if (key0(i) + 32 > w.nkeys) {
           const int jb = key0(i) + 4 * hh;
 #pragma unroll
-          for (int e = 0; e < 16; e++)
-#pragma unroll
-            for (int nt = 0; nt < NT; nt++) s[nt][e] = jb + 8 * (e >> 2) + (e & 3) < w.nkeys ? s[nt][e] : -INFINITY;
+          for (int e = 0; e < 16; e++) s[e] = jb + 8 * (e >> 2) + (e & 3) < w.nkeys ? s[e] : -INFINITY;
         }
       });
+    if (careful || !a.overflowed()) break;
+    a.clear();
+  }
+  }
+  elem *ob = static_cast<elem *>(p.out) + w.b * p.osb + w.h * p.osh;
+  if (KS == 1) {
+    // lane (query, hh) owns channels 32*dt + 8*ig + 4*hh + 0..3
+#pragma unroll
+    for (int nt = 0; nt < NT; nt++) {
+      const float inv = 1.f / half_swap_sum(a.l[nt]);
+      if (32 * nt + l32 >= w.qcnt) continue;
+      elem *row = ob + (int64_t)w.query(g, 32 * nt + l32) * p.ost + 4 * hh;
+#pragma unroll
+      for (int dt = 0; dt < 2; dt++)
+#pragma unroll
+        for (int ig = 0; ig < 4; ig++)
+          S::store4out(row + 32 * dt + 8 * ig, f32x4{a.o[nt][dt][4 * ig] * inv, a.o[nt][dt][4 * ig + 1] * inv,
+                                                     a.o[nt][dt][4 * ig + 2] * inv, a.o[nt][dt][4 * ig + 3] * inv});
+    }
+    return;
+  }
   park_state(a, wsm, ml + wave * 128, lane);
   __syncthreads();
-  // merge in wave order, normalise, store: 16 lanes per row
-  elem *ob = static_cast<elem *>(p.out) + w.b * p.osb + w.h * p.osh;
+  // merge in wave order, normalise, store: 16 lanes per row, 4 KS rows of the tile per pass
+  const int w0 = wave & ~(KS - 1);             // first wave of this tile
 #pragma unroll
-  for (int ps = 0; ps < QT / 16; ps++) {
-    const int row = 16 * ps + 4 * wave + (lane >> 4), ch = lane & 15;
-    float M = ml[2 * row], L = 0.f;
+  for (int ps = 0; ps < QT / (4 * KS); ps++) {
+    const int row = 4 * KS * ps + 4 * part + (lane >> 4), ch = lane & 15;
+    float M = ml[w0 * 128 + 2 * row], L = 0.f;
 #pragma unroll
-    for (int x = 1; x < 4; x++) M = fmaxf(M, ml[x * 128 + 2 * row]);
+    for (int x = 1; x < KS; x++) M = fmaxf(M, ml[(w0 + x) * 128 + 2 * row]);
     f32x4 O = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int x = 0; x < 4; x++) {
-      const float f = __builtin_amdgcn_exp2f(ml[x * 128 + 2 * row] - M);     // 0 for a wave without keys
-      L = __builtin_fmaf(f, ml[x * 128 + 2 * row + 1], L);
-      const f32x4 v = parked(smem, x, row, ch);
+    for (int x = 0; x < KS; x++) {
+      const float f = __builtin_amdgcn_exp2f(ml[(w0 + x) * 128 + 2 * row] - M);     // 0 for a wave without keys
+      L = __builtin_fmaf(f, ml[(w0 + x) * 128 + 2 * row + 1], L);
+      const f32x4 v = parked(smem, w0 + x, row, ch);
 #pragma unroll
       for (int e = 0; e < 4; e++) O[e] = __builtin_fmaf(f, v[e], O[e]);
     }
@@ -709,9 +946,41 @@ __device__ __forceinline__ void window_attention(const WindowParams &p, unsigned
   }
 }
 
+// Mean length of a side of the squares' key rectangles.
+inline double mean_reach(int grid, int side, int block) {
+  double sum = 0;
+  int n = 0;
+  for (int i = 0; i * side < grid; i++, n++) sum += std::min((i + 1) * side + block, grid) - std::max(i * side - block, 0);
+  return sum / n;
+}
+
+// What a launch with `ks` waves per tile costs, in steps of one wave: the mean walk of a wave and what its start
+// and end cost (3 to 4.2 steps), times the workgroups that share a CU: the first takes 1.07 us a step (it has nobody
+// to hide its latencies behind), every further one adds 0.65.
+struct WindowCost {
+  double tiles, steps;     // tiles that exist, mean 32-key steps of a tile
+  double of(int ks) const {
+    const double per_cu = tiles * ks / 4.0 / device_cu_count();
+    return 0.65 * (std::max(per_cu, 1.0) + 0.65) * (std::max(steps / ks, 1.0) + (ks == 4 ? 4.2 : (ks == 2 ? 3.7 : 3.0)));
+  }
+  // Waves per tile.  One wave per tile does the least work (no merge, one start), four fill the chip when there
+  // are few tiles and shorten the walk when it is long.  (Measured with each forced over grids of 14 to 248 a
+  // side: the choice is within a few per cent of the best.)
+  int split() const { return of(4) <= of(2) && of(4) <= of(1) ? 4 : (of(2) <= of(1) ? 2 : 1); }
+};
+inline WindowCost window_cost(const ns_attn_desc &d, int qt) {
+  const int side = d.block > 4 ? d.block : d.block * (8 / d.block);
+  const int nh = d.grid_h / side, nw = d.grid_w / side, eh = d.grid_h % side, ew = d.grid_w % side;
+  const double full = d.coords ? (double)(d.tokens - d.n_global) / ((double)d.grid_h * d.grid_w) : 1.0;
+  auto runs = [&](int h, int w) { return std::ceil(full * h * w / qt); };
+  const double per_image = (double)nh * nw * runs(side, side) + nw * runs(eh, side) + nh * runs(side, ew) + runs(eh, ew);
+  return WindowCost{per_image * d.batch * d.heads,
+                    (full * mean_reach(d.grid_h, side, d.block) * mean_reach(d.grid_w, side, d.block) + d.n_global) / 32.0 + 0.5};
+}
+
 // The geometry on the host; qt = queries per tile, rows_per_group = global rows that one global
 // workgroup handles (0: no global rows in this launch).  Workgroups to launch, or -1.
-inline long long window_geometry(const AttnArgs &a, int qt, int rows_per_group, int nchunks, WindowGeom &g) {
+inline long long window_geometry(const AttnArgs &a, int qt, int rows_per_group, int nchunks, WindowGeom &g, int &ks) {
   const ns_attn_desc &d = a.d;
   const bool lists = d.coords != nullptr;
   g.grid_h = d.grid_h; g.grid_w = d.grid_w; g.block = d.block; g.n_global = d.n_global; g.tokens = d.tokens;
@@ -728,7 +997,8 @@ inline long long window_geometry(const AttnArgs &a, int qt, int rows_per_group, 
   if (tiles > 0x7ffffff0LL || live > 0x7ffffff0LL) return -1;
   g.tiles_per_image = (int)per_image;
   g.tiles = (int)tiles;
-  g.per_xcd = (int)((tiles + 7) / 8);
+  ks = a.split ? a.split : window_cost(d, qt).split();
+  g.per_xcd = (int)((tiles * ks + 31) / 32);
   g.global_groups = groups;
   g.nchunks = nchunks;
   g.global_live = (int)live;
@@ -739,12 +1009,12 @@ inline long long window_geometry(const AttnArgs &a, int qt, int rows_per_group, 
 
 // The launch arguments; logits, partials: of the global rows, NULL partials = patch queries only
 template <class S, int NT>
-inline long long window_params(const AttnArgs &a, float *logits, float *partials, WindowParams &p) {
+inline long long window_params(const AttnArgs &a, float *logits, float *partials, WindowParams &p, int &ks) {
   const ns_attn_desc &d = a.d;
   p.r = GlobalRows{a.q, a.k, a.v, d.q_stride_b, d.q_stride_h, d.q_stride_t, d.scale, logits, partials};
   p.out = a.out;
   p.osb = d.out_stride_b; p.osh = d.out_stride_h; p.ost = d.out_stride_t;
-  return window_geometry(a, 32 * NT, partials ? global_group_rows<S>() : 0, cls_num_chunks(d.tokens), p.g);
+  return window_geometry(a, 32 * NT, partials ? global_group_rows<S>() : 0, cls_num_chunks(d.tokens), p.g, ks);
 }
 
 }  // namespace ns
