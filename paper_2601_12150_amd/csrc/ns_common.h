@@ -114,6 +114,10 @@ __device__ __forceinline__ int opaque(int x) {
   return x;
 }
 
+// a / d for 0 <= a < 2^21 with inv = 1.f / d: the quotient's fraction is at least 0.5 / d away from an
+// integer after adding 0.5, more than the two roundings can move it
+__device__ __forceinline__ int div_small(int a, float inv) { return (int)(((float)a + 0.5f) * inv); }
+
 // max / sum of a value over the two half-waves (lane l and lane l ^ 32); both lanes get it
 __device__ __forceinline__ float half_swap_max(float x) {
   auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
@@ -214,10 +218,12 @@ ns_status launch_cls_combine_scores(const ns_attn_desc &d, const float *partials
 ns_status launch_cls_scores(int B, int H, int T, int G, const float *logits, const float *lse,
                             const float *partials, int nchunks, float *scores, hipStream_t s);
 
-// linear map with fused epilogue, 256 x 256 workgroup tiles (ns_gemm256.hip)
+// linear map with fused epilogue, 256 x 256 workgroup tiles (ns_gemm256.hip); batch: so many of them with the
+// same weights, bias and residual in one launch, rows and results at the given distances in elements
 bool gemm256_supported(int M, int N, int K);
 ns_status launch_gemm256(const uint16_t *a, const uint16_t *w, const float *bias, const uint16_t *r,
-                         uint16_t *c, int M, int N, int K, bool gelu, hipStream_t s);
+                         uint16_t *c, int M, int N, int K, bool gelu, hipStream_t s, int batch = 1,
+                         long long a_stride = 0, long long c_stride = 0);
 
 // ws: topk_select_workspace_bytes(B, N) bytes, 16-byte aligned (nothing for short score rows)
 size_t topk_select_workspace_bytes(int B, int N);

@@ -40,6 +40,8 @@ struct Gemm256Params {
   int extended;      // the last row tile has 288 rows
   int n256;          // the first n256 rows of tiles have 256 token rows, the others 192 (three slabs per wave):
                      // the mix that fills the chip's rounds of workgroups best
+  int batch;         // products of the same w, bias and r: a and c of the next one follow at these distances
+  long long a_stride, c_stride;   // in elements
 };
 
 constexpr int kStageW = 256 * 128;           // bytes: 256 weight rows x 64 k
@@ -267,11 +269,19 @@ __global__ __launch_bounds__(256) void gemm256_bf16_kernel(Gemm256Params p) {
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   // workgroups are dealt round-robin to the 8 XCDs; give each XCD a contiguous run of tiles (n
   // fastest) so that the tiles sharing token rows and the weight matrix meet in one L2
-  const int total = p.ntn * p.ntm;
+  const int total = p.ntn * p.ntm * p.batch;
   int bid = blockIdx.x;
   const bool uniform = p.n256 == 0 || p.n256 == p.ntm;     // (a mix of tile heights keeps the launch order: tall tiles first)
   if (uniform && total % 8 == 0) bid = (bid & 7) * (total / 8) + (bid >> 3);
-  const int bm = bid / p.ntn, bn = bid - bm * p.ntn;
+  int bm = bid / p.ntn;
+  const int bn = bid - bm * p.ntn;
+  if (p.batch > 1) {         // (the tall tiles of all products first)
+    const int tall = p.batch * p.n256, per = bm < tall ? p.n256 : p.ntm - p.n256, x = bm < tall ? bm : bm - tall;
+    const int z = __builtin_amdgcn_readfirstlane(x / per);
+    p.a += z * p.a_stride;
+    p.c += z * p.c_stride;
+    bm = (bm < tall ? 0 : p.n256) + x - z * per;
+  }
   const int tm = bm < p.n256 ? 256 : 192;
   const int m0 = bm < p.n256 ? bm * 256 : p.n256 * 256 + (bm - p.n256) * 192, n0 = bn * 256;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -311,11 +321,12 @@ bool gemm256_supported(int M, int N, int K) {
 }
 
 ns_status launch_gemm256(const uint16_t *a, const uint16_t *w, const float *bias, const uint16_t *r,
-                         uint16_t *c, int M, int N, int K, bool gelu, hipStream_t s) {
+                         uint16_t *c, int M, int N, int K, bool gelu, hipStream_t s, int batch,
+                         long long a_stride, long long c_stride) {
   if (!gemm256_supported(M, N, K)) return fail(NS_ERR_UNSUPPORTED, "GEMM shape M=%d N=%d K=%d", M, N, K);
   if ((long long)M * K * 2 >= 0x7fffffffLL || (long long)N * K * 2 >= 0x7fffffffLL)
     return fail(NS_ERR_UNSUPPORTED, "GEMM operand beyond 2 GiB");
-  Gemm256Params p{a, w, r, bias, c, M, N, K, gelu ? 1 : 0, N / 256, 0, 0, 0};
+  Gemm256Params p{a, w, r, bias, c, M, N, K, gelu ? 1 : 0, N / 256, 0, 0, 0, batch, a_stride, c_stride};
   const int q = M / 256, rem = M % 256;
   p.extended = (rem > 0 && rem <= 32) ? 1 : 0;
   p.ntm = (rem == 0 || p.extended) ? q : q + 1;
@@ -328,8 +339,8 @@ ns_status launch_gemm256(const uint16_t *a, const uint16_t *w, const float *bias
     auto makespan = [&](long long na, long long nb) -> double {
       // na*ntn tiles of cost 1.0, then nb*ntn of cost 0.8, each given to the unit that is free first.
       // After the tall tiles n2 units are free at t2 and the other n1 one tile time earlier, at t1.
-      const long long ta = na * p.ntn;
-      long long left = nb * p.ntn;
+      const long long ta = na * p.ntn * batch;
+      long long left = nb * p.ntn * batch;
       const long long n2 = ta % cus, n1 = cus - n2;
       double t1 = (double)(ta / cus), t2 = t1 + 1.0;
       double end = n2 ? t2 : t1;
@@ -357,7 +368,7 @@ ns_status launch_gemm256(const uint16_t *a, const uint16_t *w, const float *bias
     }
     if (best_b > 0) { p.n256 = best_a; p.ntm = best_a + best_b; p.extended = 0; }
   }
-  const long long wgs = (long long)p.ntm * p.ntn;
+  const long long wgs = (long long)p.ntm * p.ntn * batch;
   if (wgs > 0x7fffffffLL) return fail(NS_ERR_UNSUPPORTED, "GEMM grid too large");
   typedef void (*kern_t)(Gemm256Params);
   static const kern_t kerns[4] = {gemm256_bf16_kernel<false, false>, gemm256_bf16_kernel<false, true>,

@@ -32,10 +32,6 @@ struct WindowGeom {
   const int32_t *lists, *counts;
 };
 
-// a / d for 0 <= a < 2^21 with inv = 1.f / d: the quotient's fraction is at least 0.5 / d away from an
-// integer after adding 0.5, more than the two roundings can move it
-__device__ __forceinline__ int div_small(int a, float inv) { return (int)(((float)a + 0.5f) * inv); }
-
 // Tile of a workgroup: everything is wave-uniform except what the token functions return.
 template <bool LISTS, int QT>
 struct WindowTile {

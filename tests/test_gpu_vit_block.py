@@ -217,7 +217,10 @@ def test_stack_pruning_of_a_long_sequence(nb):
 
 
 @pytest.mark.parametrize("B,ch,gh,gw,ps,dim", [(2, 3, 20, 24, 14, 512), (1, 3, 16, 16, 16, 1024), (1, 1, 3, 5, 7, 128),
-                                               (3, 3, 1, 1, 14, 256), (1, 3, 40, 33, 14, 1024)])
+                                               (3, 3, 1, 1, 14, 256), (1, 3, 40, 33, 14, 1024),
+                                               # odd patch side and pixels (2-byte path); batches whose images have more than one
+                                               # row of tiles; one patch that takes more than 64 KB
+                                               (2, 3, 17, 19, 15, 256), (3, 1, 26, 31, 16, 512), (1, 3, 2, 3, 106, 128)])
 def test_patch_embedding_matches_oracle(nb, B, ch, gh, gw, ps, dim):
     """Tokenisation: 14-pixel patches (588 columns, padded to 640 inside) and 16-pixel patches (768),
     grids from one patch to more than a thousand, the CLS row, position embeddings as residual."""
