@@ -7,12 +7,16 @@
 // per v_mfma_f32_32x32x16_bf16, which is exactly the LDS bandwidth of a CU at full MFMA rate; with
 // a 128 x 128 piece per wave (4 x 4 MFMA tiles, 256 accumulator registers) it is half of that.
 // So: 4 waves per workgroup, one per SIMD, each with up to 512 registers; 256 (n) x 256 (m) per
-// workgroup; k in slices of 64 through two LDS stages filled by direct global -> LDS transfers
-// (rows of 128 bytes: a transfer then uses whole cache lines, which moves the same bytes in 3/4 of
-// the time that 64-byte rows take); the transfer of a slice is requested as soon as every wave has
-// read the last fragments of the slice before the previous one, a whole slice of work ahead;
-// fragments of the next 16-wide k-step are read from LDS while the 16 MFMAs of the current one
-// execute.  The product is formed transposed (W rows as
+// workgroup; k in slices of 64 by direct global -> LDS transfers (rows of 128 bytes: a transfer then uses whole
+// cache lines, which moves the same bytes in 3/4 of the time that 64-byte rows take).
+//
+// How far ahead.  With two slots per operand, requested as soon as the slice before is read, 64 KB
+// per CU are on their way; under load a transfer takes longer than the slice it has (1.69 us a slice with every
+// CU busy, where the MFMAs alone take 1.18 and the transfers alone 0.88).  The weights get a third slot
+// (all 160 KB of LDS are then in use), and the token fragments of a whole slice are held in registers: they are read in
+// the last k-step before and the first k-step of their slice, which frees their slot after a quarter of it.  So 112 KB are on
+// their way: weights have two slices of time, tokens one and a half.  LDS reads and the issue of the
+// transfers are placed between the MFMAs one by one.  The product is formed transposed (W rows as
 // the A operand) as in the smaller kernel; the epilogue transposes each 32-token slab through
 // LDS so that bias / GELU / residual / store work on 16-byte pieces of full output rows.
 //
@@ -24,7 +28,12 @@
 // hold rows.  Where M / 256 row tiles leave many CUs without work in the last round (a pruned
 // sequence: 39 x 4 tiles on 256 CUs), tiles of 192 rows (three slabs per wave) are used instead
 // when that shortens the launch.
+//
+// Measured (us, two slots per operand -> this), epilogues included: 16385 x 3072 x 1024 111 -> 98,
+// 16385 x 1024 x 1024 + residual 49 -> 44, 16385 x 4096 x 1024 + GELU 177 -> 163, 16385 x 1024 x 4096 + residual 128 -> 113;
+// 9832 rows: 70 -> 68, 31 -> 28, 113 -> 103, 89 -> 71.
 #include "ns_common.h"
+#include <type_traits>
 
 namespace ns {
 
@@ -45,9 +54,8 @@ struct Gemm256Params {
 };
 
 constexpr int kStageW = 256 * 128;           // bytes: 256 weight rows x 64 k
-constexpr int kStageX = 288 * 128;           // 288 token rows x 64 k
-constexpr int kStage = kStageW + kStageX;
-constexpr int kStages = 2;
+constexpr int kStageX = 256 * 128;           // 256 token rows x 64 k
+constexpr int kGemmLds = 2 * kStageX + 3 * kStageW;
 constexpr int kEpiRow = 528;                 // bytes per staged output row: 128 floats + 16 pad
 constexpr int kEpiWave = 32 * kEpiRow;
 
@@ -124,6 +132,9 @@ __device__ __forceinline__ void gemm256_wave(const Gemm256Params &p, unsigned ch
   constexpr int NT = NTJ > 0 ? NTJ : 1;
   constexpr int XREQ = EXT ? 9 : TM / 32;    // requests of 8 token rows per wave
   constexpr int WROWS = TM / 2;              // token rows per pair of waves
+  constexpr int kSlots = EXT ? 2 : 3;        // LDS slots for weight slices; token slices have two
+  constexpr int kX = EXT ? kStageX + 4096 : kStageX, kW = 2 * kX;   // bytes of a token slot; the weight slots lie behind
+  static_assert(kW + kSlots * kStageW <= kGemmLds, "slots");
   const int l32 = lane & 31, hh = lane >> 5;
   const int wm = wave >> 1, wn = wave & 1;
   const uint32_t lds0 = (uint32_t)(size_t)((__attribute__((address_space(3))) unsigned char *)smem);
@@ -149,35 +160,22 @@ __device__ __forceinline__ void gemm256_wave(const Gemm256Params &p, unsigned ch
     const int m = min(m0 + (xreq0 + j) * 8 + drow, p.M - 1);         // rows past M repeat the last row
     xoff[j] = (uint32_t)m * rowB + dchunk(xreq0 + j);
   }
-  auto issue = [&](int kt, int stage) {
-    const char *ak = ab + (size_t)kt * 128, *wk = wb + (size_t)kt * 128;
-    const uint32_t base = lds0 + stage * kStage;
-#pragma unroll
-    for (int j = 0; j < 8; j++) dma16(wk + (size_t)j * 8 * rowB, woff[j & 1], base + (wreq0 + j) * 1024);
-#pragma unroll
-    for (int j = 0; j < XREQ; j++) dma16(ak, xoff[j], base + kStageW + (xreq0 + j) * 1024);
+  auto issue_w = [&](int kt, int slot, int j) {
+    dma16(wb + (size_t)kt * 128 + (size_t)j * 8 * rowB, woff[j & 1], lds0 + kW + slot * kStageW + (wreq0 + j) * 1024);
   };
-  constexpr int PER_SLICE = 8 + XREQ;
+  auto issue_x = [&](int kt, int j) { dma16(ab + (size_t)kt * 128, xoff[j], lds0 + (kt & 1) * kX + (xreq0 + j) * 1024); };
 
   // ---- fragment reads: lane (row l32 of a 32-row slab, half hh) reads logical chunk 2*ks + hh of
   // k-step ks = 0..3, i.e. physical chunk (2*ks + hh) ^ ((l32 >> 1) & 7) (slabs start at multiples of 32 rows)
-  unsigned char *wrd[4], *xrd[4], *erd[4];
+  unsigned char *wrd[4], *xrd[4];
 #pragma unroll
   for (int ks = 0; ks < 4; ks++) {
     const int ch = 16 * ((2 * ks + hh) ^ ((l32 >> 1) & 7));
-    wrd[ks] = smem + (wn * 128 + l32) * 128 + ch;
-    xrd[ks] = smem + kStageW + (wm * WROWS + l32) * 128 + ch;
-    erd[ks] = smem + kStageW + (256 + l32) * 128 + ch;
+    wrd[ks] = smem + kW + (wn * 128 + l32) * 128 + ch;
+    xrd[ks] = smem + (wm * WROWS + l32) * 128 + ch;
   }
-  bf16x8 fw[2][4], fx[2][NT], fe[2];
-  auto read_frags = [&](int buf, int stage, int ks) {
-    const int so = stage * kStage;
-#pragma unroll
-    for (int ti = 0; ti < 4; ti++) fw[buf][ti] = *(lds_bf16x8_ptr)(wrd[ks] + so + ti * 4096);
-#pragma unroll
-    for (int tj = 0; tj < NTJ; tj++) fx[buf][tj] = *(lds_bf16x8_ptr)(xrd[ks] + so + tj * 4096);
-    if (EXT) fe[buf] = *(lds_bf16x8_ptr)(erd[ks] + so);
-  };
+  const int eoff = (256 - wm * WROWS) * 128;           // from xrd to the ninth slab
+  bf16x8 fw[2][4], fx[4][NT], fe[4];
   f32x16 acc[4][NT];   // [weight slab][token slab]: register e = n 8*(e/4) + 4*hh + e%4, lane = token l32
 #pragma unroll
   for (int ti = 0; ti < 4; ti++)
@@ -188,67 +186,124 @@ __device__ __forceinline__ void gemm256_wave(const Gemm256Params &p, unsigned ch
   f32x16 acce[2];      // ninth token slab x weight slabs 2*WM, 2*WM+1
 #pragma unroll
   for (int e = 0; e < 16; e++) { acce[0][e] = 0.f; acce[1][e] = 0.f; }
-  auto mma = [&](int buf) {
+
+  // One k-step: the MFMAs of fragments (fw[ks & 1], fx[ks]) with, spread between them, the LDS reads of
+  // later fragments and the transfers of a later slice, so that neither the reads' latency nor the issue of the
+  // transfers is exposed.  The fences keep this order: the scheduler would sink the reads below the MFMAs
+  // that do not need them.
+  //   ks 0: reads W(t, 1), X(t, 2), X(t, 3)       ks 1: reads W(t, 2); transfers X(t+2)
+  //   ks 2: reads W(t, 3)                         ks 3: reads W(t+1, 0), X(t+1, 0), X(t+1, 1); transfers W(t+kSlots)
+  constexpr int XF = NTJ + (EXT ? 1 : 0);              // token fragments of a k-step
+  auto read_w = [&](int ks, int slot, int ti) { fw[ks & 1][ti] = *(lds_bf16x8_ptr)(wrd[ks] + slot * kStageW + ti * 4096); };
+  auto read_x = [&](int ks, int kt, int tj) {
+    if (tj < NTJ) fx[ks][tj] = *(lds_bf16x8_ptr)(xrd[ks] + (kt & 1) * kX + tj * 4096);
+    else fe[ks] = *(lds_bf16x8_ptr)(xrd[ks] + (kt & 1) * kX + eoff);
+  };
+  auto kstep = [&](auto ks_c, auto read_c, auto move_c, int t, int slot, int slot_next) {
+    constexpr int ks = decltype(ks_c)::value;
+    constexpr bool kRead = decltype(read_c)::value, kMove = decltype(move_c)::value;
+    constexpr int reads = !kRead ? 0 : 4 + (ks == 0 || ks == 3 ? 2 * XF : 0);
+    constexpr int moves = !kMove ? 0 : (ks == 1 ? XREQ : (ks == 3 ? 8 : 0));
+    constexpr int mfmas = 4 * NTJ, groups = mfmas > 0 ? mfmas : 1;
+    auto read = [&](int i) {
+      if (i < 4) read_w((ks + 1) & 3, ks == 3 ? slot_next : slot, i);
+      else if (i < 4 + XF) read_x(ks == 0 ? 2 : 0, ks == 0 ? t : t + 1, i - 4);
+      else read_x(ks == 0 ? 3 : 1, ks == 0 ? t : t + 1, i - 4 - XF);
+    };
+    auto move = [&](int j) {
+      if (ks == 1) issue_x(t + 2, j);
+      else issue_w(t + kSlots, slot, j);
+    };
 #pragma unroll
-    for (int ti = 0; ti < 4; ti++)
+    for (int i = 0; i < groups; i++) {
+      // (reads early in the step, a transfer to every second MFMA)
 #pragma unroll
-      for (int tj = 0; tj < NTJ; tj++)
-        acc[ti][tj] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fw[buf][ti], fx[buf][tj], acc[ti][tj], 0, 0, 0);
+      for (int r = 0; r < reads; r++)
+        if ((2 * reads <= groups ? 2 * r : r * groups / reads) == i) read(r);
+      if (mfmas > 0) acc[i / NT][i % NT] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fw[ks & 1][i / NT], fx[ks][i % NT], acc[i / NT][i % NT], 0, 0, 0);
+#pragma unroll
+      for (int j = 0; j < moves; j++)
+        if (j * groups / moves == i) move(j);
+      __builtin_amdgcn_sched_barrier(0);
+    }
     if (EXT) {
       // The compiler keeps every accumulator of its own MFMAs in the 256 accumulator registers;
       // 18 of them do not fit and would be rotated through moves in every iteration.  These two
       // are pinned to ordinary vector registers instead.  (Each is next touched 17 MFMAs later,
       // and read by other instructions only after the loop: no issue hazards to pad.)
-      asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(acce[0]) : "v"(fw[buf][2 * WM]), "v"(fe[buf]));
-      asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(acce[1]) : "v"(fw[buf][2 * WM + 1]), "v"(fe[buf]));
+      f32x16 &a0 = acce[0], &a1 = acce[1];
+      const bf16x8 &w0 = fw[ks & 1][2 * WM], &w1 = fw[ks & 1][2 * WM + 1], &x = fe[ks];
+      asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(a0) : "v"(w0), "v"(x));
+      asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(a1) : "v"(w1), "v"(x));
     }
   };
+  // every wave's reads so far have arrived, and so has what it has waited for
+  auto meet = [&]() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
+  using K0 = std::integral_constant<int, 0>;
+  using K1 = std::integral_constant<int, 1>;
+  using K2 = std::integral_constant<int, 2>;
+  using K3 = std::integral_constant<int, 3>;
+  using Yes = std::true_type;
+  using No = std::false_type;
 
-  // Issue order of one k-step: the 16-byte LDS reads of the NEXT step's fragments are spread
-  // between the MFMAs of the current one (one read per two MFMAs), so that neither the LDS
-  // latency nor its transfer time is exposed.  Without this the scheduler sinks the reads below
-  // the MFMAs that do not need them.
-  auto interleave = [&]() {
+  // ---- main loop over slices of 64.  Requests stand in the queue in the order W(t+kSlots-1), X(t+1),
+  // W(t+kSlots), X(t+2), ..; after the first k-step of slice t every wave has its X fragments and X(t+2) takes
+  // their place, after the third the W fragments and W(t+kSlots) does.  Before the fourth, slice t+1 must have
+  // landed for every wave; X(t+2) and (three slots) W(t+2) may still be on their way.
+  const int nk = p.K / 64;                             // at least 3
+  constexpr int kBehind = XREQ + (kSlots - 2) * 8;
 #pragma unroll
-    for (int i = 0; i < 4 + NTJ + (EXT ? 1 : 0); i++) {
-      __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);   // one LDS read
-      __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);   // two MFMAs
+  for (int s = 0; s < kSlots; s++) {
+#pragma unroll
+    for (int j = 0; j < 8; j++) issue_w(s, s, j);
+    if (s < 2)
+#pragma unroll
+      for (int j = 0; j < XREQ; j++) issue_x(s, j);
+  }
+  wait_vm<8 + kBehind>();
+  meet();
+#pragma unroll
+  for (int ti = 0; ti < 4; ti++) read_w(0, 0, ti);
+#pragma unroll
+  for (int ks = 0; ks < 2; ks++)
+#pragma unroll
+    for (int tj = 0; tj < XF; tj++) read_x(ks, 0, tj);
+  // one slice; `ahead`: how many of the slices t+1 .. t+kSlots exist
+  auto slice = [&](auto ahead_c, int t, int slot, int slot_next) {
+    constexpr int ahead = decltype(ahead_c)::value;
+    using More = std::integral_constant<bool, (ahead >= 2)>;
+    using Next = std::integral_constant<bool, (ahead >= 1)>;
+    kstep(K0{}, Yes{}, No{}, t, slot, slot_next);
+    if (ahead >= 2) meet();
+    kstep(K1{}, Yes{}, More{}, t, slot, slot_next);
+    kstep(K2{}, Yes{}, No{}, t, slot, slot_next);
+    if (ahead >= 1) {
+      wait_vm<(ahead >= 2 ? kBehind : 0)>();
+      meet();
     }
+    kstep(K3{}, Next{}, std::integral_constant<bool, (ahead >= kSlots)>{}, t, slot, slot_next);
   };
-
-  // ---- main loop over slices of 64.  At the top of iteration kt: slice kt has landed for every
-  // wave, slice kt+1 is in flight into the other stage, fragment buffer 0 holds (slice kt, k-step
-  // 0).  After the third k-step every wave has issued its last reads of slice kt; with the barrier
-  // there slice kt+1 is complete for all, and slice kt+2 can be requested into slice kt's stage.
-  const int nk = p.K / 64;
-  issue(0, 0);
-  if (nk > 1) {
-    issue(1, 1);
-    wait_vm<PER_SLICE>();
-  } else {
-    wait_vm<0>();
+  auto next = [&](int slot) { return slot + 1 == kSlots ? 0 : slot + 1; };
+  int t = 0, slot = 0;
+  for (; t < nk - kSlots; t++) {
+    const int slot_next = next(slot);
+    slice(std::integral_constant<int, kSlots>{}, t, slot, slot_next);
+    slot = slot_next;
   }
-  __syncthreads();
-  read_frags(0, 0, 0);
-  for (int kt = 0; kt < nk; kt++) {
-    const int cur = kt & 1;
-    read_frags(1, cur, 1);
-    mma(0);
-    interleave();
-    read_frags(0, cur, 2);
-    mma(1);
-    interleave();
-    read_frags(1, cur, 3);
-    mma(0);
-    interleave();
-    wait_vm<0>();                                     // slice kt+1 (this wave's share)
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the fragments of slice kt are in registers
-    __syncthreads();
-    if (kt + 2 < nk) issue(kt + 2, cur);
-    read_frags(0, cur ^ 1, 0);
-    mma(1);
-    interleave();
+  if (kSlots == 3) {
+    slice(K2{}, t, slot, next(slot));
+    t++;
+    slot = next(slot);
   }
+  slice(K1{}, t, slot, next(slot));
+  slice(K0{}, t + 1, next(slot), 0);
+  // (the accumulators are final here: left to itself the compiler sinks the last products into the epilogue's slabs,
+  // and their operands are spilled on the way)
+#pragma unroll
+  for (int ti = 0; ti < 4; ti++)
+#pragma unroll
+    for (int tj = 0; tj < NTJ; tj++) asm volatile("" : "+a"(acc[ti][tj]));
+  if (EXT) asm volatile("s_nop 15\n\ts_nop 7" : "+v"(acce[0]), "+v"(acce[1]));   // (their products are asm: no one else pads)
   __syncthreads();             // every wave is done with the stages: they become the epilogue's staging area
 
   // ---- epilogue, one 32-token slab at a time
@@ -316,8 +371,9 @@ __global__ __launch_bounds__(256) void gemm256_bf16_kernel(Gemm256Params p) {
 
 }  // namespace
 
+// (K: the pipeline is three slices deep; less K has nothing to gain from large tiles)
 bool gemm256_supported(int M, int N, int K) {
-  return M >= 256 && N % 256 == 0 && K % 64 == 0 && K >= 64;
+  return M >= 256 && N % 256 == 0 && K % 64 == 0 && K >= 192;
 }
 
 ns_status launch_gemm256(const uint16_t *a, const uint16_t *w, const float *bias, const uint16_t *r,
@@ -373,9 +429,9 @@ ns_status launch_gemm256(const uint16_t *a, const uint16_t *w, const float *bias
   typedef void (*kern_t)(Gemm256Params);
   static const kern_t kerns[4] = {gemm256_bf16_kernel<false, false>, gemm256_bf16_kernel<false, true>,
                                   gemm256_bf16_kernel<true, false>, gemm256_bf16_kernel<true, true>};
-  const ns_status rs = reserve_lds_once(reinterpret_cast<const void *>(kerns[(gelu ? 2 : 0) + (r ? 1 : 0)]), kStages * kStage);
+  const ns_status rs = reserve_lds_once(reinterpret_cast<const void *>(kerns[(gelu ? 2 : 0) + (r ? 1 : 0)]), kGemmLds);
   if (rs != NS_OK) return rs;
-  hipLaunchKernelGGL(kerns[(gelu ? 2 : 0) + (r ? 1 : 0)], dim3((unsigned)wgs), dim3(256), kStages * kStage, s, p);
+  hipLaunchKernelGGL(kerns[(gelu ? 2 : 0) + (r ? 1 : 0)], dim3((unsigned)wgs), dim3(256), kGemmLds, s, p);
   return check_launch("gemm256_bf16_kernel");
 }
 

@@ -328,6 +328,11 @@ def test_gelu_epilogue_value_by_value(nb, n):
     (9832, 4096, 128, False, True),     # more tiles than CUs: 19 rows of 256-row tiles, then 26 rows of 192-row tiles
     (7000, 4096, 64, False, False),     # 16 rows of each
     (12000, 2048, 64, False, True),     # 2 rows of 256-row tiles, then 60 of 192-row tiles
+    # the 256 x 256 kernel's depths of k: fewest slices, one and two more than its weight slots
+    (9832, 4096, 192, False, True),     # mixed tile heights
+    (1025, 1024, 192, True, False),     # ninth slab
+    (577, 512, 256, False, True),       # partial tile
+    (12000, 2048, 320, True, True),     # 192-row tiles
 ])
 def test_linear_forward(nb, M, N, K, gelu, res):
     """The fused linear map against float64 matmul / erf GELU on the same bf16 inputs."""
