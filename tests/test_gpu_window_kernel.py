@@ -66,3 +66,24 @@ def test_pruned_sequence(nb, monkeypatch, g, block, keep, G, dtype, split):
     torch.cuda.synchronize()
     ref = oracle.ns_attn(q, k, v, g, g, block, 0.125, coords=coords, n_global=G)
     assert_attn_close(to_np(out), ref, dtype, "window kernel, pruned sequence")
+
+
+@pytest.mark.parametrize("gh,gw,gain", [(16, 16, 1.0), (16, 32, 1.0), (17, 31, 1.0), (33, 31, 14.0), (64, 48, 1.0)])
+def test_global_row_in_a_launch_of_its_own(nb, monkeypatch, gh, gw, gain):
+    """The block kernel leaves the global row to another launch: fewer keys than a chunk (257), one over a chunk
+    (513), one over two (1024 + 1), the last chunk partly filled; peaked rows."""
+    monkeypatch.setenv("NSATTN_KERNEL", "block")
+    q, k, v = synth.small_case(40 + gw, 2, 3, 64, gh, gw, "bf16")
+    q = synth.round_to_bf16(q * gain)
+    print("global row, grid %dx%d gain %g" % (gh, gw, gain), flush=True)
+    out, logits, lse, scores = nb.ns_attn_forward_scores(*(to_dev(a, "bf16") for a in (q, k, v)), gh, gw, 16, 0.125)
+    alone = nb.ns_attn_forward(*(to_dev(a, "bf16") for a in (q, k, v)), gh, gw, 16, 0.125)
+    torch.cuda.synchronize()
+    assert torch.equal(out, alone)
+    assert_attn_close(to_np(out), oracle.ns_attn(q, k, v, gh, gw, 16, 0.125), "bf16", "global row")
+    ref_logits = 0.125 * np.einsum("bhd,bhtd->bht", q[:, :, 0].astype(np.float64), k.astype(np.float64))
+    m = ref_logits.max(axis=-1, keepdims=True)
+    ref_lse = (m + np.log(np.exp(ref_logits - m).sum(axis=-1, keepdims=True)))[..., 0]
+    np.testing.assert_allclose(to_np(logits).reshape(ref_logits.shape), ref_logits, rtol=0, atol=2e-5 * gain)
+    np.testing.assert_allclose(to_np(lse).reshape(ref_lse.shape), ref_lse, rtol=0, atol=2e-5 * gain)
+    np.testing.assert_allclose(to_np(scores), oracle.cls_scores(q, k, 0.125), rtol=5e-5 * gain, atol=1e-10)
