@@ -4,6 +4,7 @@
 // 1.5 us, the stream object 2.9 us, a ctypes structure 1.6 us, pointer wrappers) took 14 us of host time
 // on top of the launches and set the pace.  Plain CPython entry points on torch's own tensor structs: no
 // argument conversion layer, about 3 us.  Nothing is kept between calls.
+#include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
 #include <ATen/ATen.h>
 #include <cmath>
@@ -93,8 +94,8 @@ template <class F> PyObject *guarded(Py_ssize_t have, Py_ssize_t want, F f) {
   try {
     return f();
   } catch (const PyFail &) {
-  } catch (const std::exception &e) {
-    PyErr_SetString(PyExc_RuntimeError, e.what());
+  } catch (...) {                  // torch's own types: OutOfMemoryError, IndexError, ..
+    torch::translate_exception_to_python(std::current_exception());
   }
   return nullptr;
 }
@@ -243,24 +244,33 @@ const char *const kNames[kWeights] = {"ln1_g", "ln1_b", "w_qkv", "b_qkv", "w_pro
                                       "w_fc1", "b_fc1", "w_fc2", "b_fc2"};
 PyObject *g_names[kWeights];
 
-PyObject *item(PyObject *weights, int i) {         // borrowed: the mapping keeps it
-  if (PyDict_CheckExact(weights)) {
-    PyObject *o = PyDict_GetItemWithError(weights, g_names[i]);
-    if (!o) {
-      if (!PyErr_Occurred()) PyErr_SetObject(PyExc_KeyError, g_names[i]);
-      throw PyFail{};
+// What the mappings gave, held until the call has returned: a mapping may make its tensors as they are asked for,
+// and another thread may replace a dict's while the interpreter lock is given up.
+struct Held {
+  std::vector<PyObject *> objects;
+  Held() = default;
+  Held(const Held &) = delete;
+  ~Held() {
+    for (PyObject *o : objects) Py_DECREF(o);
+  }
+  PyObject *item(PyObject *weights, int i) {
+    PyObject *o;
+    if (PyDict_CheckExact(weights)) {
+      o = PyDict_GetItemWithError(weights, g_names[i]);
+      if (!o && !PyErr_Occurred()) PyErr_SetObject(PyExc_KeyError, g_names[i]);
+      Py_XINCREF(o);
+    } else {
+      o = PyObject_GetItem(weights, g_names[i]);
     }
+    if (!o) throw PyFail{};
+    objects.push_back(o);
     return o;
   }
-  PyObject *o = PyObject_GetItem(weights, g_names[i]);
-  if (!o) throw PyFail{};
-  Py_DECREF(o);
-  return o;
-}
-ns_vit_block_weights read_weights(PyObject *weights, const at::Device &dev, const char *prefix) {
+};
+ns_vit_block_weights read_weights(Held &held, PyObject *weights, const at::Device &dev, const char *prefix) {
   const void *p[kWeights];
   for (int i = 0; i < kWeights; i++) {
-    const at::Tensor &t = tensor(item(weights, i), kNames[i]);
+    const at::Tensor &t = tensor(held.item(weights, i), kNames[i]);
     const bool matrix = kNames[i][0] == 'w';
     if (t.scalar_type() != (matrix ? at::kBFloat16 : at::kFloat) || !t.is_contiguous() || t.device() != dev) {
       PyErr_Format(PyExc_ValueError, "%sweight %s must be a contiguous torch.%s tensor on %s", prefix, kNames[i],
@@ -272,7 +282,7 @@ ns_vit_block_weights read_weights(PyObject *weights, const at::Device &dev, cons
   auto f = [&](int i) { return static_cast<const float *>(p[i]); };
   return ns_vit_block_weights{f(0), f(1), p[2], f(3), p[4], f(5), f(6), f(7), p[8], f(9), p[10], f(11)};
 }
-ns_vit_block_desc block_desc(const at::Tensor &x, PyObject *weights, int64_t gh, int64_t gw, int64_t block, int64_t heads,
+ns_vit_block_desc block_desc(Held &held, const at::Tensor &x, PyObject *weights, int64_t gh, int64_t gw, int64_t block, int64_t heads,
                              double eps, PyObject *scale, int64_t G) {
   if (x.scalar_type() != at::kBFloat16 || !x.is_contiguous() || x.dim() != 3)
     value_error("x must be a contiguous bfloat16 tensor [B,T,dim]");
@@ -285,7 +295,7 @@ ns_vit_block_desc block_desc(const at::Tensor &x, PyObject *weights, int64_t gh,
   ad.tokens = (int32_t)x.size(1);
   ad.scale = scale_of(scale, x.size(2) / heads);
   d.dim = (int32_t)x.size(2);
-  d.mlp_dim = (int32_t)tensor(item(weights, 8), "w_fc1").size(0);
+  d.mlp_dim = (int32_t)tensor(held.item(weights, 8), "w_fc1").size(0);
   d.ln_eps = (float)eps;
   return d;
 }
@@ -295,8 +305,9 @@ PyObject *block(PyObject *, PyObject *const *a, Py_ssize_t n) {
   return guarded(n, 14, [&]() -> PyObject * {
     const at::Tensor &x = tensor(a[0], "x");
     const int64_t G = integer(a[13]);
-    ns_vit_block_desc d = block_desc(x, a[1], integer(a[2]), integer(a[3]), integer(a[4]), integer(a[5]), number(a[6]), a[7], G);
-    const ns_vit_block_weights w = read_weights(a[1], x.device(), "");
+    Held held;
+    ns_vit_block_desc d = block_desc(held, x, a[1], integer(a[2]), integer(a[3]), integer(a[4]), integer(a[5]), number(a[6]), a[7], G);
+    const ns_vit_block_weights w = read_weights(held, a[1], x.device(), "");
     const at::Tensor coords = optional(a[8], "coords");
     if (coords.defined()) {
       if (!i32_contiguous(coords)) value_error("coords must be a contiguous int32 tensor [B, T-1]");
@@ -331,7 +342,8 @@ PyObject *stack(PyObject *, PyObject *const *a, Py_ssize_t n) {
     }
     const int64_t gh = integer(a[2]), gw = integer(a[3]), after = integer(a[6]), keep = integer(a[7]), G = integer(a[13]);
     ns_vit_desc d{};
-    d.block = block_desc(x, PySequence_Fast_GET_ITEM(layers, 0), gh, gw, integer(a[4]), integer(a[5]), number(a[8]), a[9], G);
+    Held held;
+    d.block = block_desc(held, x, PySequence_Fast_GET_ITEM(layers, 0), gh, gw, integer(a[4]), integer(a[5]), number(a[8]), a[9], G);
     d.layers = (int32_t)L;
     d.prune_after = (int32_t)after;
     d.keep_k = (int32_t)keep;
@@ -339,7 +351,7 @@ PyObject *stack(PyObject *, PyObject *const *a, Py_ssize_t n) {
     for (Py_ssize_t i = 0; i < L; i++) {
       char prefix[32];
       snprintf(prefix, sizeof(prefix), "layer %d ", (int)i);
-      w[(size_t)i] = read_weights(PySequence_Fast_GET_ITEM(layers, i), x.device(), prefix);
+      w[(size_t)i] = read_weights(held, PySequence_Fast_GET_ITEM(layers, i), x.device(), prefix);
     }
     const int64_t B = x.size(0), T = x.size(1), dim = x.size(2);
     const bool pruning = after > 0 && keep > 0;

@@ -226,3 +226,34 @@ def test_stack_workspace_covers_the_pruned_blocks(nb):
     # the case that used to fall short: keep_k = N needs more than the full grid
     pd.attn.tokens = 1 + N
     assert nb.lib.vit_block_workspace_bytes(ctypes.byref(pd)) > nb.lib.vit_block_workspace_bytes(ctypes.byref(d.block))
+
+
+def test_weights_that_a_mapping_makes_on_demand_stay_alive(nb):
+    """The binding takes pointers out of a block's weights one after the other: each must still be alive when the
+    call is made.  (head_dim 32 is refused, so nothing is launched.)"""
+    import weakref
+    import torch
+    dim, mlp = 64, 128
+    shapes = {"w_qkv": (3 * dim, dim), "w_proj": (dim, dim), "w_fc1": (mlp, dim), "w_fc2": (dim, mlp), "b_qkv": (3 * dim,),
+              "b_fc1": (mlp,)}
+    given = []
+
+    class Lazy:
+        def __getitem__(self, name):
+            assert all(r() is not None for r in given), "a weight was released before %s was read" % name
+            t = torch.zeros(shapes.get(name, (dim,)), dtype=torch.bfloat16 if name.startswith("w_") else torch.float32)
+            given.append(weakref.ref(t))
+            return t
+
+    class Stream:
+        cuda_stream = 0
+
+    x = torch.zeros(1, 65, dim, dtype=torch.bfloat16)
+    with pytest.raises(nb.NsError):
+        nb.vit_block_forward(x, Lazy(), 8, 8, 4, 2, stream=Stream())
+    assert len(given) == 13                 # the twelve, and w_fc1 once more for its shape
+    assert all(r() is None for r in given)  # and the call keeps none of them
+    given.clear()
+    with pytest.raises(nb.NsError):
+        nb.vit_forward(x, [Lazy(), Lazy()], 8, 8, 4, 2, stream=Stream())
+    assert len(given) == 25 and all(r() is None for r in given)

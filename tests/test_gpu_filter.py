@@ -150,3 +150,9 @@ def test_scores_to_kept_set_end_to_end(nb):
     kept, _, _ = nb.topk_filter(got_scores, kk)
     torch.cuda.synchronize()
     assert_kept_sets_match(kept.cpu().numpy(), ref_kept, ref_scores, kk)
+
+
+def test_running_out_of_memory_is_reported_as_such(nb):
+    """An output that no device holds: the allocator's own exception, as from any torch call."""
+    with pytest.raises(torch.cuda.OutOfMemoryError):
+        nb.topk_filter(torch.zeros(1, 64, device="cuda"), 2 ** 42)
