@@ -263,11 +263,10 @@ __global__ __launch_bounds__(256, 2) void attn_block16_kernel(BlockParams p) {
   auto finish_tile = [&]() {
     l[0] += la[0][0] + la[0][1];
     l[1] += la[1][0] + la[1][1];
-    float big = fmaxf(fabsf(l[0]), fabsf(l[1]));
+    float big = max_abs(max_abs(0.f, l[0]), l[1]);
 #pragma unroll
     for (int i = 0; i < 16; i++)
-      big = fmaxf(fmaxf(big, fmaxf(fabsf(o[0][0][i]), fabsf(o[0][1][i]))),
-                  fmaxf(fabsf(o[1][0][i]), fabsf(o[1][1][i])));
+      big = max_abs(max_abs(max_abs(max_abs(big, o[0][0][i]), o[0][1][i]), o[1][0][i]), o[1][1][i]);
     const bool bad = __any(!(big < 1e30f));
     char *t = ob + (size_t)tile_token(R, C, wave) * (size_t)(p.ost * 2);
 #pragma unroll

@@ -306,11 +306,10 @@ __global__ __launch_bounds__(256, 2) void attn_sweep_kernel(SweepParams p) {
   auto finish_math = [&](int qc) {
     l[0] += la[0][0] + la[0][1];
     l[1] += la[1][0] + la[1][1];
-    float big = fmaxf(fabsf(l[0]), fabsf(l[1]));
+    float big = max_abs(max_abs(0.f, l[0]), l[1]);
 #pragma unroll
     for (int i = 0; i < 16; i++)
-      big = fmaxf(fmaxf(big, fmaxf(fabsf(o[0][0][i]), fabsf(o[0][1][i]))),
-                  fmaxf(fabsf(o[1][0][i]), fabsf(o[1][1][i])));
+      big = max_abs(max_abs(max_abs(max_abs(big, o[0][0][i]), o[0][1][i]), o[1][0][i]), o[1][1][i]);
     if (__any(!(big < 1e30f))) badmask |= 1u << (qc >> 2);
 #pragma unroll
     for (int nt = 0; nt < 2; nt++) {

@@ -118,6 +118,9 @@ __device__ __forceinline__ int opaque(int x) {
 // integer after adding 0.5, more than the two roundings can move it
 __device__ __forceinline__ int div_small(int a, float inv) { return (int)(((float)a + 0.5f) * inv); }
 
+// max(a, |b|), NaN if either is (v_maximum3_f32): fmaxf drops a NaN, and a check for overflow must see +inf - inf
+__device__ __forceinline__ float max_abs(float a, float b) { return __builtin_elementwise_maximum(a, __builtin_fabsf(b)); }
+
 // max / sum of a value over the two half-waves (lane l and lane l ^ 32); both lanes get it
 __device__ __forceinline__ float half_swap_max(float x) {
   auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);

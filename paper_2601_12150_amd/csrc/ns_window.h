@@ -386,6 +386,7 @@ constexpr int kWaveRings = 16384, kWaveAux = 1024 + 128, kWaveLds = kWaveRings +
 constexpr int kWindowMl = 4 * 2 * 64 * 4;                    // (max, sum) per wave and query
 constexpr int kWindowLds = 4 * kWaveLds + kWindowMl;         // two workgroups per CU
 constexpr float kNoMax = -1e30f;
+constexpr float kLargeSum = 1e30f;                           // a sum beyond this may be about to leave fp32's range
 
 // State of 32*NT queries: running reference m (log2 units), sum l (this half-wave's keys), output.
 template <class S, int NT>
@@ -404,17 +405,17 @@ struct WaveAcc {
   }
   // The reference is the first step's maximum and normally stays: a weight is exp2 of how far a logit
   // lies above it, and neither fp32 nor bf16 lose anything on weights up to 2^100.  A wave whose sums
-  // then turn out too large (or not finite) walks its keys once more and raises the reference
-  // wherever a logit exceeds it by more than 8.
-  __device__ __forceinline__ bool overflowed() const {
+  // then turn out too large (or not finite) walks its keys once more and keeps the reference at the
+  // largest logit so far: weights are then at most 1, whatever the values they multiply.
+  __device__ __forceinline__ bool exceeds(float limit) const {
     float big = 0.f;
 #pragma unroll
     for (int nt = 0; nt < NT; nt++) {
-      big = fmaxf(big, fabsf(l[nt]));
+      big = max_abs(big, l[nt]);
 #pragma unroll
-      for (int e = 0; e < 16; e++) big = fmaxf(fmaxf(big, fabsf(o[nt][0][e])), fabsf(o[nt][1][e]));
+      for (int e = 0; e < 16; e++) big = max_abs(max_abs(big, o[nt][0][e]), o[nt][1][e]);
     }
-    return __any(!(big < 1e30f));
+    return __any(!(big < limit));
   }
   __device__ __forceinline__ void reference(const f32x16 &s, int nt, float c) {
     float a = fmaxf(s[0], s[1]), b = fmaxf(s[2], s[3]);
@@ -424,7 +425,7 @@ struct WaveAcc {
       b = fmaxf(fmaxf(b, s[e + 2]), s[e + 3]);
     }
     const float top = half_swap_max(fmaxf(a, b)) * c;
-    if (__any(top > m[nt] + 8.f)) {
+    if (__any(top > m[nt])) {
       const float m_new = fmaxf(m[nt], top);
       const float alpha = __builtin_amdgcn_exp2f(m[nt] - m_new);
       m[nt] = m_new;
@@ -774,7 +775,7 @@ __device__ __forceinline__ void global_rows_chunk(const GlobalRows &p, int heads
 #pragma unroll
           for (int e = 0; e < 16; e++) s[e] = jb + 8 * (e >> 2) + (e & 3) < T ? s[e] : -INFINITY;
       });
-    if (careful || !a.overflowed()) break;
+    if (careful || !a.exceeds(kLargeSum)) break;
     a.clear();
   }
   float *ml = reinterpret_cast<float *>(smem + 4 * kWaveLds);
@@ -897,7 +898,7 @@ __device__ __forceinline__ void window_attention(const WindowParams &p, unsigned
           for (int e = 0; e < 16; e++) s[e] = jb + 8 * (e >> 2) + (e & 3) < w.nkeys ? s[e] : -INFINITY;
         }
       });
-    if (careful || !a.overflowed()) break;
+    if (careful || !a.exceeds(kLargeSum)) break;
     a.clear();
   }
   }

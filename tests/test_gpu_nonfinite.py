@@ -1,0 +1,103 @@
+"""Sums that leave fp32's range on the way to a finite result."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2601_12150_amd import synth
+from _util import assert_attn_close, to_dev, to_np
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def nb():
+    from paper_2601_12150_amd import binding
+    return binding
+
+
+def force(monkeypatch, dtype, split):
+    monkeypatch.setenv("NSATTN_KERNEL", ("lists" if dtype == "bf16" else "generic") + split)
+
+
+def high_case(N, first_high, half, dtype, logit=60.5, big=1e14):
+    """Patches from number first_high on have logits `logit` above the ones before, values of big up to patch `half`
+    and of -big/2 behind it: their weights against the first ones' maximum, times these, are beyond fp32."""
+    rnd = synth.round_to_bf16 if dtype == "bf16" else (lambda a: a.astype(np.float32))
+    q = np.zeros((1, 2, 1 + N, 64), np.float32)
+    k, v = np.zeros_like(q), np.zeros_like(q)
+    q[..., 0] = 22.0
+    k[:, :, 1 + first_high:, 0] = logit / (0.125 * 22.0)
+    v[:, :, 1 + first_high:] = big
+    v[:, :, 1 + half:] = -0.5 * big
+    return rnd(q), rnd(k), rnd(v)
+
+
+@pytest.mark.parametrize("split", ["1", "2", "4"])
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("pruned", [False, True])
+@pytest.mark.parametrize("logit,big", [(60.5, 1e14), (5.0, 2e35)])
+def test_sums_beyond_the_range(nb, monkeypatch, logit, big, dtype, split, pruned):
+    """Finite results whose sums leave fp32's range against the first step's maximum.  60.5 nats above it: some tiles hold
+    keys of both signs, and +inf - inf is NaN.  5 nats: weights of 148 are too large for the values though not
+    for the sum of weights.  (Weights of at most 1 sum up to 384 x 2e35.)"""
+    force(monkeypatch, dtype, split)
+    g, block = 24, 8
+    q, k, v = high_case(g * g, 8 * g, 16 * g, dtype, logit, big)
+    coords = np.ascontiguousarray(synth.raster_coords(g, g)[None]) if pruned else None
+    print("sums beyond the range: %g nats, values of %g, %s split %s pruned %s" % (logit, big, dtype, split, pruned), flush=True)
+    out = nb.ns_attn_forward(*(to_dev(a, dtype) for a in (q, k, v)), g, g, block, 0.125,
+                             coords=None if coords is None else torch.from_numpy(coords).cuda())
+    torch.cuda.synchronize()
+    got, ref = to_np(out), oracle.ns_attn(q, k, v, g, g, block, 0.125, coords=coords)
+    assert np.isfinite(got).all()
+    assert_attn_close(got / big, ref / big, dtype, "sums beyond the range")
+
+
+@pytest.mark.parametrize("kernel,gh,gw,block", [("sweep", 24, 24, 8), ("sweep", 20, 27, 8), ("block", 48, 48, 16), ("block", 40, 41, 16)])
+def test_sums_that_cancel_in_the_tiled_kernels(nb, monkeypatch, kernel, gh, gw, block):
+    """As above, 60.5 nats, in the kernels whose waves walk a tile's keys block after block."""
+    monkeypatch.setenv("NSATTN_KERNEL", kernel)
+    q, k, v = high_case(gh * gw, block * gw, 2 * block * gw, "bf16")
+    out = nb.ns_attn_forward(*(to_dev(a, "bf16") for a in (q, k, v)), gh, gw, block, 0.125)
+    torch.cuda.synchronize()
+    got, ref = to_np(out), oracle.ns_attn(q, k, v, gh, gw, block, 0.125)
+    assert np.isfinite(got).all()
+    assert_attn_close(got / 1e14, ref / 1e14, "bf16", "cancelling sums, %s" % kernel)
+
+
+@pytest.mark.parametrize("split", ["1", "2", "4"])
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("pruned,g,block", [(True, 24, 8), (True, 33, 16), (False, 24, 8), (False, 33, 16)])
+def test_weights_beyond_the_first_steps_reference(nb, monkeypatch, dtype, split, pruned, g, block):
+    """The second walk, with the token ring and without: every query's largest logit lies more than 2^100 above
+    those of a wave's first step (32 keys; the walk starts over where a sum exceeds 1e30)."""
+    force(monkeypatch, dtype, split)
+    rng = np.random.default_rng(g)
+    N = g * g
+    q, k, v = synth.small_case(60 + g, 1, 2, 64, g, g, dtype)
+    q = q * np.float32(12.0)
+    # keys in raster order: small ones in the first eight rows of the grid, then large ones
+    k[:, :, 1:1 + 8 * g] *= np.float32(0.05)
+    if dtype == "bf16":
+        q, k = synth.round_to_bf16(q), synth.round_to_bf16(k)
+    coords = np.ascontiguousarray(synth.raster_coords(g, g)[None]) if pruned else None
+    # the tile of the grid's middle block: it sees the rows of three blocks
+    mid = (g // 2 // block) * block
+    lo = max(mid - block, 0)
+    qm = q[:, :, 1 + mid * g + mid].astype(np.float64)
+    logits = np.einsum("bhd,bhtd->bht", qm, k.astype(np.float64)) / np.log(2.0)
+    small = np.r_[0, 1 + lo * g:1 + 8 * g]
+    assert lo < 8 and (logits.max(-1) - logits[..., small].max(-1)).min() > 110
+    print("second walk: %d block %d %s split %s pruned %s" % (g, block, dtype, split, pruned), flush=True)
+    out = nb.ns_attn_forward(*(to_dev(a, dtype) for a in (q, k, v)), g, g, block, 1.0,
+                             coords=None if coords is None else torch.from_numpy(coords).cuda())
+    torch.cuda.synchronize()
+    ref = oracle.ns_attn(q, k, v, g, g, block, 1.0, coords=coords)
+    got = to_np(out)
+    assert np.isfinite(got).all()
+    if dtype == "f32":
+        # a logit of size L carries L * 2^-24 per product and so does its weight: 64 products of up to 150
+        assert np.abs(got - ref).max() <= 1e-3
+    else:
+        assert_attn_close(got, ref, dtype, "second walk")
