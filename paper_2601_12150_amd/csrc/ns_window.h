@@ -147,6 +147,14 @@ __device__ __forceinline__ int window_tile_id(const WindowGeom &g, int bid) {
 // read it.
 // ------------------------------------------------------------------------------------------
 
+// What the passes of walk_not_finite() make of a value (the bits of a float): 0, 1: 1 where it is +inf or -inf or,
+// in both, NaN, else 0; 2: 0 in place of a value that is not finite.
+__device__ __forceinline__ uint32_t screened(uint32_t x, int pass) {
+  const bool bad = (x & 0x7f800000u) == 0x7f800000u, nan = bad && (x & 0x7fffffu) != 0;
+  if (pass == 2) return bad ? 0u : x;
+  return nan || (bad && (int)(x >> 31) == pass) ? 0x3f800000u : 0u;
+}
+
 // bf16: v_mfma_f32_32x32x16_bf16, weights rounded to bf16 for the second product.
 struct StepBf16 {
   typedef uint16_t elem;
@@ -292,6 +300,9 @@ struct StepBf16 {
           o[nt][dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, pf[nt][sp], o[nt][dt], 0, 0, 0);
       }
   }
+  static __device__ __forceinline__ uint32_t screen(uint32_t two, int pass) {
+    return screened(two & 0xffff0000u, pass) | (screened(two << 16, pass) >> 16);
+  }
   static __device__ __forceinline__ void store4out(uint16_t *p, f32x4 v) {
     *reinterpret_cast<u32x2 *>(p) = u32x2{pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3])};
   }
@@ -374,6 +385,7 @@ struct StepF32 {
         for (int nt = 0; nt < NT; nt++) o[nt][dt] = __builtin_amdgcn_mfma_f32_32x32x2f32(v, w[nt][e], o[nt][dt], 0, 0, 0);
       }
   }
+  static __device__ __forceinline__ uint32_t screen(uint32_t one, int pass) { return screened(one, pass); }
   static __device__ __forceinline__ void store4out(float *p, f32x4 v) { *reinterpret_cast<f32x4 *>(p) = v; }
   static __device__ __forceinline__ void store4out(uint16_t *p, f32x4 v) {
     *reinterpret_cast<u32x2 *>(p) = u32x2{pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3])};
@@ -572,12 +584,16 @@ __device__ __forceinline__ void walk_keys_pipelined(const S &st, WaveAcc<S, 2> &
 
 // n steps of a wave.  key_token(i): token of key `lane & 31` of step i; with RING the tokens are
 // read from memory instead: key_entry(i) is where that token stands, fix_token(i, row, tok) the last
-// word on it.  fix(i, s) edits the logits of step i and issues exactly E stores.  Vector memory
-// requests complete in issue order, so the waits count how many younger ones may still be in flight.
-template <class S, int NT, bool WITH_V, bool RING, bool LO, int E, class KeyToken, class KeyEntry, class FixToken, class Fix>
+// word on it.  fix(i, nt, s) edits the logits of step i and issues exactly E stores, screen(v) the 32 rows of V in
+// LDS.  Vector memory requests complete in issue order, so the waits count how many younger ones may still be in flight.
+struct Unscreened {
+  __device__ __forceinline__ void operator()(unsigned char *) const {}
+};
+template <class S, int NT, bool WITH_V, bool RING, bool LO, int E, class KeyToken, class KeyEntry, class FixToken, class Fix,
+          class Screen = Unscreened>
 __device__ __forceinline__ void walk_keys(const S &st, WaveAcc<S, NT> &a, const char *kb, const char *vb, int64_t rowB,
                                           unsigned char *wsm, int n, float c, bool careful, int lane, KeyToken key_token,
-                                          KeyEntry key_entry, FixToken fix_token, Fix fix) {
+                                          KeyEntry key_entry, FixToken fix_token, Fix fix, Screen screen = Screen()) {
   // (without V the K ring takes the whole space: twice the slots)
   constexpr int D = WITH_V ? S::kDepth : 2 * S::kDepth, R = S::kReq, TL = RING ? 1 : 0;
   if (n <= 0) return;
@@ -669,6 +685,7 @@ __device__ __forceinline__ void walk_keys(const S &st, WaveAcc<S, NT> &a, const 
       if (rem >= D) wait_vm<kNext + E + R + (D - 1) * TL>();
       else if (D == 2 && rem == 1) wait_vm<kNext + E>();
       else wait_vm<E>();
+      screen(wsm + kV + slot * S::kHalf);
       st.template weigh<NT, LO>(s, wsm + kV + slot * S::kHalf, a.o, lane);
       if (rem >= D) {
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
@@ -683,6 +700,58 @@ __device__ __forceinline__ void walk_keys(const S &st, WaveAcc<S, NT> &a, const 
     if (D > 3 && i + 3 < n) step(i + 3, 3);
   }
   wait_vm<0>();                               // (token requests past the end)
+}
+
+// n steps of a wave whose output sums are not finite after a careful walk: a row gets what the keys it sees give,
+// infinities of one sign as such, of both signs and NaN as NaN.  The walks above let more in: a pair that is masked and
+// a key number past the end have weight 0, and 0 times inf is NaN.  Three passes: which output values see +inf or NaN
+// (weights 1 and 0, V 1 where it is that), which see -inf or NaN, then the output with the finite values of V.
+// hide(i, nt, s): -inf in place of the logits of step i that do not count.
+template <class S, int NT, bool RING, bool LO, class KeyToken, class KeyEntry, class FixToken, class Hide>
+__device__ __forceinline__ void walk_not_finite(const S &st, WaveAcc<S, NT> &a, const char *kb, const char *vb, int64_t rowB,
+                                                unsigned char *wsm, int n, float c, int lane, KeyToken key_token,
+                                                KeyEntry key_entry, FixToken fix_token, Hide hide) {
+  uint32_t sees[2][NT] = {};                  // bit 16 dt + e
+#pragma unroll 1
+  for (int pass = 0; pass < 3; pass++) {
+    a.clear();
+    walk_keys<S, NT, true, RING, LO, 0>(
+      st, a, kb, vb, rowB, wsm, n, c, true, lane, key_token, key_entry, fix_token,
+      [&](int i, int nt, f32x16 &s) {
+        if (pass < 2)
+#pragma unroll
+          for (int e = 0; e < 16; e++) s[e] = 0.f;
+        hide(i, nt, s);
+      },
+      [&](unsigned char *v) {
+#pragma unroll
+        for (int i = 0; i < S::kHalf / 1024; i++) {
+          uint4 *const x = reinterpret_cast<uint4 *>(v + 1024 * i + 16 * lane);
+          const uint4 u = *x;
+          *x = uint4{S::screen(u.x, pass), S::screen(u.y, pass), S::screen(u.z, pass), S::screen(u.w, pass)};
+        }
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+      });
+    if (pass == 2) break;
+#pragma unroll
+    for (int nt = 0; nt < NT; nt++) {
+      uint32_t bits = 0;
+#pragma unroll
+      for (int e = 0; e < 16; e++) bits |= (a.o[nt][0][e] > 0.f ? 1u << e : 0u) | (a.o[nt][1][e] > 0.f ? 0x10000u << e : 0u);
+      sees[0][nt] = pass == 0 ? bits : sees[0][nt];
+      sees[1][nt] = pass == 0 ? 0u : bits;
+    }
+  }
+#pragma unroll
+  for (int nt = 0; nt < NT; nt++)
+#pragma unroll
+    for (int dt = 0; dt < 2; dt++)
+#pragma unroll
+      for (int e = 0; e < 16; e++) {
+        const uint32_t bit = 1u << (16 * dt + e);
+        a.o[nt][dt][e] += sees[0][nt] & bit ? INFINITY : 0.f;
+        a.o[nt][dt][e] += sees[1][nt] & bit ? -INFINITY : 0.f;
+      }
 }
 
 // a query tile's walk: pipelined where there are two slots
@@ -761,21 +830,31 @@ __device__ __forceinline__ void global_rows_chunk(const GlobalRows &p, int heads
   // (the second set of columns and the rows past G write nothing)
   const bool writes = LOGITS && l32 < GR && g < G;
   float *lrow = LOGITS ? p.logits + ((size_t)(b * heads + h) * G + min(g, G - 1)) * T : nullptr;
+  auto key_token = [&](int i) { return min(j0 + 128 * i + l32, T - 1); };
+  auto no_entry = [](int) { return (const int32_t *)nullptr; };
+  auto as_is = [](int, int, int t) { return t; };
+  auto hide = [&](int i, int, f32x16 &s) {
+    const int jb = j0 + 128 * i + 4 * hh;
+    if (j0 + 128 * i + 32 > T)
+#pragma unroll
+      for (int e = 0; e < 16; e++) s[e] = jb + 8 * (e >> 2) + (e & 3) < T ? s[e] : -INFINITY;
+  };
   for (bool careful = false;; careful = true) {
     walk_keys<S, 1, WITH_V, false, kBf16, LOGITS ? 16 : 0>(
-      st, a, kb, vb, rowB, wsm, n, c, careful, lane, [&](int i) { return min(j0 + 128 * i + l32, T - 1); },
-      [](int) { return (const int32_t *)nullptr; }, [](int, int, int t) { return t; },
-      [&](int i, int, f32x16 &s) {
+      st, a, kb, vb, rowB, wsm, n, c, careful, lane, key_token, no_entry, as_is,
+      [&](int i, int nt, f32x16 &s) {
         const int jb = j0 + 128 * i + 4 * hh;
         // (keys past the end are copies of the last one: their lanes store its logit once more)
         if (LOGITS && writes)
 #pragma unroll
           for (int e = 0; e < 16; e++) store4(lrow + min(jb + 8 * (e >> 2) + (e & 3), T - 1), s[e] * lmul);
-        if (j0 + 128 * i + 32 > T)
-#pragma unroll
-          for (int e = 0; e < 16; e++) s[e] = jb + 8 * (e >> 2) + (e & 3) < T ? s[e] : -INFINITY;
+        hide(i, nt, s);
       });
-    if (careful || !a.exceeds(kLargeSum)) break;
+    if (!a.exceeds(careful ? INFINITY : kLargeSum)) break;
+    if (careful) {
+      if (WITH_V) walk_not_finite<S, 1, false, kBf16>(st, a, kb, vb, rowB, wsm, n, c, lane, key_token, no_entry, as_is, hide);
+      break;
+    }
     a.clear();
   }
   float *ml = reinterpret_cast<float *>(smem + 4 * kWaveLds);
@@ -874,31 +953,36 @@ __device__ __forceinline__ void window_attention(const WindowParams &p, unsigned
   auto key0 = [&](int i) { return 32 * (KS * i + part); };       // first key of this wave's step i
   // (squares of several blocks: a query may see none of a step's keys, so only a first step with the
   // global tokens in it gives a reference)
+  const float c = kBf16 ? p.r.scale * kLog2e : kLog2e;
+  auto key_token = [&](int i) { return w.key(g, key0(i) + l32); };
+  auto key_entry = [&](int i) { return w.key_entry(g, key0(i) + l32); };
+  auto fix_token = [&](int i, int row, int t) { return key0(i) + row < g.n_global ? key0(i) + row : t; };
+  auto hide = [&](int i, int nt, f32x16 &s) {
+    if (MASK) {
+      if (nt == 0) {
+        codes[l32] = w.key_code(g, key0(i) + l32, inv_block);
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+      }
+#pragma unroll
+      for (int q4 = 0; q4 < 4; q4++) {
+        const uint4 kc = *reinterpret_cast<const uint4 *>(codes + 8 * q4 + 4 * hh);
+        const uint32_t k4[4] = {kc.x, kc.y, kc.z, kc.w};
+#pragma unroll
+        for (int e = 0; e < 4; e++) s[4 * q4 + e] = (k4[e] & ~qcode[nt]) == 0 ? s[4 * q4 + e] : -INFINITY;
+      }
+    } else if (key0(i) + 32 > w.nkeys) {
+      const int jb = key0(i) + 4 * hh;
+#pragma unroll
+      for (int e = 0; e < 16; e++) s[e] = jb + 8 * (e >> 2) + (e & 3) < w.nkeys ? s[e] : -INFINITY;
+    }
+  };
   for (bool careful = MASK && part != 0;; careful = true) {
-    window_walk<S, NT, LISTS, MASK>(
-      st, a, kb, vb, rowB, wsm, n, kBf16 ? p.r.scale * kLog2e : kLog2e, careful, lane,
-      [&](int i) { return w.key(g, key0(i) + l32); }, [&](int i) { return w.key_entry(g, key0(i) + l32); },
-      [&](int i, int row, int t) { return key0(i) + row < g.n_global ? key0(i) + row : t; },
-      [&](int i, int nt, f32x16 &s) {
-        if (MASK) {
-          if (nt == 0) {
-            codes[l32] = w.key_code(g, key0(i) + l32, inv_block);
-            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-          }
-#pragma unroll
-          for (int q4 = 0; q4 < 4; q4++) {
-            const uint4 kc = *reinterpret_cast<const uint4 *>(codes + 8 * q4 + 4 * hh);
-            const uint32_t k4[4] = {kc.x, kc.y, kc.z, kc.w};
-#pragma unroll
-            for (int e = 0; e < 4; e++) s[4 * q4 + e] = (k4[e] & ~qcode[nt]) == 0 ? s[4 * q4 + e] : -INFINITY;
-          }
-        } else if (key0(i) + 32 > w.nkeys) {
-          const int jb = key0(i) + 4 * hh;
-#pragma unroll
-          for (int e = 0; e < 16; e++) s[e] = jb + 8 * (e >> 2) + (e & 3) < w.nkeys ? s[e] : -INFINITY;
-        }
-      });
-    if (careful || !a.exceeds(kLargeSum)) break;
+    window_walk<S, NT, LISTS, MASK>(st, a, kb, vb, rowB, wsm, n, c, careful, lane, key_token, key_entry, fix_token, hide);
+    if (!a.exceeds(careful ? INFINITY : kLargeSum)) break;
+    if (careful) {
+      walk_not_finite<S, NT, LISTS, false>(st, a, kb, vb, rowB, wsm, n, c, lane, key_token, key_entry, fix_token, hide);
+      break;
+    }
     a.clear();
   }
   }

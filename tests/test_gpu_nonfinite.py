@@ -1,4 +1,5 @@
-"""Sums that leave fp32's range on the way to a finite result."""
+"""Values that are not finite, and sums that leave fp32's range, in the window kernels and the global rows: a row is
+what the patches it attends to make it, whatever stands in the others."""
 import numpy as np
 import pytest
 import torch
@@ -18,6 +19,76 @@ def nb():
 
 def force(monkeypatch, dtype, split):
     monkeypatch.setenv("NSATTN_KERNEL", ("lists" if dtype == "bf16" else "generic") + split)
+
+
+def assert_same_values(got, ref, dtype, what):
+    """Infinities and NaN at the same places, the rest within the parity bar."""
+    for name, test in (("NaN", np.isnan), ("+inf", np.isposinf), ("-inf", np.isneginf)):
+        wrong = np.argwhere(test(got) != test(ref))
+        assert len(wrong) == 0, "%s: %d values differ in being %s, the first at %s" % (what, len(wrong), name, wrong[0])
+    fin = np.isfinite(ref)
+    assert_attn_close(np.where(fin, got, 0.0), np.where(fin, ref, 0.0), dtype, what)
+
+
+def poison(v, G, N, n=3):
+    """inf and NaN in a few channels of a few patches; the last patch is the one that stands in for keys past a
+    tile's end."""
+    p = [N // 3, N // 2 + 1, N // 2 + 2][:n]
+    v[0, 1, G + p[0], 5] = np.inf
+    v[0, 1, G + p[1 % n], 40] = np.nan
+    v[0, 0, G + p[1 % n], 7] = np.inf
+    v[0, 0, G + p[2 % n], 7] = -np.inf
+    v[0, 0, G + N - 1, 63] = -np.inf
+    v[0, 1, G + N - 1, 0] = np.inf
+
+
+@pytest.mark.parametrize("split", ["1", "2", "4"])
+@pytest.mark.parametrize("dtype", ["bf16", "f32", "bf16 in fp32"])
+@pytest.mark.parametrize("gh,gw,block,G", [(20, 19, 1, 1), (19, 22, 2, 1), (21, 26, 3, 2), (25, 18, 4, 1), (17, 13, 5, 1), (20, 27, 8, 1),
+                                           (37, 21, 16, 1)])
+def test_values_that_are_not_finite(nb, monkeypatch, gh, gw, block, G, dtype, split):
+    """Block sides 1 to 4 put several blocks into a tile, whose queries then see different keys of it."""
+    force(monkeypatch, dtype, split)
+    dt = dtype[:4] if dtype.startswith("bf16") else dtype
+    q, k, v = synth.small_case(31 + gh * gw, 1, 2, 64, gh, gw, dt, n_global=G)
+    poison(v, G, gh * gw)
+    print("not finite: grid %dx%d block %d G=%d %s split %s" % (gh, gw, block, G, dtype, split), flush=True)
+    out = nb.ns_attn_forward(*(to_dev(a, dt) for a in (q, k, v)), gh, gw, block, 0.125, n_global=G)
+    torch.cuda.synchronize()
+    ref = oracle.ns_attn(q, k, v, gh, gw, block, 0.125, n_global=G)
+    assert not np.isfinite(ref).all() and np.isfinite(ref[:, :, G:]).mean() > 0.9
+    assert_same_values(to_np(out), ref, dt, "not finite")
+
+
+@pytest.mark.parametrize("split", ["1", "2", "4"])
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("g,block,G", [(24, 8, 1), (20, 3, 2)])
+def test_values_that_are_not_finite_in_a_pruned_sequence(nb, monkeypatch, g, block, G, dtype, split):
+    force(monkeypatch, dtype, split)
+    rng = np.random.default_rng(g)
+    kept = rng.permutation(np.flatnonzero(rng.random(g * g) < 0.6))
+    q, k, v = synth.small_case(50 + g, 1, 2, 64, 1, len(kept), dtype, n_global=G)
+    poison(v, G, len(kept))
+    coords = np.ascontiguousarray(synth.raster_coords(g, g)[kept][None])
+    print("not finite, pruned: %d of %d, block %d G=%d %s split %s" % (len(kept), g * g, block, G, dtype, split), flush=True)
+    out = nb.ns_attn_forward(*(to_dev(a, dtype) for a in (q, k, v)), g, g, block, 0.125, coords=torch.from_numpy(coords).cuda(), n_global=G)
+    torch.cuda.synchronize()
+    ref = oracle.ns_attn(q, k, v, g, g, block, 0.125, coords=coords, n_global=G)
+    assert_same_values(to_np(out), ref, dtype, "not finite, pruned")
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_a_global_token_that_is_not_finite(nb, monkeypatch, dtype):
+    """Everybody sees it: its channel is lost in every row, and no other."""
+    force(monkeypatch, dtype, "")
+    G, gh, gw = 2, 18, 21
+    q, k, v = synth.small_case(8, 1, 2, 64, gh, gw, dtype, n_global=G)
+    v[0, 0, 1, 9] = np.inf
+    v[0, 1, 0, 33] = np.nan
+    for block in (4, 8):
+        out = nb.ns_attn_forward(*(to_dev(a, dtype) for a in (q, k, v)), gh, gw, block, 0.125, n_global=G)
+        torch.cuda.synchronize()
+        assert_same_values(to_np(out), oracle.ns_attn(q, k, v, gh, gw, block, 0.125, n_global=G), dtype, "global token, block %d" % block)
 
 
 def high_case(N, first_high, half, dtype, logit=60.5, big=1e14):
