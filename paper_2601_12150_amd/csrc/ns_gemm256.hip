@@ -124,8 +124,9 @@ __device__ __forceinline__ void gemm256_emit(const Gemm256Params &p, unsigned ch
 // One wave's work on one workgroup tile.  NTJ: 32-row token slabs of its own 128 rows that this
 // wave computes (0..4).  EXT: the tile has a ninth token slab (rows 256..287); this wave then
 // also computes that slab against weight slabs 2*WM and 2*WM+1 of its n half, and every wave
-// issues 9 instead of 8 token-row requests per k-slice.
-template <int NTJ, bool EXT, int WM, bool GELU, bool RES, int TM = 256>
+// issues 9 instead of 8 token-row requests per k-slice.  NK: slices of k where there
+// are only one or two, which are all requested at the start, else 0.
+template <int NK, int NTJ, bool EXT, int WM, bool GELU, bool RES, int TM = 256>
 __device__ __forceinline__ void gemm256_wave(const Gemm256Params &p, unsigned char *smem, int m0, int n0,
                                              int wave, int lane) {
   static_assert(TM == 256 || (TM == 192 && !EXT && NTJ <= 3), "192-row tiles: three slabs per wave, no ninth slab");
@@ -250,17 +251,17 @@ __device__ __forceinline__ void gemm256_wave(const Gemm256Params &p, unsigned ch
   // W(t+kSlots), X(t+2), ..; after the first k-step of slice t every wave has its X fragments and X(t+2) takes
   // their place, after the third the W fragments and W(t+kSlots) does.  Before the fourth, slice t+1 must have
   // landed for every wave; X(t+2) and (three slots) W(t+2) may still be on their way.
-  const int nk = p.K / 64;                             // at least 3
+  const int nk = NK ? NK : p.K / 64;                   // at least 3 if not NK
   constexpr int kBehind = XREQ + (kSlots - 2) * 8;
 #pragma unroll
-  for (int s = 0; s < kSlots; s++) {
+  for (int s = 0; s < (NK ? NK : kSlots); s++) {
 #pragma unroll
     for (int j = 0; j < 8; j++) issue_w(s, s, j);
     if (s < 2)
 #pragma unroll
       for (int j = 0; j < XREQ; j++) issue_x(s, j);
   }
-  wait_vm<8 + kBehind>();
+  wait_vm<NK == 0 ? 8 + kBehind : (NK - 1) * (8 + XREQ)>();
   meet();
 #pragma unroll
   for (int ti = 0; ti < 4; ti++) read_w(0, 0, ti);
@@ -285,18 +286,24 @@ __device__ __forceinline__ void gemm256_wave(const Gemm256Params &p, unsigned ch
   };
   auto next = [&](int slot) { return slot + 1 == kSlots ? 0 : slot + 1; };
   int t = 0, slot = 0;
-  for (; t < nk - kSlots; t++) {
-    const int slot_next = next(slot);
-    slice(std::integral_constant<int, kSlots>{}, t, slot, slot_next);
-    slot = slot_next;
+  if (NK == 0) {
+    for (; t < nk - kSlots; t++) {
+      const int slot_next = next(slot);
+      slice(std::integral_constant<int, kSlots>{}, t, slot, slot_next);
+      slot = slot_next;
+    }
+    if (kSlots == 3) {
+      slice(K2{}, t, slot, next(slot));
+      t++;
+      slot = next(slot);
+    }
   }
-  if (kSlots == 3) {
-    slice(K2{}, t, slot, next(slot));
+  if (NK != 1) {
+    slice(K1{}, t, slot, next(slot));
     t++;
     slot = next(slot);
   }
-  slice(K1{}, t, slot, next(slot));
-  slice(K0{}, t + 1, next(slot), 0);
+  slice(K0{}, t, slot, 0);
   // (the accumulators are final here: left to itself the compiler sinks the last products into the epilogue's slabs,
   // and their operands are spilled on the way)
 #pragma unroll
@@ -319,7 +326,7 @@ __device__ __forceinline__ void gemm256_wave(const Gemm256Params &p, unsigned ch
   }
 }
 
-template <bool GELU, bool RES>
+template <int NK, bool GELU, bool RES>
 __global__ __launch_bounds__(256) void gemm256_bf16_kernel(Gemm256Params p) {
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   // workgroups are dealt round-robin to the 8 XCDs; give each XCD a contiguous run of tiles (n
@@ -347,33 +354,32 @@ __global__ __launch_bounds__(256) void gemm256_bf16_kernel(Gemm256Params p) {
   const int rows = min(p.M - (m0 + wm * wrows), wrows);   // may be <= 0
   const int ntj = __builtin_amdgcn_readfirstlane(rows <= 0 ? 0 : (rows + 31) / 32);
   if (ext) {   // the extended tile is full: 256 + (1..32) rows
-    if (wm) gemm256_wave<4, true, 1, GELU, RES>(p, smem, m0, n0, wave, lane);
-    else gemm256_wave<4, true, 0, GELU, RES>(p, smem, m0, n0, wave, lane);
+    if (wm) gemm256_wave<NK, 4, true, 1, GELU, RES>(p, smem, m0, n0, wave, lane);
+    else gemm256_wave<NK, 4, true, 0, GELU, RES>(p, smem, m0, n0, wave, lane);
     return;
   }
   if (tm == 192) {
     switch (ntj) {
-      case 3: gemm256_wave<3, false, 0, GELU, RES, 192>(p, smem, m0, n0, wave, lane); break;
-      case 2: gemm256_wave<2, false, 0, GELU, RES, 192>(p, smem, m0, n0, wave, lane); break;
-      case 1: gemm256_wave<1, false, 0, GELU, RES, 192>(p, smem, m0, n0, wave, lane); break;
-      default: gemm256_wave<0, false, 0, GELU, RES, 192>(p, smem, m0, n0, wave, lane); break;
+      case 3: gemm256_wave<NK, 3, false, 0, GELU, RES, 192>(p, smem, m0, n0, wave, lane); break;
+      case 2: gemm256_wave<NK, 2, false, 0, GELU, RES, 192>(p, smem, m0, n0, wave, lane); break;
+      case 1: gemm256_wave<NK, 1, false, 0, GELU, RES, 192>(p, smem, m0, n0, wave, lane); break;
+      default: gemm256_wave<NK, 0, false, 0, GELU, RES, 192>(p, smem, m0, n0, wave, lane); break;
     }
     return;
   }
   switch (ntj) {
-    case 4: gemm256_wave<4, false, 0, GELU, RES>(p, smem, m0, n0, wave, lane); break;
-    case 3: gemm256_wave<3, false, 0, GELU, RES>(p, smem, m0, n0, wave, lane); break;
-    case 2: gemm256_wave<2, false, 0, GELU, RES>(p, smem, m0, n0, wave, lane); break;
-    case 1: gemm256_wave<1, false, 0, GELU, RES>(p, smem, m0, n0, wave, lane); break;
-    default: gemm256_wave<0, false, 0, GELU, RES>(p, smem, m0, n0, wave, lane); break;
+    case 4: gemm256_wave<NK, 4, false, 0, GELU, RES>(p, smem, m0, n0, wave, lane); break;
+    case 3: gemm256_wave<NK, 3, false, 0, GELU, RES>(p, smem, m0, n0, wave, lane); break;
+    case 2: gemm256_wave<NK, 2, false, 0, GELU, RES>(p, smem, m0, n0, wave, lane); break;
+    case 1: gemm256_wave<NK, 1, false, 0, GELU, RES>(p, smem, m0, n0, wave, lane); break;
+    default: gemm256_wave<NK, 0, false, 0, GELU, RES>(p, smem, m0, n0, wave, lane); break;
   }
 }
 
 }  // namespace
 
-// (K: the pipeline is three slices deep; less K has nothing to gain from large tiles)
 bool gemm256_supported(int M, int N, int K) {
-  return M >= 256 && N % 256 == 0 && K % 64 == 0 && K >= 192;
+  return M >= 256 && N % 256 == 0 && K % 64 == 0 && K >= 64;
 }
 
 ns_status launch_gemm256(const uint16_t *a, const uint16_t *w, const float *bias, const uint16_t *r,
@@ -427,11 +433,17 @@ ns_status launch_gemm256(const uint16_t *a, const uint16_t *w, const float *bias
   const long long wgs = (long long)p.ntm * p.ntn * batch;
   if (wgs > 0x7fffffffLL) return fail(NS_ERR_UNSUPPORTED, "GEMM grid too large");
   typedef void (*kern_t)(Gemm256Params);
-  static const kern_t kerns[4] = {gemm256_bf16_kernel<false, false>, gemm256_bf16_kernel<false, true>,
-                                  gemm256_bf16_kernel<true, false>, gemm256_bf16_kernel<true, true>};
-  const ns_status rs = reserve_lds_once(reinterpret_cast<const void *>(kerns[(gelu ? 2 : 0) + (r ? 1 : 0)]), kGemmLds);
+  // K = 64 and 128: the pipeline is three slices deep, they have instantiations without it (16385 x 1024: 11.3 and
+  // 12.6 us, with residual 14.6 and 16.1; the kernel of 128 x 128 tiles 19.4 and 22.5, 27.9 and 31.2)
+#define NS_KERNS(NK)                                                                                                     \
+  {gemm256_bf16_kernel<NK, false, false>, gemm256_bf16_kernel<NK, false, true>, gemm256_bf16_kernel<NK, true, false>,     \
+   gemm256_bf16_kernel<NK, true, true>}
+  static const kern_t kerns[3][4] = {NS_KERNS(0), NS_KERNS(1), NS_KERNS(2)};
+#undef NS_KERNS
+  const kern_t kern = kerns[K >= 192 ? 0 : K / 64][(gelu ? 2 : 0) + (r ? 1 : 0)];
+  const ns_status rs = reserve_lds_once(reinterpret_cast<const void *>(kern), kGemmLds);
   if (rs != NS_OK) return rs;
-  hipLaunchKernelGGL(kerns[(gelu ? 2 : 0) + (r ? 1 : 0)], dim3((unsigned)wgs), dim3(256), kGemmLds, s, p);
+  hipLaunchKernelGGL(kern, dim3((unsigned)wgs), dim3(256), kGemmLds, s, p);
   return check_launch("gemm256_bf16_kernel");
 }
 

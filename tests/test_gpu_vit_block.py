@@ -333,6 +333,9 @@ def test_gelu_epilogue_value_by_value(nb, n):
     (1025, 1024, 192, True, False),     # ninth slab
     (577, 512, 256, False, True),       # partial tile
     (12000, 2048, 320, True, True),     # 192-row tiles
+    # one and two slices of k
+    (16385, 1024, 64, False, True), (1025, 1024, 64, True, False), (577, 512, 64, True, True),
+    (16385, 1024, 128, True, True), (1025, 1024, 128, False, True), (577, 512, 128, False, False), (12000, 2048, 128, False, True),
 ])
 def test_linear_forward(nb, M, N, K, gelu, res):
     """The fused linear map against float64 matmul / erf GELU on the same bf16 inputs."""
