@@ -13,6 +13,7 @@
 #include "ns_common.h"
 #include <algorithm>
 #include <cmath>
+#include <type_traits>
 
 namespace ns {
 
@@ -165,9 +166,16 @@ struct StepBf16 {
   uint32_t kch[2], vch;       // source chunk of this lane's 16 bytes
   uint32_t krd[4], vrd[2][2];
   int rrow;                   // row of request 0 this lane moves; request it: + 8 it
+  // The first step's first keys are global tokens, which every row sees and which can be most of a row: their weights
+  // enter with the bits they have in fp32.  Of one token: the reference is its logit, so its weight is 1.  Of
+  // several, or where the reference follows the largest logit: what bf16 rounding leaves comes in two further terms.
+  bool anchor;                // key 0 is a global token
+  int exact;                  // so many keys (8 at most) take the further terms
 
   __device__ __forceinline__ void init(int lane) {
     const int l32 = lane & 31, hh = lane >> 5;
+    anchor = false;
+    exact = 0;
     rrow = lane >> 3;
     // LDS chunk c of row r holds chunk c ^ ((r>>1)&7) of K and c ^ 4*((r>>1)&1) of V: conflict-free reads
     kch[0] = 16u * ((lane & 7) ^ (lane >> 4));
@@ -300,6 +308,32 @@ struct StepBf16 {
           o[nt][dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, pf[nt][sp], o[nt][dt], 0, 0, 0);
       }
   }
+  // O^T += V^T (w - bf16(w)) for the first `exact` keys of a step, 16 bits of it in two terms: the keys 0..7 stand
+  // in a fragment's first four elements, V's once more in the other four
+  __device__ __forceinline__ void add_rest(const f32x16 &w, const unsigned char *slot, f32x16 (&o)[2], int lane) const {
+    bf16x8 r;
+#pragma unroll
+    for (int e = 0; e < 4; e += 2) {
+      const int key = 4 * (lane >> 5) + e;
+      float a = w[e], b = w[e + 1];
+      uint32_t u = pack_bf16(a, b);
+#pragma unroll
+      for (int t = 0; t < 2; t++) {
+        a = key < exact ? a - bf16_lo(u) : 0.f;
+        b = key + 1 < exact ? b - bf16_hi(u) : 0.f;
+        u = pack_bf16(a, b);
+        const bf16x2 pk = __builtin_bit_cast(bf16x2, u);
+        r[4 * t + e] = pk[0];
+        r[4 * t + e + 1] = pk[1];
+      }
+    }
+#pragma unroll
+    for (int dt = 0; dt < 2; dt++) {
+      const bf16x4 v = __builtin_bit_cast(bf16x4, __builtin_amdgcn_ds_read_tr16_b64_v4i16((tr_ptr)(slot + vrd[dt][0])));
+      const bf16x8 vv = {v[0], v[1], v[2], v[3], v[0], v[1], v[2], v[3]};
+      o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vv, r, o[dt], 0, 0, 0);
+    }
+  }
   static __device__ __forceinline__ uint32_t screen(uint32_t two, int pass) {
     return screened(two & 0xffff0000u, pass) | (screened(two << 16, pass) >> 16);
   }
@@ -429,7 +463,8 @@ struct WaveAcc {
     }
     return __any(!(big < limit));
   }
-  __device__ __forceinline__ void reference(const f32x16 &s, int nt, float c) {
+  // key0: the logit of the step's first key, unless another exceeds it by far
+  __device__ __forceinline__ void reference(const f32x16 &s, int nt, float c, bool key0 = false) {
     float a = fmaxf(s[0], s[1]), b = fmaxf(s[2], s[3]);
 #pragma unroll
     for (int e = 4; e < 16; e += 4) {
@@ -438,7 +473,9 @@ struct WaveAcc {
     }
     const float top = half_swap_max(fmaxf(a, b)) * c;
     if (__any(top > m[nt])) {
-      const float m_new = fmaxf(m[nt], top);
+      float m_new = fmaxf(m[nt], top);
+      // (a token whose weight is below 2^-64 of the row's has no bits in the row)
+      if (key0) m_new = m_new > low_half(s[0]) * c + 64.f ? m_new : low_half(s[0]) * c;
       const float alpha = __builtin_amdgcn_exp2f(m[nt] - m_new);
       m[nt] = m_new;
       l[nt] *= alpha;
@@ -524,7 +561,8 @@ __device__ __forceinline__ void walk_keys_pipelined(const S &st, WaveAcc<S, 2> &
   st.load_k(kf, wsm);
   s0 = st.product(kf, a.q[0]);
   fix(0, 0, s0);
-  a.reference(s0, 0, c);
+  const bool key0 = st.anchor && !careful;
+  a.reference(s0, 0, c, key0);
   asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
   if (n > 2) {
     tokens(2);
@@ -535,28 +573,32 @@ __device__ __forceinline__ void walk_keys_pipelined(const S &st, WaveAcc<S, 2> &
     issue_v(1, tk);
   }
   // a higher reference for half nt, whose output product is not the open one
-  auto raise = [&](int nt, const f32x16 &s) {
+  auto raise = [&](int nt, const f32x16 &s, bool by_key0) {
     a.l[nt] = nt ? l1[0] + l1[1] : l0[0] + l0[1];
-    a.reference(s, nt, c);
+    a.reference(s, nt, c, by_key0);
     if (nt) { l1[0] = a.l[1]; l1[1] = 0.f; } else { l0[0] = a.l[0]; l0[1] = 0.f; }
   };
   // step i, whose V is in slot `odd`; `odd` = i & 1 is a constant at each place of use
-  auto step = [&](int i, int odd) {
+  auto step = [&](auto first_c, int i, int odd) {
+    constexpr bool first = decltype(first_c)::value;
     const int rem = n - 1 - i;
     // K of step i + 1 and V of step i.  Behind them: K of step i + 2 (and a token request), V of step i + 1.
     if (rem >= 2) wait_vm<2 * R + TL>();
     else if (rem == 1) wait_vm<R>();
     else wait_vm<0>();
-    const bool special = FIXED || careful || i == 0 || rem <= 1;
+    const bool special = FIXED || careful || first || rem <= 1;
     const unsigned char *vslot = wsm + kV + odd * S::kHalf;
     st.load_v(vf, vslot, 0);
     st.template half_step<true>(s0, c, -a.m[0], l0, a.o[0], a.o[1], open, vf, vslot, kf, a.q[1], s1);
+    const bool rest = first && st.exact > 0;
+    if (rest) st.add_rest(s0, vslot, a.o[0], lane);
     if (special) {
       fix(i, 1, s1);
-      if (careful || i == 0) raise(1, s1);
+      if (careful || first) raise(1, s1, key0);
     }
     st.load_k(kf, wsm + (odd ^ 1) * S::kHalf);      // (behind the last step: what the slot holds, not used)
     st.template half_step<false>(s1, c, -a.m[1], l1, a.o[1], a.o[0], open, vf, vslot, kf, a.q[0], s0);
+    if (rest) st.add_rest(s1, vslot, a.o[1], lane);
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");       // both slots have been read
     if (rem >= 3) {
       tokens(i + 3);
@@ -568,12 +610,14 @@ __device__ __forceinline__ void walk_keys_pipelined(const S &st, WaveAcc<S, 2> &
     }
     if (special && rem > 0) {
       fix(i + 1, 0, s0);
-      if (careful) raise(0, s0);
+      if (careful) raise(0, s0, false);
     }
   };
-  for (int i = 0; i < n; i += 2) {
-    step(i, 0);
-    if (i + 1 < n) step(i + 1, 1);
+  // (the first step by itself: what only it does, in the loop behind a branch, made 100 x 100 patches 97 -> 100 us)
+  step(std::true_type{}, 0, 0);
+  for (int i = 1; i < n; i += 2) {
+    step(std::false_type{}, i, 1);
+    if (i + 1 < n) step(std::false_type{}, i + 1, 0);
   }
 #pragma unroll
   for (int dt = 0; dt < 2; dt++) a.o[1][dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf.f[1][dt], open, a.o[1][dt], 0, 0, 0);
@@ -687,6 +731,10 @@ __device__ __forceinline__ void walk_keys(const S &st, WaveAcc<S, NT> &a, const 
       else wait_vm<E>();
       screen(wsm + kV + slot * S::kHalf);
       st.template weigh<NT, LO>(s, wsm + kV + slot * S::kHalf, a.o, lane);
+      if constexpr (S::kDepth == 2 && NT == 2)
+        if (slot == 0 && i == 0 && st.exact > 0)
+#pragma unroll
+          for (int nt = 0; nt < NT; nt++) st.add_rest(s[nt], wsm + kV, a.o[nt], lane);
       if (rem >= D) {
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         issue_v(slot);
@@ -976,7 +1024,9 @@ __device__ __forceinline__ void window_attention(const WindowParams &p, unsigned
       for (int e = 0; e < 16; e++) s[e] = jb + 8 * (e >> 2) + (e & 3) < w.nkeys ? s[e] : -INFINITY;
     }
   };
+  if constexpr (kBf16) st.anchor = part == 0;
   for (bool careful = MASK && part != 0;; careful = true) {
+    if constexpr (kBf16) st.exact = part == 0 && (careful || g.n_global > 1) ? min(g.n_global, 8) : 0;
     window_walk<S, NT, LISTS, MASK>(st, a, kb, vb, rowB, wsm, n, c, careful, lane, key_token, key_entry, fix_token, hide);
     if (!a.exceeds(careful ? INFINITY : kLargeSum)) break;
     if (careful) {
