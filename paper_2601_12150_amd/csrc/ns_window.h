@@ -278,35 +278,40 @@ struct StepBf16 {
     }
     open = second;
   }
-  // O^T += V^T w.  LO: lanes of columns 16..31 take what bf16 rounding leaves of a weight, w - bf16(w)
+  // O^T += V^T w.  LO: columns 16..31 are the first 16 once more and take what bf16 rounding leaves of a weight,
+  // w - bf16(w); what that leaves in turn comes in a second product, so that all 24 bits of a weight enter.
   template <int NT, bool LO>
   __device__ __forceinline__ void weigh(const f32x16 (&w)[NT], const unsigned char *slot, f32x16 (&o)[NT][2], int lane) const {
-    bf16x8 pf[NT][2];
+    bf16x8 pf[NT][2], pr[NT][2];
 #pragma unroll
     for (int nt = 0; nt < NT; nt++)
 #pragma unroll
       for (int i = 0; i < 16; i += 2) {
         uint32_t u = pack_bf16(w[nt][i], w[nt][i + 1]);
         if (LO) {
-          const uint32_t lo = pack_bf16(w[nt][i] - bf16_lo(u), w[nt][i + 1] - bf16_hi(u));
+          const float r0 = w[nt][i] - bf16_lo(u), r1 = w[nt][i + 1] - bf16_hi(u);
+          const uint32_t lo = pack_bf16(r0, r1), last = (lane & 16) ? 0u : pack_bf16(r0 - bf16_lo(lo), r1 - bf16_hi(lo));
           u = (lane & 16) ? lo : u;
+          const bf16x2 pl = __builtin_bit_cast(bf16x2, last);
+          pr[nt][i >> 3][i & 7] = pl[0];
+          pr[nt][i >> 3][(i & 7) + 1] = pl[1];
         }
         const bf16x2 pk = __builtin_bit_cast(bf16x2, u);
         pf[nt][i >> 3][i & 7] = pk[0];
         pf[nt][i >> 3][(i & 7) + 1] = pk[1];
       }
 #pragma unroll
-    for (int sp = 0; sp < 2; sp++)
+    for (int sp = 0; sp < 2; sp++) {
+      V v;
+      load_v(v, slot, sp);
 #pragma unroll
-      for (int dt = 0; dt < 2; dt++) {
-        const s16x4 lo4 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((tr_ptr)(slot + vrd[dt][0] + sp * 2048));
-        const s16x4 hi4 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((tr_ptr)(slot + vrd[dt][1] + sp * 2048));
-        const bf16x4 a = __builtin_bit_cast(bf16x4, lo4), b2 = __builtin_bit_cast(bf16x4, hi4);
-        const bf16x8 vf = {a[0], a[1], a[2], a[3], b2[0], b2[1], b2[2], b2[3]};
+      for (int term = 0; term < (LO ? 2 : 1); term++)
 #pragma unroll
-        for (int nt = 0; nt < NT; nt++)
-          o[nt][dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, pf[nt][sp], o[nt][dt], 0, 0, 0);
-      }
+        for (int dt = 0; dt < 2; dt++)
+#pragma unroll
+          for (int nt = 0; nt < NT; nt++)
+            o[nt][dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v.f[sp][dt], term ? pr[nt][sp] : pf[nt][sp], o[nt][dt], 0, 0, 0);
+    }
   }
   // O^T += V^T (w - bf16(w)) for the first `exact` keys of a step, 16 bits of it in two terms: the keys 0..7 stand
   // in a fragment's first four elements, V's once more in the other four
@@ -840,7 +845,7 @@ __device__ __forceinline__ f32x4 parked(const unsigned char *smem, int w, int ro
 // head, 32 keys a step and wave, all rows of the group against the same K and V rows (which are
 // read once however many global tokens there are).  Leaves the raw logits and one softmax partial
 // (max, sum, weighted V sum) per row and chunk.  bf16: a group is 16 rows, in the operand's columns
-// twice, so that the second product gets every weight as bf16 head and bf16 rest: 16 bits of it.
+// twice, so that the second product gets every weight as bf16 head and bf16 rest (and the rest of that).
 // ------------------------------------------------------------------------------------------
 struct GlobalRows {
   const void *q, *k, *v;

@@ -1,4 +1,4 @@
-"""Places where fp32 weights show through the rounding of the result."""
+"""Places where fp32 weights show through the rounding of the result: the global tokens as keys, and the global rows."""
 import numpy as np
 import pytest
 import torch
@@ -42,3 +42,30 @@ def test_a_global_tokens_weight_is_not_rounded(nb, monkeypatch, pruned, g, block
     err = np.abs(to_np(out)[:, :, G:][:, :, rows, :G] - ref) / ref
     # 2^-8 for the result, 64 products and N weights summed in fp32
     assert err.max() <= 2.0 ** -8 + 1e-5, "largest relative error %.3g" % err.max()
+
+
+@pytest.mark.parametrize("G", [1, 2, 20])
+@pytest.mark.parametrize("g,block,force", [(24, 8, "lists"), (40, 8, "lists"), (33, 16, "block")])
+def test_a_global_rows_weights_have_fp32s_bits(nb, monkeypatch, g, block, force, G):
+    """Channel c sums two keys with values 1 and -1 whose logits lie 2^-12 apart: the row's value is 2^-12 of a weight,
+    so a weight rounded to 16 bits (2^-17) is off by 2^-5 of the result.  fp32: exp2 of an argument below 8 is good to
+    2^-22, i.e. 2^-10 of the result, three times that with the sums; 2^-8 for its rounding."""
+    monkeypatch.setenv("NSATTN_KERNEL", force)
+    N = g * g
+    rng = np.random.default_rng(N + G)
+    q = np.zeros((1, 2, G + N, 64), np.float32)
+    k, v = np.zeros_like(q), np.zeros_like(q)
+    q[..., :2] = 1.0
+    k[..., 0] = rng.integers(-64, 65, size=k.shape[:3]) / 8.0           # logits of -1 to 1
+    a = G + rng.permutation(N)[:128].reshape(64, 2)
+    for c in range(64):
+        k[:, :, a[c, 1], 0] = k[:, :, a[c, 0], 0]
+        k[:, :, a[c, 0], 1] = 2.0 ** -9                                  # x 0.125
+        v[:, :, a[c, 0], c] = 1.0
+        v[:, :, a[c, 1], c] = -1.0
+    print("global row: %d block %d G=%d %s" % (g, block, G, force), flush=True)
+    out = nb.ns_attn_forward(*(to_dev(x, "bf16") for x in (q, k, v)), g, g, block, 0.125, n_global=G)
+    torch.cuda.synchronize()
+    ref = oracle.ns_attn(q, k, v, g, g, block, 0.125, n_global=G)[:, :, :G]
+    err = np.abs(to_np(out)[:, :, :G] - ref) / np.abs(ref)
+    assert err.max() <= 2.0 ** -8 + 3 * 2.0 ** -10, "largest relative error %.3g" % err.max()
