@@ -317,7 +317,9 @@ __global__ __launch_bounds__(kCombineThreads) void cls_combine_scores_kernel(con
 }  // namespace
 
 template <class S, bool WITH_V, bool LOGITS>
-static ns_status launch_rows(const ns_attn_desc &d, const GlobalRows &p, hipStream_t s) {
+static ns_status launch_rows(const ns_attn_desc &d, const void *q, const void *k, const void *v, float *logits, float *partials,
+                             hipStream_t s) {
+  const GlobalRows p = global_rows<S>(d, q, k, v, logits, partials);
   const int nch = cls_num_chunks(d.tokens), groups = (d.n_global + global_group_rows<S>() - 1) / global_group_rows<S>();
   const long long wgs = (long long)nch * groups * d.heads * d.batch;
   if (wgs > 0x7fffffffLL) return fail(NS_ERR_UNSUPPORTED, "launch grid too large");
@@ -330,7 +332,6 @@ static ns_status launch_rows(const ns_attn_desc &d, const GlobalRows &p, hipStre
 
 ns_status launch_cls_row(const ns_attn_desc &d, const void *q, const void *k, const void *v,
                          float *logits, float *partials, bool with_v, hipStream_t s) {
-  const GlobalRows p{q, k, v, d.q_stride_b, d.q_stride_h, d.q_stride_t, d.scale, logits, partials};
   if (d.n_global == 1 && !with_v && logits && d.heads <= 65535 && d.batch <= 65535) {
     const int nch = cls_num_chunks(d.tokens);
     dim3 grid(nch, d.heads, d.batch), blk(256);
@@ -351,8 +352,10 @@ ns_status launch_cls_row(const ns_attn_desc &d, const void *q, const void *k, co
     return check_launch("cls_scan_v_kernel");
   }
 #define NS_ROWS(S)                                                                                      \
-  (with_v ? (logits ? launch_rows<S, true, true>(d, p, s) : launch_rows<S, true, false>(d, p, s))       \
-          : (logits ? launch_rows<S, false, true>(d, p, s) : launch_rows<S, false, false>(d, p, s)))
+  (with_v ? (logits ? launch_rows<S, true, true>(d, q, k, v, logits, partials, s)                       \
+                    : launch_rows<S, true, false>(d, q, k, v, logits, partials, s))                     \
+          : (logits ? launch_rows<S, false, true>(d, q, k, v, logits, partials, s)                      \
+                    : launch_rows<S, false, false>(d, q, k, v, logits, partials, s)))
   if (d.dtype == NS_F32) return NS_ROWS(StepF32<float>);
   // (the bf16 step wants a positive scale and 32-bit row offsets)
   if (d.scale > 0.f && (long long)d.tokens * d.q_stride_t * 2 < 0x7fffffffLL) return NS_ROWS(StepBf16);

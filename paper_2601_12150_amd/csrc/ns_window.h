@@ -853,8 +853,15 @@ struct GlobalRows {
   float scale;
   float *logits;           // [B, H, G, T] or NULL
   float *partials;         // [B, H*G, nchunks, 66]
+  double nat;              // natural units of a step's exponents: what one of them is as a logit
 };
 template <class S> constexpr int global_group_rows() { return S::kDepth == 2 ? 16 : 32; }
+// (a step's exponent is q.k * c with c = scale * log2(e) rounded to fp32; fp32 rows are scaled before)
+template <class S>
+inline GlobalRows global_rows(const ns_attn_desc &d, const void *q, const void *k, const void *v, float *logits, float *partials) {
+  const double nat = S::kDepth == 2 ? (double)d.scale / (double)(d.scale * kLog2e) : 1.0 / (double)kLog2e;
+  return GlobalRows{q, k, v, d.q_stride_b, d.q_stride_h, d.q_stride_t, d.scale, logits, partials, nat};
+}
 
 template <class S, bool WITH_V, bool LOGITS>
 __device__ __forceinline__ void global_rows_chunk(const GlobalRows &p, int heads, int G, int T, int groups, int nchunks,
@@ -933,8 +940,15 @@ __device__ __forceinline__ void global_rows_chunk(const GlobalRows &p, int heads
       }
     }
     float *rec = p.partials + (((size_t)(b * heads + h) * G + gr) * nchunks + chunk) * kClsPartialFloats;
+    // The record's maximum is a logit, M an exponent: what rounding the one to fp32 leaves goes into the sums.
+    // (Left out, a log-sum-exp near 500 is off by a whole unit in the last place, 3e-5.)
+    const double m = (double)M * p.nat;
+    const float mr = (float)m, f0 = __builtin_amdgcn_exp2f((float)((m - (double)mr) * 1.4426950408889634));
+    L *= f0;
+#pragma unroll
+    for (int e = 0; e < 4; e++) O[e] *= f0;
     if (ch == 0) {
-      rec[0] = M * kLn2;
+      rec[0] = mr;
       rec[1] = L;
     }
     if (WITH_V) {
@@ -1147,7 +1161,7 @@ inline long long window_geometry(const AttnArgs &a, int qt, int rows_per_group, 
 template <class S, int NT>
 inline long long window_params(const AttnArgs &a, float *logits, float *partials, WindowParams &p, int &ks) {
   const ns_attn_desc &d = a.d;
-  p.r = GlobalRows{a.q, a.k, a.v, d.q_stride_b, d.q_stride_h, d.q_stride_t, d.scale, logits, partials};
+  p.r = global_rows<S>(d, a.q, a.k, a.v, logits, partials);
   p.out = a.out;
   p.osb = d.out_stride_b; p.osh = d.out_stride_h; p.ost = d.out_stride_t;
   return window_geometry(a, 32 * NT, partials ? global_group_rows<S>() : 0, cls_num_chunks(d.tokens), p.g, ks);

@@ -1,4 +1,5 @@
-"""Places where fp32 weights show through the rounding of the result: the global tokens as keys, and the global rows."""
+"""Places where fp32 weights and sums show through the rounding of the result: the global tokens as keys, the global
+rows, and their log-sum-exps."""
 import numpy as np
 import pytest
 import torch
@@ -69,3 +70,33 @@ def test_a_global_rows_weights_have_fp32s_bits(nb, monkeypatch, g, block, force,
     ref = oracle.ns_attn(q, k, v, g, g, block, 0.125, n_global=G)[:, :, :G]
     err = np.abs(to_np(out)[:, :, :G] - ref) / np.abs(ref)
     assert err.max() <= 2.0 ** -8 + 3 * 2.0 ** -10, "largest relative error %.3g" % err.max()
+
+
+@pytest.mark.parametrize("G,dtype,force", [(1, "bf16", "lists"), (2, "bf16", "lists"), (3, "f32", "generic"), (2, "bf16", "generic")])
+def test_log_sum_exp_of_large_logits(nb, monkeypatch, G, dtype, force):
+    """Logits of up to 900 with no rounding of their own (one product each): the log-sum-exp is the maximum plus a small
+    number, added once, so it lies half a unit in the last place from the true one (and what fp32's log2(e) and
+    the sum add: 2e-8 of it and 1e-6)."""
+    monkeypatch.setenv("NSATTN_KERNEL", force)
+    g, H = 40, 8
+    N = g * g
+    rng = np.random.default_rng(G)
+    q = np.zeros((2, H, G + N, 64), np.float32)
+    k = np.zeros_like(q)
+    v = synth.small_case(3, 2, H, 64, g, g, dtype, n_global=G)[2]
+    q[..., 0] = 1.0 + rng.integers(0, 128, size=q.shape[:3]) / 128.0
+    k[..., 0] = 8.0 * rng.integers(128, 256, size=k.shape[:3])
+    k[..., 0] += 8.0 * (np.arange(G + N) % 7 == 0)
+    k = synth.round_to_bf16(k)
+    out, logits, lse, scores = nb.ns_attn_forward_scores(*(to_dev(a, dtype) for a in (q, k, v)), g, g, 8, 0.125, n_global=G)
+    torch.cuda.synchronize()
+    ref_logits = 0.125 * q[:, :, :G, :1].astype(np.float64) * k[:, :, None, :, 0].astype(np.float64)
+    got_logits = to_np(logits).reshape(ref_logits.shape)
+    assert np.array_equal(got_logits, ref_logits)
+    m = ref_logits.max(-1, keepdims=True)
+    ref = (m + np.log(np.exp(ref_logits - m).sum(-1, keepdims=True)))[..., 0]
+    err = np.abs(lse.double().cpu().numpy().reshape(ref.shape) - ref)
+    half_ulp = 0.5 * np.spacing(ref.astype(np.float32)).astype(np.float64)
+    worst = float((err / (half_ulp + 2e-8 * ref + 1e-6)).max())
+    print("log-sum-exp G=%d %s %s: %.3f of the bound" % (G, dtype, force, worst), flush=True)
+    assert worst <= 1.0
