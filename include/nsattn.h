@@ -66,7 +66,7 @@ typedef enum { NS_F32 = 0, NS_BF16 = 1 } ns_dtype;
  * coords_out that topk_filter and gather write from valid coords_in always satisfy it.
  */
 typedef struct ns_attn_desc {
-  int32_t batch;     /* B >= 1                                                           */
+  int32_t batch;     /* B >= 1; NS_ERR_UNSUPPORTED above 65535                           */
   int32_t heads;     /* H >= 1                                                           */
   int32_t head_dim;  /* D; this build implements 64                                      */
   int32_t grid_h;    /* patch grid rows                                                  */

@@ -242,11 +242,18 @@ static ns_status launch_patch_attention(const AttnArgs &a) {
   }
 }
 
+// What a launch needs on top of a valid descriptor: images are a grid's second or third dimension.
+static ns_status validate_call(const ns_attn_desc *desc, bool need_grid = true) {
+  const ns_status st = validate_desc(desc, need_grid, need_grid);
+  if (st == NS_OK && desc->batch > 65535) return fail(NS_ERR_UNSUPPORTED, "batch above 65535");
+  return st;
+}
+
 // Shared by ns_attn_forward and the timing aid: validation, workspace carving, block lists.
 static ns_status prepare_attn(const ns_attn_desc *desc, const void *q, const void *k, const void *v,
                               void *out, void *workspace, size_t workspace_bytes, void *stream,
                               AttnArgs &a, float *&partials, bool reuse_lists = false) {
-  ns_status st = validate_desc(desc, true);
+  ns_status st = validate_call(desc);
   if (st != NS_OK) return st;
   if (!q || !k || !v || !out) return fail(NS_ERR_INVALID_ARG, "q, k, v and out must not be NULL");
   if (!aligned(q, 16) || !aligned(k, 16) || !aligned(v, 16) || !aligned(out, 16))
@@ -293,11 +300,11 @@ ns_status ns_attn_forward_scores(const ns_attn_desc *desc, const void *q, const 
 
 }  // extern "C"
 
-ns_status ns::attn_validate(const ns_attn_desc *desc) { return validate_desc(desc, true); }
+ns_status ns::attn_validate(const ns_attn_desc *desc) { return validate_call(desc); }
 
 ns_status ns::cls_scores_impl(const ns_attn_desc *desc, const void *q, const void *k, float *scores,
                               void *workspace, size_t workspace_bytes, void *stream) {
-  ns_status st = validate_desc(desc, false, false);
+  ns_status st = validate_call(desc, false);
   if (st != NS_OK) return st;
   if (!q || !k || !scores) return fail(NS_ERR_INVALID_ARG, "q, k and scores must not be NULL");
   if (!aligned(q, 16) || !aligned(k, 16) || !aligned(scores, 4))

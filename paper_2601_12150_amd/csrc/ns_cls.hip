@@ -332,7 +332,7 @@ static ns_status launch_rows(const ns_attn_desc &d, const void *q, const void *k
 
 ns_status launch_cls_row(const ns_attn_desc &d, const void *q, const void *k, const void *v,
                          float *logits, float *partials, bool with_v, hipStream_t s) {
-  if (d.n_global == 1 && !with_v && logits && d.heads <= 65535 && d.batch <= 65535) {
+  if (d.n_global == 1 && !with_v && logits) {
     const int nch = cls_num_chunks(d.tokens);
     dim3 grid(nch, d.heads, d.batch), blk(256);
     if (d.dtype == NS_F32)
@@ -344,7 +344,7 @@ ns_status launch_cls_row(const ns_attn_desc &d, const void *q, const void *k, co
                          d.scale, logits, partials, nch);
     return check_launch("cls_scan_kernel");
   }
-  if (d.n_global == 1 && with_v && d.dtype == NS_BF16 && d.heads <= 65535 && d.batch <= 65535) {
+  if (d.n_global == 1 && with_v && d.dtype == NS_BF16) {
     const int nch = cls_num_chunks(d.tokens);
     hipLaunchKernelGGL(cls_scan_v_kernel, dim3(nch, d.heads, d.batch), dim3(256), 0, s, static_cast<const uint16_t *>(q),
                        static_cast<const uint16_t *>(k), static_cast<const uint16_t *>(v), d.q_stride_b, d.q_stride_h,

@@ -137,6 +137,29 @@ def test_embed_validation(nb):
     assert call(ws_bytes=1024) == nb.NS_ERR_WORKSPACE
 
 
+def test_a_batch_no_launch_can_hold_is_refused_first(nb):
+    """The merge of the global rows, the scoring and the lists have the image in a grid dimension of 16 bits: more
+    images are refused before the attention kernel, which has not, is launched."""
+    L = nb.lib
+    d = good_desc(nb)
+    ok = d.batch
+    d.batch = 65536
+    need = L.ns_attn_workspace_bytes(ctypes.byref(d))
+    out = ctypes.c_void_p(0x90000)
+    ptrs = [ctypes.c_void_p(p) for p in (0x10000, 0x20000, 0x30000)]
+    assert L.ns_attn_forward(ctypes.byref(d), *ptrs, out, None, None, FAKE, need, None) == nb.NS_ERR_UNSUPPORTED
+    assert b"batch" in nb.lib.ns_last_error()
+    need = L.cls_scores_workspace_bytes(ctypes.byref(d))
+    assert L.cls_scores(ctypes.byref(d), *ptrs[:2], FAKE, FAKE, need, None) == nb.NS_ERR_UNSUPPORTED
+    bd = nb.ns_vit_block_desc()
+    bd.attn = d
+    bd.attn.heads, bd.attn.dtype = 8, nb.NS_BF16
+    bd.dim, bd.mlp_dim, bd.ln_eps = 512, 1024, 1e-6
+    w = nb.ns_vit_block_weights(*[0x10000] * 12)
+    assert L.vit_block_forward(ctypes.byref(bd), ctypes.byref(w), FAKE, out, None, FAKE, 1 << 62, None) == nb.NS_ERR_UNSUPPORTED
+    d.batch = ok
+
+
 def test_kernel_choice_policy(nb, monkeypatch):
     """Which kernel serves which problem (host logic; without a device the CU count defaults to 256)."""
     monkeypatch.delenv("NSATTN_KERNEL", raising=False)
