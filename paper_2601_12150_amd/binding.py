@@ -131,9 +131,6 @@ lib = _load()
 from . import _nsbind  # noqa: E402  (after libnsattn.so, which it links to)
 
 
-_nsbind.set_error(NsError)
-
-
 def _check(code: int) -> None:
     if code != NS_OK:
         raise NsError(code, lib.ns_last_error().decode())
@@ -161,6 +158,9 @@ def _raw_stream(stream) -> int:
     if stream is None:
         return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
     return stream.cuda_stream
+
+
+_nsbind.setup(NsError, _raw_stream)
 
 
 def _workspace(nbytes: int, device, workspace: Optional[torch.Tensor]) -> Optional[torch.Tensor]:
@@ -198,16 +198,15 @@ def ns_attn_forward(q, k, v, grid_h, grid_w, block, scale=None, coords=None, out
     Returns out [B,H,T,D] (allocated contiguous unless given) and, with want_cls, also the
     global query's logits [B,H,T] and log-sum-exp [B,H] (both fp32; [B,H,G,T] and [B,H,G] when
     n_global = G > 1)."""
-    return _nsbind.attn(q, k, v, grid_h, grid_w, block, scale, coords, out, workspace, _raw_stream(stream), radius,
-                        int(n_global), 1 if want_cls else 0)
+    return _nsbind.attn(q, k, v, grid_h, grid_w, block, scale, coords, out, workspace, stream, radius, int(n_global),
+                        1 if want_cls else 0)
 
 
 def ns_attn_forward_scores(q, k, v, grid_h, grid_w, block, scale=None, coords=None, out=None,
                            workspace=None, stream=None, n_global=1):
     """ns_attn_forward with the global queries' by-products, and the importance scores of the
     patches from them, in one call.  Returns (out, cls_logits, cls_lse, scores [B, T - n_global])."""
-    return _nsbind.attn(q, k, v, grid_h, grid_w, block, scale, coords, out, workspace, _raw_stream(stream), 1,
-                        int(n_global), 2)
+    return _nsbind.attn(q, k, v, grid_h, grid_w, block, scale, coords, out, workspace, stream, 1, int(n_global), 2)
 
 
 def ns_attn_patch_kernel_time(q, k, v, grid_h, grid_w, block, scale=None, coords=None, out=None,
@@ -237,7 +236,7 @@ def ns_attn_patch_kernel_name(q, grid_h, grid_w, block, scale=None, coords=None,
 
 def cls_scores(q, k, scale=None, n_global=1, scores=None, workspace=None, stream=None):
     """Head-averaged softmax weight of the global query on every patch key: [B, T-G] fp32."""
-    return _nsbind.scores(q, k, scale, n_global, scores, workspace, _raw_stream(stream))
+    return _nsbind.scores(q, k, scale, n_global, scores, workspace, stream)
 
 
 def cls_scores_static(q, k, scale=None, n_global=1, scores=None, stream=None):
@@ -273,14 +272,14 @@ def topk_filter(scores, k, x=None, coords=None, kept_idx=None, y=None, coords_ou
     scores [B,N] fp32; x optional [B,G+N,C] (G = n_global leading rows are kept); coords optional
     [B,N] int32.
     Returns (kept_idx [B,k] int32 ascending, y [B,G+k,C] or None, coords_out [B,k] or None)."""
-    return _nsbind.topk(scores, int(k), x, coords, kept_idx, y, coords_out, workspace, _raw_stream(stream), int(n_global))
+    return _nsbind.topk(scores, int(k), x, coords, kept_idx, y, coords_out, workspace, stream, int(n_global))
 
 
 def vit_embed(pixels, w_patch, b_patch, cls_token, pos_embed, patch, out=None, workspace=None, stream=None):
     """Patch embedding: pixels [B,channels,gh*patch,gw*patch] bf16 -> tokens [B, 1+gh*gw, dim] bf16
     (CLS token in front, position embeddings added).  w_patch [dim, channels*patch*patch] bf16,
     b_patch [dim] fp32, cls_token [dim] bf16, pos_embed [1+gh*gw, dim] bf16."""
-    return _nsbind.embed(pixels, w_patch, b_patch, cls_token, pos_embed, patch, out, workspace, _raw_stream(stream))
+    return _nsbind.embed(pixels, w_patch, b_patch, cls_token, pos_embed, patch, out, workspace, stream)
 
 
 WEIGHT_NAMES = ("ln1_g", "ln1_b", "w_qkv", "b_qkv", "w_proj", "b_proj", "ln2_g", "ln2_b",
@@ -294,7 +293,7 @@ def vit_block_forward(x, weights, grid_h, grid_w, block, heads, ln_eps=1e-6, sca
     x [B,T,dim] bf16 contiguous; weights: dict of device tensors (matrices bf16 [out,in], vectors
     fp32).  Returns x_out [B,T,dim] (and the importance scores [B,T-n_global] with want_scores)."""
     return _nsbind.block(x, weights, grid_h, grid_w, block, heads, ln_eps, scale, coords, want_scores, out, workspace,
-                         _raw_stream(stream), int(n_global))
+                         stream, int(n_global))
 
 
 def linear_forward(x, w, bias, residual=None, gelu=False, out=None, stream=None):
@@ -325,7 +324,7 @@ def vit_forward(x, layer_weights, grid_h, grid_w, block, heads, prune_after=0, k
     (ascending 1-based block numbers) also a list of feature maps [B, grid_h*grid_w, dim], the patch
     tokens after those blocks in raster order."""
     return _nsbind.stack(x, layer_weights, grid_h, grid_w, block, heads, int(prune_after), int(keep_k), ln_eps, scale, out,
-                         workspace, _raw_stream(stream), int(n_global), tap_layers)
+                         workspace, stream, int(n_global), tap_layers)
 
 
 def vit_forward_stages(x, layer_weights, grid_h, grid_w, block, heads, stage_after, stage_keep, ln_eps=1e-6,

@@ -14,6 +14,7 @@
 namespace {
 
 PyObject *g_error = nullptr;       // binding.NsError
+PyObject *g_raw_stream = nullptr;  // binding._raw_stream
 
 struct PyFail {};                  // a Python exception is set
 
@@ -65,7 +66,16 @@ at::Tensor workspace(PyObject *o, size_t nbytes, const at::Tensor &like) {
   return nbytes ? empty({(int64_t)nbytes}, at::kByte, like) : at::Tensor();
 }
 size_t bytes_of(const at::Tensor &ws) { return ws.defined() ? (size_t)ws.numel() : 0; }
-void *stream_of(PyObject *o) { return reinterpret_cast<void *>((intptr_t)integer(o)); }
+// hipStream_t of a stream object or of the current stream.  Asked for when the arguments have been looked at, so that
+// what is wrong with them is reported also where there is no device.
+void *stream_of(PyObject *o) {
+  PyObject *s = PyObject_CallFunctionObjArgs(g_raw_stream, o, nullptr);
+  if (!s) throw PyFail{};
+  const long long v = PyLong_AsLongLong(s);
+  Py_DECREF(s);
+  if (v == -1 && PyErr_Occurred()) throw PyFail{};
+  return reinterpret_cast<void *>((intptr_t)v);
+}
 bool i32_contiguous(const at::Tensor &t) { return t.scalar_type() == at::kInt && t.is_contiguous(); }
 
 PyObject *wrap(const at::Tensor &t) {
@@ -392,16 +402,22 @@ PyObject *stack(PyObject *, PyObject *const *a, Py_ssize_t n) {
   });
 }
 
-PyObject *set_error(PyObject *, PyObject *cls) {
-  Py_INCREF(cls);
-  Py_XDECREF(g_error);
-  g_error = cls;
-  Py_RETURN_NONE;
+// setup(error class, function: stream or None -> hipStream_t)
+PyObject *setup(PyObject *, PyObject *const *a, Py_ssize_t n) {
+  return guarded(n, 2, [&]() -> PyObject * {
+    Py_INCREF(a[0]);
+    Py_INCREF(a[1]);
+    Py_XDECREF(g_error);
+    Py_XDECREF(g_raw_stream);
+    g_error = a[0];
+    g_raw_stream = a[1];
+    Py_RETURN_NONE;
+  });
 }
 
 #define NS_FAST(f) {#f, reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)(void)>(f)), METH_FASTCALL, nullptr}
 PyMethodDef methods[] = {NS_FAST(attn), NS_FAST(scores), NS_FAST(topk), NS_FAST(embed), NS_FAST(block), NS_FAST(stack),
-                         {"set_error", set_error, METH_O, nullptr}, {nullptr, nullptr, 0, nullptr}};
+                         NS_FAST(setup), {nullptr, nullptr, 0, nullptr}};
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_nsbind", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
 
 }  // namespace

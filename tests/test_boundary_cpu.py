@@ -251,6 +251,29 @@ def test_stack_workspace_covers_the_pruned_blocks(nb):
     assert nb.lib.vit_block_workspace_bytes(ctypes.byref(pd)) > nb.lib.vit_block_workspace_bytes(ctypes.byref(d.block))
 
 
+def test_wrong_arguments_are_reported_without_a_device(nb):
+    """What is wrong with the arguments comes before the current stream is asked for."""
+    import torch
+    q = torch.zeros(1, 1, 65, 64, dtype=torch.bfloat16)
+    x = torch.zeros(1, 65, 64, dtype=torch.bfloat16)
+    with pytest.raises(ValueError):
+        nb.ns_attn_forward(q, q[:, :, :3], q, 8, 8, 8)
+    with pytest.raises(ValueError):
+        nb.ns_attn_forward_scores(q, q.float(), q, 8, 8, 8)
+    with pytest.raises(TypeError):
+        nb.ns_attn_forward(q, q, q, 8.0, 8, 8)
+    with pytest.raises(ValueError):
+        nb.cls_scores(q, q[:, :, 1:])
+    with pytest.raises(ValueError):
+        nb.topk_filter(torch.zeros(1, 3, dtype=torch.float64), 1)
+    with pytest.raises(ValueError):
+        nb.vit_embed(q, q, q, q, q, 14)
+    with pytest.raises(KeyError):
+        nb.vit_block_forward(x, {}, 8, 8, 8, 1)
+    with pytest.raises(ValueError):
+        nb.vit_forward(q, [{}], 8, 8, 8, 1)
+
+
 def test_weights_that_a_mapping_makes_on_demand_stay_alive(nb):
     """The binding takes pointers out of a block's weights one after the other: each must still be alive when the
     call is made.  (head_dim 32 is refused, so nothing is launched.)"""
