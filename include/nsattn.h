@@ -321,9 +321,8 @@ ns_status ns_attn_patch_kernel_time(const ns_attn_desc *desc, const void *q, con
                                     void *stream);
 
 /*
- * Name of the kernel family that the patch queries of `desc` belong to on the current device; "" for an
- * invalid descriptor.  Host only, launches nothing.  (A problem of the sweep, block, persistent or plain
- * family is handed to the window kernel, attn_mfma_ragged_kernel, where that one is faster.)
+ * Name of the kernel that ns_attn_forward launches for the patch queries of `desc` on the current device; "" for
+ * an invalid descriptor.  Host only, launches nothing.
  */
 const char *ns_attn_patch_kernel_name(const ns_attn_desc *desc);
 

@@ -152,82 +152,47 @@ size_t ns_attn_workspace_bytes(const ns_attn_desc *desc) {
   return attn_workspace_layout(*desc).total;
 }
 
-// The kernel family of a problem, by its shape.  bf16, head_dim 64, complete grid: blocks of 8x8, 4x4
-// and 2x2 with at least one row of 8x8 tiles per CU are the sweep's (key tiles shared along a row of
-// blocks, the global query's row computed on the way), block sides that are multiples of 16 with two
-// 16x16 squares per CU the block kernel's, smaller tiled grids the persistent or the plain
-// one-wave-per-tile kernel's.  Every other bf16 problem with head_dim 64 (pruned sequences, other
-// block sides, small grids, many global tokens) is the window kernel's, and the rest (fp32, other scales
-// and strides) the fp32 kernel's.
-// NSATTN_KERNEL = sweep | block | persist | mfma | lists | generic forces one of them where it applies;
-// a digit 1, 2 or 4 behind `lists` or `generic` also forces the waves per query tile.
+// The kernel that computes the patch queries of a problem.  bf16 with head_dim 64 and a positive scale is the window
+// kernel's (ns_attn_ragged.hip, which shares a tile's keys out over one, two or four waves and takes the global rows
+// along) unless one of these is faster; the rest (fp32, other scales and strides) is the fp32 kernel's.
+//   - The sweep (8x8 blocks, one global token; also computes the global row on the way) needs a row of blocks per
+//     CU, and strips that fill the CUs twice over in whole rounds: 512 strips of 16 columns 118 against 137 us, 528
+//     strips of 11 columns 111 against 99 us.  7.2 us a column and round, 8 % more with short edge blocks.
+//     4x4 and 2x2 blocks it takes only where forced: its 3x3 tiles of 8x8 hold 4 or 5.8 times the keys a query sees,
+//     the window kernel's rectangle 1.8 or 2.3 times (245x245, 2x2 blocks: 249 against 169 us).  Several global
+//     tokens likewise: they cost it a pass over K and V of its own.
+//   - The block kernel (block sides that are multiples of 16, up to eight global tokens) needs five 16x16 squares per
+//     CU; with fewer the window kernel's 64-query tiles fill the chip better (53x53 with 32x32 blocks, 512 squares:
+//     139 against 100 us).
+// NSATTN_KERNEL = sweep | block | persist | mfma | lists | generic forces one of them where it applies (persist and
+// mfma run only so: 16x16 grid, 16 heads: 18.4 against 11.7 us; 32x32 with 16x16 blocks: 32.1 against 19.4); a
+// digit 1, 2 or 4 behind `lists` or `generic` also forces the waves per query tile.
 enum PatchKernel { PK_SWEEP, PK_BLOCK16, PK_PERSIST, PK_MFMA, PK_RAGGED, PK_GENERIC };
 
-static int device_cus() { return device_cu_count(); }
-
-// (the environment is read once per call, here; the choice travels in AttnArgs::kernel)
-static PatchKernel choose_patch_kernel(const ns_attn_desc &d) {
+// split: forced waves per query tile, or 0.  (The environment is read once per call, here; the choice travels in
+// AttnArgs::kernel.)
+static PatchKernel choose_patch_kernel(const ns_attn_desc &d, int &split) {
   const char *e = getenv("NSATTN_KERNEL");
-  const char force = e ? e[0] : 0;
-  if (force == 'g') return PK_GENERIC;        // serves every problem
-  const bool tiled_ok = mfma_attn_supported(d);               // block side 8 or 16 dividing the grid
+  const char force = e ? e[0] : 0, last = force ? e[strlen(e) - 1] : 0;
+  split = last == '1' || last == '2' || last == '4' ? last - '0' : 0;
   const bool sweep_ok = sweep_attn_supported(d);              // block side 8, 4 or 2, any grid
   const bool block16_ok = block16_attn_supported(d);          // block side a multiple of 16, any grid
-  const long long strips8 = (long long)d.batch * d.heads * ((d.grid_h + 7) / 8);   // the sweep's workgroups
-  const long long squares16 = (long long)d.batch * d.heads * ((d.grid_h + 15) / 16) * ((d.grid_w + 15) / 16);   // the block kernel's
+  const bool window_ok = ragged_attn_supported(d);            // implied by the others
+  if (force == 'g' || !window_ok) return PK_GENERIC;          // serves every problem
   if (force == 's' && sweep_ok) return PK_SWEEP;
   if (force == 'b' && block16_ok) return PK_BLOCK16;
-  if (force == 'l' && ragged_attn_supported(d)) return PK_RAGGED;
-  if (tiled_ok) {
-    const bool persist_ok = persist_attn_supported(d);
-    if (force == 'p' && persist_ok) return PK_PERSIST;
-    if (force == 'm') return PK_MFMA;
-    if (sweep_ok && strips8 >= device_cus()) return PK_SWEEP;
-    if (block16_ok && squares16 >= 2LL * device_cus()) return PK_BLOCK16;
-    if (persist_ok) return PK_PERSIST;
-    return PK_MFMA;
-  }
-  // short edge blocks, 4x4 and 2x2 blocks: the sweep (and, for the former, the block kernel) takes them
-  if (force != 'l' && sweep_ok && strips8 >= device_cus()) return PK_SWEEP;
-  if (force != 'l' && block16_ok && squares16 >= 2LL * device_cus()) return PK_BLOCK16;
-  if (ragged_attn_supported(d)) return PK_RAGGED;   // its lists: wants_lists()
-  return PK_GENERIC;
-}
-
-// The kernel that is launched: the family's own, unless the window kernel is faster on the problem.
-//   - Small tiled grids: the window kernel shares a tile's keys out over four waves and takes the global
-//     rows along (16x16 grid, 16 heads: 11.7 against 18.4 us; 32x32 with 16x16 blocks: 19.4 against 32.1).
-//   - 4x4 and 2x2 blocks: the sweep's 3x3 tiles of 8x8 hold 4 or 5.8 times the keys a query sees, the window
-//     kernel's rectangle 1.8 or 2.3 times (245x245, 2x2 blocks: 169 against 249 us).
-//   - Several global tokens: they cost the sweep a pass over K and V of its own.
-//   - 8x8 blocks: the sweep needs strips that fill the CUs twice over in whole rounds (512 strips, 16 columns: 118
-//     against 137 us; 528 strips, 11 columns: 111 against 99 us); 7.2 us a column and round, 8 % more
-//     with short edge blocks.
-//   - The block kernel has 16x16 squares to fill the chip with; below about five per CU the window kernel's
-//     64-query tiles do it better (53x53 with 32x32 blocks, 512 squares: 139 against 100 us).
-static PatchKernel choose_launch_kernel(const ns_attn_desc &d, int &split) {
-  const PatchKernel family = choose_patch_kernel(d);
-  const char *e = getenv("NSATTN_KERNEL");
-  split = 0;
-  if (e && e[0]) {
-    const char last = e[strlen(e) - 1];
-    if (last == '1' || last == '2' || last == '4') split = last - '0';
-    return family;
-  }
-  if (family == PK_RAGGED || family == PK_GENERIC || !ragged_attn_supported(d)) return family;
-  const long long images = (long long)d.batch * d.heads;
-  const double cus = device_cus();
-  if (family == PK_SWEEP) {
-    if (d.block < 8 || d.n_global > 1) return PK_RAGGED;
-    const double rounds = images * ((d.grid_h + 7) / 8) / (2.0 * cus);
-    const double edge = d.grid_h % 8 || d.grid_w % 8 ? 1.08 : 1.0;
+  if (force == 'p' && persist_attn_supported(d)) return PK_PERSIST;
+  if (force == 'm' && mfma_attn_supported(d)) return PK_MFMA;
+  if (force == 'l') return PK_RAGGED;
+  const double images = (double)d.batch * d.heads, cus = device_cu_count();
+  const double strips = images * ((d.grid_h + 7) / 8);
+  if (sweep_ok && d.block == 8 && d.n_global == 1 && strips >= cus) {
+    const double rounds = strips / (2.0 * cus), edge = d.grid_h % 8 || d.grid_w % 8 ? 1.08 : 1.0;
     const double sweep_us = ((d.grid_w + 7) / 8) * 7.2 * edge * (rounds <= 1.0 ? 1.0 : rounds + 0.35);
-    return ragged_attn_us(d) < sweep_us ? PK_RAGGED : PK_SWEEP;
+    if (ragged_attn_us(d) >= sweep_us) return PK_SWEEP;
   }
-  if (family == PK_BLOCK16) {
-    const double squares = (double)images * ((d.grid_h + 15) / 16) * ((d.grid_w + 15) / 16);
-    return squares < 5.0 * cus ? PK_RAGGED : PK_BLOCK16;
-  }
+  const double squares = images * ((d.grid_h + 15) / 16) * ((d.grid_w + 15) / 16);
+  if (block16_ok && squares >= 5.0 * cus) return PK_BLOCK16;
   return PK_RAGGED;
 }
 
@@ -269,7 +234,7 @@ static ns_status prepare_attn(const ns_attn_desc *desc, const void *q, const voi
   a.d = d; a.q = q; a.k = k; a.v = v; a.out = out; a.stream = s;
   BlockGeom &g = a.geom;
   g.lists = nullptr; g.counts = nullptr;
-  a.kernel = choose_launch_kernel(d, a.split);
+  a.kernel = choose_patch_kernel(d, a.split);
   if (wants_lists(d)) {
     int32_t *lists = reinterpret_cast<int32_t *>(ws + w.lists_off);
     int32_t *counts = reinterpret_cast<int32_t *>(ws + w.counts_off);
@@ -386,7 +351,8 @@ ns_status ns_attn_patch_kernel_time(const ns_attn_desc *desc, const void *q, con
 
 const char *ns_attn_patch_kernel_name(const ns_attn_desc *desc) {
   if (validate_desc(desc, true) != NS_OK) return "";
-  switch (choose_patch_kernel(*desc)) {
+  int split;
+  switch (choose_patch_kernel(*desc, split)) {
     case PK_SWEEP: return "attn_sweep_kernel";
     case PK_BLOCK16: return "attn_block16_kernel";
     case PK_PERSIST: return "attn_mfma_persist_kernel";

@@ -161,16 +161,17 @@ def test_a_batch_no_launch_can_hold_is_refused_first(nb):
 
 
 def test_kernel_choice_policy(nb, monkeypatch):
-    """Which kernel serves which problem (host logic; without a device the CU count defaults to 256)."""
+    """Which kernel is launched for which problem, both sides of every rule (host logic; without a device the CU count
+    defaults to 256)."""
     monkeypatch.delenv("NSATTN_KERNEL", raising=False)
 
-    def desc(B, H, g, block, dtype=None, coords=False):
+    def desc(B, H, g, block, dtype=None, coords=False, G=1, gw=None):
         d = nb.ns_attn_desc()
         d.batch, d.heads, d.head_dim = B, H, 64
-        d.grid_h = d.grid_w = g
-        d.block, d.radius, d.n_global = block, 1, 1
+        d.grid_h, d.grid_w = g, gw or g
+        d.block, d.radius, d.n_global = block, 1, G
         d.dtype = nb.NS_BF16 if dtype is None else dtype
-        d.tokens = 1 + g * g if not coords else 1 + (g * g) // 2
+        d.tokens = G + d.grid_h * d.grid_w if not coords else G + (d.grid_h * d.grid_w) // 2
         d.scale = 0.125
         T = d.tokens
         d.q_stride_b, d.q_stride_h, d.q_stride_t = H * T * 64, T * 64, 64
@@ -179,24 +180,47 @@ def test_kernel_choice_policy(nb, monkeypatch):
         return d
 
     name = lambda d: nb.lib.ns_attn_patch_kernel_name(ctypes.byref(d)).decode()
-    assert name(desc(2, 16, 128, 8)) == "attn_sweep_kernel"            # 512 rows of blocks
-    assert name(desc(1, 4, 24, 8)) == "attn_mfma_persist_kernel"        # too few rows of blocks for the sweep
-    assert name(desc(1, 16, 256, 16)) == "attn_block16_kernel"          # 16x16 blocks, 4096 of them
-    assert name(desc(1, 2, 32, 16)) == "attn_mfma_persist_kernel"       # 16x16 blocks, too few for a workgroup each
-    assert name(desc(1, 2, 8, 8)) == "attn_mfma_kernel"                 # a single block
-    assert name(desc(1, 2, 24, 8, dtype=nb.NS_F32)) == "attn_generic_kernel"
-    assert name(desc(1, 2, 24, 4)) == "attn_mfma_ragged_kernel"         # 4x4 blocks on the full grid
-    assert name(desc(1, 16, 100, 8)) == "attn_mfma_ragged_kernel"       # the block side does not divide the grid
-    assert name(desc(2, 16, 100, 8)) == "attn_sweep_kernel"             # ... 416 rows of blocks: short edge blocks in the sweep
-    assert name(desc(1, 16, 245, 2)) == "attn_sweep_kernel"             # 2x2 blocks on the sweep's 8x8 tiles (496 rows of tiles)
-    assert name(desc(1, 16, 245, 3)) == "attn_mfma_ragged_kernel"       # 3 does not divide 8
-    assert name(desc(1, 16, 245, 16)) == "attn_block16_kernel"          # short edge blocks in the 16x16 kernel
-    assert name(desc(1, 16, 245, 64)) == "attn_block16_kernel"           # blocks of 4x4 squares of 16x16
-    assert name(desc(1, 16, 245, 32)) == "attn_block16_kernel"
-    assert name(desc(1, 16, 245, 24)) == "attn_mfma_ragged_kernel"       # 24 is no multiple of 16 (nor does it divide 8)
-    assert name(desc(1, 2, 100, 8, dtype=nb.NS_F32)) == "attn_generic_kernel"
-    assert name(desc(1, 2, 24, 8, coords=True)) == "attn_mfma_ragged_kernel"
-    assert name(desc(1, 2, 32, 16, coords=True)) == "attn_mfma_ragged_kernel"
+    sweep, block16, window, fp32 = "attn_sweep_kernel", "attn_block16_kernel", "attn_mfma_ragged_kernel", "attn_generic_kernel"
+    # 8x8 blocks: rows of blocks ("strips") that fill 256 CUs twice over in whole rounds are the sweep's
+    assert name(desc(2, 16, 128, 8)) == sweep                           # 512 strips of 16 columns
+    assert name(desc(4, 16, 64, 8)) == sweep                            # 512 of 8
+    assert name(desc(1, 16, 128, 8)) == window                          # 256 of 16: one round, half full
+    assert name(desc(1, 16, 120, 8)) == window                          # 240: not one per CU
+    assert name(desc(3, 16, 88, 8)) == window                           # 528 of 11: a second round for 16
+    assert name(desc(1, 4, 24, 8)) == window
+    assert name(desc(1, 16, 16, 8)) == window
+    assert name(desc(1, 2, 8, 8)) == window                             # a single block
+    assert name(desc(2, 16, 128, 8, G=2)) == window                     # several global tokens
+    assert name(desc(2, 16, 64, 8, G=5)) == window
+    # 4x4 and 2x2 blocks, other sides
+    assert name(desc(2, 16, 128, 4)) == window
+    assert name(desc(1, 16, 245, 2)) == window
+    assert name(desc(1, 16, 245, 3)) == window
+    assert name(desc(1, 16, 245, 24)) == window                         # no multiple of 16
+    # multiples of 16: five 16x16 squares per CU are the block kernel's
+    assert name(desc(1, 16, 256, 16)) == block16                        # 4096
+    assert name(desc(1, 16, 144, 16)) == block16                        # 1296
+    assert name(desc(1, 16, 140, 16, gw=144)) == block16                # 1296, short edge blocks
+    assert name(desc(1, 16, 128, 16)) == window                         # 1024
+    assert name(desc(1, 2, 32, 16)) == window
+    assert name(desc(1, 16, 53, 32, gw=128)) == window                  # 512
+    assert name(desc(1, 16, 245, 16)) == block16
+    assert name(desc(1, 16, 245, 32)) == block16
+    assert name(desc(1, 16, 245, 64)) == block16                        # blocks of 4x4 squares
+    assert name(desc(1, 16, 256, 16, G=8)) == block16
+    assert name(desc(1, 16, 256, 16, G=9)) == window
+    # pruned sequences
+    assert name(desc(1, 2, 24, 8, coords=True)) == window
+    assert name(desc(2, 16, 256, 16, coords=True)) == window
+    # fp32; bf16 with a scale or strides that the matrix-instruction kernels do not take
+    assert name(desc(1, 2, 24, 8, dtype=nb.NS_F32)) == fp32
+    assert name(desc(2, 16, 128, 8, dtype=nb.NS_F32)) == fp32
+    d = desc(2, 16, 128, 8)
+    d.scale = -0.125
+    assert name(d) == fp32
+    d = desc(1, 16, 256, 16)
+    d.q_stride_t = 16384                                                # 65537 tokens x 32 KB: beyond 31 bits
+    assert name(d) == fp32
     monkeypatch.setenv("NSATTN_KERNEL", "mfma")
     assert name(desc(2, 16, 128, 8)) == "attn_mfma_kernel"
     monkeypatch.setenv("NSATTN_KERNEL", "persist")

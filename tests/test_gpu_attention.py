@@ -66,7 +66,7 @@ def test_list_kernel_strided_views(nb):
     run_case(nb, 304, 2, 4, 27, 22, 8, "bf16", scale=0.3, strided=True)
 
 
-# MFMA kernel: 8x8 blocks (one tile each) and 16x16 blocks (four tiles each)
+# small grids of 8x8 blocks (one tile each) and 16x16 blocks (four tiles each), as chosen by size
 @pytest.mark.parametrize("gh,gw,block", [(16, 16, 8), (24, 40, 8), (8, 8, 8), (8, 24, 8), (32, 32, 16),
                                          (16, 48, 16), (48, 48, 8)])
 def test_mfma_kernel(nb, gh, gw, block):

@@ -79,22 +79,22 @@ def test_tiled_kernels_with_several_global_tokens(nb, monkeypatch, force, G, gh,
     assert torch.equal(out, out2)
 
 
-def test_sweep_is_chosen_for_a_few_global_tokens_at_size(nb, monkeypatch):
-    """A backbone with register tokens on a grid large enough to fill the chip: the tiled kernel is
-    the default, nine or more global tokens go to the list kernel."""
+def test_several_global_tokens_at_size(nb, monkeypatch):
+    """A backbone with register tokens on grids large enough to fill the chip: the window kernel with 8x8 blocks, the
+    block kernel with 16x16 blocks and enough of them, and each of them as launched."""
     monkeypatch.delenv("NSATTN_KERNEL", raising=False)
-    B, H, g, G = 2, 16, 64, 5
-    q, k, v = synth.small_case(600, B, H, 64, g, g, "bf16", n_global=G)
-    dq, dk, dv = (to_dev(a, "bf16") for a in (q, k, v))
-    assert nb.ns_attn_patch_kernel_name(dq, g, g, 8, n_global=G) == "attn_sweep_kernel"
-    assert nb.ns_attn_patch_kernel_name(dq, g, g, 16, n_global=G) == "attn_block16_kernel"
-    for block in (8, 16):
+    H, G = 16, 5
+    for B, g, block, kernel in ((2, 64, 8, "attn_mfma_ragged_kernel"), (2, 64, 16, "attn_mfma_ragged_kernel"),
+                                (3, 96, 16, "attn_block16_kernel")):
+        q, k, v = synth.small_case(600, B, H, 64, g, g, "bf16", n_global=G)
+        dq, dk, dv = (to_dev(a, "bf16") for a in (q, k, v))
+        assert nb.ns_attn_patch_kernel_name(dq, g, g, block, n_global=G) == kernel
         ref = oracle.ns_attn(q, k, v, g, g, block, 0.125, n_global=G)
         out = nb.ns_attn_forward(dq, dk, dv, g, g, block, 0.125, n_global=G)
         torch.cuda.synchronize()
-        assert_attn_close(to_np(out), ref, "bf16", "G = 5 on the 64 x 64 grid, block %d" % block)
-    q9, k9, v9 = synth.small_case(601, 1, H, 64, g, g, "bf16", n_global=9)
-    assert nb.ns_attn_patch_kernel_name(to_dev(q9, "bf16"), g, g, 8, n_global=9) == "attn_mfma_ragged_kernel"
+        assert_attn_close(to_np(out), ref, "bf16", "G = 5 on the %d x %d grid, block %d" % (g, g, block))
+    q9, k9, v9 = synth.small_case(601, 1, H, 64, 64, 64, "bf16", n_global=9)
+    assert nb.ns_attn_patch_kernel_name(to_dev(q9, "bf16"), 64, 64, 8, n_global=9) == "attn_mfma_ragged_kernel"
 
 
 def test_pruned_sequence_with_several_global_tokens(nb):
