@@ -153,14 +153,7 @@ def _stream(stream) -> ctypes.c_void_p:
     return ctypes.c_void_p(s.cuda_stream)
 
 
-def _raw_stream(stream) -> int:
-    """hipStream_t of `stream`, or of the current device's current stream."""
-    if stream is None:
-        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
-    return stream.cuda_stream
-
-
-_nsbind.setup(NsError, _raw_stream)
+_nsbind.setup(NsError, torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream)
 
 
 def _workspace(nbytes: int, device, workspace: Optional[torch.Tensor]) -> Optional[torch.Tensor]:

@@ -14,7 +14,8 @@
 namespace {
 
 PyObject *g_error = nullptr;       // binding.NsError
-PyObject *g_raw_stream = nullptr;  // binding._raw_stream
+PyObject *g_device = nullptr;      // () -> the current device's number
+PyObject *g_stream = nullptr;      // device number -> hipStream_t of its current stream
 
 struct PyFail {};                  // a Python exception is set
 
@@ -69,7 +70,15 @@ size_t bytes_of(const at::Tensor &ws) { return ws.defined() ? (size_t)ws.numel()
 // hipStream_t of a stream object or of the current stream.  Asked for when the arguments have been looked at, so that
 // what is wrong with them is reported also where there is no device.
 void *stream_of(PyObject *o) {
-  PyObject *s = PyObject_CallFunctionObjArgs(g_raw_stream, o, nullptr);
+  PyObject *s;
+  if (o == Py_None) {
+    PyObject *dev = PyObject_CallNoArgs(g_device);
+    if (!dev) throw PyFail{};
+    s = PyObject_CallOneArg(g_stream, dev);
+    Py_DECREF(dev);
+  } else {
+    s = PyObject_GetAttrString(o, "cuda_stream");
+  }
   if (!s) throw PyFail{};
   const long long v = PyLong_AsLongLong(s);
   Py_DECREF(s);
@@ -402,15 +411,15 @@ PyObject *stack(PyObject *, PyObject *const *a, Py_ssize_t n) {
   });
 }
 
-// setup(error class, function: stream or None -> hipStream_t)
+// setup(error class, function giving the current device, function giving a device's current stream)
 PyObject *setup(PyObject *, PyObject *const *a, Py_ssize_t n) {
-  return guarded(n, 2, [&]() -> PyObject * {
-    Py_INCREF(a[0]);
-    Py_INCREF(a[1]);
-    Py_XDECREF(g_error);
-    Py_XDECREF(g_raw_stream);
-    g_error = a[0];
-    g_raw_stream = a[1];
+  return guarded(n, 3, [&]() -> PyObject * {
+    PyObject **const to[3] = {&g_error, &g_device, &g_stream};
+    for (int i = 0; i < 3; i++) {
+      Py_INCREF(a[i]);
+      Py_XDECREF(*to[i]);
+      *to[i] = a[i];
+    }
     Py_RETURN_NONE;
   });
 }
