@@ -164,10 +164,9 @@ size_t ns_attn_workspace_bytes(const ns_attn_desc *desc) {
 //   - The block kernel (block sides that are multiples of 16, up to eight global tokens) needs five 16x16 squares per
 //     CU; with fewer the window kernel's 64-query tiles fill the chip better (53x53 with 32x32 blocks, 512 squares:
 //     139 against 100 us).
-// NSATTN_KERNEL = sweep | block | persist | mfma | lists | generic forces one of them where it applies (persist and
-// mfma run only so: 16x16 grid, 16 heads: 18.4 against 11.7 us; 32x32 with 16x16 blocks: 32.1 against 19.4); a
-// digit 1, 2 or 4 behind `lists` or `generic` also forces the waves per query tile.
-enum PatchKernel { PK_SWEEP, PK_BLOCK16, PK_PERSIST, PK_MFMA, PK_RAGGED, PK_GENERIC };
+// NSATTN_KERNEL = sweep | block | lists | generic forces one of them where it applies; a digit 1, 2 or 4 behind
+// `lists` or `generic` also forces the waves per query tile.
+enum PatchKernel { PK_SWEEP, PK_BLOCK16, PK_RAGGED, PK_GENERIC };
 
 // split: forced waves per query tile, or 0.  (The environment is read once per call, here; the choice travels in
 // AttnArgs::kernel.)
@@ -181,8 +180,6 @@ static PatchKernel choose_patch_kernel(const ns_attn_desc &d, int &split) {
   if (force == 'g' || !window_ok) return PK_GENERIC;          // serves every problem
   if (force == 's' && sweep_ok) return PK_SWEEP;
   if (force == 'b' && block16_ok) return PK_BLOCK16;
-  if (force == 'p' && persist_attn_supported(d)) return PK_PERSIST;
-  if (force == 'm' && mfma_attn_supported(d)) return PK_MFMA;
   if (force == 'l') return PK_RAGGED;
   const double images = (double)d.batch * d.heads, cus = device_cu_count();
   const double strips = images * ((d.grid_h + 7) / 8);
@@ -200,8 +197,6 @@ static ns_status launch_patch_attention(const AttnArgs &a) {
   switch (a.kernel) {
     case PK_SWEEP: return launch_attn_sweep(a, nullptr, nullptr);
     case PK_BLOCK16: return launch_attn_block16(a);
-    case PK_PERSIST: return launch_attn_persist(a);
-    case PK_MFMA: return launch_attn_mfma(a);
     case PK_RAGGED: return launch_attn_ragged(a, nullptr, nullptr);
     default: return launch_attn_generic(a, nullptr, nullptr);
   }
@@ -281,7 +276,7 @@ ns_status ns::cls_scores_impl(const ns_attn_desc *desc, const void *q, const voi
   float *logits = static_cast<float *>(workspace);
   float *partials = reinterpret_cast<float *>(static_cast<unsigned char *>(workspace) +
                                               align_up((size_t)d.batch * d.heads * d.n_global * d.tokens * 4, 256));
-  st = launch_cls_row(d, q, k, nullptr, logits, partials, false, s);
+  st = launch_cls_row(d, q, k, nullptr, logits, partials, s);
   if (st != NS_OK) return st;
   return launch_cls_scores(d.batch, d.heads, d.tokens, d.n_global, logits, nullptr, partials,
                            cls_num_chunks(d.tokens), scores, s);
@@ -312,7 +307,7 @@ ns_status ns::attn_forward_impl(const ns_attn_desc *desc, const void *q, const v
   } else {
     st = launch_patch_attention(a);
     if (st != NS_OK) return st;
-    st = launch_cls_row(d, q, k, v, cls_logits, partials, true, a.stream);
+    st = launch_cls_row(d, q, k, v, cls_logits, partials, a.stream);
     if (st != NS_OK) return st;
   }
   if (scores) return launch_cls_combine_scores(d, partials, out, cls_lse, cls_logits, scores, a.stream);
@@ -355,8 +350,6 @@ const char *ns_attn_patch_kernel_name(const ns_attn_desc *desc) {
   switch (choose_patch_kernel(*desc, split)) {
     case PK_SWEEP: return "attn_sweep_kernel";
     case PK_BLOCK16: return "attn_block16_kernel";
-    case PK_PERSIST: return "attn_mfma_persist_kernel";
-    case PK_MFMA: return "attn_mfma_kernel";
     case PK_RAGGED: return "attn_mfma_ragged_kernel";
     default: return "attn_generic_kernel";
   }

@@ -9,7 +9,7 @@
 // uses every one of them: one fetch from L2 instead of four, and no wave ever idles.  One
 // s_barrier per key tile makes the tile visible to all and frees the slot that the next transfer
 // overwrites.  Mathematics, register formulation, fixed exponent reference and the redo of query
-// tiles that overflow it are those of ns_attn_mfma.hip / ns_attn_sweep.hip.
+// tiles that overflow it are those of ns_attn_sweep.hip.
 #include "ns_common.h"
 
 namespace ns {

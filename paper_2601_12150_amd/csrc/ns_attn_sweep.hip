@@ -13,10 +13,13 @@
 // key tile costs a third of the L2 traffic, and with two workgroups per CU (two waves per SIMD)
 // the off-time of one wave is the other's compute time.
 //
-// Mathematics and register formulation are those of ns_attn_mfma.hip: S^T = K Q^T and
-// O^T += V^T P^T with v_mfma_f32_32x32x16_bf16, P kept in registers, the global token's logit as
-// fixed exponent reference, a check for overflow at the end of each query block and a redo with
-// a running maximum for the (rare) blocks that fail it.
+// Everything is computed transposed, S^T = K Q^T and O^T += V^T P^T with v_mfma_f32_32x32x16_bf16, so
+// that a query's state lives in its own lane pair, and S^T's accumulator layout (lane = query
+// column, 16 keys per 32x32 tile) is, after exp2 and bf16 packing, the B-operand layout of the second
+// product: P stays in registers.  The exponent reference is the global token's logit and is not
+// raised tile by tile, which makes the weights element-wise (no row maximum, no rescale of O^T, no
+// branch): exact as long as no weight overflows, with a check at the end of each query block and a
+// redo with a running maximum for the (rare) blocks that fail it.
 //
 // The global (CLS) query rides along: it attends to every key, and every key tile of block row R
 // passes through the LDS of strip R exactly once.  In column c the wave that has its column off,
@@ -144,7 +147,10 @@ __global__ __launch_bounds__(256, 2) void attn_sweep_kernel(SweepParams p) {
   uint32_t krd[4];
 #pragma unroll
   for (int s = 0; s < 4; s++) krd[s] = l32 * 128 + 16 * ((4 * hh + s) ^ ((l32 >> 1) & 7));
-  // V transposed reads (see ns_attn_mfma.hip for the layout argument)
+  // V transposed reads (ds_read_b64_tr_b16): within a 16-lane group, lane i receives element i%4 of the
+  // 8-byte chunks addressed by lanes i/4, i/4+4, i/4+8, i/4+12.  Source lane s therefore points at row
+  // key0 + s/4, channels dbase + 4*(s%4), and lane i ends up with V[key0 + 0..3][dbase + i]: four
+  // consecutive keys of one channel, half of an A-operand fragment.
   uint32_t vrd[2][2];
   {
     const int g = lane >> 4, s = lane & 15;

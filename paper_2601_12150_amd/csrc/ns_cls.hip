@@ -331,36 +331,34 @@ static ns_status launch_rows(const ns_attn_desc &d, const void *q, const void *k
 }
 
 ns_status launch_cls_row(const ns_attn_desc &d, const void *q, const void *k, const void *v,
-                         float *logits, float *partials, bool with_v, hipStream_t s) {
-  if (d.n_global == 1 && !with_v && logits) {
-    const int nch = cls_num_chunks(d.tokens);
-    dim3 grid(nch, d.heads, d.batch), blk(256);
-    if (d.dtype == NS_F32)
-      hipLaunchKernelGGL(cls_scan_kernel<float>, grid, blk, 0, s, static_cast<const float *>(q), static_cast<const float *>(k),
-                         d.q_stride_b, d.q_stride_h, d.q_stride_t, d.tokens, d.heads, d.scale, logits, partials, nch);
-    else
-      hipLaunchKernelGGL(cls_scan_kernel<uint16_t>, grid, blk, 0, s, static_cast<const uint16_t *>(q),
-                         static_cast<const uint16_t *>(k), d.q_stride_b, d.q_stride_h, d.q_stride_t, d.tokens, d.heads,
-                         d.scale, logits, partials, nch);
-    return check_launch("cls_scan_kernel");
-  }
-  if (d.n_global == 1 && with_v && d.dtype == NS_BF16) {
-    const int nch = cls_num_chunks(d.tokens);
-    hipLaunchKernelGGL(cls_scan_v_kernel, dim3(nch, d.heads, d.batch), dim3(256), 0, s, static_cast<const uint16_t *>(q),
-                       static_cast<const uint16_t *>(k), static_cast<const uint16_t *>(v), d.q_stride_b, d.q_stride_h,
-                       d.q_stride_t, d.tokens, d.heads, d.scale, logits, partials, nch);
+                         float *logits, float *partials, hipStream_t s) {
+  const dim3 grid(cls_num_chunks(d.tokens), d.heads, d.batch), blk(256);
+  const bool single = d.n_global == 1;
+  if (v) {
+    // (bf16, a positive scale, 32-bit row offsets: what the kernels take that leave the rows to this launch)
+    if (!single)
+      return logits ? launch_rows<StepBf16, true, true>(d, q, k, v, logits, partials, s)
+                    : launch_rows<StepBf16, true, false>(d, q, k, v, logits, partials, s);
+    hipLaunchKernelGGL(cls_scan_v_kernel, grid, blk, 0, s, static_cast<const uint16_t *>(q), static_cast<const uint16_t *>(k),
+                       static_cast<const uint16_t *>(v), d.q_stride_b, d.q_stride_h, d.q_stride_t, d.tokens, d.heads, d.scale,
+                       logits, partials, (int)grid.x);
     return check_launch("cls_scan_v_kernel");
   }
-#define NS_ROWS(S)                                                                                      \
-  (with_v ? (logits ? launch_rows<S, true, true>(d, q, k, v, logits, partials, s)                       \
-                    : launch_rows<S, true, false>(d, q, k, v, logits, partials, s))                     \
-          : (logits ? launch_rows<S, false, true>(d, q, k, v, logits, partials, s)                      \
-                    : launch_rows<S, false, false>(d, q, k, v, logits, partials, s)))
-  if (d.dtype == NS_F32) return NS_ROWS(StepF32<float>);
-  // (the bf16 step wants a positive scale and 32-bit row offsets)
-  if (d.scale > 0.f && (long long)d.tokens * d.q_stride_t * 2 < 0x7fffffffLL) return NS_ROWS(StepBf16);
-  return NS_ROWS(StepF32<uint16_t>);
-#undef NS_ROWS
+  if (!single) {
+    if (d.dtype == NS_F32) return launch_rows<StepF32<float>, false, true>(d, q, k, v, logits, partials, s);
+    // (the bf16 step wants a positive scale and 32-bit row offsets)
+    if (d.scale > 0.f && (long long)d.tokens * d.q_stride_t * 2 < 0x7fffffffLL)
+      return launch_rows<StepBf16, false, true>(d, q, k, v, logits, partials, s);
+    return launch_rows<StepF32<uint16_t>, false, true>(d, q, k, v, logits, partials, s);
+  }
+  if (d.dtype == NS_F32)
+    hipLaunchKernelGGL(cls_scan_kernel<float>, grid, blk, 0, s, static_cast<const float *>(q), static_cast<const float *>(k),
+                       d.q_stride_b, d.q_stride_h, d.q_stride_t, d.tokens, d.heads, d.scale, logits, partials, (int)grid.x);
+  else
+    hipLaunchKernelGGL(cls_scan_kernel<uint16_t>, grid, blk, 0, s, static_cast<const uint16_t *>(q),
+                       static_cast<const uint16_t *>(k), d.q_stride_b, d.q_stride_h, d.q_stride_t, d.tokens, d.heads,
+                       d.scale, logits, partials, (int)grid.x);
+  return check_launch("cls_scan_kernel");
 }
 
 ns_status launch_cls_combine(const ns_attn_desc &d, const float *partials, void *out, float *lse,

@@ -195,10 +195,6 @@ ns_status launch_block_lists(const ns_attn_desc &d, int32_t *lists, int32_t *cou
 // partials != NULL: the launch also computes the global rows' chunk records [B, H*G, cls_num_chunks, 66] and,
 // with logits, their raw logits [B,H,G,T]
 ns_status launch_attn_generic(const AttnArgs &a, float *logits, float *partials);
-bool mfma_attn_supported(const ns_attn_desc &d);
-ns_status launch_attn_mfma(const AttnArgs &a);
-bool persist_attn_supported(const ns_attn_desc &d);
-ns_status launch_attn_persist(const AttnArgs &a);
 bool sweep_attn_supported(const ns_attn_desc &d);    // 8x8 blocks: key tiles shared along a row of blocks
 // cls_partials != NULL: the kernel also computes the global query's row, [B,H,4*nbh,66] partial records
 // (sweep_cls_chunks of them per head-image) and, with cls_logits, its raw logits [B,H,T]
@@ -215,8 +211,9 @@ constexpr int kClsChunk = 512;                      // keys per workgroup of the
 inline int cls_num_chunks(int tokens) { return (tokens + kClsChunk - 1) / kClsChunk; }
 // partial record per (b, h, chunk): m, l, o[64]
 constexpr int kClsPartialFloats = 2 + 64;
+// v: NULL for scoring, which wants logits; else of a bf16 problem, logits or NULL
 ns_status launch_cls_row(const ns_attn_desc &d, const void *q, const void *k, const void *v,
-                         float *logits /* [B,H,T] */, float *partials, bool with_v, hipStream_t s);
+                         float *logits /* [B,H,G,T] */, float *partials, hipStream_t s);
 ns_status launch_cls_combine(const ns_attn_desc &d, const float *partials, void *out, float *lse,
                              bool with_v, hipStream_t s, int nchunks = 0 /* 0: cls_num_chunks(tokens) */);
 // lse given directly, or (lse == nullptr) recomputed from the row kernel's partials

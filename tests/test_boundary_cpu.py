@@ -221,10 +221,10 @@ def test_kernel_choice_policy(nb, monkeypatch):
     d = desc(1, 16, 256, 16)
     d.q_stride_t = 16384                                                # 65537 tokens x 32 KB: beyond 31 bits
     assert name(d) == fp32
-    monkeypatch.setenv("NSATTN_KERNEL", "mfma")
-    assert name(desc(2, 16, 128, 8)) == "attn_mfma_kernel"
-    monkeypatch.setenv("NSATTN_KERNEL", "persist")
-    assert name(desc(2, 16, 128, 8)) == "attn_mfma_persist_kernel"
+    monkeypatch.setenv("NSATTN_KERNEL", "lists")
+    assert name(desc(2, 16, 128, 8)) == window
+    monkeypatch.setenv("NSATTN_KERNEL", "sweep")
+    assert name(desc(1, 1, 8, 2, G=8)) == sweep
     monkeypatch.setenv("NSATTN_KERNEL", "generic")
     assert name(desc(1, 16, 100, 8)) == "attn_generic_kernel"
     assert name(desc(2, 16, 128, 8)) == "attn_generic_kernel"

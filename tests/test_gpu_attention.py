@@ -147,7 +147,7 @@ def test_pruned_sequence_mfma_kernel(nb, monkeypatch, g, block, shuffle, gain):
 
 
 @pytest.mark.parametrize("variant,gh,gw", [(None, 24, 24), ("sweep", 24, 24), ("sweep", 16, 40), ("sweep", 8, 8),
-                                           ("sweep", 40, 8), ("persist", 24, 24), ("mfma", 24, 24)])
+                                           ("sweep", 40, 8), ("lists", 24, 24), ("generic", 24, 24)])
 def test_cls_by_products_and_determinism(nb, monkeypatch, variant, gh, gw):
     """Global-query by-products (raw logits, log-sum-exp) and its output row, for every way they are
     produced: the chunked row kernel, and the sweep kernel that computes them on the way."""
@@ -268,16 +268,16 @@ def test_invalid_call_launches_nothing(nb):
     assert bool((out == 7.0).all())
 
 
-@pytest.mark.parametrize("variant", ["mfma", "persist", "sweep", "block"])
+@pytest.mark.parametrize("variant", ["lists", "generic", "sweep", "block"])
 @pytest.mark.parametrize("gh,gw,block", [(24, 40, 8), (8, 8, 8), (32, 32, 16), (48, 48, 8), (64, 64, 8), (96, 64, 16), (16, 72, 8), (40, 8, 8)])
-def test_persistent_kernel_variant(nb, gh, gw, block, variant, monkeypatch):
-    # the persistent-wave kernels compute the same function (grids too small for them fall back)
+def test_kernel_variant(nb, gh, gw, block, variant, monkeypatch):
+    # the kernels compute the same function (a block side that a forced one does not take: as chosen by size)
     monkeypatch.setenv("NSATTN_KERNEL", variant)
     run_case(nb, 303, 2, 5, gh, gw, block, "bf16")
 
 
-@pytest.mark.parametrize("variant", ["mfma", "persist", "sweep", "block"])
-def test_persistent_kernel_variant_overflow_fallback(nb, variant, monkeypatch):
+@pytest.mark.parametrize("variant", ["lists", "generic", "sweep", "block"])
+def test_kernel_variant_overflow_fallback(nb, variant, monkeypatch):
     monkeypatch.setenv("NSATTN_KERNEL", variant)
     q, k, v = synth.small_case(7, 1, 2, 64, 16, 16, "bf16")
     q = synth.round_to_bf16(q * 12.0)
@@ -285,11 +285,11 @@ def test_persistent_kernel_variant_overflow_fallback(nb, variant, monkeypatch):
     out = nb.ns_attn_forward(*(to_dev(a, "bf16") for a in (q, k, v)), 16, 16, 8, 1.0)
     torch.cuda.synchronize()
     assert np.isfinite(to_np(out)).all()
-    assert_attn_close(to_np(out), ref, "bf16", "large logits, persistent kernel")
+    assert_attn_close(to_np(out), ref, "bf16", "large logits, %s" % variant)
 
 
-@pytest.mark.parametrize("variant", ["mfma", "persist", "sweep", "block"])
-def test_persistent_kernel_partial_overflow(nb, variant, monkeypatch):
+@pytest.mark.parametrize("variant", ["lists", "generic", "sweep", "block"])
+def test_kernel_variant_partial_overflow(nb, variant, monkeypatch):
     """Only some query tiles overflow the fixed exponent reference: those are redone, the others not."""
     monkeypatch.setenv("NSATTN_KERNEL", variant)
     q, k, v = synth.small_case(11, 1, 3, 64, 32, 32, "bf16")
@@ -299,7 +299,7 @@ def test_persistent_kernel_partial_overflow(nb, variant, monkeypatch):
     out = nb.ns_attn_forward(*(to_dev(a, "bf16") for a in (q, k, v)), 32, 32, 8, 1.0)
     torch.cuda.synchronize()
     assert np.isfinite(to_np(out)).all()
-    assert_attn_close(to_np(out), ref, "bf16", "partly large logits, persistent kernel")
+    assert_attn_close(to_np(out), ref, "bf16", "partly large logits, %s" % variant)
 
 
 def _random_cases(n, seed):

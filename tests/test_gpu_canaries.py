@@ -95,7 +95,7 @@ def attention_case(nb, monkeypatch, force, B, H, gh, gw, block, dtype, keep=None
 @pytest.mark.parametrize("force,B,H,gh,gw,block,dtype", [
     ("sweep", 1, 2, 32, 32, 8, "bf16"), ("sweep", 2, 1, 20, 27, 8, "bf16"), ("sweep", 1, 2, 24, 24, 4, "bf16"),
     ("sweep", 1, 1, 19, 18, 2, "bf16"), ("block", 1, 2, 48, 48, 16, "bf16"), ("block", 1, 1, 40, 37, 16, "bf16"),
-    ("block", 1, 1, 70, 70, 32, "bf16"), ("persist", 1, 2, 32, 32, 8, "bf16"), ("mfma", 1, 2, 16, 16, 8, "bf16"),
+    ("block", 1, 1, 70, 70, 32, "bf16"), ("lists", 1, 2, 32, 32, 8, "bf16"), ("lists", 1, 2, 16, 16, 8, "bf16"),
     ("lists", 1, 2, 21, 21, 7, "bf16"), ("generic", 1, 2, 12, 13, 4, "f32"), ("generic", 1, 1, 9, 9, 3, "bf16"),
     ("", 1, 16, 64, 64, 8, "bf16")])
 def test_attention_writes_stay_inside_their_buffers(nb, monkeypatch, force, B, H, gh, gw, block, dtype):

@@ -24,7 +24,7 @@ def nb():
 def test_attention_and_scores_on_random_problems(nb, monkeypatch, seed):
     rng = random.Random(seed)
     for it in range(40):
-        force = rng.choice(["", "", "sweep", "block", "persist", "mfma", "lists", "generic"])
+        force = rng.choice(["", "", "sweep", "block", "lists1", "lists4", "lists", "generic"])
         block = rng.choice([2, 4, 8, 8, 8, 16, 16, 32, 3, 5, 7, 12])
         gh, gw = rng.randint(1, 70), rng.randint(1, 70)
         if rng.random() < 0.4:     # grids the block side divides
