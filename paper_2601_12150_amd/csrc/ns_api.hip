@@ -161,8 +161,11 @@ size_t ns_attn_workspace_bytes(const ns_attn_desc *desc) {
 //     4x4 and 2x2 blocks it takes only where forced: its 3x3 tiles of 8x8 hold 4 or 5.8 times the keys a query sees,
 //     the window kernel's rectangle 1.8 or 2.3 times (245x245, 2x2 blocks: 249 against 169 us).  Several global
 //     tokens likewise: they cost it a pass over K and V of its own.
-//   - The block kernel (block sides that are multiples of 16, up to eight global tokens) needs five 16x16 squares per
-//     CU; with fewer the window kernel's 64-query tiles fill the chip better (53x53 with 32x32 blocks, 512 squares:
+//   - The block kernel (block sides that are multiples of 16, up to eight global tokens) does the same tile in less time
+//     but has 16x16 squares to fill the chip with, and works on short ones as on whole ones.  Where 16 divides the grid,
+//     three squares per CU are enough (128x128, 16 heads, 64x64 blocks: 1035 against 1234 us; 12 heads, three per CU:
+//     805 against 932; 2.25 per CU, 96x96: 434 against 408), and two for 16x16 blocks and one global token (96x96:
+//     103 against 107 us); with short squares five (120x120, four: 1008 against 997; 53x53 with 32x32 blocks, 512:
 //     139 against 100 us).
 // NSATTN_KERNEL = sweep | block | lists | generic forces one of them where it applies; a digit 1, 2 or 4 behind
 // `lists` or `generic` also forces the waves per query tile.
@@ -189,7 +192,9 @@ static PatchKernel choose_patch_kernel(const ns_attn_desc &d, int &split) {
     if (ragged_attn_us(d) >= sweep_us) return PK_SWEEP;
   }
   const double squares = images * ((d.grid_h + 15) / 16) * ((d.grid_w + 15) / 16);
-  if (block16_ok && squares >= 5.0 * cus) return PK_BLOCK16;
+  const bool whole = d.grid_h % 16 == 0 && d.grid_w % 16 == 0;
+  const double enough = !whole ? 5.0 : (d.block == 16 && d.n_global == 1 ? 2.0 : 3.0);
+  if (block16_ok && squares >= enough * cus) return PK_BLOCK16;
   return PK_RAGGED;
 }
 

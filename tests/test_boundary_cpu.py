@@ -197,11 +197,17 @@ def test_kernel_choice_policy(nb, monkeypatch):
     assert name(desc(1, 16, 245, 2)) == window
     assert name(desc(1, 16, 245, 3)) == window
     assert name(desc(1, 16, 245, 24)) == window                         # no multiple of 16
-    # multiples of 16: five 16x16 squares per CU are the block kernel's
+    # multiples of 16: so many 16x16 squares per CU are the block kernel's: five, three where all are whole, two of
+    # these for 16x16 blocks and one global token
     assert name(desc(1, 16, 256, 16)) == block16                        # 4096
     assert name(desc(1, 16, 144, 16)) == block16                        # 1296
     assert name(desc(1, 16, 140, 16, gw=144)) == block16                # 1296, short edge blocks
-    assert name(desc(1, 16, 128, 16)) == window                         # 1024
+    assert name(desc(1, 16, 120, 16)) == window                         # 1024, short edge blocks
+    assert name(desc(1, 12, 128, 64)) == block16                        # 768
+    assert name(desc(1, 16, 96, 64)) == window                          # 576
+    assert name(desc(1, 16, 96, 16)) == block16
+    assert name(desc(1, 16, 96, 16, G=2)) == window
+    assert name(desc(1, 16, 80, 16)) == window                          # 400
     assert name(desc(1, 2, 32, 16)) == window
     assert name(desc(1, 16, 53, 32, gw=128)) == window                  # 512
     assert name(desc(1, 16, 245, 16)) == block16
