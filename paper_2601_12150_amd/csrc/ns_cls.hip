@@ -33,7 +33,12 @@ __device__ __forceinline__ void load_row8(const uint16_t *p, float (&x)[8]) { un
 // in flight at once.  Bound: HBM.  For a single row the matrix instructions of the kernel below
 // are work for 15 or 31 padding columns: 2 x 16384 keys x 16 heads bf16 took 13.9 us here and
 // 16.4 us there, 4 x 9825 x 24 fp32 43 against 57 us.
-template <typename T>
+//
+// LEAN: a logit is stored as soon as it is known, and fewer loads are in flight; bf16 then takes 42 registers instead
+// of 71, eight workgroups per CU instead of seven.  All loads first is faster by itself (2 x 16384 keys 21.8
+// against 23.0 us, 8 x 16384 59.6 against 63.5), the eighth workgroup where it saves a round of workgroups (60000 keys,
+// 1888 workgroups: 40.4 against 35.4 us; 4 x 9825 x 24 heads, 1920: 38.0 against 33.8; 2 x 60000: 62.6 against 58.6).
+template <typename T, bool LEAN>
 __global__ __launch_bounds__(256) void cls_scan_kernel(const T *q, const T *k, int64_t sb, int64_t sh, int64_t st,
                                                        int T_, int H, float scale, float *logits, float *partials,
                                                        int nchunks) {
@@ -66,10 +71,12 @@ __global__ __launch_bounds__(256) void cls_scan_kernel(const T *q, const T *k, i
     acc += __shfl_xor(acc, 4);
     s[i] = key < T_ ? acc : -INFINITY;
     mx = fmaxf(mx, s[i]);
+    if (LEAN && sub == 0 && key < T_) lrow[key] = acc;
   }
+  if (!LEAN)
 #pragma unroll
-  for (int i = 0; i < kSteps; i++)
-    if (sub == 0 && key0 + i * 8 < T_) lrow[key0 + i * 8] = s[i];
+    for (int i = 0; i < kSteps; i++)
+      if (sub == 0 && key0 + i * 8 < T_) lrow[key0 + i * 8] = s[i];
   mx = fmaxf(mx, __shfl_xor(mx, 8));
   mx = fmaxf(mx, __shfl_xor(mx, 16));
   mx = fmaxf(mx, __shfl_xor(mx, 32));
@@ -351,13 +358,16 @@ ns_status launch_cls_row(const ns_attn_desc &d, const void *q, const void *k, co
       return launch_rows<StepBf16, false, true>(d, q, k, v, logits, partials, s);
     return launch_rows<StepF32<uint16_t>, false, true>(d, q, k, v, logits, partials, s);
   }
-  if (d.dtype == NS_F32)
-    hipLaunchKernelGGL(cls_scan_kernel<float>, grid, blk, 0, s, static_cast<const float *>(q), static_cast<const float *>(k),
+  if (d.dtype == NS_F32) {
+    hipLaunchKernelGGL((cls_scan_kernel<float, false>), grid, blk, 0, s, static_cast<const float *>(q), static_cast<const float *>(k),
                        d.q_stride_b, d.q_stride_h, d.q_stride_t, d.tokens, d.heads, d.scale, logits, partials, (int)grid.x);
-  else
-    hipLaunchKernelGGL(cls_scan_kernel<uint16_t>, grid, blk, 0, s, static_cast<const uint16_t *>(q),
-                       static_cast<const uint16_t *>(k), d.q_stride_b, d.q_stride_h, d.q_stride_t, d.tokens, d.heads,
-                       d.scale, logits, partials, (int)grid.x);
+  } else {
+    const long long wgs = (long long)grid.x * d.heads * d.batch, seven = 7LL * device_cu_count(), eight = 8LL * device_cu_count();
+    const bool lean = (wgs + seven - 1) / seven > (wgs + eight - 1) / eight;
+    hipLaunchKernelGGL((lean ? cls_scan_kernel<uint16_t, true> : cls_scan_kernel<uint16_t, false>), grid, blk, 0, s,
+                       static_cast<const uint16_t *>(q), static_cast<const uint16_t *>(k), d.q_stride_b, d.q_stride_h,
+                       d.q_stride_t, d.tokens, d.heads, d.scale, logits, partials, (int)grid.x);
+  }
   return check_launch("cls_scan_kernel");
 }
 
