@@ -220,7 +220,9 @@ def test_stack_pruning_of_a_long_sequence(nb):
                                                (3, 3, 1, 1, 14, 256), (1, 3, 40, 33, 14, 1024),
                                                # odd patch side and pixels (2-byte path); batches whose images have more than one
                                                # row of tiles; one patch that takes more than 64 KB
-                                               (2, 3, 17, 19, 15, 256), (3, 1, 26, 31, 16, 512), (1, 3, 2, 3, 106, 128)])
+                                               (2, 3, 17, 19, 15, 256), (3, 1, 26, 31, 16, 512), (1, 3, 2, 3, 106, 128),
+                                               # batches whose images end in a ninth slab (784 = 3 x 256 + 16): 640, 64 and 128 columns
+                                               (2, 3, 28, 28, 14, 256), (3, 1, 28, 28, 8, 256), (2, 2, 28, 28, 8, 512)])
 def test_patch_embedding_matches_oracle(nb, B, ch, gh, gw, ps, dim):
     """Tokenisation: 14-pixel patches (588 columns, padded to 640 inside) and 16-pixel patches (768),
     grids from one patch to more than a thousand, the CLS row, position embeddings as residual."""
