@@ -167,14 +167,11 @@ struct StepBf16 {
   uint32_t krd[4], vrd[2][2];
   int rrow;                   // row of request 0 this lane moves; request it: + 8 it
   // The first step's first keys are global tokens, which every row sees and which can be most of a row: their weights
-  // enter with the bits they have in fp32.  Of one token: the reference is its logit, so its weight is 1.  Of
-  // several, or where the reference follows the largest logit: what bf16 rounding leaves comes in two further terms.
-  bool anchor;                // key 0 is a global token
-  int exact;                  // so many keys (8 at most) take the further terms
+  // enter with the bits they have in fp32, what bf16 rounding leaves in two further terms.
+  int exact;                  // so many keys (8 at most) do
 
   __device__ __forceinline__ void init(int lane) {
     const int l32 = lane & 31, hh = lane >> 5;
-    anchor = false;
     exact = 0;
     rrow = lane >> 3;
     // LDS chunk c of row r holds chunk c ^ ((r>>1)&7) of K and c ^ 4*((r>>1)&1) of V: conflict-free reads
@@ -468,8 +465,7 @@ struct WaveAcc {
     }
     return __any(!(big < limit));
   }
-  // key0: the logit of the step's first key, unless another exceeds it by far
-  __device__ __forceinline__ void reference(const f32x16 &s, int nt, float c, bool key0 = false) {
+  __device__ __forceinline__ void reference(const f32x16 &s, int nt, float c) {
     float a = fmaxf(s[0], s[1]), b = fmaxf(s[2], s[3]);
 #pragma unroll
     for (int e = 4; e < 16; e += 4) {
@@ -478,9 +474,7 @@ struct WaveAcc {
     }
     const float top = half_swap_max(fmaxf(a, b)) * c;
     if (__any(top > m[nt])) {
-      float m_new = fmaxf(m[nt], top);
-      // (a token whose weight is below 2^-64 of the row's has no bits in the row)
-      if (key0) m_new = m_new > low_half(s[0]) * c + 64.f ? m_new : low_half(s[0]) * c;
+      const float m_new = fmaxf(m[nt], top);
       const float alpha = __builtin_amdgcn_exp2f(m[nt] - m_new);
       m[nt] = m_new;
       l[nt] *= alpha;
@@ -566,8 +560,7 @@ __device__ __forceinline__ void walk_keys_pipelined(const S &st, WaveAcc<S, 2> &
   st.load_k(kf, wsm);
   s0 = st.product(kf, a.q[0]);
   fix(0, 0, s0);
-  const bool key0 = st.anchor && !careful;
-  a.reference(s0, 0, c, key0);
+  a.reference(s0, 0, c);
   asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
   if (n > 2) {
     tokens(2);
@@ -578,9 +571,9 @@ __device__ __forceinline__ void walk_keys_pipelined(const S &st, WaveAcc<S, 2> &
     issue_v(1, tk);
   }
   // a higher reference for half nt, whose output product is not the open one
-  auto raise = [&](int nt, const f32x16 &s, bool by_key0) {
+  auto raise = [&](int nt, const f32x16 &s) {
     a.l[nt] = nt ? l1[0] + l1[1] : l0[0] + l0[1];
-    a.reference(s, nt, c, by_key0);
+    a.reference(s, nt, c);
     if (nt) { l1[0] = a.l[1]; l1[1] = 0.f; } else { l0[0] = a.l[0]; l0[1] = 0.f; }
   };
   // step i, whose V is in slot `odd`; `odd` = i & 1 is a constant at each place of use
@@ -599,7 +592,7 @@ __device__ __forceinline__ void walk_keys_pipelined(const S &st, WaveAcc<S, 2> &
     if (rest) st.add_rest(s0, vslot, a.o[0], lane);
     if (special) {
       fix(i, 1, s1);
-      if (careful || first) raise(1, s1, key0);
+      if (careful || first) raise(1, s1);
     }
     st.load_k(kf, wsm + (odd ^ 1) * S::kHalf);      // (behind the last step: what the slot holds, not used)
     st.template half_step<false>(s1, c, -a.m[1], l1, a.o[1], a.o[0], open, vf, vslot, kf, a.q[0], s0);
@@ -615,7 +608,7 @@ __device__ __forceinline__ void walk_keys_pipelined(const S &st, WaveAcc<S, 2> &
     }
     if (special && rem > 0) {
       fix(i + 1, 0, s0);
-      if (careful) raise(0, s0, false);
+      if (careful) raise(0, s0);
     }
   };
   // (the first step by itself: what only it does, in the loop behind a branch, made 100 x 100 patches 97 -> 100 us)
@@ -1005,6 +998,7 @@ __device__ __forceinline__ void window_attention(const WindowParams &p, unsigned
   float *ml = reinterpret_cast<float *>(smem + 4 * kWaveLds);
   S st;
   st.init(lane);
+  if constexpr (kBf16) st.exact = part == 0 ? min(g.n_global, 8) : 0;
   WaveAcc<S, NT> a;
   a.clear();
   if (KS != 2 || live) {
@@ -1043,9 +1037,7 @@ __device__ __forceinline__ void window_attention(const WindowParams &p, unsigned
       for (int e = 0; e < 16; e++) s[e] = jb + 8 * (e >> 2) + (e & 3) < w.nkeys ? s[e] : -INFINITY;
     }
   };
-  if constexpr (kBf16) st.anchor = part == 0;
   for (bool careful = MASK && part != 0;; careful = true) {
-    if constexpr (kBf16) st.exact = part == 0 && (careful || g.n_global > 1) ? min(g.n_global, 8) : 0;
     window_walk<S, NT, LISTS, MASK>(st, a, kb, vb, rowB, wsm, n, c, careful, lane, key_token, key_entry, fix_token, hide);
     if (!a.exceeds(careful ? INFINITY : kLargeSum)) break;
     if (careful) {
