@@ -245,6 +245,10 @@ struct StepBf16 {
   __device__ __forceinline__ void half_step(f32x16 &cur, float c, float nm, float (&l)[2], f32x16 (&o)[2], f32x16 (&o_open)[2],
                                             bf16x8 &open, V &v, const unsigned char *vslot, const K &k, const Q &q,
                                             f32x16 &nxt) const {
+    // The sums are those of the rounded weights that the product takes, two in one instruction (in place of two
+    // additions: same time): what rounding does to a key that outweighs the others cancels.  Relative error of rows with
+    // logits of +-8: 0.0021 -> 0.0017 (rounding the true result alone: 0.0016); of +-1: 0.00220 -> 0.00218.
+    const bf16x2 ones = {(__bf16)1.f, (__bf16)1.f};
     bf16x8 first, second;
     nxt = f32x16{0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -262,9 +266,8 @@ struct StepBf16 {
         cur[2 * j + 4] = __builtin_fmaf(cur[2 * j + 4], c, nm);
         cur[2 * j + 5] = __builtin_fmaf(cur[2 * j + 5], c, nm);
       }
-      l[0] += cur[2 * j];
-      l[1] += cur[2 * j + 1];
       const bf16x2 pk = __builtin_bit_cast(bf16x2, pack_bf16(cur[2 * j], cur[2 * j + 1]));
+      l[j & 1] = __builtin_amdgcn_fdot2_f32_bf16(pk, ones, l[j & 1], false);
       if (j < 4) { first[2 * j] = pk[0]; first[2 * j + 1] = pk[1]; }
       else { second[2 * j - 8] = pk[0]; second[2 * j - 7] = pk[1]; }
       if (j < 2) o_open[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v.f[1][j], open, o_open[j], 0, 0, 0);
@@ -311,9 +314,11 @@ struct StepBf16 {
     }
   }
   // O^T += V^T (w - bf16(w)) for the first `exact` keys of a step, 16 bits of it in two terms: the keys 0..7 stand
-  // in a fragment's first four elements, V's once more in the other four
-  __device__ __forceinline__ void add_rest(const f32x16 &w, const unsigned char *slot, f32x16 (&o)[2], int lane) const {
+  // in a fragment's first four elements, V's once more in the other four.  Returns the sum of what is left (of this
+  // half-wave's keys).
+  __device__ __forceinline__ float add_rest(const f32x16 &w, const unsigned char *slot, f32x16 (&o)[2], int lane) const {
     bf16x8 r;
+    float sum = 0.f;
 #pragma unroll
     for (int e = 0; e < 4; e += 2) {
       const int key = 4 * (lane >> 5) + e;
@@ -323,6 +328,7 @@ struct StepBf16 {
       for (int t = 0; t < 2; t++) {
         a = key < exact ? a - bf16_lo(u) : 0.f;
         b = key + 1 < exact ? b - bf16_hi(u) : 0.f;
+        if (t == 0) sum += a + b;
         u = pack_bf16(a, b);
         const bf16x2 pk = __builtin_bit_cast(bf16x2, u);
         r[4 * t + e] = pk[0];
@@ -335,6 +341,7 @@ struct StepBf16 {
       const bf16x8 vv = {v[0], v[1], v[2], v[3], v[0], v[1], v[2], v[3]};
       o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vv, r, o[dt], 0, 0, 0);
     }
+    return sum;
   }
   static __device__ __forceinline__ uint32_t screen(uint32_t two, int pass) {
     return screened(two & 0xffff0000u, pass) | (screened(two << 16, pass) >> 16);
@@ -589,14 +596,14 @@ __device__ __forceinline__ void walk_keys_pipelined(const S &st, WaveAcc<S, 2> &
     st.load_v(vf, vslot, 0);
     st.template half_step<true>(s0, c, -a.m[0], l0, a.o[0], a.o[1], open, vf, vslot, kf, a.q[1], s1);
     const bool rest = first && st.exact > 0;
-    if (rest) st.add_rest(s0, vslot, a.o[0], lane);
+    if (rest) l0[0] += st.add_rest(s0, vslot, a.o[0], lane);
     if (special) {
       fix(i, 1, s1);
       if (careful || first) raise(1, s1);
     }
     st.load_k(kf, wsm + (odd ^ 1) * S::kHalf);      // (behind the last step: what the slot holds, not used)
     st.template half_step<false>(s1, c, -a.m[1], l1, a.o[1], a.o[0], open, vf, vslot, kf, a.q[0], s0);
-    if (rest) st.add_rest(s1, vslot, a.o[1], lane);
+    if (rest) l1[0] += st.add_rest(s1, vslot, a.o[1], lane);
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");       // both slots have been read
     if (rem >= 3) {
       tokens(i + 3);
