@@ -962,7 +962,9 @@ __device__ __forceinline__ void global_rows_chunk(const GlobalRows &p, int heads
 // One launch: the leading workgroups own chunks of the global rows, the others a query tile each,
 // whose keys the four waves share out step by step; the waves' partial states are merged through
 // LDS.  Bound at small sizes by the latency of the few steps a wave walks, at larger ones by the
-// instruction issue of the steps.
+// instruction issue of the steps while both waves of a SIMD are there, and by how often only one is
+// (100x100 grid, 16 heads, 2 images, five global tokens: 95 us, matrix pipes 23 % busy, vector ALUs
+// 41 %, 1.4 waves per SIMD, a quarter of a wave's time in waits).
 // ------------------------------------------------------------------------------------------
 struct WindowParams {
   GlobalRows r;            // q, k, v, strides, scale; logits and partials for the global rows
@@ -1114,7 +1116,10 @@ struct WindowCost {
   }
   // Waves per tile.  One wave per tile does the least work (no merge, one start), four fill the chip when there
   // are few tiles and shorten the walk when it is long.  (Measured with each forced over grids of 14 to 248 a
-  // side: the choice is within a few per cent of the best.)
+  // side: the choice is within a few per cent of the best.  Squares of several blocks take longer a step, for their
+  // masks, than this says - 245x245, 2x2 blocks: 174 us, not 98 -, but by about the same factor for each split: of eight
+  // such grids in bf16 the choice is the best on seven and 3 % off on one, of seven in fp32 on five, 7 % off
+  // on one, and on 32x32 with 2x2 blocks two waves take 24.9 us where one or four take 20.3.)
   int split() const { return of(4) <= of(2) && of(4) <= of(1) ? 4 : (of(2) <= of(1) ? 2 : 1); }
 };
 inline WindowCost window_cost(const ns_attn_desc &d, int qt) {

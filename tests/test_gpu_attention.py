@@ -119,8 +119,8 @@ def test_pruned_sequence(nb, dtype, block):
 def test_pruned_sequence_mfma_kernel(nb, monkeypatch, g, block, shuffle, gain):
     """bf16, head_dim 64: the MFMA kernel for pruned sequences.  Covers grids the block does not
     divide, blocks of more than 64 tokens (several runs per block, the last one partly filled),
-    survivors in arbitrary sequence order, logits large enough to need the running maximum, and
-    agreement with the fp32 FMA kernel on the same inputs."""
+    survivors in arbitrary sequence order, peaked rows, and agreement with the fp32 kernel on the same
+    inputs."""
     rng = np.random.default_rng(g * 100 + block)
     N = g * g
     keep = rng.random(N) < 0.6

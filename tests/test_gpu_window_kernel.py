@@ -19,7 +19,8 @@ def nb():
 
 # (grid_h, grid_w, block, global tokens, gain): one key step for four waves, one step each, a step more than the
 # ring has slots, tiles of a single query, squares of several blocks (side 1, 2, 3, 4), a query tile whose
-# first keys it may not see, global tokens in one and in two groups, weights beyond the fixed reference
+# first keys it may not see, global tokens in one and in two groups, peaked rows (25x18: beyond the fixed reference; the
+# second walk by itself is tested in test_gpu_nonfinite.py)
 SHAPES = [(1, 1, 8, 1, 1.0), (5, 6, 8, 1, 1.0), (11, 11, 8, 7, 1.0), (12, 24, 8, 1, 1.0), (9, 17, 8, 2, 1.0), (13, 15, 5, 3, 1.0),
           (10, 11, 1, 1, 1.0), (20, 19, 2, 1, 1.0), (14, 13, 3, 5, 1.0), (25, 18, 4, 1, 14.0), (7, 33, 7, 17, 1.0), (18, 20, 16, 33, 1.0),
           (33, 17, 12, 1, 14.0), (16, 40, 64, 1, 1.0)]
