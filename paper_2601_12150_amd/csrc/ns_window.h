@@ -169,10 +169,17 @@ struct StepBf16 {
   // The first step's first keys are global tokens, which every row sees and which can be most of a row: their weights
   // enter with the bits they have in fp32, what bf16 rounding leaves in two further terms.
   int exact;                  // so many keys (8 at most) do
+  // Selects, as the left operand of v_mfma_f32_16x16x32_bf16, the lanes whose bit 4 is the row's bit 0.  The weights of
+  // a fragment (lane: query l32, eight keys) as right operand then give query lane % 16's sum in the even registers of the
+  // result and query 16 + lane % 16's in the odd ones: both halves' keys, no vector instruction.
+  bf16x8 sel;
 
   __device__ __forceinline__ void init(int lane) {
     const int l32 = lane & 31, hh = lane >> 5;
     exact = 0;
+    const __bf16 one = (__bf16)(((lane ^ (lane >> 4)) & 1) ? 0.f : 1.f);
+#pragma unroll
+    for (int i = 0; i < 8; i++) sel[i] = one;
     rrow = lane >> 3;
     // LDS chunk c of row r holds chunk c ^ ((r>>1)&7) of K and c ^ 4*((r>>1)&1) of V: conflict-free reads
     kch[0] = 16u * ((lane & 7) ^ (lane >> 4));
@@ -191,7 +198,8 @@ struct StepBf16 {
     }
   }
   // (rows are addressed with 32-bit byte offsets from the head's first row: checked by the launcher)
-  __device__ __forceinline__ void load_q(Q &q, const char *base, int64_t rowB, int tok, int lane, float) const {
+  template <class F>                  // Q or K: a row's fragments, straight from memory
+  __device__ __forceinline__ void load_q(F &q, const char *base, int64_t rowB, int tok, int lane, float) const {
     const char *row = base + (uint32_t)tok * (uint32_t)rowB + 64 * (lane >> 5);
 #pragma unroll
     for (int s = 0; s < 4; s++) q.f[s] = *reinterpret_cast<const bf16x8 *>(row + 16 * s);
@@ -239,16 +247,16 @@ struct StepBf16 {
   // the logits `nxt` of the other queries, the first half of this output product.  One matrix instruction
   // (32 cycles) to the seven vector instructions of two weights (36 cycles); a weight's three links are a
   // group apart, so that no result is waited for.  The fences keep this order: left to itself the
-  // scheduler groups the exponentials and then the matrix instructions.
+  // scheduler groups the exponentials and then the matrix instructions.  (Sums by matrix instruction and the weights kept
+  // in this order: 100 x 100 patches, 8 x 8 blocks, five global tokens, 104.3 -> 101.3 us a call.)
   // LOADV: load the second half of V once the open product has taken the old one.
   template <bool LOADV>
-  __device__ __forceinline__ void half_step(f32x16 &cur, float c, float nm, float (&l)[2], f32x16 (&o)[2], f32x16 (&o_open)[2],
-                                            bf16x8 &open, V &v, const unsigned char *vslot, const K &k, const Q &q,
-                                            f32x16 &nxt) const {
-    // The sums are those of the rounded weights that the product takes, two in one instruction (in place of two
-    // additions: same time): what rounding does to a key that outweighs the others cancels.  Relative error of rows with
-    // logits of +-8: 0.0021 -> 0.0017 (rounding the true result alone: 0.0016); of +-1: 0.00220 -> 0.00218.
-    const bf16x2 ones = {(__bf16)1.f, (__bf16)1.f};
+  __device__ __forceinline__ void half_step(f32x16 &cur, float c, float nm, f32x4 &l, f32x16 (&o)[2], f32x4 &l_open,
+                                            f32x16 (&o_open)[2], bf16x8 &open, V &v, const unsigned char *vslot, const K &k,
+                                            const Q &q, f32x16 &nxt) const {
+    // The sums are those of the rounded weights that the product takes, which adds them itself (add_weights): what
+    // rounding does to a key that outweighs the others cancels.  Relative error of rows with logits of +-8, against sums
+    // of the weights before rounding: 0.0021 -> 0.0017 (rounding the true result alone: 0.0016); of +-1: 0.00220 -> 0.00218.
     bf16x8 first, second;
     nxt = f32x16{0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -266,18 +274,28 @@ struct StepBf16 {
         cur[2 * j + 4] = __builtin_fmaf(cur[2 * j + 4], c, nm);
         cur[2 * j + 5] = __builtin_fmaf(cur[2 * j + 5], c, nm);
       }
-      const bf16x2 pk = __builtin_bit_cast(bf16x2, pack_bf16(cur[2 * j], cur[2 * j + 1]));
-      l[j & 1] = __builtin_amdgcn_fdot2_f32_bf16(pk, ones, l[j & 1], false);
+      uint32_t packed = pack_bf16(cur[2 * j], cur[2 * j + 1]);
+      // (used here: the compiler would otherwise sink the second half of the weights behind a branch that follows, out of
+      // the matrix instructions' shadow)
+      asm volatile("" : "+v"(packed));
+      const bf16x2 pk = __builtin_bit_cast(bf16x2, packed);
       if (j < 4) { first[2 * j] = pk[0]; first[2 * j + 1] = pk[1]; }
       else { second[2 * j - 8] = pk[0]; second[2 * j - 7] = pk[1]; }
       if (j < 2) o_open[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v.f[1][j], open, o_open[j], 0, 0, 0);
       else if (j < 6) nxt = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k.f[j - 2], q.f[j - 2], nxt, 0, 0, 0);
       else o[j - 6] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v.f[0][j - 6], first, o[j - 6], 0, 0, 0);
+      if (j == 1) add_weights(l_open, open);
+      if (j == 7) add_weights(l, first);
       __builtin_amdgcn_sched_barrier(0);
       if (LOADV && j == 1) load_v(v, vslot, 1);
     }
     open = second;
   }
+  // a row's sum += a fragment's weights; what the sum is for this lane's query (of both half-waves' keys)
+  __device__ __forceinline__ void add_weights(f32x4 &l, const bf16x8 &w) const {
+    l = __builtin_amdgcn_mfma_f32_16x16x32_bf16(sel, w, l, 0, 0, 0);
+  }
+  static __device__ __forceinline__ float row_sum(const f32x4 &l, int lane) { return lane & 16 ? l[1] : l[0]; }
   // O^T += V^T w.  LO: columns 16..31 are the first 16 once more and take what bf16 rounding leaves of a weight,
   // w - bf16(w); what that leaves in turn comes in a second product, so that all 24 bits of a weight enter.
   template <int NT, bool LO>
@@ -560,7 +578,7 @@ __device__ __forceinline__ void walk_keys_pipelined(const S &st, WaveAcc<S, 2> &
   // the output product behind: none yet
   bf16x8 open = {};
   vf.f[1][0] = vf.f[1][1] = open;
-  float l0[2] = {0.f, 0.f}, l1[2] = {0.f, 0.f};
+  f32x4 l0 = {0.f, 0.f, 0.f, 0.f}, l1 = l0;   // sums since the reference was last raised
   // the first step's logits; then K2 takes its slot
   if (n > 1) wait_vm<2 * R>();
   else wait_vm<R>();
@@ -578,10 +596,13 @@ __device__ __forceinline__ void walk_keys_pipelined(const S &st, WaveAcc<S, 2> &
     issue_v(1, tk);
   }
   // a higher reference for half nt, whose output product is not the open one
+  auto take_sums = [&](int nt, f32x4 &l) {
+    a.l[nt] += lane < 32 ? S::row_sum(l, lane) : 0.f;
+    l = f32x4{0.f, 0.f, 0.f, 0.f};
+  };
   auto raise = [&](int nt, const f32x16 &s) {
-    a.l[nt] = nt ? l1[0] + l1[1] : l0[0] + l0[1];
+    take_sums(nt, nt ? l1 : l0);
     a.reference(s, nt, c);
-    if (nt) { l1[0] = a.l[1]; l1[1] = 0.f; } else { l0[0] = a.l[0]; l0[1] = 0.f; }
   };
   // step i, whose V is in slot `odd`; `odd` = i & 1 is a constant at each place of use
   auto step = [&](auto first_c, int i, int odd) {
@@ -594,16 +615,16 @@ __device__ __forceinline__ void walk_keys_pipelined(const S &st, WaveAcc<S, 2> &
     const bool special = FIXED || careful || first || rem <= 1;
     const unsigned char *vslot = wsm + kV + odd * S::kHalf;
     st.load_v(vf, vslot, 0);
-    st.template half_step<true>(s0, c, -a.m[0], l0, a.o[0], a.o[1], open, vf, vslot, kf, a.q[1], s1);
+    st.template half_step<true>(s0, c, -a.m[0], l0, a.o[0], l1, a.o[1], open, vf, vslot, kf, a.q[1], s1);
     const bool rest = first && st.exact > 0;
-    if (rest) l0[0] += st.add_rest(s0, vslot, a.o[0], lane);
+    if (rest) a.l[0] += st.add_rest(s0, vslot, a.o[0], lane);
     if (special) {
       fix(i, 1, s1);
       if (careful || first) raise(1, s1);
     }
     st.load_k(kf, wsm + (odd ^ 1) * S::kHalf);      // (behind the last step: what the slot holds, not used)
-    st.template half_step<false>(s1, c, -a.m[1], l1, a.o[1], a.o[0], open, vf, vslot, kf, a.q[0], s0);
-    if (rest) l1[0] += st.add_rest(s1, vslot, a.o[1], lane);
+    st.template half_step<false>(s1, c, -a.m[1], l1, a.o[1], l0, a.o[0], open, vf, vslot, kf, a.q[0], s0);
+    if (rest) a.l[1] += st.add_rest(s1, vslot, a.o[1], lane);
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");       // both slots have been read
     if (rem >= 3) {
       tokens(i + 3);
@@ -626,8 +647,9 @@ __device__ __forceinline__ void walk_keys_pipelined(const S &st, WaveAcc<S, 2> &
   }
 #pragma unroll
   for (int dt = 0; dt < 2; dt++) a.o[1][dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf.f[1][dt], open, a.o[1][dt], 0, 0, 0);
-  a.l[0] = l0[0] + l0[1];
-  a.l[1] = l1[0] + l1[1];
+  st.add_weights(l1, open);
+  take_sums(0, l0);
+  take_sums(1, l1);
   wait_vm<0>();                               // (token requests past the end)
 }
 
