@@ -201,7 +201,7 @@ static PatchKernel choose_patch_kernel(const ns_attn_desc &d, int &split) {
 static ns_status launch_patch_attention(const AttnArgs &a) {
   switch (a.kernel) {
     case PK_SWEEP: return launch_attn_sweep(a, nullptr, nullptr);
-    case PK_BLOCK16: return launch_attn_block16(a);
+    case PK_BLOCK16: return launch_attn_block16(a, nullptr, nullptr);
     case PK_RAGGED: return launch_attn_ragged(a, nullptr, nullptr);
     default: return launch_attn_generic(a, nullptr, nullptr);
   }
@@ -306,15 +306,14 @@ ns_status ns::attn_forward_impl(const ns_attn_desc *desc, const void *q, const v
   }
   // the global rows: chunk partials (in the same launch where the kernel takes them along), then the
   // merge that also writes out[:, :, 0..G-1, :]
-  if (a.kernel == PK_RAGGED || a.kernel == PK_GENERIC) {
-    st = a.kernel == PK_RAGGED ? launch_attn_ragged(a, cls_logits, partials) : launch_attn_generic(a, cls_logits, partials);
-    if (st != NS_OK) return st;
-  } else {
+  if (a.kernel == PK_SWEEP) {
     st = launch_patch_attention(a);
-    if (st != NS_OK) return st;
-    st = launch_cls_row(d, q, k, v, cls_logits, partials, a.stream);
-    if (st != NS_OK) return st;
+    if (st == NS_OK) st = launch_cls_row(d, q, k, v, cls_logits, partials, a.stream);
+  } else {
+    st = a.kernel == PK_RAGGED ? launch_attn_ragged(a, cls_logits, partials)
+         : a.kernel == PK_BLOCK16 ? launch_attn_block16(a, cls_logits, partials) : launch_attn_generic(a, cls_logits, partials);
   }
+  if (st != NS_OK) return st;
   if (scores) return launch_cls_combine_scores(d, partials, out, cls_lse, cls_logits, scores, a.stream);
   return launch_cls_combine(d, partials, out, cls_lse, true, a.stream);
 }

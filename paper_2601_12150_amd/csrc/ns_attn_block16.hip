@@ -25,9 +25,9 @@ namespace ns {
 namespace {
 
 struct BlockParams {
-  const uint16_t *q, *k, *v;
+  GlobalRows r;         // q, k, v, strides, scale; logits and partials for the global rows
   uint16_t *out;
-  int64_t qsb, qsh, qst, osb, osh, ost;
+  int64_t osb, osh, ost;
   float c;              // scale * log2(e)
   int grid_h, grid_w, block, nbh, nbw;   // blocks per side: ceil(grid / block)
   int heads;
@@ -36,6 +36,8 @@ struct BlockParams {
   int images;           // batch * heads
   int inner_xcd, rim_xcd;   // workgroups of either kind per XCD
   int n_global;         // G leading global tokens, 1 .. 8 (their K and V rows sit in LDS)
+  int tokens, nchunks;
+  int row_wgs, row_xcd; // workgroups that own a chunk of a head's global rows; per XCD
 };
 
 typedef bf16x8 __attribute__((address_space(3))) *lds_bf16x8_ptr;
@@ -51,8 +53,11 @@ constexpr int kBlockLds = kSlots * kSlot + 2048;
 
 constexpr float kMasked = -1e30f;     // logit of a key number past the end
 
-// grid: 8 XCDs x (inner_xcd + rim_xcd) workgroups of 256 threads, each 256 queries of a block.
+// grid: 8 XCDs x (row_xcd + inner_xcd + rim_xcd) workgroups of 256 threads, each 256 queries of a block or a chunk of the
+// global rows.  ROWS: 0: no global rows, 1: one, 2: several.
+template <int ROWS>
 __global__ __launch_bounds__(256, 2) void attn_block16_kernel(BlockParams p) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   const int tid = threadIdx.x, wave = NS_U(tid >> 6), lane = tid & 63;
   const int l32 = lane & 31, hh = lane >> 5;
 
@@ -62,6 +67,18 @@ __global__ __launch_bounds__(256, 2) void attn_block16_kernel(BlockParams p) {
   int img, R, C, part;
   {
     int i = (int)blockIdx.x >> 3;
+    // The chunks of the global rows, a few microseconds each, come last: they fill what the last round of tiles leaves
+    // idle (against a launch of their own, 16 heads: 256x256, 16x16 blocks 612 -> 598 us a call, 96x96 102 -> 94, 128x128
+    // with 64x64 blocks and five global tokens 1030 -> 1007).  (Spread among the tiles, so that their loads run beside products, they put launches of whole rounds of tiles
+    // into another round: 128x128, 64x64 blocks, five global tokens, 1056 -> 1192 us.)
+    if (ROWS && i >= p.inner_xcd + p.rim_xcd) {
+      const int id = ((int)blockIdx.x & 7) * p.row_xcd + i - p.inner_xcd - p.rim_xcd;
+      if (id >= p.row_wgs) return;
+      if (ROWS == 1) global_row_chunk(p.r, p.heads, p.tokens, p.nchunks, id, smem, tid);
+      else if (p.r.logits) global_rows_chunk<StepBf16, true, true>(p.r, p.heads, p.n_global, p.tokens, 1, p.nchunks, id, smem, wave, lane);
+      else global_rows_chunk<StepBf16, true, false>(p.r, p.heads, p.n_global, p.tokens, 1, p.nchunks, id, smem, wave, lane);
+      return;
+    }
     const bool rim = i >= p.inner_xcd;
     i = rim ? ((int)blockIdx.x & 7) * p.rim_xcd + i - p.inner_xcd : ((int)blockIdx.x & 7) * p.inner_xcd + i;
     const int per = (rim ? p.rim : p.inner) * p.parts;
@@ -95,15 +112,15 @@ __global__ __launch_bounds__(256, 2) void attn_block16_kernel(BlockParams p) {
   const int steps = (nk + 63) >> 6;
   const int q0 = part * 256 + wave * 64, qcnt = NS_U(min(qn - q0, 64));     // this wave's queries, if any
 
-  const char *qb = reinterpret_cast<const char *>(p.q + b * p.qsb + h * p.qsh);
-  const char *kb = reinterpret_cast<const char *>(p.k + b * p.qsb + h * p.qsh);
-  const char *vb = reinterpret_cast<const char *>(p.v + b * p.qsb + h * p.qsh);
+  const int64_t head = b * p.r.sb + h * p.r.sh;
+  const char *qb = reinterpret_cast<const char *>(static_cast<const uint16_t *>(p.r.q) + head);
+  const char *kb = reinterpret_cast<const char *>(static_cast<const uint16_t *>(p.r.k) + head);
+  const char *vb = reinterpret_cast<const char *>(static_cast<const uint16_t *>(p.r.v) + head);
   char *ob = reinterpret_cast<char *>(p.out + b * p.osb + h * p.osh);
 
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   const uint32_t lds_base = (uint32_t)(size_t)((__attribute__((address_space(3))) unsigned char *)smem);
 
-  const uint32_t rowB = (uint32_t)p.qst * 2u;
+  const uint32_t rowB = (uint32_t)p.r.st * 2u;
   // token of a query slot (slots past the end repeat the last one) and of a key number (likewise)
   auto query = [&](int i) {
     const int s = q0 + min(i, qcnt - 1), r = div_small(s, 1.f / (float)bw);
@@ -361,14 +378,11 @@ bool block16_attn_supported(const ns_attn_desc &d) {
          (long long)d.tokens * d.out_stride_t * 2 < 0x7fffffffLL;
 }
 
-ns_status launch_attn_block16(const AttnArgs &a) {
+ns_status launch_attn_block16(const AttnArgs &a, float *logits, float *partials) {
   const ns_attn_desc &d = a.d;
   BlockParams p;
-  p.q = static_cast<const uint16_t *>(a.q);
-  p.k = static_cast<const uint16_t *>(a.k);
-  p.v = static_cast<const uint16_t *>(a.v);
+  p.r = global_rows<StepBf16>(d, a.q, a.k, a.v, logits, partials);
   p.out = static_cast<uint16_t *>(a.out);
-  p.qsb = d.q_stride_b; p.qsh = d.q_stride_h; p.qst = d.q_stride_t;
   p.osb = d.out_stride_b; p.osh = d.out_stride_h; p.ost = d.out_stride_t;
   p.c = d.scale * kLog2e;
   p.grid_h = d.grid_h;
@@ -382,13 +396,23 @@ ns_status launch_attn_block16(const AttnArgs &a) {
   p.heads = d.heads;
   p.images = d.batch * d.heads;
   p.n_global = d.n_global;
+  p.tokens = d.tokens;
+  p.nchunks = cls_num_chunks(d.tokens);
+  static_assert(8 <= global_group_rows<StepBf16>(), "the global rows of a head are one group");
   const long long inner = ((long long)p.images * p.inner * p.parts + 7) / 8, rim = ((long long)p.images * p.rim * p.parts + 7) / 8;
-  if (8 * (inner + rim) > 0x7fffffffLL) return fail(NS_ERR_UNSUPPORTED, "launch grid too large");
+  const long long rows = partials ? (long long)p.images * p.nchunks : 0, wgs = 8 * (inner + rim + (rows + 7) / 8);
+  if (wgs > 0x7fffffffLL) return fail(NS_ERR_UNSUPPORTED, "launch grid too large");
   p.inner_xcd = (int)inner;
   p.rim_xcd = (int)rim;
-  const ns_status rs = reserve_lds_once(reinterpret_cast<const void *>(attn_block16_kernel), kBlockLds);
+  p.row_wgs = (int)rows;
+  p.row_xcd = (int)((rows + 7) / 8);
+  typedef void (*kern_t)(BlockParams);
+  const kern_t kern = !partials ? attn_block16_kernel<0> : (d.n_global == 1 ? attn_block16_kernel<1> : attn_block16_kernel<2>);
+  const int lds = partials && d.n_global > 1 ? kWindowLds : kBlockLds;
+  static_assert(kBlockLds <= kWindowLds && kScanLds <= kBlockLds, "LDS");
+  const ns_status rs = reserve_lds_once(reinterpret_cast<const void *>(kern), lds);
   if (rs != NS_OK) return rs;
-  hipLaunchKernelGGL(attn_block16_kernel, dim3((unsigned)(8 * (inner + rim))), dim3(256), kBlockLds, a.stream, p);
+  hipLaunchKernelGGL(kern, dim3((unsigned)wgs), dim3(256), lds, a.stream, p);
   return check_launch("attn_block16_kernel");
 }
 

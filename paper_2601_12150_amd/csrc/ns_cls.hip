@@ -21,11 +21,6 @@ __device__ __forceinline__ void load_row8(const float *p, float (&x)[8]) {
 #pragma unroll
   for (int e = 0; e < 4; e++) { x[e] = a[e]; x[4 + e] = b[e]; }
 }
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ void unpack8(const u32x4 &u, float (&x)[8]) {
-  x[0] = bf16_lo(u[0]); x[1] = bf16_hi(u[0]); x[2] = bf16_lo(u[1]); x[3] = bf16_hi(u[1]);
-  x[4] = bf16_lo(u[2]); x[5] = bf16_hi(u[2]); x[6] = bf16_lo(u[3]); x[7] = bf16_hi(u[3]);
-}
 __device__ __forceinline__ void load_row8(const uint16_t *p, float (&x)[8]) { unpack8(*reinterpret_cast<const u32x4 *>(p), x); }
 
 // One global token and K only (scoring without an attention output): grid (chunks, H, B), 256
@@ -96,93 +91,6 @@ __global__ __launch_bounds__(256) void cls_scan_kernel(const T *q, const T *k, i
     rec[0] = M;
     rec[1] = (red[0] + red[1]) + (red[2] + red[3]);
   }
-}
-
-// One global token, bf16, K and V (the row of a problem whose patch kernel does not take it along): lanes as
-// above, V's rows requested before the weights are known.  Bound: HBM, K and V are read once and past the
-// caches (non-temporal loads: 57 -> 51 us on a 256 x 256 grid, 16 heads; a whole call with 16x16 blocks 10 us
-// less of 642 than with the kernel below, whose matrix instructions are work for 15 padding columns).
-__global__ __launch_bounds__(256, 4) void cls_scan_v_kernel(const uint16_t *q, const uint16_t *k, const uint16_t *v, int64_t sb,
-                                                         int64_t sh, int64_t st, int T_, int H, float scale, float *logits,
-                                                         float *partials, int nchunks) {
-  constexpr int kSteps = kClsChunk / (4 * 8);
-  const int chunk = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  const int slot = lane >> 3, sub = lane & 7;
-  const int64_t head = b * sb + h * sh + sub * 8;
-  __shared__ float red[4];
-  __shared__ float osum[4][64];
-
-  float q8[8];
-  load_row8(q + head, q8);
-#pragma unroll
-  for (int e = 0; e < 8; e++) q8[e] *= scale;
-  const int key0 = chunk * kClsChunk + wave * (kSteps * 8) + slot;
-  u32x4 row[kSteps];                       // (clamped, not skipped: a branch would wait for each load)
-#pragma unroll
-  for (int i = 0; i < kSteps; i++)
-    row[i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(k + head + (int64_t)min(key0 + i * 8, T_ - 1) * st));
-  float s[kSteps];
-  float mx = -INFINITY;
-#pragma unroll
-  for (int i = 0; i < kSteps; i++) {
-    float k8[8];
-    unpack8(row[i], k8);
-    row[i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(v + head + (int64_t)min(key0 + i * 8, T_ - 1) * st));
-    float acc = 0.f;
-#pragma unroll
-    for (int e = 0; e < 8; e++) acc = __builtin_fmaf(q8[e], k8[e], acc);
-    acc += __shfl_xor(acc, 1);
-    acc += __shfl_xor(acc, 2);
-    acc += __shfl_xor(acc, 4);
-    s[i] = key0 + i * 8 < T_ ? acc : -INFINITY;
-    mx = fmaxf(mx, s[i]);
-  }
-  mx = fmaxf(mx, __shfl_xor(mx, 8));
-  mx = fmaxf(mx, __shfl_xor(mx, 16));
-  mx = fmaxf(mx, __shfl_xor(mx, 32));
-  if (lane == 0) red[wave] = mx;
-  __syncthreads();
-  const float M = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));   // finite: chunk non-empty
-  __syncthreads();
-  float l = 0.f;
-  float o8[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-  for (int i = 0; i < kSteps; i++) {
-    const bool in = key0 + i * 8 < T_;
-    const float pr = __builtin_amdgcn_exp2f((s[i] - M) * kLog2e);
-    float v8[8];
-    unpack8(row[i], v8);
-    l += pr;
-#pragma unroll
-    for (int e = 0; e < 8; e++) o8[e] = __builtin_fmaf(pr, in ? v8[e] : 0.f, o8[e]);
-  }
-  // (stores behind the loads: waiting for a load also waits for every older store)
-  if (logits) {
-    float *lrow = logits + ((size_t)b * H + h) * T_;
-#pragma unroll
-    for (int i = 0; i < kSteps; i++)
-      if (sub == 0 && key0 + i * 8 < T_) lrow[key0 + i * 8] = s[i];
-  }
-  // across the 8 key slots of the wave (not across channel slices)
-#pragma unroll
-  for (int sft = 8; sft < 64; sft <<= 1) {
-    l += __shfl_xor(l, sft);
-#pragma unroll
-    for (int e = 0; e < 8; e++) o8[e] += __shfl_xor(o8[e], sft);
-  }
-  if (lane == 0) red[wave] = l;
-  if (slot == 0) {
-#pragma unroll
-    for (int e = 0; e < 8; e++) osum[wave][sub * 8 + e] = o8[e];
-  }
-  __syncthreads();
-  float *rec = partials + (((size_t)b * H + h) * nchunks + chunk) * kClsPartialFloats;
-  if (tid == 0) {
-    rec[0] = M;
-    rec[1] = (red[0] + red[1]) + (red[2] + red[3]);
-  }
-  if (tid < 64) rec[2 + tid] = (osum[0][tid] + osum[1][tid]) + (osum[2][tid] + osum[3][tid]);
 }
 
 // grid (chunks * groups of global rows * H * B): one workgroup per chunk of 512 keys and group of
@@ -341,16 +249,9 @@ ns_status launch_cls_row(const ns_attn_desc &d, const void *q, const void *k, co
                          float *logits, float *partials, hipStream_t s) {
   const dim3 grid(cls_num_chunks(d.tokens), d.heads, d.batch), blk(256);
   const bool single = d.n_global == 1;
-  if (v) {
-    // (bf16, a positive scale, 32-bit row offsets: what the kernels take that leave the rows to this launch)
-    if (!single)
-      return logits ? launch_rows<StepBf16, true, true>(d, q, k, v, logits, partials, s)
-                    : launch_rows<StepBf16, true, false>(d, q, k, v, logits, partials, s);
-    hipLaunchKernelGGL(cls_scan_v_kernel, grid, blk, 0, s, static_cast<const uint16_t *>(q), static_cast<const uint16_t *>(k),
-                       static_cast<const uint16_t *>(v), d.q_stride_b, d.q_stride_h, d.q_stride_t, d.tokens, d.heads, d.scale,
-                       logits, partials, (int)grid.x);
-    return check_launch("cls_scan_v_kernel");
-  }
+  if (v)     // several rows in bf16, a positive scale, 32-bit row offsets (the sweep, where it is forced on them)
+    return logits ? launch_rows<StepBf16, true, true>(d, q, k, v, logits, partials, s)
+                  : launch_rows<StepBf16, true, false>(d, q, k, v, logits, partials, s);
   if (!single) {
     if (d.dtype == NS_F32) return launch_rows<StepF32<float>, false, true>(d, q, k, v, logits, partials, s);
     // (the bf16 step wants a positive scale and 32-bit row offsets)

@@ -195,8 +195,8 @@ bool sweep_attn_supported(const ns_attn_desc &d);    // 8x8 blocks: key tiles sh
 // (sweep_cls_chunks of them per head-image) and, with cls_logits, its raw logits [B,H,T]
 ns_status launch_attn_sweep(const AttnArgs &a, float *cls_logits, float *cls_partials);
 inline int sweep_cls_chunks(const ns_attn_desc &d) { return 4 * ((d.grid_h + 7) / 8); }
-bool block16_attn_supported(const ns_attn_desc &d);  // 16x16 blocks: key tiles shared by a block's four query tiles
-ns_status launch_attn_block16(const AttnArgs &a);
+bool block16_attn_supported(const ns_attn_desc &d);  // blocks of 16 and its multiples: key tiles shared by a block's query tiles
+ns_status launch_attn_block16(const AttnArgs &a, float *logits, float *partials);
 bool ragged_attn_supported(const ns_attn_desc &d);   // bf16, head_dim 64: any complete grid or pruned sequence
 ns_status launch_attn_ragged(const AttnArgs &a, float *logits, float *partials);
 double ragged_attn_us(const ns_attn_desc &d);         // what its launch takes on a complete grid, roughly

@@ -980,6 +980,100 @@ __device__ __forceinline__ void global_rows_chunk(const GlobalRows &p, int heads
   }
 }
 
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ void unpack8(const u32x4 &u, float (&x)[8]) {
+  x[0] = bf16_lo(u[0]); x[1] = bf16_hi(u[0]); x[2] = bf16_lo(u[1]); x[3] = bf16_hi(u[1]);
+  x[4] = bf16_lo(u[2]); x[5] = bf16_hi(u[2]); x[6] = bf16_lo(u[3]); x[7] = bf16_hi(u[3]);
+}
+// ------------------------------------------------------------------------------------------
+// One global row in bf16 on the vector ALU, workgroup `id` = (head, chunk): lane = (key slot, 8-channel slice), 8 lanes
+// per key row, all of a wave's 128 rows of K and then of V on their way at once.  For a single row the matrix
+// instructions above are work for 15 or 31 padding columns.  Bound: HBM.  Past the caches (non-temporal
+// loads): 0.7 % of a whole call with 16x16 blocks on 256x256.
+// ------------------------------------------------------------------------------------------
+constexpr int kScanLds = 4 * 64 * 4 + 16;    // bytes
+__device__ __forceinline__ void global_row_chunk(const GlobalRows &p, int H, int T_, int nchunks, int id, unsigned char *smem,
+                                                 int tid) {
+  constexpr int kSteps = kClsChunk / (4 * 8);   // 4 waves x 8 keys per wave-step
+  const int chunk = id % nchunks, bh = id / nchunks, b = bh / H, h = bh - b * H;
+  const int wave = tid >> 6, lane = tid & 63, slot = lane >> 3, sub = lane & 7;
+  const int64_t head = b * p.sb + h * p.sh + sub * 8;
+  const uint16_t *k = static_cast<const uint16_t *>(p.k) + head, *v = static_cast<const uint16_t *>(p.v) + head;
+  float (*const osum)[64] = reinterpret_cast<float (*)[64]>(smem);
+  float *const red = reinterpret_cast<float *>(smem + 4 * 64 * 4);
+
+  float q8[8];
+  unpack8(*reinterpret_cast<const u32x4 *>(static_cast<const uint16_t *>(p.q) + head), q8);
+#pragma unroll
+  for (int e = 0; e < 8; e++) q8[e] *= p.scale;
+  const int key0 = chunk * kClsChunk + wave * (kSteps * 8) + slot;
+  u32x4 row[kSteps];                       // (clamped, not skipped: a branch would wait for each load)
+#pragma unroll
+  for (int i = 0; i < kSteps; i++)
+    row[i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(k + (int64_t)min(key0 + i * 8, T_ - 1) * p.st));
+  float s[kSteps];
+  float mx = -INFINITY;
+#pragma unroll
+  for (int i = 0; i < kSteps; i++) {
+    float k8[8];
+    unpack8(row[i], k8);
+    row[i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(v + (int64_t)min(key0 + i * 8, T_ - 1) * p.st));
+    float acc = 0.f;
+#pragma unroll
+    for (int e = 0; e < 8; e++) acc = __builtin_fmaf(q8[e], k8[e], acc);
+    acc += __shfl_xor(acc, 1);
+    acc += __shfl_xor(acc, 2);
+    acc += __shfl_xor(acc, 4);
+    s[i] = key0 + i * 8 < T_ ? acc : -INFINITY;
+    mx = fmaxf(mx, s[i]);
+  }
+  mx = fmaxf(mx, __shfl_xor(mx, 8));
+  mx = fmaxf(mx, __shfl_xor(mx, 16));
+  mx = fmaxf(mx, __shfl_xor(mx, 32));
+  if (lane == 0) red[wave] = mx;
+  __syncthreads();
+  const float M = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));   // finite: chunk non-empty
+  __syncthreads();
+  float l = 0.f;
+  float o8[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int i = 0; i < kSteps; i++) {
+    const bool in = key0 + i * 8 < T_;
+    const float pr = __builtin_amdgcn_exp2f((s[i] - M) * kLog2e);
+    float v8[8];
+    unpack8(row[i], v8);
+    l += pr;
+#pragma unroll
+    for (int e = 0; e < 8; e++) o8[e] = __builtin_fmaf(pr, in ? v8[e] : 0.f, o8[e]);
+  }
+  // (stores behind the loads: waiting for a load also waits for every older store)
+  if (p.logits) {
+    float *lrow = p.logits + ((size_t)b * H + h) * T_;
+#pragma unroll
+    for (int i = 0; i < kSteps; i++)
+      if (sub == 0 && key0 + i * 8 < T_) lrow[key0 + i * 8] = s[i];
+  }
+  // across the 8 key slots of the wave (not across channel slices)
+#pragma unroll
+  for (int sft = 8; sft < 64; sft <<= 1) {
+    l += __shfl_xor(l, sft);
+#pragma unroll
+    for (int e = 0; e < 8; e++) o8[e] += __shfl_xor(o8[e], sft);
+  }
+  if (lane == 0) red[wave] = l;
+  if (slot == 0) {
+#pragma unroll
+    for (int e = 0; e < 8; e++) osum[wave][sub * 8 + e] = o8[e];
+  }
+  __syncthreads();
+  float *rec = p.partials + (((size_t)b * H + h) * nchunks + chunk) * kClsPartialFloats;
+  if (tid == 0) {
+    rec[0] = M;
+    rec[1] = (red[0] + red[1]) + (red[2] + red[3]);
+  }
+  if (tid < 64) rec[2 + tid] = (osum[0][tid] + osum[1][tid]) + (osum[2][tid] + osum[3][tid]);
+}
+
 // ------------------------------------------------------------------------------------------
 // One launch: the leading workgroups own chunks of the global rows, the others a query tile each,
 // whose keys the four waves share out step by step; the waves' partial states are merged through
