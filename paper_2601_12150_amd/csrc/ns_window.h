@@ -26,8 +26,8 @@ struct WindowGeom {
   int tiles_per_image;     // nbh * nbw * tpb
   int tiles;               // batch * heads * tiles_per_image
   int per_xcd;             // workgroups per XCD
-  int global_wgs;          // leading workgroups that own chunks of the global rows: a multiple of 8
-  int global_live;         // ... of which this many have work
+  int row_wgs;             // workgroups that own chunks of the global rows
+  int rows_at, tiles_at;   // first workgroup of these and of the tiles' (a multiple of 8)
   int global_groups;       // groups of global rows per head
   int nchunks;             // key chunks per head-image
   const int32_t *lists, *counts;
@@ -131,8 +131,7 @@ struct WindowTile {
   }
 };
 
-// Position of workgroup `bid` (of those behind the leading global ones, whose number is a multiple
-// of 8): workgroups are dealt round-robin to the 8 XCDs, and each XCD gets a contiguous range of
+// Position of workgroup `bid`: workgroups are dealt round-robin to the 8 XCDs, and each XCD gets a contiguous range of
 // tiles, so that the K and V rows which neighbouring tiles share are fetched into one L2.
 __device__ __forceinline__ int window_tile_id(const WindowGeom &g, int bid) {
   return (bid & 7) * g.per_xcd + (bid >> 3);
@@ -1075,9 +1074,8 @@ __device__ __forceinline__ void global_row_chunk(const GlobalRows &p, int H, int
 }
 
 // ------------------------------------------------------------------------------------------
-// One launch: the leading workgroups own chunks of the global rows, the others a query tile each,
-// whose keys the four waves share out step by step; the waves' partial states are merged through
-// LDS.  Bound at small sizes by the latency of the few steps a wave walks, at larger ones by the
+// One launch: a workgroup owns a query tile, whose keys the four waves share out step by step; the waves' partial
+// states are merged through LDS.  Others own chunks of the global rows.  Bound at small sizes by the latency of the few steps a wave walks, at larger ones by the
 // instruction issue of the steps while both waves of a SIMD are there, and by how often only one is
 // (100x100 grid, 16 heads, 2 images, five global tokens: 95 us, matrix pipes 23 % busy, vector ALUs
 // 41 %, 1.4 waves per SIMD, a quarter of a wave's time in waits).
@@ -1096,16 +1094,18 @@ __device__ __forceinline__ void window_attention(const WindowParams &p, unsigned
   constexpr bool kBf16 = S::kDepth == 2;
   const WindowGeom &g = p.g;
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
-  if ((int)blockIdx.x < g.global_wgs) {
-    if ((int)blockIdx.x >= g.global_live) return;
+  const int gid = (int)blockIdx.x - g.rows_at;
+  if (gid >= 0 && gid < g.row_wgs) {
     if (p.r.logits)
-      global_rows_chunk<S, true, true>(p.r, g.heads, g.n_global, g.tokens, g.global_groups, g.nchunks, blockIdx.x, smem, wave, lane);
+      global_rows_chunk<S, true, true>(p.r, g.heads, g.n_global, g.tokens, g.global_groups, g.nchunks, gid, smem, wave, lane);
     else
-      global_rows_chunk<S, true, false>(p.r, g.heads, g.n_global, g.tokens, g.global_groups, g.nchunks, blockIdx.x, smem, wave, lane);
+      global_rows_chunk<S, true, false>(p.r, g.heads, g.n_global, g.tokens, g.global_groups, g.nchunks, gid, smem, wave, lane);
     return;
   }
+  const int bid = (int)blockIdx.x - g.tiles_at;
+  if (bid < 0 || bid >= 8 * g.per_xcd) return;       // (the rows' workgroups are filled up to a multiple of 8)
   // waves part, part + 1, .. part + KS - 1 share a tile
-  const int part = wave & (KS - 1), id = window_tile_id(g, blockIdx.x - g.global_wgs) * (4 / KS) + wave / KS;
+  const int part = wave & (KS - 1), id = window_tile_id(g, bid) * (4 / KS) + wave / KS;
   WindowTile<LISTS, QT> w;
   // (a wave without a tile takes part in the barrier below and touches no memory: with an empty tile
   // there is no query slot, hence no token to look up)
@@ -1271,9 +1271,15 @@ inline long long window_geometry(const AttnArgs &a, int qt, int rows_per_group, 
   g.per_xcd = (int)((tiles * ks + 31) / 32);
   g.global_groups = groups;
   g.nchunks = nchunks;
-  g.global_live = (int)live;
-  g.global_wgs = (int)((live + 7) / 8 * 8);
-  const long long wgs = g.global_wgs + 8LL * g.per_xcd;
+  // The chunks of the global rows come last, where they fill what the last round of tiles leaves idle (against first,
+  // whole calls: 100x100, 8x8 blocks, two images, five global tokens 104.0 -> 100.6 us, fp32 64x64 110.7 -> 104.0).  Where all
+  // workgroups fit the chip at once there is no such round and a chunk takes longest: first (28x28, 7x7 blocks,
+  // 13.4 us, last 14.5).
+  const long long tile_wgs = 8LL * g.per_xcd, wgs = tile_wgs + (live + 7) / 8 * 8;
+  const bool first = wgs <= 2LL * device_cu_count();
+  g.row_wgs = (int)live;
+  g.rows_at = first ? 0 : (int)tile_wgs;
+  g.tiles_at = first ? (int)(wgs - tile_wgs) : 0;
   return wgs > 0x7fffffffLL ? -1 : wgs;
 }
 
