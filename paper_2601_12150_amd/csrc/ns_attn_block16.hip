@@ -221,7 +221,7 @@ __global__ __launch_bounds__(256, 2) void attn_block16_kernel(BlockParams p) {
     }
   };
   // normalise and store; returns whether a weight overflowed the fixed reference (then some sum or
-  // output is not finite).  Lane (query, hh) owns channels 32*dt + 8*ig + 4*hh + 0..3.
+  // output is not finite).  Lane (query, hh) stores channels 32*dt + 16*ig + 8*hh + 0..7.
   auto finish_tile = [&]() {
     float big = max_abs(max_abs(0.f, l[0]), l[1]);
 #pragma unroll
@@ -231,15 +231,14 @@ __global__ __launch_bounds__(256, 2) void attn_block16_kernel(BlockParams p) {
 #pragma unroll
     for (int nt = 0; nt < 2; nt++) {
       const float inv = 1.f / half_swap_sum(l[nt]);
-      if (32 * nt + l32 >= qcnt) continue;
-      char *row = ob + (size_t)query(32 * nt + l32) * (size_t)(p.ost * 2) + 8 * hh;
+      char *row = ob + (size_t)query(32 * nt + l32) * (size_t)(p.ost * 2) + 16 * hh;
 #pragma unroll
       for (int dt = 0; dt < 2; dt++)
 #pragma unroll
-        for (int ig = 0; ig < 4; ig++)
-          *reinterpret_cast<u32x2 *>(row + 64 * dt + 16 * ig) =
-              u32x2{pack_bf16(o[nt][dt][4 * ig] * inv, o[nt][dt][4 * ig + 1] * inv),
-                    pack_bf16(o[nt][dt][4 * ig + 2] * inv, o[nt][dt][4 * ig + 3] * inv)};
+        for (int ig = 0; ig < 2; ig++) {
+          const u32x4 u = row_pieces(o[nt][dt], 8 * ig, inv);
+          if (32 * nt + l32 < qcnt) *reinterpret_cast<u32x4 *>(row + 64 * dt + 32 * ig) = u;
+        }
     }
     return bad;
   };
@@ -307,7 +306,7 @@ __global__ __launch_bounds__(256, 2) void attn_block16_kernel(BlockParams p) {
     for (int dt = 0; dt < 2; dt++) o[1][dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf.f[1][dt], open, o[1][dt], 0, 0, 0);
     st.add_weights(ls[1], open);
 #pragma unroll
-    for (int nt = 0; nt < 2; nt++) l[nt] += hh == 0 ? StepBf16::row_sum(ls[nt], lane) : 0.f;
+    for (int nt = 0; nt < 2; nt++) l[nt] += StepBf16::row_sum(ls[nt], lane);
     bad = finish_tile();
   }
   // (the ring is free behind the last barrier: each wave takes a slot of it below)

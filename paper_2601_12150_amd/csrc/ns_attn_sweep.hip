@@ -34,7 +34,7 @@
 // "at most N outstanding" means all but the N youngest have arrived); the barrier then makes the
 // tile visible to all and, at the same time, tells that everybody is done with the slot that
 // the next transfer overwrites.
-#include "ns_common.h"
+#include "ns_window.h"
 
 namespace ns {
 
@@ -56,7 +56,6 @@ struct SweepParams {
   float *cls_partials;  // [B,H,4*nbh,66] softmax partials of the global query, or NULL: no global row
 };
 
-typedef s16x4 __attribute__((address_space(3))) *lds_s16x4_ptr;
 typedef bf16x8 __attribute__((address_space(3))) *lds_bf16x8_ptr;
 
 constexpr uint32_t kSlot = 16384;     // one key tile: K [64][64] bf16, then V [64][64] bf16
@@ -66,7 +65,7 @@ constexpr uint32_t kK0Row = 3 * 16384;         // k_0 in the first 128 bytes of 
 constexpr uint32_t kV0Row = 3 * 16384 + 1024;  // v_0 likewise
 constexpr uint32_t kQ0Row = 3 * 16384 + 2048;  // q_0 likewise
 constexpr uint32_t kClsState = 3 * 16384 + 3072;   // per wave 512 B: o[64], m, l of the global query's partial
-constexpr uint32_t kClsLogit = 3 * 16384 + 3072 + 4 * 512;   // per wave 256 B: a tile's 64 logits
+constexpr uint32_t kClsWeight = 3 * 16384 + 3072 + 4 * 512;  // per wave 256 B: a tile's 64 weights
 constexpr float kEmptyMax = -1e30f;
 constexpr float kMasked = -1e30f;     // logit of a key that does not exist (edge blocks of a grid 8 does not divide)
 
@@ -140,29 +139,9 @@ __global__ __launch_bounds__(256, 2) void attn_sweep_kernel(SweepParams p) {
   // (lane%8) ^ ((row>>1)&7) for K and (lane%8) ^ 4*((row>>1)&1) for V.  This wave issues requests
   // 2*wave and 2*wave+1 of K and of V; (row>>1)&7 = (4*(it&1) + (lane/8 >> 1)) & 7.
   const int drow = lane >> 3;
-  const uint32_t dma_koff[2] = {drow * rowB + 16u * ((lane & 7) ^ ((drow >> 1) & 7)),
-                                drow * rowB + 16u * ((lane & 7) ^ ((4 + (drow >> 1)) & 7))};
-  const uint32_t dma_voff = drow * rowB + 16u * ((lane & 7) ^ (((drow >> 1) & 1) << 2));
-  // K fragment reads: lane (row l32 [+32], half hh) needs logical chunks 4*hh + s
-  uint32_t krd[4];
-#pragma unroll
-  for (int s = 0; s < 4; s++) krd[s] = l32 * 128 + 16 * ((4 * hh + s) ^ ((l32 >> 1) & 7));
-  // V transposed reads (ds_read_b64_tr_b16): within a 16-lane group, lane i receives element i%4 of the
-  // 8-byte chunks addressed by lanes i/4, i/4+4, i/4+8, i/4+12.  Source lane s therefore points at row
-  // key0 + s/4, channels dbase + 4*(s%4), and lane i ends up with V[key0 + 0..3][dbase + i]: four
-  // consecutive keys of one channel, half of an A-operand fragment.
-  uint32_t vrd[2][2];
-  {
-    const int g = lane >> 4, s = lane & 15;
-    const int dbyte = (16 * (g & 1) + 4 * (s & 3)) * 2;
-#pragma unroll
-    for (int half = 0; half < 2; half++) {
-      const int key = 8 * half + 4 * hh + (s >> 2);
-      const int off = key * 128 + (dbyte ^ (((key >> 1) & 1) << 6));
-      vrd[0][half] = kVOff + off;
-      vrd[1][half] = kVOff + (off ^ 64);
-    }
-  }
+  StepBf16 st;
+  st.init(lane);
+  const uint32_t dma_koff[2] = {drow * rowB + st.kch[0], drow * rowB + st.kch[1]}, dma_voff = drow * rowB + st.vch;
   const uint32_t qoff0 = tile_off(l32, hvq, 8) + 64u * hh;
   const uint32_t qoff1 = tile_off(l32 + 32, hvq, 8) + 64u * hh;
 
@@ -197,42 +176,13 @@ __global__ __launch_bounds__(256, 2) void attn_sweep_kernel(SweepParams p) {
   };
 
   // ---- register state of the query block in progress
-  bf16x8 qf[2][4];
-  f32x16 o[2][2];
-  float m[2], l[2], nm[2], la[2][2];
+  StepBf16::Q qf[2];
+  f32x16 o[2][2];                    // [query half][channels 32 dt ..]
+  float m[2], l[2];
+  // sums of the weights (a copied query must get its original's bits)
+  typedef typename std::conditional<EDGE, StepBf16::LaneSums, StepBf16::LeanSums>::type Sums;
+  Sums ls[2];
 
-  auto stage_a = [&](const bf16x8 (&kf)[4], int nt) {
-    f32x16 s = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int ks = 0; ks < 4; ks++) s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[ks], qf[nt][ks], s, 0, 0, 0);
-    return s;
-  };
-  auto stage_b = [&](const f32x16 &s, int nt, bf16x8 (&pf)[2]) {
-#pragma unroll
-    for (int i = 0; i < 16; i += 2) {
-      const float p0 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[i], p.c, nm[nt]));
-      const float p1 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[i + 1], p.c, nm[nt]));
-      la[nt][0] += p0;
-      la[nt][1] += p1;
-      const bf16x2 pk = __builtin_bit_cast(bf16x2, pack_bf16(p0, p1));
-      pf[i >> 3][i & 7] = pk[0];
-      pf[i >> 3][(i & 7) + 1] = pk[1];
-    }
-  };
-  // O^T[:, nt] += V^T[:, keys 32*mt ..] P^T; slot: byte offset of the key tile's ring slot
-  auto stage_c = [&](int mt, int nt, const bf16x8 (&pf)[2], uint32_t slot) {
-#pragma unroll
-    for (int sp = 0; sp < 2; sp++)
-#pragma unroll
-      for (int dt = 0; dt < 2; dt++) {
-        const uint32_t off = slot + (2 * mt + sp) * 2048;
-        const s16x4 lo4 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(smem + vrd[dt][0] + off));
-        const s16x4 hi4 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(smem + vrd[dt][1] + off));
-        const bf16x4 a = __builtin_bit_cast(bf16x4, lo4), b2 = __builtin_bit_cast(bf16x4, hi4);
-        const bf16x8 vf = {a[0], a[1], a[2], a[3], b2[0], b2[1], b2[2], b2[3]};
-        o[dt][nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, pf[sp], o[dt][nt], 0, 0, 0);
-      }
-  };
   // Q fragments of query block qc by ordinary loads
   auto load_block = [&](int qc) {
     const char *t = qb + block_base(R, qc);
@@ -240,8 +190,8 @@ __global__ __launch_bounds__(256, 2) void attn_sweep_kernel(SweepParams p) {
     if (EDGE && qc == ncols - 1 && wv_last < 8) back = (uint32_t)max((l32 & 7) - (wv_last - 1), 0) * rowB;
 #pragma unroll
     for (int s = 0; s < 4; s++) {
-      qf[0][s] = *reinterpret_cast<const bf16x8 *>(t + (qoff0 - back) + 16 * s);
-      qf[1][s] = *reinterpret_cast<const bf16x8 *>(t + (qoff1 - back) + 16 * s);
+      qf[0].f[s] = *reinterpret_cast<const bf16x8 *>(t + (qoff0 - back) + 16 * s);
+      qf[1].f[s] = *reinterpret_cast<const bf16x8 *>(t + (qoff1 - back) + 16 * s);
     }
   };
   // The state the global token gives a query block: m = its logit (the fixed exponent reference),
@@ -250,45 +200,26 @@ __global__ __launch_bounds__(256, 2) void attn_sweep_kernel(SweepParams p) {
   // Further global tokens (rows 1 .. G-1 of the same LDS areas) are added one by one with a
   // running maximum, so the reference becomes the largest of the global tokens' logits.
   auto init_block = [&]() {
-    bf16x8 k0[4];
+    for (int g = 0; g < p.n_global; g++) {
+      StepBf16::K kg;
 #pragma unroll
-    for (int s = 0; s < 4; s++) k0[s] = *(lds_bf16x8_ptr)(smem + kK0Row + 64 * hh + 16 * s);
-#pragma unroll
-    for (int nt = 0; nt < 2; nt++) {
-      const f32x16 s = stage_a(k0, nt);
-      m[nt] = s[0] * p.c;
-      nm[nt] = -m[nt];
-      l[nt] = hh == 0 ? 1.f : 0.f;
-      la[nt][0] = 0.f; la[nt][1] = 0.f;
-    }
-#pragma unroll
-    for (int dt = 0; dt < 2; dt++)
-#pragma unroll
-      for (int ig = 0; ig < 4; ig++) {
-        const u32x2 v2 = *(u32x2 __attribute__((address_space(3))) *)(smem + kV0Row + 64 * dt + 16 * ig + 8 * hh);
-        const bf16x4 v4 = __builtin_bit_cast(bf16x4, v2);
-#pragma unroll
-        for (int e = 0; e < 4; e++) {
-          o[dt][0][4 * ig + e] = (float)v4[e];
-          o[dt][1][4 * ig + e] = (float)v4[e];
-        }
-      }
-    for (int g = 1; g < p.n_global; g++) {
-      bf16x8 kg[4];
-#pragma unroll
-      for (int s = 0; s < 4; s++) kg[s] = *(lds_bf16x8_ptr)(smem + kK0Row + 128 * g + 64 * hh + 16 * s);
+      for (int s = 0; s < 4; s++) kg.f[s] = *(lds_bf16x8_ptr)(smem + kK0Row + 128 * g + 64 * hh + 16 * s);
       float pg[2];
 #pragma unroll
       for (int nt = 0; nt < 2; nt++) {
-        const f32x16 s = stage_a(kg, nt);
-        const float sg = s[0] * p.c, m_new = fmaxf(m[nt], sg);
-        const float alpha = __builtin_amdgcn_exp2f(m[nt] - m_new);
+        const f32x16 s = st.product(kg, qf[nt]);
+        const float sg = s[0] * p.c;
+        if (g == 0) {
+          m[nt] = sg;
+          l[nt] = hh == 0 ? 1.f : 0.f;
+          continue;
+        }
+        const float m_new = fmaxf(m[nt], sg), alpha = __builtin_amdgcn_exp2f(m[nt] - m_new);
         pg[nt] = __builtin_amdgcn_exp2f(sg - m_new);
         m[nt] = m_new;
-        nm[nt] = -m_new;
         l[nt] = __builtin_fmaf(l[nt], alpha, hh == 0 ? pg[nt] : 0.f);
 #pragma unroll
-        for (int e = 0; e < 16; e++) { o[0][nt][e] *= alpha; o[1][nt][e] *= alpha; }
+        for (int e = 0; e < 16; e++) { o[nt][0][e] *= alpha; o[nt][1][e] *= alpha; }
       }
 #pragma unroll
       for (int dt = 0; dt < 2; dt++)
@@ -297,21 +228,22 @@ __global__ __launch_bounds__(256, 2) void attn_sweep_kernel(SweepParams p) {
           const u32x2 v2 = *(u32x2 __attribute__((address_space(3))) *)(smem + kV0Row + 128 * g + 64 * dt + 16 * ig + 8 * hh);
           const bf16x4 v4 = __builtin_bit_cast(bf16x4, v2);
 #pragma unroll
-          for (int e = 0; e < 4; e++) {
-            o[dt][0][4 * ig + e] = __builtin_fmaf(pg[0], (float)v4[e], o[dt][0][4 * ig + e]);
-            o[dt][1][4 * ig + e] = __builtin_fmaf(pg[1], (float)v4[e], o[dt][1][4 * ig + e]);
-          }
+          for (int e = 0; e < 4; e++)
+#pragma unroll
+            for (int nt = 0; nt < 2; nt++)
+              o[nt][dt][4 * ig + e] = g == 0 ? (float)v4[e] : __builtin_fmaf(pg[nt], (float)v4[e], o[nt][dt][4 * ig + e]);
         }
     }
+    ls[0] = ls[1] = Sums{};
   };
   uint32_t badmask = 0;              // bit j: this wave's j-th query block has to be redone
-  // Normalised rows of the finished block, packed: lane (query, hh) owns channels
-  // 32*dt + 8*ig + 4*hh + 0..3.  Also notes whether a weight overflowed the fixed reference
+  // Normalised rows of the finished block, packed: lane (query, hh) stores channels
+  // 32*dt + 16*ig + 8*hh + 0..7.  Also notes whether a weight overflowed the fixed reference
   // (then some sum or output is not finite).
-  u32x2 packed[2][2][4];
+  u32x4 packed[2][2][2];
   auto finish_math = [&](int qc) {
-    l[0] += la[0][0] + la[0][1];
-    l[1] += la[1][0] + la[1][1];
+#pragma unroll
+    for (int nt = 0; nt < 2; nt++) l[nt] += StepBf16::row_sum(ls[nt], lane);
     float big = max_abs(max_abs(0.f, l[0]), l[1]);
 #pragma unroll
     for (int i = 0; i < 16; i++)
@@ -323,156 +255,93 @@ __global__ __launch_bounds__(256, 2) void attn_sweep_kernel(SweepParams p) {
 #pragma unroll
       for (int dt = 0; dt < 2; dt++)
 #pragma unroll
-        for (int ig = 0; ig < 4; ig++)
-          packed[nt][dt][ig] = u32x2{pack_bf16(o[dt][nt][4 * ig] * inv, o[dt][nt][4 * ig + 1] * inv),
-                                     pack_bf16(o[dt][nt][4 * ig + 2] * inv, o[dt][nt][4 * ig + 3] * inv)};
+        for (int ig = 0; ig < 2; ig++) packed[nt][dt][ig] = row_pieces(o[nt][dt], 8 * ig, inv);
     }
   };
-  constexpr int kStores = 16;        // requests of store_block
+  constexpr int kStores = 8;         // requests of store_block
   auto store_block = [&](int qc) {
     char *t = ob + (size_t)block_token(R, qc) * (size_t)(p.ost * 2);
 #pragma unroll
     for (int nt = 0; nt < 2; nt++) {
       const int i = l32 + 32 * nt;
       const int wvq = EDGE && qc == ncols - 1 ? wv_last : 8;
-      char *row = t + (size_t)(min(i >> 3, hvq - 1) * p.grid_w + min(i & 7, wvq - 1)) * (size_t)(p.ost * 2) + 8 * hh;
+      char *row = t + (size_t)(min(i >> 3, hvq - 1) * p.grid_w + min(i & 7, wvq - 1)) * (size_t)(p.ost * 2) + 16 * hh;
 #pragma unroll
       for (int dt = 0; dt < 2; dt++)
 #pragma unroll
-        for (int ig = 0; ig < 4; ig++) store8(row + 64 * dt + 16 * ig, packed[nt][dt][ig]);
+        for (int ig = 0; ig < 2; ig++) store16(row + 64 * dt + 32 * ig, packed[nt][dt][ig]);
     }
   };
 
   // ---- the global query's share of a key tile (see the head of the file).  State in LDS per
   // wave: o[64] in channel order, then the running maximum (log2 domain) and the sum.
   float *const cls_state = reinterpret_cast<float *>(smem + kClsState + wave * 512);
-  float *const cls_logit = reinterpret_cast<float *>(smem + kClsLogit + wave * 256);
+  float *const cls_weight = reinterpret_cast<float *>(smem + kClsWeight + wave * 256);
   float *const logit_row = p.cls_logits ? p.cls_logits + ((size_t)b * p.heads + h) * p.tokens : nullptr;
   auto cls_duty = [&](uint32_t slot, int col, bool with_global_key) {
     const int wvc = EDGE && col == ncols - 1 ? wv_last : 8;    // the tile is block (R, col): hvq rows, wvc columns
-    // q_0 as B operand, the same in all 32 columns: channels 32*hh + 8*s + j
-    bf16x8 q0f[4], kA[4], kB[4];
-#pragma unroll
-    for (int t = 0; t < 4; t++) {
-      q0f[t] = *(lds_bf16x8_ptr)(smem + kQ0Row + 64 * hh + 16 * t);
-      kA[t] = *(lds_bf16x8_ptr)(smem + slot + krd[t]);
-      kB[t] = *(lds_bf16x8_ptr)(smem + slot + 4096 + krd[t]);
-    }
-    f32x16 sa = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f}, sb = sa;
-#pragma unroll
-    for (int ks = 0; ks < 4; ks++) {
-      sa = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kA[ks], q0f[ks], sa, 0, 0, 0);
-      sb = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kB[ks], q0f[ks], sb, 0, 0, 0);
-    }
-    if (EDGE && (hvq < 8 || wvc < 8)) {
-      mask_keys(sa, 0, hvq, wvc);
-      mask_keys(sb, 1, hvq, wvc);
-    }
-    // register e of sa is key 8*(e/4) + 4*hh + e%4 of the tile (sb: + 32), whatever the column
+    // On the vector ALU, lane = key (grid row 8R + lane/8, grid column 8*col + lane%8) for the logits, then (half of the
+    // keys, two channels) for the weighted sum: one row would be one of 32 columns of a matrix instruction, and its 64
+    // exponentials 32 instructions instead of one.
+    // (addresses computed here, from an untraceable copy of the lane number: hoisted out of the key-tile loop they cost
+    // registers that the compute branch does not have, and their reload from scratch memory waits for every transfer in
+    // flight)
+    const int ln = opaque(lane);
+    const unsigned char *krow = smem + slot + ln * 128, *vrow = smem + slot + kVOff + (ln >> 5) * 4096;
+    auto dot = [&](const unsigned char *row, int swizzle) {
+      float d0 = 0.f, d1 = 0.f;
+#pragma unroll 2
+      for (int ch = 0; ch < 8; ch++) {
+        const uint4 kk = *reinterpret_cast<const uint4 *>(row + 16 * (ch ^ swizzle));
+        const uint4 qq = *reinterpret_cast<const uint4 *>(smem + kQ0Row + 16 * ch);
+        d0 = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, kk.x), __builtin_bit_cast(bf16x2, qq.x), d0, false);
+        d1 = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, kk.y), __builtin_bit_cast(bf16x2, qq.y), d1, false);
+        d0 = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, kk.z), __builtin_bit_cast(bf16x2, qq.z), d0, false);
+        d1 = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, kk.w), __builtin_bit_cast(bf16x2, qq.w), d1, false);
+      }
+      return d0 + d1;
+    };
+    const int kr = ln >> 3, kc = ln & 7;
+    const bool in = !EDGE || (kr < hvq && kc < wvc);
+    const float x = dot(krow, (ln >> 1) & 7);
+    // key 0 (the global token itself) belongs to the first tile of the image
+    const float own = with_global_key ? dot(smem + kK0Row, 0) : kEmptyMax;
     if (logit_row) {
-      if (l32 == 0) {
-#pragma unroll
-        for (int g = 0; g < 4; g++) {
-          const f32x4 va = {sa[4 * g] * p.scale, sa[4 * g + 1] * p.scale, sa[4 * g + 2] * p.scale, sa[4 * g + 3] * p.scale};
-          const f32x4 vb2 = {sb[4 * g] * p.scale, sb[4 * g + 1] * p.scale, sb[4 * g + 2] * p.scale, sb[4 * g + 3] * p.scale};
-          *reinterpret_cast<f32x4 *>(cls_logit + 8 * g + 4 * hh) = va;
-          *reinterpret_cast<f32x4 *>(cls_logit + 32 + 8 * g + 4 * hh) = vb2;
-        }
-      }
-      // lane = key of the tile: token (grid row 8R + lane/8, grid column 8*col + lane%8); the lane of
-      // a key that does not exist repeats the store of the key it copies
-      // (addresses computed here, from an untraceable copy of the lane number: hoisted out of the
-      // key-tile loop they cost three registers that the compute branch does not have, and their
-      // reload from scratch memory waits for every transfer in flight)
-      const int ln = opaque(lane);
-      const int kr = min(ln >> 3, hvq - 1), kc = min(ln & 7, wvc - 1);
-      const float x = cls_logit[8 * kr + kc];
-      store4(logit_row + block_token(R, col) + kr * p.grid_w + kc, x);
+      // (the lane of a key that does not exist is that of a copy: it repeats its original's store)
+      store4(logit_row + block_token(R, col) + (EDGE ? min(kr, hvq - 1) * p.grid_w + min(kc, wvc - 1) : kr * p.grid_w + kc), x * p.scale);
+      if (with_global_key && lane == 0) store4(logit_row, own * p.scale);
     }
-    float mx = fmaxf(sa[0], sb[0]);
-#pragma unroll
-    for (int e = 1; e < 16; e++) mx = fmaxf(mx, fmaxf(sa[e], sb[e]));
-    mx = half_swap_max(mx) * p.c;
-    float m2 = cls_state[64], l0 = cls_state[65];
-    float k0logit = 0.f;
-    if (with_global_key) {
-      // key 0 (the global token itself) belongs to the first tile of the image
-      bf16x8 k0[4];
-#pragma unroll
-      for (int t = 0; t < 4; t++) k0[t] = *(lds_bf16x8_ptr)(smem + kK0Row + 64 * hh + 16 * t);
-      f32x16 s0 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int ks = 0; ks < 4; ks++) s0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k0[ks], q0f[ks], s0, 0, 0, 0);
-      k0logit = s0[0];
-      mx = fmaxf(mx, k0logit * p.c);
-      if (logit_row && lane == 0) store4(logit_row, k0logit * p.scale);
-    }
-    const float m_new = fmaxf(m2, mx);
+    const float m2 = cls_state[64], l0 = cls_state[65];
+    const float m_new = fmaxf(m2, wave_max(fmaxf(in ? x : kEmptyMax, own)) * p.c);
     const float alpha = __builtin_amdgcn_exp2f(m2 - m_new), nmm = -m_new;
-    float ls = 0.f;
-    bf16x8 pa[2], pb[2];
+    const float wt = in ? __builtin_amdgcn_exp2f(__builtin_fmaf(x, p.c, nmm)) : 0.f;
+    const float wown = with_global_key ? __builtin_amdgcn_exp2f(__builtin_fmaf(own, p.c, nmm)) : 0.f;
+    cls_weight[ln] = wt;
+    const float sum = wave_sum(wt) + wown;
+    const f32x2 old = *reinterpret_cast<const f32x2 *>(cls_state + 2 * (ln & 31));
+    float a0 = hh == 0 ? old[0] * alpha : 0.f, a1 = hh == 0 ? old[1] * alpha : 0.f;
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+#pragma unroll 2
+    for (int i = 0; i < 32; i += 4) {
+      const f32x4 w4 = *reinterpret_cast<const f32x4 *>(cls_weight + 32 * (ln >> 5) + i);
 #pragma unroll
-    for (int e = 0; e < 16; e += 2) {
-      const float a0 = __builtin_amdgcn_exp2f(__builtin_fmaf(sa[e], p.c, nmm));
-      const float a1 = __builtin_amdgcn_exp2f(__builtin_fmaf(sa[e + 1], p.c, nmm));
-      const float b0 = __builtin_amdgcn_exp2f(__builtin_fmaf(sb[e], p.c, nmm));
-      const float b1 = __builtin_amdgcn_exp2f(__builtin_fmaf(sb[e + 1], p.c, nmm));
-      ls += (a0 + a1) + (b0 + b1);
-      const bf16x2 ka = __builtin_bit_cast(bf16x2, pack_bf16(a0, a1));
-      const bf16x2 kb2 = __builtin_bit_cast(bf16x2, pack_bf16(b0, b1));
-      pa[e >> 3][e & 7] = ka[0]; pa[e >> 3][(e & 7) + 1] = ka[1];
-      pb[e >> 3][e & 7] = kb2[0]; pb[e >> 3][(e & 7) + 1] = kb2[1];
-    }
-    ls = half_swap_sum(ls);                       // the two half-waves hold different keys
-    // O (one column's worth, the same in every column): channel 32*dt + 8*(e/4) + 4*hh + e%4
-    f32x16 oc[2];
-#pragma unroll
-    for (int dt = 0; dt < 2; dt++)
-#pragma unroll
-      for (int g = 0; g < 4; g++) {
-        const f32x4 v = *reinterpret_cast<const f32x4 *>(cls_state + 32 * dt + 8 * g + 4 * hh);
-#pragma unroll
-        for (int e = 0; e < 4; e++) oc[dt][4 * g + e] = v[e] * alpha;
+      for (int e = 0; e < 4; e++) {
+        const uint32_t v2 = *reinterpret_cast<const uint32_t *>(vrow + (i + e) * 128 + ((4 * (ln & 31)) ^ ((((i + e) >> 1) & 1) << 6)));
+        a0 = __builtin_fmaf(w4[e], bf16_lo(v2), a0);
+        a1 = __builtin_fmaf(w4[e], bf16_hi(v2), a1);
       }
-    float pk0 = 0.f;
-    if (with_global_key) {
-      pk0 = __builtin_amdgcn_exp2f(__builtin_fmaf(k0logit, p.c, nmm));
-      ls += pk0;
-#pragma unroll
-      for (int dt = 0; dt < 2; dt++)
-#pragma unroll
-        for (int g = 0; g < 4; g++) {
-          const u32x2 v2 = *(u32x2 __attribute__((address_space(3))) *)(smem + kV0Row + 64 * dt + 16 * g + 8 * hh);
-          const bf16x4 v4 = __builtin_bit_cast(bf16x4, v2);
-#pragma unroll
-          for (int e = 0; e < 4; e++) oc[dt][4 * g + e] = __builtin_fmaf(pk0, (float)v4[e], oc[dt][4 * g + e]);
-        }
     }
-#pragma unroll
-    for (int mt = 0; mt < 2; mt++)
-#pragma unroll
-      for (int sp = 0; sp < 2; sp++)
-#pragma unroll
-        for (int dt = 0; dt < 2; dt++) {
-          const uint32_t off = slot + (2 * mt + sp) * 2048;
-          const s16x4 lo4 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(smem + vrd[dt][0] + off));
-          const s16x4 hi4 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(smem + vrd[dt][1] + off));
-          const bf16x4 a = __builtin_bit_cast(bf16x4, lo4), b2 = __builtin_bit_cast(bf16x4, hi4);
-          const bf16x8 vf = {a[0], a[1], a[2], a[3], b2[0], b2[1], b2[2], b2[3]};
-          oc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, mt == 0 ? pa[sp] : pb[sp], oc[dt], 0, 0, 0);
-        }
-    if (l32 == 0) {
-#pragma unroll
-      for (int dt = 0; dt < 2; dt++)
-#pragma unroll
-        for (int g = 0; g < 4; g++) {
-          const f32x4 v = {oc[dt][4 * g], oc[dt][4 * g + 1], oc[dt][4 * g + 2], oc[dt][4 * g + 3]};
-          *reinterpret_cast<f32x4 *>(cls_state + 32 * dt + 8 * g + 4 * hh) = v;
-        }
-      if (hh == 0) {
-        cls_state[64] = m_new;
-        cls_state[65] = __builtin_fmaf(l0, alpha, ls);
-      }
+    if (with_global_key && hh == 0) {
+      const uint32_t v2 = *reinterpret_cast<const uint32_t *>(smem + kV0Row + 4 * (ln & 31));
+      a0 = __builtin_fmaf(wown, bf16_lo(v2), a0);
+      a1 = __builtin_fmaf(wown, bf16_hi(v2), a1);
+    }
+    a0 = half_swap_sum(a0);
+    a1 = half_swap_sum(a1);
+    if (hh == 0) *reinterpret_cast<f32x2 *>(cls_state + 2 * (ln & 31)) = f32x2{a0, a1};
+    if (lane == 0) {
+      cls_state[64] = m_new;
+      cls_state[65] = __builtin_fmaf(l0, alpha, sum);
     }
   };
 
@@ -515,37 +384,35 @@ __global__ __launch_bounds__(256, 2) void attn_sweep_kernel(SweepParams p) {
     int extra = 0;                   // stores issued in this step
     if (qc < ncols && c + 1 >= qc && c <= qc + 1) {
       // ---- key tile s against this wave's query block
-      bf16x8 kA[4], kB[4], p0[2], p1[2], p2[2], p3[2];
-#pragma unroll
-      for (int t = 0; t < 4; t++) {
-        kA[t] = *(lds_bf16x8_ptr)(smem + slot + krd[t]);
-        kB[t] = *(lds_bf16x8_ptr)(smem + slot + 4096 + krd[t]);
-      }
       // (a short key block: its missing keys get the logit kMasked)
       const int hvk = EDGE && r0 + ri == p.nbh - 1 ? hv_last : 8, wvk = EDGE && c == ncols - 1 ? wv_last : 8;
       const bool edge = EDGE && (hvk < 8 || wvk < 8);
       const int dr = r0 + ri - R, dc = c - qc;
       const int wvq = EDGE && qc == ncols - 1 ? wv_last : 8;
-      f32x16 s00 = stage_a(kA, 0);
-      if (edge) mask_keys(s00, 0, hvk, wvk);
-      if (W < 8) mask_window(s00, 0, 0, dr, dc, wvq);
-      f32x16 s01 = stage_a(kA, 1);
-      if (edge) mask_keys(s01, 0, hvk, wvk);
-      if (W < 8) mask_window(s01, 0, 1, dr, dc, wvq);
-      stage_b(s00, 0, p0);
-      f32x16 s10 = stage_a(kB, 0);
-      if (edge) mask_keys(s10, 1, hvk, wvk);
-      if (W < 8) mask_window(s10, 1, 0, dr, dc, wvq);
-      stage_b(s01, 1, p1);
-      stage_c(0, 0, p0, slot);
-      f32x16 s11 = stage_a(kB, 1);
-      if (edge) mask_keys(s11, 1, hvk, wvk);
-      if (W < 8) mask_window(s11, 1, 1, dr, dc, wvq);
-      stage_b(s10, 0, p2);
-      stage_c(0, 1, p1, slot);
-      stage_b(s11, 1, p3);
-      stage_c(1, 0, p2, slot);
-      stage_c(1, 1, p3, slot);
+      auto mask = [&](f32x16 &sv, int mt, int nt) {
+        if (edge) mask_keys(sv, mt, hvk, wvk);
+        if (W < 8) mask_window(sv, mt, nt, dr, dc, wvq);
+      };
+      const unsigned char *ks = smem + slot, *vs = ks + kVOff;
+      StepBf16::K kf;
+      StepBf16::V vf;
+      bf16x8 open;
+      st.load_k(kf, ks);
+      f32x16 s0 = st.product(kf, qf[0]), s1;
+      mask(s0, 0, 0);
+      st.load_v(vf, vs, 0);
+      st.template half_step<true, true, false>(s0, p.c, -m[0], ls[0], o[0], ls[1], o[1], open, vf, vs, kf, qf[1], s1);
+      mask(s1, 0, 1);
+      st.load_k(kf, ks + 4096);
+      st.template half_step<false>(s1, p.c, -m[1], ls[1], o[1], ls[0], o[0], open, vf, vs, kf, qf[0], s0);
+      mask(s0, 1, 0);
+      st.load_v(vf, vs + 4096, 0);
+      st.template half_step<true>(s0, p.c, -m[0], ls[0], o[0], ls[1], o[1], open, vf, vs + 4096, kf, qf[1], s1);
+      mask(s1, 1, 1);
+      st.template half_step<false, false>(s1, p.c, -m[1], ls[1], o[1], ls[0], o[0], open, vf, vs + 4096, kf, qf[0], s0);
+#pragma unroll
+      for (int dt = 0; dt < 2; dt++) o[1][dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf.f[1][dt], open, o[1][dt], 0, 0, 0);
+      st.add_weights(ls[1], open);
       extra = 0;
     } else if (qc < ncols && c > qc + 1) {
       // ---- the column off: finish the block, start this wave's next one.  Order: request the
@@ -615,12 +482,12 @@ __global__ __launch_bounds__(256, 2) void attn_sweep_kernel(SweepParams p) {
       for (int rr = r0; rr <= r1; rr++) {
         const uint32_t base = block_base(rr, cc);
         const int hvk = EDGE && rr == p.nbh - 1 ? hv_last : 8, wvk = EDGE && cc == ncols - 1 ? wv_last : 8;
-        bf16x8 kt[2][4];
+        StepBf16::K kt[2];
 #pragma unroll
         for (int mt = 0; mt < 2; mt++)
 #pragma unroll
           for (int t = 0; t < 4; t++)
-            kt[mt][t] = *reinterpret_cast<const bf16x8 *>(kb + base + tile_off(l32 + 32 * mt, hvk, wvk) + 64 * hh + 16 * t);
+            kt[mt].f[t] = *reinterpret_cast<const bf16x8 *>(kb + base + tile_off(l32 + 32 * mt, hvk, wvk) + 64 * hh + 16 * t);
         const uint32_t back = (uint32_t)max(drow - (wvk - 1), 0) * rowB;
 #pragma unroll
         for (int it = 0; it < 8; it++)
@@ -628,45 +495,42 @@ __global__ __launch_bounds__(256, 2) void attn_sweep_kernel(SweepParams p) {
         wait_vm<0>();               // also the K fragments above
 #pragma unroll
         for (int nt = 0; nt < 2; nt++) {
-          f32x16 s0 = stage_a(kt[0], nt), s1 = stage_a(kt[1], nt);
-          if (EDGE && (hvk < 8 || wvk < 8)) {
-            mask_keys(s0, 0, hvk, wvk);
-            mask_keys(s1, 1, hvk, wvk);
-          }
-          if (W < 8) {
-            const int wvq = EDGE && qr == ncols - 1 ? wv_last : 8;
-            mask_window(s0, 0, nt, rr - R, cc - qr, wvq);
-            mask_window(s1, 1, nt, rr - R, cc - qr, wvq);
-          }
-          float mx0 = fmaxf(s0[0], s0[1]), mx1 = fmaxf(s1[0], s1[1]);
+          f32x16 sv[2] = {st.product(kt[0], qf[nt]), st.product(kt[1], qf[nt])};
+          const int wvq = EDGE && qr == ncols - 1 ? wv_last : 8;
 #pragma unroll
-          for (int e = 2; e < 16; e += 2) {
-            mx0 = fmaxf(fmaxf(mx0, s0[e]), s0[e + 1]);
-            mx1 = fmaxf(fmaxf(mx1, s1[e]), s1[e + 1]);
+          for (int mt = 0; mt < 2; mt++) {
+            if (EDGE && (hvk < 8 || wvk < 8)) mask_keys(sv[mt], mt, hvk, wvk);
+            if (W < 8) mask_window(sv[mt], mt, nt, rr - R, cc - qr, wvq);
           }
-          const float m_new = fmaxf(m[nt], half_swap_max(fmaxf(mx0, mx1)) * p.c);
+          float mx = fmaxf(sv[0][0], sv[1][0]);
+#pragma unroll
+          for (int e = 1; e < 16; e++) mx = fmaxf(fmaxf(mx, sv[0][e]), sv[1][e]);
+          const float m_new = fmaxf(m[nt], half_swap_max(mx) * p.c);
           const float alpha = __builtin_amdgcn_exp2f(m[nt] - m_new);
           m[nt] = m_new;
-          const float nmm = -m_new;
-          float ls = 0.f;
-          bf16x8 pa[2], pb[2];
+          l[nt] *= alpha;
 #pragma unroll
-          for (int e = 0; e < 16; e += 2) {
-            const float a0 = __builtin_amdgcn_exp2f(__builtin_fmaf(s0[e], p.c, nmm));
-            const float a1 = __builtin_amdgcn_exp2f(__builtin_fmaf(s0[e + 1], p.c, nmm));
-            const float b0 = __builtin_amdgcn_exp2f(__builtin_fmaf(s1[e], p.c, nmm));
-            const float b1 = __builtin_amdgcn_exp2f(__builtin_fmaf(s1[e + 1], p.c, nmm));
-            ls += (a0 + a1) + (b0 + b1);
-            const bf16x2 ka = __builtin_bit_cast(bf16x2, pack_bf16(a0, a1));
-            const bf16x2 kb2 = __builtin_bit_cast(bf16x2, pack_bf16(b0, b1));
-            pa[e >> 3][e & 7] = ka[0]; pa[e >> 3][(e & 7) + 1] = ka[1];
-            pb[e >> 3][e & 7] = kb2[0]; pb[e >> 3][(e & 7) + 1] = kb2[1];
+          for (int e = 0; e < 16; e++) { o[nt][0][e] *= alpha; o[nt][1][e] *= alpha; }
+#pragma unroll
+          for (int mt = 0; mt < 2; mt++) {
+            bf16x8 w[2];
+#pragma unroll
+            for (int e = 0; e < 16; e += 2) {
+              const uint32_t u = pack_bf16(__builtin_amdgcn_exp2f(__builtin_fmaf(sv[mt][e], p.c, -m_new)),
+                                           __builtin_amdgcn_exp2f(__builtin_fmaf(sv[mt][e + 1], p.c, -m_new)));
+              l[nt] += bf16_lo(u) + bf16_hi(u);
+              const bf16x2 pk = __builtin_bit_cast(bf16x2, u);
+              w[e >> 3][e & 7] = pk[0];
+              w[e >> 3][(e & 7) + 1] = pk[1];
+            }
+#pragma unroll
+            for (int sp = 0; sp < 2; sp++) {
+              StepBf16::V v;
+              st.load_v(v, smem + mine + kVOff + 4096 * mt, sp);
+#pragma unroll
+              for (int dt = 0; dt < 2; dt++) o[nt][dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v.f[sp][dt], w[sp], o[nt][dt], 0, 0, 0);
+            }
           }
-          l[nt] = __builtin_fmaf(l[nt], alpha, ls);
-#pragma unroll
-          for (int e = 0; e < 16; e++) { o[0][nt][e] *= alpha; o[1][nt][e] *= alpha; }
-          stage_c(0, nt, pa, mine);
-          stage_c(1, nt, pb, mine);
         }
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // V reads done before the next transfer into the slot
       }

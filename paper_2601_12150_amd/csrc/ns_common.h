@@ -106,6 +106,7 @@ inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
 // ---- device helpers shared by the MFMA kernels ------------------------------
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 // A value the compiler can no longer trace back: what is computed from it stays where it is written
 // instead of being hoisted out of a loop into registers that live for the whole kernel.
@@ -130,6 +131,36 @@ __device__ __forceinline__ float half_swap_sum(float x) {
   auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
   return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
+// ... over the rows of 16 lanes (lane l and lane l ^ 16)
+__device__ __forceinline__ float row_swap_max(float x) {
+  auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+__device__ __forceinline__ float row_swap_sum(float x) {
+  auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+// x of another lane of the same 16 (DPP control CTRL)
+template <int CTRL>
+__device__ __forceinline__ float dpp(float x) {
+  return __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(x), CTRL, 0xf, 0xf, true));
+}
+constexpr int kDppXor1 = 0xB1, kDppXor2 = 0x4E, kDppMirror8 = 0x141, kDppMirror16 = 0x140;
+// max / sum over the wave, in every lane
+__device__ __forceinline__ float wave_max(float x) {
+  x = fmaxf(x, dpp<kDppXor1>(x));
+  x = fmaxf(x, dpp<kDppXor2>(x));
+  x = fmaxf(x, dpp<kDppMirror8>(x));
+  x = fmaxf(x, dpp<kDppMirror16>(x));
+  return half_swap_max(row_swap_max(x));
+}
+__device__ __forceinline__ float wave_sum(float x) {
+  x += dpp<kDppXor1>(x);
+  x += dpp<kDppXor2>(x);
+  x += dpp<kDppMirror8>(x);
+  x += dpp<kDppMirror16>(x);
+  return half_swap_sum(row_swap_sum(x));
+}
 // 16 bytes per lane, global -> LDS, no registers: LDS address = lds + 16 * lane.  Issued as asm
 // so that the compiler does not guard later LDS reads with a full vmcnt(0) wait (it cannot tell
 // one tile's transfer from the next tile's, which is still in flight); the kernels order and
@@ -138,12 +169,14 @@ __device__ __forceinline__ void dma16(const char *base, uint32_t voff, uint32_t 
   asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2"
                :: "s"(lds), "v"(voff), "s"(base) : "memory", "m0");
 }
-// 4 / 8 bytes per lane to global memory, issued from asm so that each is exactly one request
+// 4 / 16 bytes per lane to global memory, issued from asm so that each is exactly one request
 __device__ __forceinline__ void store4(void *ptr, float v) {
   asm volatile("global_store_dword %0, %1, off" :: "v"(ptr), "v"(v) : "memory");
 }
-__device__ __forceinline__ void store8(void *ptr, u32x2 v) {
-  asm volatile("global_store_dwordx2 %0, %1, off" :: "v"(ptr), "v"(v) : "memory");
+// (a store of more than 8 bytes reads its data after it has been issued: two wait states before a vector instruction
+// may write these registers, which the compiler cannot know of)
+__device__ __forceinline__ void store16(void *ptr, u32x4 v) {
+  asm volatile("global_store_dwordx4 %0, %1, off\n\ts_nop 2" :: "v"(ptr), "v"(v) : "memory");
 }
 // at most N vector memory requests of this wave still in flight (they complete in issue order)
 template <int N>

@@ -171,14 +171,12 @@ struct StepBf16 {
   // Selects, as the left operand of v_mfma_f32_16x16x32_bf16, the lanes whose bit 4 is the row's bit 0.  The weights of
   // a fragment (lane: query l32, eight keys) as right operand then give query lane % 16's sum in the even registers of the
   // result and query 16 + lane % 16's in the odd ones: both halves' keys, no vector instruction.
-  bf16x8 sel;
+  uint32_t sel;               // (two equal values; the operand is four of these)
 
   __device__ __forceinline__ void init(int lane) {
     const int l32 = lane & 31, hh = lane >> 5;
     exact = 0;
-    const __bf16 one = (__bf16)(((lane ^ (lane >> 4)) & 1) ? 0.f : 1.f);
-#pragma unroll
-    for (int i = 0; i < 8; i++) sel[i] = one;
+    sel = ((lane ^ (lane >> 4)) & 1) ? 0u : 0x3f803f80u;
     rrow = lane >> 3;
     // LDS chunk c of row r holds chunk c ^ ((r>>1)&7) of K and c ^ 4*((r>>1)&1) of V: conflict-free reads
     kch[0] = 16u * ((lane & 7) ^ (lane >> 4));
@@ -248,16 +246,17 @@ struct StepBf16 {
   // group apart, so that no result is waited for.  The fences keep this order: left to itself the
   // scheduler groups the exponentials and then the matrix instructions.  (Sums by matrix instruction and the weights kept
   // in this order: 100 x 100 patches, 8 x 8 blocks, five global tokens, 104.3 -> 101.3 us a call.)
-  // LOADV: load the second half of V once the open product has taken the old one.
-  template <bool LOADV>
-  __device__ __forceinline__ void half_step(f32x16 &cur, float c, float nm, f32x4 &l, f32x16 (&o)[2], f32x4 &l_open,
+  // LOADV: load the second half of V once the open product has taken the old one.  NEXT: there are other logits to form.
+  // OPEN: there is an open product.
+  template <bool LOADV, bool NEXT = true, bool OPEN = true, class L>
+  __device__ __forceinline__ void half_step(f32x16 &cur, float c, float nm, L &l, f32x16 (&o)[2], L &l_open,
                                             f32x16 (&o_open)[2], bf16x8 &open, V &v, const unsigned char *vslot, const K &k,
                                             const Q &q, f32x16 &nxt) const {
     // The sums are those of the rounded weights that the product takes, which adds them itself (add_weights): what
     // rounding does to a key that outweighs the others cancels.  Relative error of rows with logits of +-8, against sums
     // of the weights before rounding: 0.0021 -> 0.0017 (rounding the true result alone: 0.0016); of +-1: 0.00220 -> 0.00218.
     bf16x8 first, second;
-    nxt = f32x16{0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    if (NEXT) nxt = f32x16{0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int e = 0; e < 4; e++) cur[e] = __builtin_fmaf(cur[e], c, nm);
     cur[0] = __builtin_amdgcn_exp2f(cur[0]);
@@ -278,23 +277,44 @@ struct StepBf16 {
       // the matrix instructions' shadow)
       asm volatile("" : "+v"(packed));
       const bf16x2 pk = __builtin_bit_cast(bf16x2, packed);
+      add_pair(l, pk, j);
       if (j < 4) { first[2 * j] = pk[0]; first[2 * j + 1] = pk[1]; }
       else { second[2 * j - 8] = pk[0]; second[2 * j - 7] = pk[1]; }
-      if (j < 2) o_open[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v.f[1][j], open, o_open[j], 0, 0, 0);
-      else if (j < 6) nxt = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k.f[j - 2], q.f[j - 2], nxt, 0, 0, 0);
+      if (j < 2) { if (OPEN) o_open[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v.f[1][j], open, o_open[j], 0, 0, 0); }
+      else if (j < 6) { if (NEXT) nxt = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k.f[j - 2], q.f[j - 2], nxt, 0, 0, 0); }
       else o[j - 6] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v.f[0][j - 6], first, o[j - 6], 0, 0, 0);
-      if (j == 1) add_weights(l_open, open);
+      if (OPEN && j == 1) add_weights(l_open, open);
       if (j == 7) add_weights(l, first);
       __builtin_amdgcn_sched_barrier(0);
       if (LOADV && j == 1) load_v(v, vslot, 1);
     }
     open = second;
   }
-  // a row's sum += a fragment's weights; what the sum is for this lane's query (of both half-waves' keys)
-  __device__ __forceinline__ void add_weights(f32x4 &l, const bf16x8 &w) const {
-    l = __builtin_amdgcn_mfma_f32_16x16x32_bf16(sel, w, l, 0, 0, 0);
+  // A row's sum += a fragment's weights; what the sum is for this lane's query (of both half-waves' keys).  Sums: four
+  // registers that the product adds to, LeanSums: the two of them that count, for a kernel that is short of registers.
+  // LaneSums: each lane its own, for a kernel that computes a query in several lanes and needs the same bits in all.
+  typedef f32x4 Sums;
+  typedef f32x2 LeanSums;
+  struct LaneSums { float l[2]; };
+  __device__ __forceinline__ void add_weights(Sums &l, const bf16x8 &w) const {
+    l = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, u32x4{sel, sel, sel, sel}), w, l, 0, 0, 0);
   }
-  static __device__ __forceinline__ float row_sum(const f32x4 &l, int lane) { return lane & 16 ? l[1] : l[0]; }
+  __device__ __forceinline__ void add_weights(LeanSums &l, const bf16x8 &w) const {
+    uint32_t x = sel;
+    asm volatile("" : "+v"(x));               // (put together here: not four registers that live through the loop)
+    const f32x4 s = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, u32x4{x, x, x, x}), w, f32x4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+    l[0] += s[0];
+    l[1] += s[1];
+  }
+  __device__ __forceinline__ void add_weights(LaneSums &, const bf16x8 &) const {}
+  __device__ __forceinline__ void add_pair(LaneSums &l, const bf16x2 &w, int j) const {
+    l.l[j & 1] = __builtin_amdgcn_fdot2_f32_bf16(w, bf16x2{(__bf16)1.f, (__bf16)1.f}, l.l[j & 1], false);
+  }
+  template <class L> __device__ __forceinline__ void add_pair(L &, const bf16x2 &, int) const {}
+  // what half-wave hh adds to its query's sum
+  static __device__ __forceinline__ float row_sum(const LaneSums &l, int) { return l.l[0] + l.l[1]; }
+  template <class L>
+  static __device__ __forceinline__ float row_sum(const L &l, int lane) { return lane >= 32 ? 0.f : (lane & 16 ? l[1] : l[0]); }
   // O^T += V^T w.  LO: columns 16..31 are the first 16 once more and take what bf16 rounding leaves of a weight,
   // w - bf16(w); what that leaves in turn comes in a second product, so that all 24 bits of a weight enter.
   template <int NT, bool LO>
@@ -596,7 +616,7 @@ __device__ __forceinline__ void walk_keys_pipelined(const S &st, WaveAcc<S, 2> &
   }
   // a higher reference for half nt, whose output product is not the open one
   auto take_sums = [&](int nt, f32x4 &l) {
-    a.l[nt] += lane < 32 ? S::row_sum(l, lane) : 0.f;
+    a.l[nt] += S::row_sum(l, lane);
     l = f32x4{0.f, 0.f, 0.f, 0.f};
   };
   auto raise = [&](int nt, const f32x16 &s) {
@@ -835,6 +855,16 @@ __device__ __forceinline__ void window_walk(const S &st, WaveAcc<S, NT> &a, Args
   else walk_keys<S, NT, true, RING, false, 0>(st, a, args...);
 }
 
+// 16 channels of a row, o[at .. at+7] of the two half-waves' lanes, times inv, as bf16: the lane of half hh has channels
+// 4*hh + 0..3 and 8 + 4*hh + 0..3 and gets, to store 16 bytes at once, channels 8*hh + 0..7.
+__device__ __forceinline__ u32x4 row_pieces(const f32x16 &o, int at, float inv) {
+  uint32_t u[4];
+#pragma unroll
+  for (int i = 0; i < 4; i++) u[i] = pack_bf16(o[at + 2 * i] * inv, o[at + 2 * i + 1] * inv);
+  const auto x = __builtin_amdgcn_permlane32_swap(u[0], u[2], false, false), y = __builtin_amdgcn_permlane32_swap(u[1], u[3], false, false);
+  return u32x4{x[0], y[0], x[1], y[1]};
+}
+
 // A wave's state -> LDS: output rows of 64 floats in its rings (16-byte chunk c of row r at c ^ (r & 15)),
 // (max, sum) in ml.
 template <class S, int NT>
@@ -979,7 +1009,6 @@ __device__ __forceinline__ void global_rows_chunk(const GlobalRows &p, int heads
   }
 }
 
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ void unpack8(const u32x4 &u, float (&x)[8]) {
   x[0] = bf16_lo(u[0]); x[1] = bf16_hi(u[0]); x[2] = bf16_lo(u[1]); x[3] = bf16_hi(u[1]);
   x[4] = bf16_lo(u[2]); x[5] = bf16_hi(u[2]); x[6] = bf16_lo(u[3]); x[7] = bf16_hi(u[3]);
