@@ -4,13 +4,14 @@
 // Exact k-th largest score on an order-preserving integer image of the floats, then an
 // in-index-order compaction, so the kept indices come out ascending and exact ties resolve to
 // the lower index.
-//   topk_select_reg_kernel: rows of up to 32768 scores, one workgroup of 16 waves per image, keys
-//     in registers, 8-bit digit passes (radix select) until at most 1024 candidates are left, which
-//     are ranked against each other: latency-bound, a score row is 64 - 128 KB.
+//   topk_select_reg_kernel: rows of up to 32768 scores, one launch.  Every workgroup selects from all keys of its
+//     image, held in registers, by 11-bit digits (radix select) until at most 256 candidates are left, which are ranked
+//     against each other, and places its share of the outputs: latency-bound, a score row is 64 - 128 KB.
 //   topk_digit_pass_kernel / topk_place_kernel: longer rows, several
 //     workgroups per image, four 8-bit digit passes (radix select), one launch each.
 // gather_rows_kernel: copies the kept token rows (and the global rows) with 16-byte accesses.
 #include "ns_common.h"
+#include <algorithm>
 
 namespace ns {
 
@@ -66,6 +67,16 @@ __device__ __forceinline__ uint32_t wave_suffix_incl(uint32_t x, int lane) {
   const int row = lane >> 4;
   return x + (row < 1 ? r1 : 0u) + (row < 2 ? r2 : 0u) + (row < 3 ? r3 : 0u);
 }
+// Smallest / largest of the 64 lanes, the same in every lane.
+__device__ __forceinline__ uint32_t wave_max(uint32_t x) {
+  x = max(x, (uint32_t)__builtin_amdgcn_update_dpp((int)x, (int)x, 0x111, 0xf, 0xf, false));
+  x = max(x, (uint32_t)__builtin_amdgcn_update_dpp((int)x, (int)x, 0x112, 0xf, 0xf, false));
+  x = max(x, (uint32_t)__builtin_amdgcn_update_dpp((int)x, (int)x, 0x114, 0xf, 0xf, false));
+  x = max(x, (uint32_t)__builtin_amdgcn_update_dpp((int)x, (int)x, 0x118, 0xf, 0xf, false));
+  return max(max((uint32_t)__builtin_amdgcn_readlane((int)x, 15), (uint32_t)__builtin_amdgcn_readlane((int)x, 31)),
+             max((uint32_t)__builtin_amdgcn_readlane((int)x, 47), (uint32_t)__builtin_amdgcn_readlane((int)x, 63)));
+}
+__device__ __forceinline__ uint32_t wave_min(uint32_t x) { return ~wave_max(~x); }
 // Sum of x over lanes 0..15 (one DPP row), the same in every lane.
 __device__ __forceinline__ uint32_t row0_total(uint32_t x) {
   x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xf, 0xf, true);
@@ -98,12 +109,20 @@ __device__ __forceinline__ void choose_digit(uint32_t tot, uint32_t need, int ti
   __syncthreads();
 }
 
-constexpr int kDirectMax = 1024;   // candidates that the direct ranking below takes: one per thread
+constexpr int kDirectMax = 256;    // candidates that are ranked against each other instead of by a further digit
+constexpr int kDigitBits = 11, kDigits = 1 << kDigitBits;
 
-// Rows of N <= 1024 * KPT scores, one workgroup per image, every key in a register: the selection
-// and the compaction read global memory exactly once.  Wave w owns the 64*KPT consecutive indices
-// from w*64*KPT; in its group i (256 indices) lane l holds the four indices 256*i + 4*l .. + 3.
-// So a wave loads 1 KB of consecutive scores per instruction, index order is (wave, group, lane,
+// Rows of N <= 1024 * KPT scores, several workgroups per image in one launch.  Every one of them selects for itself, all
+// keys of its image in registers (after the first reader they come from the L2), and places the outputs [k*c/chunks, k*(c+1)/chunks)
+// of its chunk c: ranges of outputs, not of inputs, because kept tokens cluster.  The selection is a chain of barriers and
+// one CU's instruction issue, which several CUs that do the same do not lengthen; the placement, which one CU took 2.4 us for at
+// 16384 scores, is shared.  Two images of 16384 scores, the copy of 60 % of 2 KB rows included: 29.8 -> 24.7 us a call (one
+// workgroup per image, digits of 8 bits -> this).  Copying the rows in this launch too was slower wherever the copy is
+// large (8 x 16384: 63 -> 70 us): 16 waves per CU keep fewer bytes on their way than the copy kernel's 32.  Scores that are NaN have no place in the order; any bit pattern but the padding's gets a
+// key, so that counts and indices stay in range whatever the scores hold.
+//
+// Wave w owns the 64*KPT consecutive indices from w*64*KPT; in its group i (256 indices) lane l holds the four indices
+// 256*i + 4*l .. + 3.  So a wave loads 1 KB of consecutive scores per instruction, index order is (wave, group, lane,
 // element), and the kept indices of a group go to consecutive output positions in lane order.
 template <int KPT>
 __global__ __launch_bounds__(kSelThreads) void topk_select_reg_kernel(const float *scores, int N, int k,
@@ -111,15 +130,16 @@ __global__ __launch_bounds__(kSelThreads) void topk_select_reg_kernel(const floa
                                                                       int32_t *kept,
                                                                       int32_t *coords_out) {
   static_assert(KPT % 4 == 0, "keys are held in groups of four");
-  const int b = blockIdx.x;
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  const int b = blockIdx.y, chunk = blockIdx.x, chunks = gridDim.x;
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const float *sc = scores + (size_t)b * N;
-  __shared__ __attribute__((aligned(16))) uint32_t hist[256 * 32];
-  __shared__ uint32_t wsum[4], sel[3], ncand;
+  __shared__ __attribute__((aligned(16))) uint32_t hist[kDigits * 4];
+  __shared__ __attribute__((aligned(16))) uint32_t cand[kDirectMax];
+  __shared__ uint32_t ranks[kDirectMax];
+  __shared__ uint32_t wsum[kSelWaves], sel[3], ncand, wlo[kSelWaves], whi[kSelWaves];
   __shared__ uint32_t wgt[kSelWaves], weq[kSelWaves];
 
-  // Padding slots hold key 0.  A real key is never 0 (that would be a NaN bit pattern), and
-  // tau, the k-th largest real key, is therefore > 0: padding never passes "> tau" or "== tau".
+  // Padding slots hold key 0, real ones at least 1.
   uint32_t key[KPT];
   const int j0 = wave * (64 * KPT) + 4 * lane;       // index of key[4*i + e]: j0 + 256*i + e
   const bool vec = (reinterpret_cast<uintptr_t>(sc) & 15) == 0;
@@ -127,135 +147,166 @@ __global__ __launch_bounds__(kSelThreads) void topk_select_reg_kernel(const floa
   for (int i = 0; i < KPT / 4; i++) {
     const int j = j0 + 256 * i;
     if (vec && j + 4 <= N) {
-      const f32x4 x = *reinterpret_cast<const f32x4 *>(sc + j);
+      const f32x4 v = *reinterpret_cast<const f32x4 *>(sc + j);
 #pragma unroll
-      for (int e = 0; e < 4; e++) key[4 * i + e] = order_key(x[e]);
+      for (int e = 0; e < 4; e++) key[4 * i + e] = max(order_key(v[e]), 1u);
     } else {
 #pragma unroll
-      for (int e = 0; e < 4; e++) key[4 * i + e] = j + e < N ? order_key(sc[j + e]) : 0u;
+      for (int e = 0; e < 4; e++) key[4 * i + e] = j + e < N ? max(order_key(sc[j + e]), 1u) : 0u;
     }
   }
+  // The range of the keys: scores are softmax weights of one row, a few octaves out of the 256 that a float's
+  // leading bits span, and digits counted from the smallest key tell them apart at once.
+  uint32_t lo = 0xffffffffu, hi = 0u;
+#pragma unroll
+  for (int i = 0; i < KPT; i++) {
+    lo = min(lo, key[i] - 1u);                       // (padding wraps around to the largest)
+    hi = max(hi, key[i]);
+  }
+  lo = wave_min(lo);
+  hi = wave_max(hi);
+  if (lane == 0) { wlo[wave] = lo; whi[wave] = hi; }
+  if (tid < 3) sel[tid] = 0;
   if (tid == 0) ncand = 0;
-  // k-th largest key by 8-bit digit passes, most significant digit first (radix select): a pass
-  // histograms the digit of the keys that match the prefix chosen so far, and the digit that holds
-  // the left-th largest candidate extends the prefix.  The histogram is kept in 32 copies, bin d of
-  // copy c at word 32*d + c, and lane l adds to copy l % 32: scores that cluster (most keys of a
-  // wave in one bin) then still spread over 32 LDS banks instead of serialising on one address, so
-  // a pass costs the same whatever the scores look like.  Once the candidates are few enough (after
-  // two digits, as a rule), they are ranked against each other directly instead.
-  // In the end `left` is the number of keys equal to tau that are kept.
-  uint32_t tau = 0, left = (uint32_t)k;
+  if (tid < kDirectMax) { cand[tid] = 0u; ranks[tid] = 0u; }       // (a key 0 is below every real key)
   uint4 *hist4 = reinterpret_cast<uint4 *>(hist);
-  for (int pass = 0; pass < 4; pass++) {
-    const uint32_t mask = pass ? 0xffffffffu << (32 - 8 * pass) : 0u;
-    if (pass > 0 && sel[2] <= (uint32_t)kDirectMax) {
-      // ---- the candidates (keys that match the prefix) into a list, in any order: one atomic
-      // per wave reserves the places of the wave's candidates
-      uint32_t *cand = hist;
-      __syncthreads();                       // everybody has read sel
-      cand[tid] = 0u;                        // (a key 0 is below every real key)
-      uint32_t m = 0;
+  hist4[tid] = make_uint4(0u, 0u, 0u, 0u);
+  hist4[tid + kSelThreads] = make_uint4(0u, 0u, 0u, 0u);
+  __syncthreads();
+  lo = wave_min(wlo[lane & (kSelWaves - 1)]) + 1u;
+  hi = wave_max(whi[lane & (kSelWaves - 1)]);
+
+  // k-th largest key by digits of key - lo, most significant first (radix select): a pass histograms the digit of
+  // the keys in [lo, lo + span], and the digit that holds the left-th largest of them becomes the next range.  The
+  // histogram is kept in four copies, digit d of copy c at word 4*d + c, and lane l adds to copy l % 4: the copies of a digit are
+  // one 16-byte read, and equal scores serialise over 16 lanes and not 64.  Once the candidates are few enough (after
+  // one pass, as a rule: a digit of 11 bits takes a smooth score row's 16384 keys apart to a few dozen), they are
+  // ranked against each other directly.  Digits of 8 bits leave 200 to 500 of them, whose ranking took 6 us of 11.
+  // (key - lo <= span holds for no key below lo: lo + span <= hi does not wrap around, the difference does.)
+  // In the end `left` is the number of keys equal to tau that are kept.
+  uint32_t span = hi - lo, left = (uint32_t)k;
+  int shift = max(32 - kDigitBits - __clz((int)span), 0);         // (span 0: clz 32)
+  uint32_t tau;
+  for (;;) {
 #pragma unroll
-      for (int i = 0; i < KPT; i++) m += key[i] != 0u && (key[i] & mask) == tau;
-      const uint32_t incl = wave_prefix_incl(m, lane);
-      const uint32_t wave_m = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+    for (int i = 0; i < KPT; i++) {
+      const uint32_t u = key[i] - lo;
+      if (u <= span) atomicAdd(&hist[((u >> shift) << 2) + (lane & 3)], 1u);
+    }
+    __syncthreads();
+    {
+      // thread t has digits 2t and 2t + 1; of a wave's keys above, its own lanes' and then the later waves'
+      const uint4 h0 = hist4[2 * tid], h1 = hist4[2 * tid + 1];
+      const uint32_t n0 = (h0.x + h0.y) + (h0.z + h0.w), n1 = (h1.x + h1.y) + (h1.z + h1.w);
+      const uint32_t incl = wave_suffix_incl(n0 + n1, lane);
+      if (lane == 0) wsum[wave] = incl;
       __syncthreads();
-      if (wave_m) {                          // (uniform in the wave)
-        uint32_t base = 0;
-        if (lane == 0) base = atomicAdd(&ncand, wave_m);
-        uint32_t at = (uint32_t)__builtin_amdgcn_readlane((int)base, 0) + incl - m;
-        if (m) {
+      const uint32_t later = row0_total(lane > wave ? wsum[lane & (kSelWaves - 1)] : 0u);
+      const uint32_t above1 = later + incl - (n0 + n1), above0 = above1 + n1;   // keys above digit 2t + 1, above digit 2t
+      if (above1 < left && left <= above1 + n1) { sel[0] = 2 * tid + 1; sel[1] = left - above1; sel[2] = n1; }
+      if (above0 < left && left <= above0 + n0) { sel[0] = 2 * tid; sel[1] = left - above0; sel[2] = n0; }
+      __syncthreads();
+    }
+    const uint32_t before = sel[0] << shift;
+    lo += before;
+    left = sel[1];
+    const uint32_t nc = sel[2];
+    tau = lo;
+    if (shift == 0) break;
+    span = min(span - before, (1u << shift) - 1u);
+    if (nc <= (uint32_t)kDirectMax) {
+      // ---- the candidates into a list, in any order
 #pragma unroll
-          for (int i = 0; i < KPT; i++)
-            if (key[i] != 0u && (key[i] & mask) == tau) cand[at++] = key[i];
-        }
+      for (int i = 0; i < KPT; i++)
+        if (key[i] - lo <= span) cand[min(atomicAdd(&ncand, 1u), (uint32_t)kDirectMax - 1u)] = key[i];
+      __syncthreads();
+      // 16, 8 or 4 threads count the candidates above one candidate (low half) and not below it (high half), each in its
+      // part of the list
+      const int bits = nc <= 64u ? 6 : nc <= 128u ? 7 : 8, slot = tid & ((1 << bits) - 1);
+      const uint4 *cand4 = reinterpret_cast<const uint4 *>(cand);
+      const uint32_t mine = cand[slot], n4 = (nc + 3u) >> 2, per = (n4 + (kSelThreads >> bits) - 1u) >> (10 - bits);
+      const uint32_t c0 = (uint32_t)(wave >> (bits - 6)) * per, c1 = min(c0 + per, n4);
+      uint32_t gt = 0, ge = 0;
+#pragma unroll 4
+      for (uint32_t c = c0; c < c1; c++) {
+        const uint4 o = cand4[c];
+        gt += (o.x > mine) + (o.y > mine) + (o.z > mine) + (o.w > mine);
+        ge += (o.x >= mine) + (o.y >= mine) + (o.z >= mine) + (o.w >= mine);
       }
+      if (ge) atomicAdd(&ranks[slot], gt | (ge << 16));
       __syncthreads();
-      // thread t ranks candidate t: tau is the candidate with fewer than `left` candidates above it
-      // and at least `left` candidates not below it (equal candidates all say the same)
-      // (waves without a candidate have nothing to do: the list is short)
-      const uint32_t nc = ncand;
-      if ((uint32_t)(tid & ~63) < nc) {
-        const uint32_t n4 = (nc + 3u) >> 2, mine = cand[tid];
-        uint32_t gt = 0, ge = 0;
-        for (uint32_t c = 0; c < n4; c++) {
-          const uint4 o = hist4[c];
-          gt += (o.x > mine) + (o.y > mine) + (o.z > mine) + (o.w > mine);
-          ge += (o.x >= mine) + (o.y >= mine) + (o.z >= mine) + (o.w >= mine);
-        }
-        if (mine != 0u && gt < left && left <= ge) {
-          sel[0] = mine;
-          sel[1] = left - gt;
-        }
+      // tau is the candidate with fewer than `left` above it and at least `left` not below it (equal ones all say the same)
+      if (tid < kDirectMax) {
+        const uint32_t c = cand[tid], n = ranks[tid];
+        if (c != 0u && (n & 0xffffu) < left && left <= (n >> 16)) { sel[0] = c; sel[1] = left - (n & 0xffffu); }
       }
       __syncthreads();
       tau = sel[0];
       left = sel[1];
       break;
     }
-    const int shift = 24 - 8 * pass;
-    __syncthreads();                         // (sel and the previous pass's histogram have been read)
+    shift = max(shift - kDigitBits, 0);
+    __syncthreads();                         // (sel and this pass's histogram have been read)
     hist4[tid] = make_uint4(0u, 0u, 0u, 0u);
     hist4[tid + kSelThreads] = make_uint4(0u, 0u, 0u, 0u);
     __syncthreads();
-#pragma unroll
-    for (int i = 0; i < KPT; i++)
-      if (key[i] != 0u && (key[i] & mask) == tau) atomicAdd(&hist[(((key[i] >> shift) & 255u) << 5) + (lane & 31)], 1u);
-    __syncthreads();
-    uint32_t tot = 0;
-    if (tid < 256) {
-      // (four copies per read, group (c + tid) % 8 in round c: two lanes per bank group in every
-      // quarter wave, which is what a 16-byte read costs anyway)
-#pragma unroll
-      for (int c = 0; c < 8; c++) {
-        const uint4 h4 = hist4[(tid << 3) + ((c + tid) & 7)];
-        tot += (h4.x + h4.y) + (h4.z + h4.w);
-      }
-    }
-    choose_digit(tot, left, tid, wave, lane, wsum, sel);
-    tau |= sel[0] << shift;
-    left = sel[1];
   }
+
   // every score above tau is kept; of those equal to it, the first `need` in index order
   const uint32_t need = left;
-  // keys above tau and equal to it in this wave: counted on the scalar unit from the compare masks
+  // keys above tau and equal to it, by group: counted on the scalar unit from the compare masks
+  uint32_t group_gt[KPT / 4], group_eq[KPT / 4];
   {
     uint32_t wave_gt = 0, wave_eq = 0;
 #pragma unroll
-    for (int i = 0; i < KPT; i++) {
-      wave_gt += (uint32_t)__popcll(__ballot(key[i] > tau));
-      wave_eq += (uint32_t)__popcll(__ballot(key[i] == tau));
+    for (int i = 0; i < KPT / 4; i++) {
+      group_gt[i] = group_eq[i] = 0;
+#pragma unroll
+      for (int e = 0; e < 4; e++) {
+        group_gt[i] += (uint32_t)__popcll(__ballot(key[4 * i + e] > tau));
+        group_eq[i] += (uint32_t)__popcll(__ballot(key[4 * i + e] == tau));
+      }
+      wave_gt += group_gt[i];
+      wave_eq += group_eq[i];
     }
     if (lane == 0) { wgt[wave] = wave_gt; weq[wave] = wave_eq; }
   }
   __syncthreads();
   const uint32_t og = lane < wave ? wgt[lane & (kSelWaves - 1)] : 0u, oe = lane < wave ? weq[lane & (kSelWaves - 1)] : 0u;
   uint32_t run_gt = row0_total(og), run_eq = row0_total(oe);   // in the waves before this one (wave < 16 lanes of row 0)
+  // this workgroup's outputs
+  const uint32_t p0 = (uint32_t)((unsigned long long)k * chunk / chunks), p1 = (uint32_t)((unsigned long long)k * (chunk + 1) / chunks);
+  asm volatile("" : "+v"(tau));   // (compare again below: kept from the counts, the masks of all groups would spill)
   int32_t *kb = kept + (size_t)b * k;
 #pragma unroll
   for (int i = 0; i < KPT / 4; i++) {
-    uint32_t c = 0;
+    const uint32_t first = run_gt + min(run_eq, need);
+    const uint32_t last = run_gt + group_gt[i] + min(run_eq + group_eq[i], need);
+    if (first < p1 && last > p0) {                               // (uniform in the wave)
+      uint32_t c = 0;
 #pragma unroll
-    for (int e = 0; e < 4; e++) c += (uint32_t)(key[4 * i + e] > tau) + ((uint32_t)(key[4 * i + e] == tau) << 16);
-    const uint32_t incl = wave_prefix_incl(c, lane);           // at most 256 per half
-    const uint32_t group = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
-    uint32_t ngt = run_gt + ((incl - c) & 0xffffu), neq = run_eq + ((incl - c) >> 16);
+      for (int e = 0; e < 4; e++) c += (uint32_t)(key[4 * i + e] > tau) + ((uint32_t)(key[4 * i + e] == tau) << 16);
+      const uint32_t incl = wave_prefix_incl(c, lane);           // at most 256 per half
+      uint32_t ngt = run_gt + ((incl - c) & 0xffffu), neq = run_eq + ((incl - c) >> 16);
+      int32_t xy[4] = {0, 0, 0, 0};
+      if (coords_in)
 #pragma unroll
-    for (int e = 0; e < 4; e++) {
-      const bool gt = key[4 * i + e] > tau, eq = key[4 * i + e] == tau;
-      if (gt || (eq && neq < need)) {
+        for (int e = 0; e < 4; e++) xy[e] = coords_in[(size_t)b * N + min(j0 + 256 * i + e, N - 1)];
+#pragma unroll
+      for (int e = 0; e < 4; e++) {
+        const bool gt = key[4 * i + e] > tau, eq = key[4 * i + e] == tau;
         const uint32_t pos = ngt + min(neq, need);
-        const int j = j0 + 256 * i + e;
-        if (pos < (uint32_t)k) {   // always
+        if ((gt || (eq && neq < need)) && pos >= p0 && pos < p1) {
+          const int j = j0 + 256 * i + e;
           kb[pos] = j;
-          if (coords_in) coords_out[(size_t)b * k + pos] = coords_in[(size_t)b * N + j];
+          if (coords_in) coords_out[(size_t)b * k + pos] = xy[e];
         }
+        ngt += gt;
+        neq += eq;
       }
-      ngt += gt;
-      neq += eq;
     }
-    run_gt += group & 0xffffu;
-    run_eq += group >> 16;
+    run_gt += group_gt[i];
+    run_eq += group_eq[i];
   }
 }
 
@@ -448,15 +499,19 @@ size_t topk_select_workspace_bytes(int B, int N) {
 ns_status launch_topk_select(int B, int N, int k, const float *scores, const int32_t *coords_in,
                              int32_t *kept, int32_t *coords_out, void *ws, hipStream_t s) {
   if (N <= kRegMaxKeys * kSelThreads) {
-    const dim3 grid(B), block(kSelThreads);
-    if (N <= 4 * kSelThreads)
-      hipLaunchKernelGGL(topk_select_reg_kernel<4>, grid, block, 0, s, scores, N, k, coords_in, kept, coords_out);
-    else if (N <= 8 * kSelThreads)
-      hipLaunchKernelGGL(topk_select_reg_kernel<8>, grid, block, 0, s, scores, N, k, coords_in, kept, coords_out);
-    else if (N <= 16 * kSelThreads)
-      hipLaunchKernelGGL(topk_select_reg_kernel<16>, grid, block, 0, s, scores, N, k, coords_in, kept, coords_out);
-    else
-      hipLaunchKernelGGL(topk_select_reg_kernel<32>, grid, block, 0, s, scores, N, k, coords_in, kept, coords_out);
+    // up to 16 workgroups per image, as long as every one has a CU, for at least 64 outputs each; one where an output lies
+    // over the scores, which are then all read before the first index is written
+    auto over_scores = [&](const int32_t *out) {
+      const uintptr_t o = reinterpret_cast<uintptr_t>(out), i = reinterpret_cast<uintptr_t>(scores);
+      return out && o < i + (size_t)4 * B * N && i < o + (size_t)4 * B * k;
+    };
+    const bool apart = !over_scores(kept) && !over_scores(coords_out);
+    const dim3 grid(apart ? std::max(1, std::min({16, device_cu_count() / B, k / 64})) : 1, B), block(kSelThreads);
+    const auto kern = N <= 4 * kSelThreads    ? topk_select_reg_kernel<4>
+                      : N <= 8 * kSelThreads  ? topk_select_reg_kernel<8>
+                      : N <= 16 * kSelThreads ? topk_select_reg_kernel<16>
+                                              : topk_select_reg_kernel<32>;
+    hipLaunchKernelGGL(kern, grid, block, 0, s, scores, N, k, coords_in, kept, coords_out);
     return check_launch("topk_select_reg_kernel");
   }
   const int kpt = multi_kpt(N), nchunk = multi_chunks(N);

@@ -140,6 +140,38 @@ def test_gather_and_coords_compaction_bit_exact(nb):
     assert np.array_equal(yf.cpu().numpy(), oracle.gather(xf, ref_kept))
 
 
+@pytest.mark.parametrize("B,N,keep,G,C,dtype,clustered", [
+    (1, 16384, 9831, 1, 64, "bf16", False),     # 16 workgroups
+    (2, 4096, 2458, 5, 1024, "bf16", True),     # four keys per thread, all kept rows in one half of the row
+    (3, 4097, 1230, 1, 520, "bf16", True),      # eight keys per thread, unaligned score rows
+    (1, 32768, 32768, 3, 8, "bf16", False),     # everything is kept, 32 keys per thread
+    (128, 300, 150, 2, 8, "bf16", False),       # two workgroups per image
+    (129, 300, 150, 2, 8, "bf16", True),        # one
+    (2, 50, 7, 9, 24, "f32", False),            # fewer outputs than one workgroup's least
+    (1, 1, 1, 1, 4, "f32", False)])
+def test_selection_by_several_workgroups(nb, B, N, keep, G, C, dtype, clustered):
+    """Edges of the ranges of outputs that an image's workgroups place; exact."""
+    rng = np.random.default_rng(B * 1000 + N)
+    scores = rng.random((B, N)).astype(np.float32)
+    if clustered:
+        scores[:, : N // 2] = 0.125 + 1e-6 * scores[:, : N // 2]      # near ties
+        scores[:, N // 2::5] = 0.75                                   # exact ones
+    bits = np.uint16 if dtype == "bf16" else np.uint32
+    x = rng.integers(0, np.iinfo(bits).max, size=(B, G + N, C), dtype=bits, endpoint=True)
+    signed = x.view(np.int16 if dtype == "bf16" else np.int32)
+    dx = torch.from_numpy(signed).cuda().view(torch.bfloat16 if dtype == "bf16" else torch.float32)
+    coords = rng.integers(0, 2 ** 31 - 1, size=(B, N), dtype=np.int32)
+    y = torch.empty((B, G + keep, C), dtype=dx.dtype, device="cuda")
+    kept, y, cout = nb.topk_filter(torch.from_numpy(scores).cuda(), keep, x=dx, y=y, coords=torch.from_numpy(coords).cuda(),
+                                   n_global=G)
+    torch.cuda.synchronize()
+    ref = oracle.topk(scores, keep)
+    assert np.array_equal(kept.cpu().numpy(), ref)
+    assert np.array_equal(cout.cpu().numpy(), np.take_along_axis(coords, ref.astype(np.int64), axis=1))
+    want = np.concatenate([x[:, :G], np.take_along_axis(x[:, G:], ref.astype(np.int64)[:, :, None], axis=1)], axis=1)
+    assert np.array_equal(y.view(torch.int16 if dtype == "bf16" else torch.int32).cpu().numpy().view(bits), want)
+
+
 def test_scores_to_kept_set_end_to_end(nb):
     g = 40
     q, k, v = synth.small_case(77, 2, 16, 64, g, g, "bf16")
@@ -156,3 +188,13 @@ def test_running_out_of_memory_is_reported_as_such(nb):
     """An output that no device holds: the allocator's own exception, as from any torch call."""
     with pytest.raises(torch.cuda.OutOfMemoryError):
         nb.topk_filter(torch.zeros(1, 64, device="cuda"), 2 ** 42)
+
+
+def test_indices_written_over_the_scores(nb):
+    """The one row's scores are all read before the first index is written, where they share memory."""
+    rng = np.random.default_rng(12)
+    scores = rng.random((1, 16384)).astype(np.float32)
+    buf = torch.from_numpy(scores).cuda()
+    kept, _, _ = nb.topk_filter(buf, 9831, kept_idx=buf.view(torch.int32)[:, :9831])
+    torch.cuda.synchronize()
+    assert np.array_equal(kept.cpu().numpy(), oracle.topk(scores, 9831))
