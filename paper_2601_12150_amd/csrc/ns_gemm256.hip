@@ -187,6 +187,9 @@ __device__ __forceinline__ void gemm256_wave(const Gemm256Params &p, unsigned ch
   f32x16 acce[2];      // ninth token slab x weight slabs 2*WM, 2*WM+1
 #pragma unroll
   for (int e = 0; e < 16; e++) { acce[0][e] = 0.f; acce[1][e] = 0.f; }
+  // (their products are asm, for which the compiler pads no hazard: a matrix instruction right behind the vector instruction
+  // that clears its accumulator reads what the register held before.  So they are cleared here, not next to it.)
+  if (EXT) asm volatile("s_nop 1" : "+v"(acce[0]), "+v"(acce[1]));
 
   // One k-step: the MFMAs of fragments (fw[ks & 1], fx[ks]) with, spread between them, the LDS reads of
   // later fragments and the transfers of a later slice, so that neither the reads' latency nor the issue of the
@@ -231,10 +234,11 @@ __device__ __forceinline__ void gemm256_wave(const Gemm256Params &p, unsigned ch
       // The compiler keeps every accumulator of its own MFMAs in the 256 accumulator registers;
       // 18 of them do not fit and would be rotated through moves in every iteration.  These two
       // are pinned to ordinary vector registers instead.  (Each is next touched 17 MFMAs later,
-      // and read by other instructions only after the loop: no issue hazards to pad.)
+      // and read by other instructions only after the loop; the wait states cover a fragment or accumulator that a
+      // vector instruction has just written.)
       f32x16 &a0 = acce[0], &a1 = acce[1];
       const bf16x8 &w0 = fw[ks & 1][2 * WM], &w1 = fw[ks & 1][2 * WM + 1], &x = fe[ks];
-      asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(a0) : "v"(w0), "v"(x));
+      asm volatile("s_nop 1\n\tv_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(a0) : "v"(w0), "v"(x));
       asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(a1) : "v"(w1), "v"(x));
     }
   };
