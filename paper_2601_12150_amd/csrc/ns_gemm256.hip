@@ -29,9 +29,9 @@
 // sequence: 39 x 4 tiles on 256 CUs), tiles of 192 rows (three slabs per wave) are used instead
 // when that shortens the launch.
 //
-// Measured (us, two slots per operand -> this), epilogues included: 16385 x 3072 x 1024 111 -> 98,
-// 16385 x 1024 x 1024 + residual 49 -> 44, 16385 x 4096 x 1024 + GELU 177 -> 163, 16385 x 1024 x 4096 + residual 128 -> 113;
-// 9832 rows: 70 -> 68, 31 -> 28, 113 -> 103, 89 -> 71.
+// Measured (us, two slots per operand and an epilogue that waits for each of its loads -> this): 16385 x 3072 x 1024 111 -> 98,
+// 16385 x 1024 x 1024 + residual 49 -> 37, 16385 x 4096 x 1024 + GELU 177 -> 148, 16385 x 1024 x 4096 + residual 128 -> 114;
+// 9832 rows: 70 -> 61, 31 -> 24, 113 -> 96, 89 -> 73.
 #include "ns_common.h"
 #include <type_traits>
 
@@ -63,63 +63,78 @@ typedef bf16x8 __attribute__((address_space(3))) *lds_bf16x8_ptr;
 
 
 
-// Accumulators of NS weight slabs x one 32-token slab -> LDS (fp32, [token][32*NS n]) -> lanes that
-// own 8 consecutive n of one token: + bias, GELU, + residual, one 16-byte store.
-// Waiting for a load also waits for every older store (one in-order counter), so no load may
-// follow a store here: the bias is waited for up front and the residual rows of all passes are
-// requested before the first store.
-template <int NS, bool GELU, bool RES>
-__device__ __forceinline__ void gemm256_emit(const Gemm256Params &p, unsigned char *ebuf, const f32x16 *const (&slab)[NS],
-                                             int mbase, int nbase, int lane) {
-  constexpr int LPT = NS * 4;                 // lanes per token row
-  constexpr int PASSES = LPT / 2, TPP = 64 / LPT;   // tokens per pass
-  const int l32 = lane & 31, hh = lane >> 5;
-  const int nl = 8 * (lane & (LPT - 1));
-  const int ncol = nbase + nl;
-  f32x4 b0 = *reinterpret_cast<const f32x4 *>(p.bias + ncol);
-  f32x4 b1 = *reinterpret_cast<const f32x4 *>(p.bias + ncol + 4);
-  uint4 res[RES ? PASSES : 1];
-  if (RES) {
-#pragma unroll
-    for (int ps = 0; ps < PASSES; ps++) {
-      const int m = min(mbase + TPP * ps + lane / LPT, p.M - 1);
-      res[ps] = *reinterpret_cast<const uint4 *>(p.r + (size_t)m * p.N + ncol);
-    }
+// ---- epilogue of NS weight slabs x one 32-token slab: accumulators -> LDS (fp32, [token][32*NS n]) -> lanes that
+// own 8 consecutive n of one token: + bias, GELU, + residual, one 16-byte store.  A wave has its SIMD to itself here, so
+// every latency it waits for is lost: the next slab is staged (two buffers) and its residual rows are requested before
+// this one is finished, the staged values are read four passes ahead, and nothing is loaded behind a store that
+// would have to be waited for with it (one in-order counter).  Lanes past the last row, whose inputs repeat it, store
+// its values once more, to the same place: no branch around the stores.  Against an epilogue that staged, loaded and read each
+// slab and pass in turn (32 LDS latencies and four drained stores a tile; whole calls): 16385 x 1024 x 1024 + residual 38.0 -> 36.7 us,
+// 16385 x 4096 x 1024 + GELU 153 -> 148; 9832 rows: 26.0 -> 24.0 and 100 -> 96, x 3072 x 1024 63 -> 61; K = 4096 as before.
+template <int NS>
+struct Epi {
+  static constexpr int LPT = NS * 4;                          // lanes per token row
+  static constexpr int TPP = 64 / LPT, PASSES = LPT / 2;      // tokens per pass
+  static constexpr int AHEAD = 4;
+  static __device__ __forceinline__ int col(int nbase, int lane) { return nbase + 8 * (lane & (LPT - 1)); }
+  static __device__ __forceinline__ size_t at(const Gemm256Params &p, int mbase, int nbase, int ps, int lane) {
+    return (size_t)min(mbase + TPP * ps + lane / LPT, p.M - 1) * p.N + col(nbase, lane);
   }
+  static __device__ __forceinline__ void load_bias(const Gemm256Params &p, int nbase, int lane, f32x4 (&b)[2]) {
+    b[0] = *reinterpret_cast<const f32x4 *>(p.bias + col(nbase, lane));
+    b[1] = *reinterpret_cast<const f32x4 *>(p.bias + col(nbase, lane) + 4);
+  }
+  static __device__ __forceinline__ void load_residual(const Gemm256Params &p, int mbase, int nbase, int lane, uint4 (&res)[PASSES]) {
 #pragma unroll
-  for (int ti = 0; ti < NS; ti++)
+    for (int ps = 0; ps < PASSES; ps++) res[ps] = *reinterpret_cast<const uint4 *>(p.r + at(p, mbase, nbase, ps, lane));
+  }
+  static __device__ __forceinline__ void stage(unsigned char *ebuf, const f32x16 *const (&slab)[NS], int lane) {
 #pragma unroll
-    for (int g = 0; g < 4; g++) {
-      const f32x16 &a = *slab[ti];
-      const f32x4 v = {a[4 * g], a[4 * g + 1], a[4 * g + 2], a[4 * g + 3]};
-      *reinterpret_cast<f32x4 *>(ebuf + l32 * kEpiRow + (32 * ti + 8 * g + 4 * hh) * 4) = v;
-    }
-  asm volatile("" : "+v"(b0), "+v"(b1));      // the bias has arrived before the first store is issued
-  auto pass = [&](int ps, const uint4 &r4) {
-    const int t = TPP * ps + lane / LPT;
-    const int m = mbase + t;
-    const f32x4 v0 = *reinterpret_cast<const f32x4 *>(ebuf + t * kEpiRow + nl * 4);
-    const f32x4 v1 = *reinterpret_cast<const f32x4 *>(ebuf + t * kEpiRow + nl * 4 + 16);
-    float o[8] = {v0[0] + b0[0], v0[1] + b0[1], v0[2] + b0[2], v0[3] + b0[3],
-                  v1[0] + b1[0], v1[1] + b1[1], v1[2] + b1[2], v1[3] + b1[3]};
-    if (GELU) gelu_erf8(o);
-    if (RES) {
-      o[0] += bf16_lo(r4.x); o[1] += bf16_hi(r4.x); o[2] += bf16_lo(r4.y); o[3] += bf16_hi(r4.y);
-      o[4] += bf16_lo(r4.z); o[5] += bf16_hi(r4.z); o[6] += bf16_lo(r4.w); o[7] += bf16_hi(r4.w);
-    }
-    if (m < p.M) {
+    for (int ti = 0; ti < NS; ti++)
+#pragma unroll
+      for (int g = 0; g < 4; g++) {
+        const f32x16 &a = *slab[ti];
+        const f32x4 v = {a[4 * g], a[4 * g + 1], a[4 * g + 2], a[4 * g + 3]};
+        *reinterpret_cast<f32x4 *>(ebuf + (lane & 31) * kEpiRow + (32 * ti + 8 * g + 4 * (lane >> 5)) * 4) = v;
+      }
+  }
+  // finishes the slab staged in ebuf; `then` is called when the first values have been asked for
+  template <bool GELU, bool RES, class F>
+  static __device__ __forceinline__ void emit(const Gemm256Params &p, const unsigned char *ebuf, const f32x4 (&b)[2],
+                                              const uint4 (&res)[PASSES], int mbase, int nbase, int lane, F then) {
+    const unsigned char *src = ebuf + lane / LPT * kEpiRow + 32 * (lane & (LPT - 1));
+    f32x4 v[AHEAD][2];
+    auto fetch = [&](int ps, f32x4 (&x)[2]) {
+      x[0] = *reinterpret_cast<const f32x4 *>(src + TPP * kEpiRow * ps);
+      x[1] = *reinterpret_cast<const f32x4 *>(src + TPP * kEpiRow * ps + 16);
+    };
+#pragma unroll
+    for (int i = 0; i < AHEAD; i++) fetch(i, v[i]);
+    then();
+    auto pass = [&](int ps, f32x4 (&x)[2], const uint4 &r4) {
+      float o[8];
+#pragma unroll
+      for (int i = 0; i < 8; i++) o[i] = x[i >> 2][i & 3] + b[i >> 2][i & 3];
+      fetch(min(ps + AHEAD, PASSES - 1), x);
+      if (GELU) gelu_erf8(o);
+      if (RES) {
+        o[0] += bf16_lo(r4.x); o[1] += bf16_hi(r4.x); o[2] += bf16_lo(r4.y); o[3] += bf16_hi(r4.y);
+        o[4] += bf16_lo(r4.z); o[5] += bf16_hi(r4.z); o[6] += bf16_lo(r4.w); o[7] += bf16_hi(r4.w);
+      }
       const uint4 u = {pack_bf16(o[0], o[1]), pack_bf16(o[2], o[3]), pack_bf16(o[4], o[5]), pack_bf16(o[6], o[7])};
-      *reinterpret_cast<uint4 *>(p.c + (size_t)m * p.N + ncol) = u;
-    }
-  };
-  if (RES) {
+      *reinterpret_cast<uint4 *>(p.c + at(p, mbase, nbase, ps, lane)) = u;
+    };
+    if (RES) {
 #pragma unroll
-    for (int ps = 0; ps < PASSES; ps++) pass(ps, res[ps]);
-  } else {
-#pragma unroll 2
-    for (int ps = 0; ps < PASSES; ps++) pass(ps, res[0]);
+      for (int ps = 0; ps < PASSES; ps++) pass(ps, v[ps % AHEAD], res[ps]);
+    } else {
+#pragma unroll 1
+      for (int ps = 0; ps < PASSES; ps += AHEAD)
+#pragma unroll
+        for (int i = 0; i < AHEAD; i++) pass(ps + i, v[i], res[0]);
+    }
   }
-}
+};
 
 // One wave's work on one workgroup tile.  NTJ: 32-row token slabs of its own 128 rows that this
 // wave computes (0..4).  EXT: the tile has a ninth token slab (rows 256..287); this wave then
@@ -307,6 +322,15 @@ __device__ __forceinline__ void gemm256_wave(const Gemm256Params &p, unsigned ch
     t++;
     slot = next(slot);
   }
+  // (no transfer is on its way any more: what the epilogue starts with may be asked for)
+  using E4 = Epi<4>;
+  using E2 = Epi<2>;
+  const int mw = m0 + wm * WROWS, nw = n0 + wn * 128, ne = nw + 64 * WM;   // ne: columns of the ninth slab
+  f32x4 bias[2], biase[2];
+  uint4 res[2][E4::PASSES] = {}, rese[E2::PASSES] = {};
+  E4::load_bias(p, nw, lane, bias);
+  if (EXT) E2::load_bias(p, ne, lane, biase);
+  if (RES && NTJ > 0) E4::load_residual(p, mw, nw, lane, res[0]);
   slice(K0{}, t, slot, 0);
   // (the accumulators are final here: left to itself the compiler sinks the last products into the epilogue's slabs,
   // and their operands are spilled on the way)
@@ -318,16 +342,26 @@ __device__ __forceinline__ void gemm256_wave(const Gemm256Params &p, unsigned ch
   __syncthreads();             // every wave is done with the stages: they become the epilogue's staging area
 
   // ---- epilogue, one 32-token slab at a time
-  unsigned char *ebuf = smem + wave * kEpiWave;
+  unsigned char *const ebuf[2] = {smem + wave * kEpiWave, smem + (4 + wave) * kEpiWave};
+  static_assert(8 * kEpiWave <= kGemmLds, "two staged slabs per wave");
+  auto stage = [&](int tj) {
+    if (tj < NTJ) {
+      const f32x16 *const slab[4] = {&acc[0][tj], &acc[1][tj], &acc[2][tj], &acc[3][tj]};
+      E4::stage(ebuf[tj & 1], slab, lane);
+    } else if (EXT) {
+      const f32x16 *const slab[2] = {&acce[0], &acce[1]};
+      E2::stage(ebuf[tj & 1], slab, lane);
+    }
+  };
+  stage(0);
 #pragma unroll
-  for (int tj = 0; tj < NTJ; tj++) {
-    const f32x16 *const slab[4] = {&acc[0][tj], &acc[1][tj], &acc[2][tj], &acc[3][tj]};
-    gemm256_emit<4, GELU, RES>(p, ebuf, slab, m0 + wm * WROWS + tj * 32, n0 + wn * 128, lane);
-  }
-  if (EXT) {
-    const f32x16 *const slab[2] = {&acce[0], &acce[1]};
-    gemm256_emit<2, GELU, RES>(p, ebuf, slab, m0 + 256, n0 + wn * 128 + 64 * WM, lane);
-  }
+  for (int tj = 0; tj < NTJ; tj++)
+    E4::template emit<GELU, RES>(p, ebuf[tj & 1], bias, res[tj & 1], mw + tj * 32, nw, lane, [&]() {
+      if (RES && tj + 1 < NTJ) E4::load_residual(p, mw + (tj + 1) * 32, nw, lane, res[(tj + 1) & 1]);
+      if (RES && EXT && tj + 1 == NTJ) E2::load_residual(p, m0 + 256, ne, lane, rese);
+      stage(tj + 1);
+    });
+  if (EXT) E2::template emit<GELU, RES>(p, ebuf[NTJ & 1], biase, rese, m0 + 256, ne, lane, []() {});
 }
 
 template <int NK, bool GELU, bool RES>
