@@ -123,3 +123,46 @@ def test_addresses_stay_in_bounds_on_random_grids():
         gh, gw = rng.randint(1, 75), rng.randint(1, 75)
         assert check_sweep(gh, gw) == 0, (gh, gw)
         assert check_block16(gh, gw, rng.choice([1, 2, 4])) == 0, (gh, gw)
+
+
+# ---- the block kernel as it numbers queries and keys: in raster order within the block and within the rectangle of its keys
+
+
+def block_of(blk, rim, nbh, nbw):
+    if not rim:
+        R = blk // (nbw - 2)
+        return R + 1, 1 + blk - R * (nbw - 2)
+    ends, b2 = min(nbw, 2), blk - nbw
+    b3 = b2 - max(nbh - 2, 0) * ends
+    if b2 < 0:
+        return 0, blk
+    return (1 + b2 // ends, nbw - 1 if b2 % ends else 0) if b3 < 0 else (nbh - 1, b3)
+
+
+@pytest.mark.parametrize("gh,gw,block", [(16, 16, 16), (17, 33, 16), (245, 245, 64), (100, 53, 32), (48, 20, 64), (33, 64, 16), (80, 3, 16)])
+def test_block_kernel_numbering(gh, gw, block):
+    """Every token is the query of one slot and every key of a block's rectangle is brought in once, at the place where
+    the next 64 keys follow by steps of whole rows and columns, as the kernel's lanes advance."""
+    nbh, nbw, parts = -(-gh // block), -(-gw // block), -(-block * block // 256)
+    inner = max(nbh - 2, 0) * max(nbw - 2, 0)
+    blocks = [block_of(i, False, nbh, nbw) for i in range(inner)] + [block_of(i, True, nbh, nbw) for i in range(nbh * nbw - inner)]
+    assert sorted(blocks) == [(R, C) for R in range(nbh) for C in range(nbw)]
+    queries = []
+    for R, C in blocks:
+        r0, c0 = R * block, C * block
+        bw = min(block, gw - c0)
+        qn = min(block, gh - r0) * bw
+        assert qn <= 256 * parts
+        queries += [(r0 + s // bw) * gw + c0 + s % bw for s in range(qn)]
+        kr0, kc0 = max(r0 - block, 0), max(c0 - block, 0)
+        kw = min(c0 + 2 * block, gw) - kc0
+        nk = (min(r0 + 2 * block, gh) - kr0) * kw
+        right, step, wrap = 64 % kw, (64 // kw) * gw + 64 % kw, gw - kw
+        for i in range(64):                        # the key rows that place i of a tile takes, tile by tile
+            col, at = i % kw, (kr0 + i // kw) * gw + kc0 + i % kw
+            for j in range(i, nk, 64):
+                assert at == (kr0 + j // kw) * gw + kc0 + j % kw < gh * gw
+                col, at = col + right, at + step
+                if col >= kw:
+                    col, at = col - kw, at + wrap
+    assert sorted(queries) == list(range(gh * gw))
