@@ -320,6 +320,29 @@ def test_gelu_epilogue_value_by_value(nb, n):
     assert np.all(got[x >= 0] >= 0) and np.all(got[x < 0] <= 0)
 
 
+@pytest.mark.parametrize("K", [64, 128, 192])
+@pytest.mark.parametrize("M", [256, 257, 288, 289, 351, 384, 447, 511])
+def test_linear_forward_last_rows(nb, M, K):
+    """Sequences that end inside a pass of four rows, a slab, the ninth slab: the lanes past the end store the last row's values
+    once more.  Nothing behind the end is written, and every row is right (one rounding to bf16, 2^-9 relative, on top of
+    fp32 accumulation)."""
+    N = 256
+    rng = np.random.default_rng(M + K)
+    x = synth.round_to_bf16(rng.standard_normal((M, K)).astype(np.float32))
+    w = synth.round_to_bf16((rng.standard_normal((N, K)) / np.sqrt(K)).astype(np.float32))
+    b = rng.standard_normal(N).astype(np.float32)
+    r = synth.round_to_bf16(rng.standard_normal((M, N)).astype(np.float32))
+    dev = lambda a: torch.from_numpy(a).to(torch.bfloat16).cuda()
+    lin = x.astype(np.float64) @ w.astype(np.float64).T + b
+    for gelu, res in ((False, False), (True, False), (False, True), (True, True)):
+        buf = torch.full((M + 64, N), 7.0, dtype=torch.bfloat16, device="cuda")
+        nb.linear_forward(dev(x), dev(w), torch.from_numpy(b).cuda(), dev(r) if res else None, gelu=gelu, out=buf[:M])
+        torch.cuda.synchronize()
+        ref = (ov.gelu(lin) if gelu else lin) + (r if res else 0.0)
+        np.testing.assert_allclose(to_np(buf[:M]).astype(np.float64), ref, rtol=2.0 ** -8, atol=1e-3)
+        assert torch.all(buf[M:] == 7.0)
+
+
 @pytest.mark.parametrize("M,N,K,gelu,res", [
     (1025, 1024, 1024, False, True),    # one extended row tile chain: 4 tiles, the last with a ninth slab
     (577, 512, 256, True, False),       # remainder 65: a partial tile of its own (3 slabs)
