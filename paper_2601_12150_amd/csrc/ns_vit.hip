@@ -172,10 +172,10 @@ __global__ __launch_bounds__(256, 2) void gemm_bf16_kernel(GemmParams p) {
         const f32x4 b4 = *reinterpret_cast<const f32x4 *>(p.bias + n);
         float o[4];
 #pragma unroll
-        for (int e = 0; e < 4; e++) {
-          o[e] = acc[nt][mt][4 * ig + e] + b4[e];
-          if (p.gelu) o[e] = gelu_erf(o[e]);
-        }
+        for (int e = 0; e < 4; e++) o[e] = acc[nt][mt][4 * ig + e] + b4[e];
+        if (p.gelu)                       // (one branch: the four dependency chains run side by side)
+#pragma unroll
+          for (int e = 0; e < 4; e++) o[e] = gelu_erf(o[e]);
         if (p.r) {
           const uint2 r2 = *reinterpret_cast<const uint2 *>(p.r + (size_t)m * p.N + n);
           o[0] += bf16_lo(r2.x); o[1] += bf16_hi(r2.x); o[2] += bf16_lo(r2.y); o[3] += bf16_hi(r2.y);

@@ -1,4 +1,6 @@
 """GPU parity: vit_block_forward (through the C ABI) against the float64 block oracle."""
+import math
+
 import numpy as np
 import pytest
 import torch
@@ -318,6 +320,21 @@ def test_gelu_epilogue_value_by_value(nb, n):
     worst = int(np.argmax(err / bound))
     assert np.all(err <= bound), (x.flat[worst], got.flat[worst], ref.flat[worst])
     assert np.all(got[x >= 0] >= 0) and np.all(got[x < 0] <= 0)
+
+
+@pytest.mark.parametrize("n", [256, 128])
+def test_gelu_beyond_its_fit(nb, n):
+    """GELU below -6.5, outside the range that the epilogue's polynomial is fitted on: within 6e-13 of the true value (the
+    truth itself is 2.6e-10 at -6.5) on top of one rounding to bf16 (eight bits: 2^-8), and never positive.  The reference is
+    x erfc(-x / sqrt 2) / 2 in float64, which does not cancel."""
+    M = 256
+    x = synth.round_to_bf16(np.linspace(-13.5, -6.5, M * n).astype(np.float32)).reshape(M, n)
+    dev = lambda a: torch.from_numpy(a).to(torch.bfloat16).cuda()
+    y = nb.linear_forward(dev(x), dev(np.eye(n, dtype=np.float32)), torch.zeros(n, device="cuda"), None, gelu=True)
+    torch.cuda.synchronize()
+    ref = np.array([0.5 * v * math.erfc(-v / math.sqrt(2.0)) for v in x.astype(np.float64).flat]).reshape(M, n)
+    got = to_np(y)
+    assert np.all(np.abs(got - ref) <= 2.0 ** -8 * np.abs(ref) + 6e-13) and np.all(got <= 0.0)
 
 
 @pytest.mark.parametrize("K", [64, 128, 192])
