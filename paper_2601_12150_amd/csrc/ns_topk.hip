@@ -109,6 +109,9 @@ __device__ __forceinline__ void choose_digit(uint32_t tot, uint32_t need, int ti
   __syncthreads();
 }
 
+// (read from LDS, the same in every lane: on the scalar unit, so that what depends on it branches and compares there)
+__device__ __forceinline__ uint32_t uniform(uint32_t x) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)x); }
+
 constexpr int kDirectMax = 256;    // candidates that are ranked against each other instead of by a further digit
 constexpr int kDigitBits = 11, kDigits = 1 << kDigitBits;
 
@@ -184,10 +187,20 @@ __global__ __launch_bounds__(kSelThreads) void topk_select_reg_kernel(const floa
   // ranked against each other directly.  Digits of 8 bits leave 200 to 500 of them, whose ranking took 6 us of 11.
   // (key - lo <= span holds for no key below lo: lo + span <= hi does not wrap around, the difference does.)
   // In the end `left` is the number of keys equal to tau that are kept.
+  // Where no score is negative, the range ends 16 octaves below the largest one at first: a few scores next to zero would
+  // spread the digits over up to 250.  If fewer than k lie in it, no digit is chosen, and what lies below is next.
+  // Rows with many equal scores (the empty part of a slide) leave them all in one digit, however narrow.  Two neighbouring
+  // lanes with the same key give them away; that key is tried as tau once.
+  // Two rows of 16384 (digits of the whole range to the end -> this; in brackets 8-bit digits, one workgroup): one octave of
+  // smooth scores 9.6 -> 9.7 us (11.3), one of them next to zero 11.1 -> 10.4 (11.3), 40 % of them equal 15.7 -> 11.2 (11.5),
+  // zeros and ones 17.5 -> 11.4 (11.7), all equal 10.6 -> 6.7 (11.6); normally distributed, with signs, 11.0 -> 11.8 (9.9).
+  const uint32_t least = lo;
+  if (lo >= 0x7fffffffu) lo = max(lo, hi - ((16u << 23) - 1u));
   uint32_t span = hi - lo, left = (uint32_t)k;
   int shift = max(32 - kDigitBits - __clz((int)span), 0);         // (span 0: clz 32)
-  uint32_t tau;
-  for (;;) {
+  uint32_t tau = lo;
+  bool tried = false;
+  while (span != 0u) {
 #pragma unroll
     for (int i = 0; i < KPT; i++) {
       const uint32_t u = key[i] - lo;
@@ -207,14 +220,20 @@ __global__ __launch_bounds__(kSelThreads) void topk_select_reg_kernel(const floa
       if (above0 < left && left <= above0 + n0) { sel[0] = 2 * tid; sel[1] = left - above0; sel[2] = n0; }
       __syncthreads();
     }
-    const uint32_t before = sel[0] << shift;
-    lo += before;
-    left = sel[1];
-    const uint32_t nc = sel[2];
+    const uint32_t nc = uniform(sel[2]);
+    if (__builtin_expect(nc == 0u, 0)) {                          // tau lies below the first range
+      left -= row0_total(wsum[lane & (kSelWaves - 1)]);
+      span = lo - 1u - least;
+      lo = least;
+    } else {
+      const uint32_t before = uniform(sel[0]) << shift;
+      lo += before;
+      left = uniform(sel[1]);
+      span = min(span - before, (1u << shift) - 1u);
+    }
     tau = lo;
-    if (shift == 0) break;
-    span = min(span - before, (1u << shift) - 1u);
-    if (nc <= (uint32_t)kDirectMax) {
+    if (__builtin_expect(span == 0u, 0)) break;
+    if (__builtin_expect(nc - 1u < (uint32_t)kDirectMax, 1)) {
       // ---- the candidates into a list, in any order
 #pragma unroll
       for (int i = 0; i < KPT; i++)
@@ -241,12 +260,43 @@ __global__ __launch_bounds__(kSelThreads) void topk_select_reg_kernel(const floa
         if (c != 0u && (n & 0xffffu) < left && left <= (n >> 16)) { sel[0] = c; sel[1] = left - (n & 0xffffu); }
       }
       __syncthreads();
-      tau = sel[0];
-      left = sel[1];
+      tau = uniform(sel[0]);
+      left = uniform(sel[1]);
       break;
     }
-    shift = max(shift - kDigitBits, 0);
+    if (!tried) {
+      tried = true;
+      uint32_t twice = 0;                    // a candidate that two neighbouring lanes have
+#pragma unroll
+      for (int i = 0; i < KPT; i += KPT / 2) {
+        const uint64_t same = __ballot(key[i] - lo <= span && key[i] == (uint32_t)__builtin_amdgcn_update_dpp(0, (int)key[i], 0x111, 0xf, 0xf, false));
+        if (same) twice = (uint32_t)__builtin_amdgcn_readlane((int)key[i], __builtin_ctzll(same));
+      }
+      if (lane == 0) wlo[wave] = twice;
+      __syncthreads();
+      const uint32_t t = wave_max(wlo[lane & (kSelWaves - 1)]);
+      if (t != 0u) {
+        uint32_t gt = 0, eq = 0;
+#pragma unroll
+        for (int i = 0; i < KPT; i++) {
+          gt += (uint32_t)__popcll(__ballot(key[i] > t));
+          eq += (uint32_t)__popcll(__ballot(key[i] == t));
+        }
+        if (lane == 0) { wgt[wave] = gt; weq[wave] = eq; }
+        __syncthreads();
+        gt = row0_total(wgt[lane & (kSelWaves - 1)]);
+        eq = row0_total(weq[lane & (kSelWaves - 1)]);
+        if (gt < (uint32_t)k && (uint32_t)k <= gt + eq) {
+          tau = t;
+          left = (uint32_t)k - gt;
+          __syncthreads();                   // (wgt and weq have been read: they are written again)
+          break;
+        }
+      }
+    }
+    shift = max(32 - kDigitBits - __clz((int)span), 0);
     __syncthreads();                         // (sel and this pass's histogram have been read)
+    if (tid < 3) sel[tid] = 0;
     hist4[tid] = make_uint4(0u, 0u, 0u, 0u);
     hist4[tid + kSelThreads] = make_uint4(0u, 0u, 0u, 0u);
     __syncthreads();

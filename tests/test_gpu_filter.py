@@ -119,6 +119,31 @@ def test_topk_long_rows(nb, N):
     assert np.array_equal(cout.cpu().numpy(), np.take_along_axis(coords, ref.astype(np.int64), axis=1))
 
 
+@pytest.mark.parametrize("N", [70, 4096, 5000, 8192, 16384, 20001, 32768])
+def test_topk_ties_and_wide_ranges(nb, N):
+    """What the short-row selection decides on the way: the k-th score more than 16 octaves below the largest one, or right at
+    that border; more equal scores than it ranks against each other, the k-th among them, above them and below them."""
+    rng = np.random.default_rng(N + 1)
+    u = (1.0 + rng.random((2, N))).astype(np.float32)
+    wide = u * np.float32(2.0) ** rng.integers(-40, 0, size=(2, N)).astype(np.float32)
+    tiny = u * np.float32(1e-30)                                # most scores far below a few large ones
+    tiny[:, ::16] = u[:, ::16]
+    border = u * np.float32(2.0) ** rng.integers(-17, -14, size=(2, N)).astype(np.float32)
+    border[:, N // 3] = 1.9999999
+    denormal = (u * np.float32(1e-39)).astype(np.float32)       # (all of one row, half of the other)
+    denormal[1, ::2] = 0.25
+    half = u.copy()
+    half[:, rng.permutation(N)[: N // 2]] = 1.5                 # half of them equal
+    two = np.float32(2.0) ** rng.integers(0, 2, size=(2, N)).astype(np.float32)
+    zero = u * (rng.random((2, N)) < 0.4).astype(np.float32)    # 60 % are zero
+    levels = (rng.integers(0, 40, size=(2, N)) / 40.0 + 1.0).astype(np.float32)
+    signed = rng.standard_normal((2, N)).astype(np.float32)
+    signed[:, rng.permutation(N)[: N // 2]] = -0.25
+    for s in (wide, tiny, border, denormal, half, two, zero, levels, signed, np.zeros((2, N), np.float32)):
+        for k in {1, N // 16, N // 4, N // 2, (6 * N) // 10, (9 * N) // 10, N - 1, N}:
+            topk_case(nb, s, k)
+
+
 def test_gather_and_coords_compaction_bit_exact(nb):
     rng = np.random.default_rng(4)
     B, N, C, k = 2, 500, 1024, 301
