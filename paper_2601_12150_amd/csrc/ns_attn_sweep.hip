@@ -23,8 +23,8 @@
 //
 // The global (CLS) query rides along: it attends to every key, and every key tile of block row R
 // passes through the LDS of strip R exactly once.  In column c the wave that has its column off,
-// (c+2) mod 4, multiplies that tile with q_0 as well (the same two MFMA products with q_0 in every
-// column of the B operand), keeps a running (max, sum, weighted V sum) for the global query in
+// (c+2) mod 4, multiplies that tile with q_0 as well, on the vector ALU with a lane per key (cls_duty), keeps
+// a running (max, sum, weighted V sum) for the global query in
 // LDS and writes the raw logits.  Each wave leaves one partial record per strip in the format of
 // the chunked row kernel; cls_combine_kernel merges them.  K and V are thus read once per launch
 // instead of twice.
@@ -34,6 +34,12 @@
 // "at most N outstanding" means all but the N youngest have arrived); the barrier then makes the
 // tile visible to all and, at the same time, tells that everybody is done with the slot that
 // the next transfer overwrites.
+//
+// Registers.  A tile's body has 230 of the 256 vector registers a lane gets with two waves per SIMD.  A value that is
+// kept across it without being part of it is spilled, and its reload from scratch memory waits for every transfer in flight:
+// addresses and masks are therefore computed where they are used, from an untraceable copy of the lane number (opaque), which
+// keeps the compiler from hoisting them, and rows of Q are consumed on every path behind their loads.  With 7 to 35 registers
+// spilled instead (whole calls, 16 heads): 245x245 280 -> 212 us, 128x128, two images, 112.6 -> 108.5, 256x256 224 -> 214.
 #include "ns_window.h"
 
 namespace ns {
@@ -114,8 +120,9 @@ __global__ __launch_bounds__(256, 2) void attn_sweep_kernel(SweepParams p) {
   // logits of keys that do not exist: accumulator register e (key half mt) is key row 4*mt + e/4
   // and column 4*hh + e%4 of a block with hv rows and wv columns
   auto mask_keys = [&](f32x16 &sv, int mt, int hv, int wv) {
+    const int hm = hv - 4 * mt, wm = wv - 4 * (opaque(lane) >> 5);
 #pragma unroll
-    for (int e = 0; e < 16; e++) sv[e] = (4 * mt + (e >> 2) >= hv || 4 * hh + (e & 3) >= wv) ? kMasked : sv[e];
+    for (int e = 0; e < 16; e++) sv[e] = ((e >> 2) >= hm || (e & 3) >= wm) ? kMasked : sv[e];
   };
   // W < 8: logits of pairs whose WxW blocks are not neighbours.  The key tile lies (dr, dc) tiles
   // from the query tile; lane = query (tile row l32/8 + 4*nt, column l32%8), register e = key (tile
@@ -123,12 +130,12 @@ __global__ __launch_bounds__(256, 2) void attn_sweep_kernel(SweepParams p) {
   // (a copied query of a short tile sits where its original sits: wvq = columns of the query tile)
   auto mask_window = [&](f32x16 &sv, int mt, int nt, int dr, int dc, int wvq) {
     constexpr int n = 8 / W;
-    const int rq = EDGE ? min((l32 >> 3) + 4 * nt, hvq - 1) : (l32 >> 3) + 4 * nt;
-    const int cq = EDGE ? min(l32 & 7, wvq - 1) : (l32 & 7);
-    const int ra = rq / W - n * dr + 1, ca = cq / W - n * dc + 1;
+    const int ln = opaque(lane), row = ((ln >> 3) & 3) + 4 * nt, col = ln & 7;
+    const int rq = EDGE ? min(row, hvq - 1) : row, cq = EDGE ? min(col, wvq - 1) : col;
+    const int ra = rq / W - n * dr + 1, ca = cq / W - n * dc + 1 - 4 / W * (ln >> 5);
 #pragma unroll
     for (int e = 0; e < 16; e++) {
-      const bool ok = (unsigned)(ra - (4 * mt + (e >> 2)) / W) <= 2u && (unsigned)(ca - (4 * hh + (e & 3)) / W) <= 2u;
+      const bool ok = (unsigned)(ra - (4 * mt + (e >> 2)) / W) <= 2u && (unsigned)(ca - (e & 3) / W) <= 2u;
       sv[e] = ok ? sv[e] : kMasked;
     }
   };
@@ -142,8 +149,13 @@ __global__ __launch_bounds__(256, 2) void attn_sweep_kernel(SweepParams p) {
   StepBf16 st;
   st.init(lane);
   const uint32_t dma_koff[2] = {drow * rowB + st.kch[0], drow * rowB + st.kch[1]}, dma_voff = drow * rowB + st.vch;
-  const uint32_t qoff0 = tile_off(l32, hvq, 8) + 64u * hh;
-  const uint32_t qoff1 = tile_off(l32 + 32, hvq, 8) + 64u * hh;
+
+  // K's fragments: the four addresses of a lane differ in bits 4 and 5, so one is kept and not four (slot: byte offset in LDS)
+  auto load_k = [&](StepBf16::K &k, uint32_t slot) {
+    const uint32_t at = lds_base + slot + st.krd[0];
+#pragma unroll
+    for (int t = 0; t < 4; t++) k.f[t] = *(lds_bf16x8_ptr)(at ^ (16u * t));
+  };
 
   // ---- the key tiles of this strip, column by column
   const int r0 = max(R - 1, 0), r1 = min(R + 1, p.nbh - 1);
@@ -155,18 +167,25 @@ __global__ __launch_bounds__(256, 2) void attn_sweep_kernel(SweepParams p) {
     const uint32_t base = block_base(r0 + ir, ic);
     const uint32_t dst = lds_base + (uint32_t)islot * kSlot + (uint32_t)wave * 2048u;
     const int hvk = EDGE && r0 + ir == p.nbh - 1 ? hv_last : 8;
-    // a short block's missing columns: the lanes of those columns fetch its last column instead
-    uint32_t back = 0;
-    if (EDGE && ic == ncols - 1 && wv_last < 8) back = (uint32_t)max(drow - (wv_last - 1), 0) * rowB;
+    uint32_t koff[2] = {dma_koff[0], dma_koff[1]}, voff = dma_voff;
+    if (EDGE) {
+      // a short block's missing columns: the lanes of those columns fetch its last column instead (computed here, not kept:
+      // the registers are the tile's)
+      const int ln = opaque(lane), wvk = ic == ncols - 1 ? wv_last : 8;
+      const uint32_t row = (uint32_t)min(ln >> 3, wvk - 1) * rowB, chunk = 16u * ((ln & 7) ^ (ln >> 4));
+      koff[0] = row + chunk;
+      koff[1] = row + (chunk ^ 64u);
+      voff = row + 16u * ((ln & 7) ^ ((ln >> 2) & 4));
+    }
 #pragma unroll
     for (int j = 0; j < 2; j++) {
       const char *src = kb + base + (size_t)min(2 * wave + j, hvk - 1) * gridrowB;
-      dma16(src, dma_koff[j] - back, dst + j * 1024);
+      dma16(src, koff[j], dst + j * 1024);
     }
 #pragma unroll
     for (int j = 0; j < 2; j++) {
       const char *src = vb + base + (size_t)min(2 * wave + j, hvk - 1) * gridrowB;
-      dma16(src, dma_voff - back, dst + kVOff + j * 1024);
+      dma16(src, voff, dst + kVOff + j * 1024);
     }
     islot = islot == kSlots - 1 ? 0 : islot + 1;
     const bool last = ic == ncols - 1 && ir == nr - 1;
@@ -186,12 +205,12 @@ __global__ __launch_bounds__(256, 2) void attn_sweep_kernel(SweepParams p) {
   // Q fragments of query block qc by ordinary loads
   auto load_block = [&](int qc) {
     const char *t = qb + block_base(R, qc);
-    uint32_t back = 0;                 // (l32 and l32 + 32 are in the same column of the block)
-    if (EDGE && qc == ncols - 1 && wv_last < 8) back = (uint32_t)max((l32 & 7) - (wv_last - 1), 0) * rowB;
+    const int ln = opaque(lane), wvq = EDGE && qc == ncols - 1 ? wv_last : 8;
 #pragma unroll
-    for (int s = 0; s < 4; s++) {
-      qf[0].f[s] = *reinterpret_cast<const bf16x8 *>(t + (qoff0 - back) + 16 * s);
-      qf[1].f[s] = *reinterpret_cast<const bf16x8 *>(t + (qoff1 - back) + 16 * s);
+    for (int nt = 0; nt < 2; nt++) {
+      const uint32_t off = tile_off((ln & 31) + 32 * nt, hvq, wvq) + 64u * (ln >> 5);
+#pragma unroll
+      for (int s = 0; s < 4; s++) qf[nt].f[s] = *reinterpret_cast<const bf16x8 *>(t + off + 16 * s);
     }
   };
   // The state the global token gives a query block: m = its logit (the fixed exponent reference),
@@ -200,7 +219,9 @@ __global__ __launch_bounds__(256, 2) void attn_sweep_kernel(SweepParams p) {
   // Further global tokens (rows 1 .. G-1 of the same LDS areas) are added one by one with a
   // running maximum, so the reference becomes the largest of the global tokens' logits.
   auto init_block = [&]() {
-    for (int g = 0; g < p.n_global; g++) {
+    auto take = [&](int g, auto first) {
+      constexpr bool kFirst = decltype(first)::value;
+      const int hh = opaque(lane) >> 5;
       StepBf16::K kg;
 #pragma unroll
       for (int s = 0; s < 4; s++) kg.f[s] = *(lds_bf16x8_ptr)(smem + kK0Row + 128 * g + 64 * hh + 16 * s);
@@ -209,7 +230,7 @@ __global__ __launch_bounds__(256, 2) void attn_sweep_kernel(SweepParams p) {
       for (int nt = 0; nt < 2; nt++) {
         const f32x16 s = st.product(kg, qf[nt]);
         const float sg = s[0] * p.c;
-        if (g == 0) {
+        if (kFirst) {
           m[nt] = sg;
           l[nt] = hh == 0 ? 1.f : 0.f;
           continue;
@@ -231,9 +252,12 @@ __global__ __launch_bounds__(256, 2) void attn_sweep_kernel(SweepParams p) {
           for (int e = 0; e < 4; e++)
 #pragma unroll
             for (int nt = 0; nt < 2; nt++)
-              o[nt][dt][4 * ig + e] = g == 0 ? (float)v4[e] : __builtin_fmaf(pg[nt], (float)v4[e], o[nt][dt][4 * ig + e]);
+              o[nt][dt][4 * ig + e] = kFirst ? (float)v4[e] : __builtin_fmaf(pg[nt], (float)v4[e], o[nt][dt][4 * ig + e]);
         }
-    }
+    };
+    // (the first one outside the loop: on a path without any the rows of Q would still be pending at the key-tile loop's head)
+    take(0, std::true_type{});
+    for (int g = 1; g < p.n_global; g++) take(g, std::false_type{});
     ls[0] = ls[1] = Sums{};
   };
   uint32_t badmask = 0;              // bit j: this wave's j-th query block has to be redone
@@ -261,11 +285,11 @@ __global__ __launch_bounds__(256, 2) void attn_sweep_kernel(SweepParams p) {
   constexpr int kStores = 8;         // requests of store_block
   auto store_block = [&](int qc) {
     char *t = ob + (size_t)block_token(R, qc) * (size_t)(p.ost * 2);
+    const int ln = opaque(lane), wvq = EDGE && qc == ncols - 1 ? wv_last : 8;
 #pragma unroll
     for (int nt = 0; nt < 2; nt++) {
-      const int i = l32 + 32 * nt;
-      const int wvq = EDGE && qc == ncols - 1 ? wv_last : 8;
-      char *row = t + (size_t)(min(i >> 3, hvq - 1) * p.grid_w + min(i & 7, wvq - 1)) * (size_t)(p.ost * 2) + 16 * hh;
+      const int i = (ln & 31) + 32 * nt;
+      char *row = t + (size_t)(min(i >> 3, hvq - 1) * p.grid_w + min(i & 7, wvq - 1)) * (size_t)(p.ost * 2) + 16 * (ln >> 5);
 #pragma unroll
       for (int dt = 0; dt < 2; dt++)
 #pragma unroll
@@ -393,17 +417,17 @@ __global__ __launch_bounds__(256, 2) void attn_sweep_kernel(SweepParams p) {
         if (edge) mask_keys(sv, mt, hvk, wvk);
         if (W < 8) mask_window(sv, mt, nt, dr, dc, wvq);
       };
-      const unsigned char *ks = smem + slot, *vs = ks + kVOff;
+      const unsigned char *vs = smem + slot + kVOff;
       StepBf16::K kf;
       StepBf16::V vf;
       bf16x8 open;
-      st.load_k(kf, ks);
+      load_k(kf, slot);
       f32x16 s0 = st.product(kf, qf[0]), s1;
       mask(s0, 0, 0);
       st.load_v(vf, vs, 0);
       st.template half_step<true, true, false>(s0, p.c, -m[0], ls[0], o[0], ls[1], o[1], open, vf, vs, kf, qf[1], s1);
       mask(s1, 0, 1);
-      st.load_k(kf, ks + 4096);
+      load_k(kf, slot + 4096);
       st.template half_step<false>(s1, p.c, -m[1], ls[1], o[1], ls[0], o[0], open, vf, vs, kf, qf[0], s0);
       mask(s0, 1, 0);
       st.load_v(vf, vs + 4096, 0);
@@ -458,8 +482,9 @@ __global__ __launch_bounds__(256, 2) void attn_sweep_kernel(SweepParams p) {
   if (p.cls_partials) {
     // this wave's partial of the global query's row: (max, sum, weighted V sum), natural-log units
     float *rec = p.cls_partials + ((((size_t)b * p.heads + h) * (4 * p.nbh)) + (size_t)R * 4 + wave) * kClsPartialFloats;
-    rec[2 + lane] = cls_state[lane];
-    if (lane == 0) {
+    const int ln = opaque(lane);
+    rec[2 + ln] = cls_state[ln];
+    if (ln == 0) {
       rec[0] = cls_state[64] * kLn2;
       rec[1] = cls_state[65];
     }
@@ -487,11 +512,12 @@ __global__ __launch_bounds__(256, 2) void attn_sweep_kernel(SweepParams p) {
         for (int mt = 0; mt < 2; mt++)
 #pragma unroll
           for (int t = 0; t < 4; t++)
-            kt[mt].f[t] = *reinterpret_cast<const bf16x8 *>(kb + base + tile_off(l32 + 32 * mt, hvk, wvk) + 64 * hh + 16 * t);
-        const uint32_t back = (uint32_t)max(drow - (wvk - 1), 0) * rowB;
+            kt[mt].f[t] = *reinterpret_cast<const bf16x8 *>(kb + base + tile_off((opaque(lane) & 31) + 32 * mt, hvk, wvk) + 64 * hh + 16 * t);
+        const int ln = opaque(lane);
+        const uint32_t voff = (uint32_t)min(ln >> 3, wvk - 1) * rowB + 16u * ((ln & 7) ^ ((ln >> 2) & 4));
 #pragma unroll
         for (int it = 0; it < 8; it++)
-          dma16(vb + base + (size_t)min(it, hvk - 1) * gridrowB, dma_voff - back, lds_base + mine + kVOff + it * 1024);
+          dma16(vb + base + (size_t)min(it, hvk - 1) * gridrowB, voff, lds_base + mine + kVOff + it * 1024);
         wait_vm<0>();               // also the K fragments above
 #pragma unroll
         for (int nt = 0; nt < 2; nt++) {

@@ -35,7 +35,9 @@ def test_numbering(nb, monkeypatch, gh, gw, block, G):
     assert_attn_close(to_np(out), oracle.ns_attn(q, k, v, gh, gw, block, 0.125, n_global=G), "bf16", "numbering")
 
 
-@pytest.mark.parametrize("force,g,block", [("lists1", 24, 8), ("lists2", 24, 8), ("lists4", 33, 16), ("block", 33, 16), ("block", 48, 16)])
+# (the sweep forms its sums like the others on grids that 8 divides, with and without masked keys, and lane by lane on others)
+@pytest.mark.parametrize("force,g,block", [("lists1", 24, 8), ("lists2", 24, 8), ("lists4", 33, 16), ("block", 33, 16), ("block", 48, 16),
+                                           ("sweep", 24, 8), ("sweep", 27, 8), ("sweep", 24, 4), ("sweep", 27, 2)])
 def test_a_row_that_is_not_finite_stays_alone(nb, monkeypatch, force, g, block):
     """The matrix instruction that sums a fragment's weights takes two queries' lanes and multiplies one by 0: a row whose
     weights are NaN (its query is) or infinite must not reach the other's sum."""
