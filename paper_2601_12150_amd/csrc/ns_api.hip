@@ -6,6 +6,7 @@
 
 #include "ns_common.h"
 #include <algorithm>
+#include <cmath>
 #include <mutex>
 #include <vector>
 
@@ -156,17 +157,21 @@ size_t ns_attn_workspace_bytes(const ns_attn_desc *desc) {
 // kernel's (ns_attn_ragged.hip, which shares a tile's keys out over one, two or four waves and takes the global rows
 // along) unless one of these is faster; the rest (fp32, other scales and strides) is the fp32 kernel's.
 //   - The sweep (8x8 blocks, one global token; also computes the global row on the way) needs a row of blocks per
-//     CU, and strips that fill the CUs twice over in whole rounds: 512 strips of 16 columns 118 against 137 us, 528
-//     strips of 11 columns 111 against 99 us.  7.2 us a column and round, 8 % more with short edge blocks.
+//     CU, and strips that fill the CUs twice over in whole rounds: 512 strips of 16 columns 105 against 127 us, 576 strips
+//     of 8 columns 85 against 74.  A full round takes 6.5 us a column, one that is filled to a fraction f 3.8 + 3.4 f.  (Over
+//     125 grids of 32 to 256 patches a side, 8 to 96 heads, the choice takes 0.4 % more than the better of the two; at worst
+//     11 % more, 120x120, 72 heads.)
 //     4x4 and 2x2 blocks it takes only where forced: its 3x3 tiles of 8x8 hold 4 or 5.8 times the keys a query sees,
 //     the window kernel's rectangle 1.8 or 2.3 times (245x245, 2x2 blocks: 249 against 169 us).  Several global
 //     tokens likewise: they cost it a pass over K and V of its own.
-//   - The block kernel (block sides that are multiples of 16, up to eight global tokens) does the same tile in less time
-//     but has 16x16 squares to fill the chip with, and works on short ones as on whole ones.  Where 16 divides the grid,
-//     three squares per CU are enough (128x128, 16 heads, 64x64 blocks: 1035 against 1234 us; 12 heads, three per CU:
-//     805 against 932; 2.25 per CU, 96x96: 434 against 408), and two for 16x16 blocks and one global token (96x96:
-//     103 against 107 us); with short squares five (120x120, four: 1008 against 997; 53x53 with 32x32 blocks, 512:
-//     139 against 100 us).
+//   - The block kernel (block sides that are multiples of 16, up to eight global tokens) does the same work in less time
+//     but has workgroups of 256 queries of a block to fill the chip with.  With 16x16 blocks one per CU is enough (64x64,
+//     16 heads: 45 against 50 us; 100x100, three per CU: 96 against 105; the worst, 48x48, 32 heads, five global tokens: 64
+//     against 60).  Those of larger blocks last long, and their last round is dear: three per CU (120x120, 16 heads, 64x64
+//     blocks, 3.6: 824 against 925; 72x72, 32 heads, 32x32 blocks, 2.6: 239 against 231), or two where no block is short
+//     (96x96, 16 heads, 32x32 blocks, 2.25: 224 against 249; 8 heads, 1.1: 158 against 134).  (Over 328 grids of 32 to 192 a
+//     side the choice takes 1.2 % more than the better of the two; a count of 16x16 squares, which priced copies that an
+//     earlier kernel filled short blocks with, took 4.0 %.)
 // NSATTN_KERNEL = sweep | block | lists | generic forces one of them where it applies; a digit 1, 2 or 4 behind
 // `lists` or `generic` also forces the waves per query tile.
 enum PatchKernel { PK_SWEEP, PK_BLOCK16, PK_RAGGED, PK_GENERIC };
@@ -187,14 +192,16 @@ static PatchKernel choose_patch_kernel(const ns_attn_desc &d, int &split) {
   const double images = (double)d.batch * d.heads, cus = device_cu_count();
   const double strips = images * ((d.grid_h + 7) / 8);
   if (sweep_ok && d.block == 8 && d.n_global == 1 && strips >= cus) {
-    const double rounds = strips / (2.0 * cus), edge = d.grid_h % 8 || d.grid_w % 8 ? 1.08 : 1.0;
-    const double sweep_us = ((d.grid_w + 7) / 8) * 7.2 * edge * (rounds <= 1.0 ? 1.0 : rounds + 0.35);
+    const double rounds = strips / (2.0 * cus), whole = std::floor(rounds), f = rounds - whole;
+    const double sweep_us = 8.0 + ((d.grid_w + 7) / 8) * (6.5 * whole + (f > 0.0 ? 3.8 + 3.4 * f : 0.0));
     if (ragged_attn_us(d) >= sweep_us) return PK_SWEEP;
   }
-  const double squares = images * ((d.grid_h + 15) / 16) * ((d.grid_w + 15) / 16);
-  const bool whole = d.grid_h % 16 == 0 && d.grid_w % 16 == 0;
-  const double enough = !whole ? 5.0 : (d.block == 16 && d.n_global == 1 ? 2.0 : 3.0);
-  if (block16_ok && squares >= enough * cus) return PK_BLOCK16;
+  if (block16_ok) {
+    const int nh = d.grid_h / d.block, nw = d.grid_w / d.block, eh = d.grid_h % d.block, ew = d.grid_w % d.block;
+    auto parts = [](int h, int w) { return (double)((h * w + 255) / 256); };
+    const double wgs = images * (nh * nw * parts(d.block, d.block) + nw * parts(eh, d.block) + nh * parts(d.block, ew) + parts(eh, ew));
+    if (wgs >= (d.block == 16 ? 1.0 : (eh == 0 && ew == 0 ? 2.0 : 3.0)) * cus) return PK_BLOCK16;
+  }
   return PK_RAGGED;
 }
 

@@ -26,10 +26,11 @@ bool ragged_attn_supported(const ns_attn_desc &d) {
          (long long)d.tokens * d.out_stride_t * 2 < 0x7fffffffLL;
 }
 
-// (a step of the cost model is 1.1 to 1.2 us: 128 x 128 x 16 heads x 2 with 8x8 blocks 113 steps, 127 us)
+// (a step of the cost model is 1.05 to 1.2 us: 128 x 128 x 16 heads x 2 with 8x8 blocks 113 steps, 127 us; where the sweep is the
+// alternative, many tiles, the upper end)
 double ragged_attn_us(const ns_attn_desc &d) {
   const WindowCost c = window_cost(d, 64);
-  return 1.15 * c.of(c.split()) + 6.0;
+  return 1.2 * c.of(c.split()) + 6.0;
 }
 
 ns_status launch_attn_ragged(const AttnArgs &a, float *logits, float *partials) {

@@ -181,12 +181,16 @@ def test_kernel_choice_policy(nb, monkeypatch):
 
     name = lambda d: nb.lib.ns_attn_patch_kernel_name(ctypes.byref(d)).decode()
     sweep, block16, window, fp32 = "attn_sweep_kernel", "attn_block16_kernel", "attn_mfma_ragged_kernel", "attn_generic_kernel"
-    # 8x8 blocks: rows of blocks ("strips") that fill 256 CUs twice over in whole rounds are the sweep's
+    # 8x8 blocks: rows of blocks ("strips") that fill 256 CUs twice over in whole rounds, or nearly, are the sweep's
     assert name(desc(2, 16, 128, 8)) == sweep                           # 512 strips of 16 columns
     assert name(desc(4, 16, 64, 8)) == sweep                            # 512 of 8
+    assert name(desc(4, 16, 128, 8)) == sweep                           # 1024 of 16: two rounds
+    assert name(desc(3, 24, 160, 8)) == sweep                           # 1440 of 20: 2.8
+    assert name(desc(1, 16, 245, 8)) == sweep                           # 496 of 31, short edge blocks
     assert name(desc(1, 16, 128, 8)) == window                          # 256 of 16: one round, half full
     assert name(desc(1, 16, 120, 8)) == window                          # 240: not one per CU
     assert name(desc(3, 16, 88, 8)) == window                           # 528 of 11: a second round for 16
+    assert name(desc(3, 24, 64, 8)) == window                           # 576 of 8
     assert name(desc(1, 4, 24, 8)) == window
     assert name(desc(1, 16, 16, 8)) == window
     assert name(desc(1, 2, 8, 8)) == window                             # a single block
@@ -197,22 +201,28 @@ def test_kernel_choice_policy(nb, monkeypatch):
     assert name(desc(1, 16, 245, 2)) == window
     assert name(desc(1, 16, 245, 3)) == window
     assert name(desc(1, 16, 245, 24)) == window                         # no multiple of 16
-    # multiples of 16: so many 16x16 squares per CU are the block kernel's: five, three where all are whole, two of
-    # these for 16x16 blocks and one global token
+    # multiples of 16: so many workgroups of 256 queries of a block per CU are the block kernel's: one with 16x16 blocks, else
+    # three, or two where the block divides the grid
     assert name(desc(1, 16, 256, 16)) == block16                        # 4096
-    assert name(desc(1, 16, 144, 16)) == block16                        # 1296
     assert name(desc(1, 16, 140, 16, gw=144)) == block16                # 1296, short edge blocks
-    assert name(desc(1, 16, 120, 16)) == window                         # 1024, short edge blocks
-    assert name(desc(1, 12, 128, 64)) == block16                        # 768
-    assert name(desc(1, 16, 96, 64)) == window                          # 576
-    assert name(desc(1, 16, 96, 16)) == block16
-    assert name(desc(1, 16, 96, 16, G=2)) == window
-    assert name(desc(1, 16, 80, 16)) == window                          # 400
+    assert name(desc(1, 16, 120, 16)) == block16                        # 1024, short edge blocks
+    assert name(desc(1, 16, 64, 16)) == block16                         # 256
+    assert name(desc(1, 16, 64, 16, G=5)) == block16
+    assert name(desc(1, 15, 64, 16)) == window                          # 240
+    assert name(desc(1, 16, 50, 16, gw=64)) == block16                  # 256: 12 whole blocks, 4 of 2 x 16
     assert name(desc(1, 2, 32, 16)) == window
-    assert name(desc(1, 16, 53, 32, gw=128)) == window                  # 512
+    assert name(desc(1, 12, 128, 64)) == block16                        # 768
+    assert name(desc(1, 8, 128, 64)) == block16                         # 512, no short block
+    assert name(desc(1, 7, 128, 64)) == window                          # 448
+    assert name(desc(1, 16, 96, 32)) == block16                         # 576, no short block
+    assert name(desc(1, 16, 96, 64)) == window                          # 576: 16 + 8 + 8 + 4 an image
+    assert name(desc(1, 16, 120, 64)) == block16                        # 912: 16 + 14 + 14 + 13
+    assert name(desc(1, 16, 53, 32, gw=128)) == window                  # 448: four of 4 and of 3
+    assert name(desc(1, 27, 53, 32, gw=128)) == window                  # 756
+    assert name(desc(1, 28, 53, 32, gw=128)) == block16                 # 784
     assert name(desc(1, 16, 245, 16)) == block16
     assert name(desc(1, 16, 245, 32)) == block16
-    assert name(desc(1, 16, 245, 64)) == block16                        # blocks of 4x4 squares
+    assert name(desc(1, 16, 245, 64)) == block16
     assert name(desc(1, 16, 256, 16, G=8)) == block16
     assert name(desc(1, 16, 256, 16, G=9)) == window
     # pruned sequences
