@@ -193,9 +193,8 @@ def test_sweep_on_grids_8_does_not_divide(nb, monkeypatch, gh, gw, gain):
 @pytest.mark.parametrize("gh,gw,gain", [(20, 27, 1.0), (37, 21, 1.0), (16, 50, 1.0), (33, 16, 1.0), (1, 1, 1.0), (5, 70, 1.0),
                                         (45, 60, 1.0), (19, 30, 14.0), (3, 3, 1.0)])
 def test_block_kernel_on_grids_16_does_not_divide(nb, monkeypatch, gh, gw, gain):
-    """The kernel for 16x16 blocks with short blocks at the right and bottom edge (query tiles
-    with few or no rows of their own, key tiles partly or wholly made of copies); gain 14 sends
-    edge tiles through the running-maximum path as well."""
+    """16x16 blocks on the block kernel, short ones at the right and bottom edge (waves with few or no queries, last key tiles
+    of a few keys); gain 14 sends edge tiles through the running-maximum path as well."""
     monkeypatch.setenv("NSATTN_KERNEL", "block")
     q, k, v = synth.small_case(67, 2, 3, 64, gh, gw, "bf16")
     q = synth.round_to_bf16(q * gain)
@@ -218,8 +217,8 @@ def test_block_kernel_on_grids_16_does_not_divide(nb, monkeypatch, gh, gw, gain)
                                               (128, 64, 64, 1.0), (100, 75, 64, 1.0), (150, 40, 48, 1.0), (5, 5, 64, 1.0),
                                               (50, 70, 32, 14.0), (16, 16, 32, 1.0)])
 def test_block_kernel_with_blocks_of_several_squares(nb, monkeypatch, gh, gw, block, gain):
-    """Block sides 32, 48 and 64 on the block kernel: a 16x16 square of queries walks the squares of
-    the 3x3 blocks around its own block.  Divisible grids, grids neither 16 nor the block side
+    """Block sides 32, 48 and 64 on the block kernel: several workgroups of 256 queries a block, each of which walks the
+    rectangle of the 3x3 blocks around it.  Divisible grids, grids neither 16 nor the block side
     divides, a block larger than the grid (dense attention), and the running-maximum path (gain 14)."""
     monkeypatch.setenv("NSATTN_KERNEL", "block")
     q, k, v = synth.small_case(69, 1, 2, 64, gh, gw, "bf16")
