@@ -51,7 +51,7 @@ constexpr int kBlockLds = kSlots * kSlot + 2048;
 
 #define NS_U(x) __builtin_amdgcn_readfirstlane(x)
 
-constexpr float kMasked = -1e30f;     // logit of a key number past the end
+constexpr float kMasked = -INFINITY;  // logit of a key number past the end: below any other, times any scale
 
 // grid: 8 XCDs x (row_xcd + inner_xcd + rim_xcd) workgroups of 256 threads, each 256 queries of a block or a chunk of the
 // global rows.  ROWS: 0: no global rows, 1: one, 2: several.

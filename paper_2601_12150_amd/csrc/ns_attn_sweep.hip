@@ -73,7 +73,7 @@ constexpr uint32_t kQ0Row = 3 * 16384 + 2048;  // q_0 likewise
 constexpr uint32_t kClsState = 3 * 16384 + 3072;   // per wave 512 B: o[64], m, l of the global query's partial
 constexpr uint32_t kClsWeight = 3 * 16384 + 3072 + 4 * 512;  // per wave 256 B: a tile's 64 weights
 constexpr float kEmptyMax = -1e30f;
-constexpr float kMasked = -1e30f;     // logit of a key that does not exist (edge blocks of a grid 8 does not divide)
+constexpr float kMasked = -INFINITY;  // logit of a key that does not exist (edge blocks of a grid 8 does not divide): below any other, times any scale
 
 
 #define NS_U(x) __builtin_amdgcn_readfirstlane(x)

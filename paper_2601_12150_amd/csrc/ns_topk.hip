@@ -87,8 +87,7 @@ __device__ __forceinline__ uint32_t row0_total(uint32_t x) {
 }
 
 // Threads 0..255 bring the number of candidates per digit; sel[0] = the digit that holds the
-// need-th largest candidate, sel[1] = how many keys of that digit are still needed, sel[2] = how
-// many candidates that digit holds.
+// need-th largest candidate, sel[1] = how many keys of that digit are still needed.
 __device__ __forceinline__ void choose_digit(uint32_t tot, uint32_t need, int tid, int wave, int lane,
                                              uint32_t *wtot, uint32_t *sel) {
   uint32_t above = 0;
@@ -103,7 +102,6 @@ __device__ __forceinline__ void choose_digit(uint32_t tot, uint32_t need, int ti
     if (above < need && need <= above + tot) {   // exactly one digit satisfies this
       sel[0] = (uint32_t)tid;
       sel[1] = need - above;
-      sel[2] = tot;
     }
   }
   __syncthreads();
@@ -410,7 +408,7 @@ __global__ __launch_bounds__(kSelThreads) void topk_digit_pass_kernel(const floa
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const float *sc = scores + (size_t)b * N;
   __shared__ uint32_t hist[kSelWaves][256];
-  __shared__ uint32_t wtot[4], sel[3], wabove[kSelWaves];
+  __shared__ uint32_t wtot[4], sel[2], wabove[kSelWaves];
   SelState st = {0u, (uint32_t)k};
   if (pass > 0)     // (the first rows of hist serve as its exchange buffer)
     st = advance_state(pass - 1, b, B, k, nchunk, part, state, c == 0, -1, tid, wave, lane, wtot, sel, hist);
@@ -460,7 +458,7 @@ __global__ __launch_bounds__(kSelThreads) void topk_place_kernel(const float *sc
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const float *sc = scores + (size_t)b * N;
   __shared__ uint32_t quarter[8][256];
-  __shared__ uint32_t wtot[4], sel[3];
+  __shared__ uint32_t wtot[4], sel[2];
   __shared__ uint32_t wgt[kSelWaves], weq[kSelWaves];
   const uint32_t above_mine = tid < c ? above[(size_t)b * nchunk + tid] : 0u;     // at most 128 chunks
   const SelState st = advance_state(3, b, B, k, nchunk, part, state, false, c, tid, wave, lane, wtot, sel, quarter);
@@ -541,7 +539,7 @@ static int multi_chunks(int N) { return (N + multi_kpt(N) * kSelThreads - 1) / (
 constexpr int kRegMaxKeys = 32;
 
 size_t topk_select_workspace_bytes(int B, int N) {
-  if (N <= kRegMaxKeys * kSelThreads) return 0;                    // one workgroup per image, state in registers and LDS
+  if (N <= kRegMaxKeys * kSelThreads) return 0;                    // one launch, state in registers and LDS
   return (size_t)4 * B * multi_chunks(N) * 256 * sizeof(uint32_t) + (size_t)4 * B * sizeof(SelState) +
          (size_t)B * multi_chunks(N) * sizeof(uint32_t);
 }

@@ -190,6 +190,21 @@ def test_sweep_on_grids_8_does_not_divide(nb, monkeypatch, gh, gw, gain):
     np.testing.assert_allclose(to_np(lse), ref_lse, rtol=0, atol=2e-5 * gain)
 
 
+@pytest.mark.parametrize("force,gh,gw,block", [("sweep", 20, 27, 8), ("sweep", 24, 24, 4), ("sweep", 27, 27, 2), ("block", 20, 27, 16),
+                                               ("block", 70, 53, 32)])
+@pytest.mark.parametrize("gain,scale", [(1.0, 1e-31), (1e16, 2e-33)])
+def test_keys_that_do_not_count_with_a_tiny_scale(nb, monkeypatch, force, gh, gw, block, gain, scale):
+    """Keys past the end and keys of blocks that are no neighbours have no weight, however small the scale and however far
+    below zero the other keys' products are."""
+    monkeypatch.setenv("NSATTN_KERNEL", force)
+    q, k, v = synth.small_case(71, 1, 2, 64, gh, gw, "bf16")
+    q, k = synth.round_to_bf16(q * np.float32(gain)), synth.round_to_bf16(k * np.float32(gain))
+    print("tiny scale: %s %dx%d block %d gain %g" % (force, gh, gw, block, gain), flush=True)
+    out = nb.ns_attn_forward(*(to_dev(a, "bf16") for a in (q, k, v)), gh, gw, block, scale)
+    torch.cuda.synchronize()
+    assert_attn_close(to_np(out), oracle.ns_attn(q, k, v, gh, gw, block, scale), "bf16", "tiny scale")
+
+
 @pytest.mark.parametrize("gh,gw,gain", [(20, 27, 1.0), (37, 21, 1.0), (16, 50, 1.0), (33, 16, 1.0), (1, 1, 1.0), (5, 70, 1.0),
                                         (45, 60, 1.0), (19, 30, 14.0), (3, 3, 1.0)])
 def test_block_kernel_on_grids_16_does_not_divide(nb, monkeypatch, gh, gw, gain):
