@@ -107,9 +107,6 @@ __device__ __forceinline__ void choose_digit(uint32_t tot, uint32_t need, int ti
   __syncthreads();
 }
 
-// (read from LDS, the same in every lane: on the scalar unit, so that what depends on it branches and compares there)
-__device__ __forceinline__ uint32_t uniform(uint32_t x) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)x); }
-
 constexpr int kDirectMax = 256;    // candidates that are ranked against each other instead of by a further digit
 constexpr int kDigitBits = 11, kDigits = 1 << kDigitBits;
 
@@ -218,15 +215,15 @@ __global__ __launch_bounds__(kSelThreads) void topk_select_reg_kernel(const floa
       if (above0 < left && left <= above0 + n0) { sel[0] = 2 * tid; sel[1] = left - above0; sel[2] = n0; }
       __syncthreads();
     }
-    const uint32_t nc = uniform(sel[2]);
+    const uint32_t nc = sel[2];
     if (__builtin_expect(nc == 0u, 0)) {                          // tau lies below the first range
       left -= row0_total(wsum[lane & (kSelWaves - 1)]);
       span = lo - 1u - least;
       lo = least;
     } else {
-      const uint32_t before = uniform(sel[0]) << shift;
+      const uint32_t before = sel[0] << shift;
       lo += before;
-      left = uniform(sel[1]);
+      left = sel[1];
       span = min(span - before, (1u << shift) - 1u);
     }
     tau = lo;
@@ -258,8 +255,8 @@ __global__ __launch_bounds__(kSelThreads) void topk_select_reg_kernel(const floa
         if (c != 0u && (n & 0xffffu) < left && left <= (n >> 16)) { sel[0] = c; sel[1] = left - (n & 0xffffu); }
       }
       __syncthreads();
-      tau = uniform(sel[0]);
-      left = uniform(sel[1]);
+      tau = sel[0];
+      left = sel[1];
       break;
     }
     if (!tried) {

@@ -190,6 +190,39 @@ def test_sweep_on_grids_8_does_not_divide(nb, monkeypatch, gh, gw, gain):
     np.testing.assert_allclose(to_np(lse), ref_lse, rtol=0, atol=2e-5 * gain)
 
 
+# sizes at either side of where the choice turns to the sweep (rounds of strips) and to the block kernel (workgroups per CU)
+@pytest.mark.parametrize("B,H,gh,gw,block,G,kernel", [
+    (4, 16, 128, 64, 8, 1, "attn_sweep_kernel"), (4, 16, 126, 61, 8, 1, "attn_sweep_kernel"), (2, 24, 100, 60, 8, 1, "attn_mfma_ragged_kernel"),
+    (1, 16, 64, 64, 16, 1, "attn_block16_kernel"), (1, 16, 100, 70, 16, 5, "attn_block16_kernel"),
+    (1, 15, 64, 64, 16, 1, "attn_mfma_ragged_kernel"), (2, 16, 64, 64, 32, 8, "attn_block16_kernel"), (1, 28, 53, 128, 32, 1, "attn_block16_kernel")])
+@pytest.mark.parametrize("fused", [False, True])
+def test_chosen_kernel_against_the_window_kernel(nb, monkeypatch, B, H, gh, gw, block, G, kernel, fused):
+    """The kernel that the sizes choose and the window kernel, which serves every such problem, agree: outputs to twice what
+    either may be from the truth (assert_attn_close: the two round their weights against different references), logits, log-sum-exps and scores to
+    fp32 sums in another order."""
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(gh * gw + H)
+    T = G + gh * gw
+    if fused:
+        x = torch.randn((B, T, 3, H, 64), generator=gen, device="cuda").to(torch.bfloat16)
+        q, k, v = (x[:, :, i].transpose(1, 2) for i in range(3))
+    else:
+        q, k, v = torch.randn((3, B, H, T, 64), generator=gen, device="cuda").to(torch.bfloat16)
+    monkeypatch.delenv("NSATTN_KERNEL", raising=False)
+    assert nb.ns_attn_patch_kernel_name(q, gh, gw, block, n_global=G) == kernel
+    print("choice: %d x %d heads, %dx%d block %d G=%d fused=%s" % (B, H, gh, gw, block, G, fused), flush=True)
+    got = nb.ns_attn_forward_scores(q, k, v, gh, gw, block, n_global=G)
+    monkeypatch.setenv("NSATTN_KERNEL", "lists")
+    ref = nb.ns_attn_forward_scores(q, k, v, gh, gw, block, n_global=G)
+    torch.cuda.synchronize()
+    out, want = to_np(got[0]), to_np(ref[0])
+    err, rms = np.abs(out - want), float(np.sqrt(np.mean(want ** 2)))
+    assert np.all(err <= 2 * (2e-2 * np.abs(want) + 2e-2 * rms)), (err.max(), rms)
+    assert np.sqrt(np.mean(err ** 2)) <= 2 * 1e-2 * rms
+    for a, b in zip(got[1:], ref[1:]):
+        np.testing.assert_allclose(to_np(a), to_np(b), rtol=2e-5, atol=2e-5)
+
+
 @pytest.mark.parametrize("force,gh,gw,block", [("sweep", 20, 27, 8), ("sweep", 24, 24, 4), ("sweep", 27, 27, 2), ("block", 20, 27, 16),
                                                ("block", 70, 53, 32)])
 @pytest.mark.parametrize("gain,scale", [(1.0, 1e-31), (1e16, 2e-33)])
