@@ -4,8 +4,12 @@
 // Bound: bf16 MFMA, 2*M*N*K FLOP.
 //
 // Why this shape.  A wave that owns a 64x64 piece of the output reads 1 KB of fragments from LDS
-// per v_mfma_f32_32x32x16_bf16, which is exactly the LDS bandwidth of a CU at full MFMA rate; with
-// a 128 x 128 piece per wave (4 x 4 MFMA tiles, 256 accumulator registers) it is half of that.
+// per 32 matrix-pipe cycles, which is exactly the LDS bandwidth of a CU at full MFMA rate; with
+// a 128 x 128 piece per wave (8 x 8 MFMA tiles, 256 accumulator registers) it is half of that.
+// v_mfma_f32_16x16x32_bf16 and not 32x32x16: the chip is limited by power under either (the clock falls from 2.4 to
+// 1.7 GHz), and the smaller one takes less of it: products of random values from registers alone sustain 2.07 against 1.80 PFLOP/s,
+// 1.94 where both operands change with every instruction.  Whole launches, 32x32x16 -> 16x16x32, us: 16385 x 3072 x 1024 91.0 ->
+// 83.7, 16385 x 1024 x 4096 + residual 109.4 -> 100.3, 9832 x 4096 x 1024 + GELU 90.9 -> 84.5.
 // So: 4 waves per workgroup, one per SIMD, each with up to 512 registers; 256 (n) x 256 (m) per
 // workgroup; k in slices of 64 by direct global -> LDS transfers (rows of 128 bytes: a transfer then uses whole
 // cache lines, which moves the same bytes in 3/4 of the time that 64-byte rows take).
@@ -23,15 +27,15 @@
 // Rows.  With M = 256 q + rem and 0 < rem <= 32 (a full-grid sequence: rem is the number of
 // global tokens in the batch) the last row tile takes the extra rows as a ninth 32-row slab
 // instead of opening a nearly empty tile row, which would cost a whole extra round on a launch
-// that otherwise fills the chip exactly once; the slab's 8 MFMA tiles are shared out two per
+// that otherwise fills the chip exactly once; the slab's 32 MFMA tiles are shared out eight per
 // wave.  Any other remainder gets a tile of its own whose waves only compute the slabs that
 // hold rows.  Where M / 256 row tiles leave many CUs without work in the last round (a pruned
 // sequence: 39 x 4 tiles on 256 CUs), tiles of 192 rows (three slabs per wave) are used instead
 // when that shortens the launch.
 //
-// Measured (us, two slots per operand and an epilogue that waits for each of its loads -> this): 16385 x 3072 x 1024 111 -> 98,
-// 16385 x 1024 x 1024 + residual 49 -> 37, 16385 x 4096 x 1024 + GELU 177 -> 148, 16385 x 1024 x 4096 + residual 128 -> 114;
-// 9832 rows: 70 -> 61, 31 -> 24, 113 -> 96, 89 -> 73.
+// Measured (us, two slots per operand, 32x32x16 products and an epilogue that waits for each of its loads -> this): 16385 x 3072 x 1024
+// 111 -> 84, 16385 x 1024 x 1024 + residual 49 -> 32, 16385 x 4096 x 1024 + GELU 177 -> 131, 16385 x 1024 x 4096 + residual 128 -> 100;
+// 9832 rows: 70 -> 55, 31 -> 21, 113 -> 84, 89 -> 63.
 #include "ns_common.h"
 #include <type_traits>
 
@@ -88,15 +92,12 @@ struct Epi {
 #pragma unroll
     for (int ps = 0; ps < PASSES; ps++) res[ps] = *reinterpret_cast<const uint4 *>(p.r + at(p, mbase, nbase, ps, lane));
   }
-  static __device__ __forceinline__ void stage(unsigned char *ebuf, const f32x16 *const (&slab)[NS], int lane) {
+  // half: tokens 0..15 or 16..31 of the slab.  (A row of the staging area is four banks further than the one before: 16
+  // lanes write 64 different banks.)
+  static __device__ __forceinline__ void stage(unsigned char *ebuf, const f32x4 *(&tile)[2 * NS], int half, int lane) {
 #pragma unroll
-    for (int ti = 0; ti < NS; ti++)
-#pragma unroll
-      for (int g = 0; g < 4; g++) {
-        const f32x16 &a = *slab[ti];
-        const f32x4 v = {a[4 * g], a[4 * g + 1], a[4 * g + 2], a[4 * g + 3]};
-        *reinterpret_cast<f32x4 *>(ebuf + (lane & 31) * kEpiRow + (32 * ti + 8 * g + 4 * (lane >> 5)) * 4) = v;
-      }
+    for (int ti = 0; ti < 2 * NS; ti++)
+      *reinterpret_cast<f32x4 *>(ebuf + (16 * half + (lane & 15)) * kEpiRow + (16 * ti + 4 * (lane >> 4)) * 4) = *tile[ti];
   }
   // finishes the slab staged in ebuf; `then` is called when the first values have been asked for
   template <bool GELU, bool RES, class F>
@@ -151,7 +152,7 @@ __device__ __forceinline__ void gemm256_wave(const Gemm256Params &p, unsigned ch
   constexpr int kSlots = EXT ? 2 : 3;        // LDS slots for weight slices; token slices have two
   constexpr int kX = EXT ? kStageX + 4096 : kStageX, kW = 2 * kX;   // bytes of a token slot; the weight slots lie behind
   static_assert(kW + kSlots * kStageW <= kGemmLds, "slots");
-  const int l32 = lane & 31, hh = lane >> 5;
+  const int l16 = lane & 15;
   const int wm = wave >> 1, wn = wave & 1;
   const uint32_t lds0 = (uint32_t)(size_t)((__attribute__((address_space(3))) unsigned char *)smem);
   const uint32_t rowB = (uint32_t)p.K * 2u;
@@ -181,53 +182,62 @@ __device__ __forceinline__ void gemm256_wave(const Gemm256Params &p, unsigned ch
   };
   auto issue_x = [&](int kt, int j) { dma16(ab + (size_t)kt * 128, xoff[j], lds0 + (kt & 1) * kX + (xreq0 + j) * 1024); };
 
-  // ---- fragment reads: lane (row l32 of a 32-row slab, half hh) reads logical chunk 2*ks + hh of
-  // k-step ks = 0..3, i.e. physical chunk (2*ks + hh) ^ ((l32 >> 1) & 7) (slabs start at multiples of 32 rows)
-  unsigned char *wrd[4], *xrd[4];
+  // ---- fragment reads: lane (row l16 of a 16-row tile, quarter lane/16) reads logical chunk 4*h + lane/16 of
+  // half h of the slice, i.e. physical chunk (4*h + lane/16) ^ (l16 >> 1) (tiles start at multiples of 16 rows)
+  unsigned char *wrd[2], *xrd[2];
 #pragma unroll
-  for (int ks = 0; ks < 4; ks++) {
-    const int ch = 16 * ((2 * ks + hh) ^ ((l32 >> 1) & 7));
-    wrd[ks] = smem + kW + (wn * 128 + l32) * 128 + ch;
-    xrd[ks] = smem + (wm * WROWS + l32) * 128 + ch;
+  for (int h = 0; h < 2; h++) {
+    const int ch = 16 * ((4 * h + (lane >> 4)) ^ (l16 >> 1));
+    wrd[h] = smem + kW + (wn * 128 + l16) * 128 + ch;
+    xrd[h] = smem + (wm * WROWS + l16) * 128 + ch;
   }
   const int eoff = (256 - wm * WROWS) * 128;           // from xrd to the ninth slab
-  bf16x8 fw[2][4], fx[4][NT], fe[4];
-  f32x16 acc[4][NT];   // [weight slab][token slab]: register e = n 8*(e/4) + 4*hh + e%4, lane = token l32
+  bf16x8 fw[2][4], fx[2][2 * NT], fe[2][2];
+  f32x4 acc[8][2 * NT];   // [16 weights][16 tokens]: register e = n 4*(lane/16) + e, token l16
 #pragma unroll
-  for (int ti = 0; ti < 4; ti++)
+  for (int ti = 0; ti < 8; ti++)
 #pragma unroll
-    for (int tj = 0; tj < NT; tj++)
+    for (int tj = 0; tj < 2 * NT; tj++) {
+      acc[ti][tj] = {0.f, 0.f, 0.f, 0.f};
+      asm volatile("" : "+a"(acc[ti][tj]));   // (64 separate values: as copies of one zero the compiler moves them about behind the loop)
+    }
+  f32x4 acce[4][2];       // weights 64*WM + 16*i, ninth slab's tokens 16*j
 #pragma unroll
-      for (int e = 0; e < 16; e++) acc[ti][tj][e] = 0.f;
-  f32x16 acce[2];      // ninth token slab x weight slabs 2*WM, 2*WM+1
+  for (int i = 0; i < 4; i++)
 #pragma unroll
-  for (int e = 0; e < 16; e++) { acce[0][e] = 0.f; acce[1][e] = 0.f; }
+    for (int j = 0; j < 2; j++)
+#pragma unroll
+      for (int e = 0; e < 4; e++) acce[i][j][e] = 0.f;
   // (their products are asm, for which the compiler pads no hazard: a matrix instruction right behind the vector instruction
   // that clears its accumulator reads what the register held before.  So they are cleared here, not next to it.)
-  if (EXT) asm volatile("s_nop 1" : "+v"(acce[0]), "+v"(acce[1]));
+  if (EXT)
+#pragma unroll
+    for (int i = 0; i < 4; i++) asm volatile("s_nop 1" : "+v"(acce[i][0]), "+v"(acce[i][1]));
 
-  // One k-step: the MFMAs of fragments (fw[ks & 1], fx[ks]) with, spread between them, the LDS reads of
+  // One quarter of a slice: half ks/2 of its k with weights 64*(ks & 1) .. + 63 of the wave's 128, i.e. the MFMAs of fragments
+  // (fw[ks & 1], fx[ks >> 1]) with, spread between them, the LDS reads of
   // later fragments and the transfers of a later slice, so that neither the reads' latency nor the issue of the
   // transfers is exposed.  The fences keep this order: the scheduler would sink the reads below the MFMAs
-  // that do not need them.
-  //   ks 0: reads W(t, 1), X(t, 2), X(t, 3)       ks 1: reads W(t, 2); transfers X(t+2)
-  //   ks 2: reads W(t, 3)                         ks 3: reads W(t+1, 0), X(t+1, 0), X(t+1, 1); transfers W(t+kSlots)
-  constexpr int XF = NTJ + (EXT ? 1 : 0);              // token fragments of a k-step
-  auto read_w = [&](int ks, int slot, int ti) { fw[ks & 1][ti] = *(lds_bf16x8_ptr)(wrd[ks] + slot * kStageW + ti * 4096); };
-  auto read_x = [&](int ks, int kt, int tj) {
-    if (tj < NTJ) fx[ks][tj] = *(lds_bf16x8_ptr)(xrd[ks] + (kt & 1) * kX + tj * 4096);
-    else fe[ks] = *(lds_bf16x8_ptr)(xrd[ks] + (kt & 1) * kX + eoff);
+  // that do not need them.  A weight fragment stays for all token fragments: an operand that does not change costs less power.
+  //   ks 0: reads W(t, 1), X(t, half 1)           ks 1: reads W(t, 2); transfers X(t+2)
+  //   ks 2: reads W(t, 3)                         ks 3: reads W(t+1, 0), X(t+1, half 0); transfers W(t+kSlots)
+  constexpr int XF = 2 * (NTJ + (EXT ? 1 : 0));        // token fragments of half a slice
+  auto read_w = [&](int ks, int slot, int i) {
+    fw[ks & 1][i] = *(lds_bf16x8_ptr)(wrd[ks >> 1] + slot * kStageW + (4 * (ks & 1) + i) * 2048);
+  };
+  auto read_x = [&](int h, int kt, int tj) {
+    if (tj < 2 * NTJ) fx[h][tj] = *(lds_bf16x8_ptr)(xrd[h] + (kt & 1) * kX + tj * 2048);
+    else fe[h][tj - 2 * NTJ] = *(lds_bf16x8_ptr)(xrd[h] + (kt & 1) * kX + eoff + (tj - 2 * NTJ) * 2048);
   };
   auto kstep = [&](auto ks_c, auto read_c, auto move_c, int t, int slot, int slot_next) {
     constexpr int ks = decltype(ks_c)::value;
     constexpr bool kRead = decltype(read_c)::value, kMove = decltype(move_c)::value;
-    constexpr int reads = !kRead ? 0 : 4 + (ks == 0 || ks == 3 ? 2 * XF : 0);
+    constexpr int reads = !kRead ? 0 : 4 + (ks == 0 || ks == 3 ? XF : 0);
     constexpr int moves = !kMove ? 0 : (ks == 1 ? XREQ : (ks == 3 ? 8 : 0));
-    constexpr int mfmas = 4 * NTJ, groups = mfmas > 0 ? mfmas : 1;
+    constexpr int mfmas = 8 * NTJ, groups = mfmas > 0 ? mfmas : 1;
     auto read = [&](int i) {
       if (i < 4) read_w((ks + 1) & 3, ks == 3 ? slot_next : slot, i);
-      else if (i < 4 + XF) read_x(ks == 0 ? 2 : 0, ks == 0 ? t : t + 1, i - 4);
-      else read_x(ks == 0 ? 3 : 1, ks == 0 ? t : t + 1, i - 4 - XF);
+      else read_x(ks == 0 ? 1 : 0, ks == 0 ? t : t + 1, i - 4);
     };
     auto move = [&](int j) {
       if (ks == 1) issue_x(t + 2, j);
@@ -235,26 +245,38 @@ __device__ __forceinline__ void gemm256_wave(const Gemm256Params &p, unsigned ch
     };
 #pragma unroll
     for (int i = 0; i < groups; i++) {
-      // (reads early in the step, a transfer to every second MFMA)
+      // (reads early in the step, a transfer to every fourth MFMA)
 #pragma unroll
       for (int r = 0; r < reads; r++)
         if ((2 * reads <= groups ? 2 * r : r * groups / reads) == i) read(r);
-      if (mfmas > 0) acc[i / NT][i % NT] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fw[ks & 1][i / NT], fx[ks][i % NT], acc[i / NT][i % NT], 0, 0, 0);
+      // (asm: with the builtin, whose result may lie elsewhere than its accumulator, the compiler rotates the 256 registers through
+      // moves in every slice.  It pads no hazard for asm: nothing but these products and reads from LDS, which the compiler
+      // waits for, touches an operand inside the loop.)
+      if (mfmas > 0) {
+        f32x4 &c = acc[4 * (ks & 1) + i / (2 * NT)][i % (2 * NT)];
+        const bf16x8 &w = fw[ks & 1][i / (2 * NT)], &x = fx[ks >> 1][i % (2 * NT)];
+        asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(w), "v"(x));
+      }
 #pragma unroll
       for (int j = 0; j < moves; j++)
         if (j * groups / moves == i) move(j);
       __builtin_amdgcn_sched_barrier(0);
     }
-    if (EXT) {
+    if (EXT && (ks & 1) == WM) {
       // The compiler keeps every accumulator of its own MFMAs in the 256 accumulator registers;
-      // 18 of them do not fit and would be rotated through moves in every iteration.  These two
-      // are pinned to ordinary vector registers instead.  (Each is next touched 17 MFMAs later,
+      // 8 of 64 + 8 do not fit and would be rotated through moves in every iteration.  These
+      // are pinned to ordinary vector registers instead.  (Each is next touched two quarters later,
       // and read by other instructions only after the loop; the wait states cover a fragment or accumulator that a
       // vector instruction has just written.)
-      f32x16 &a0 = acce[0], &a1 = acce[1];
-      const bf16x8 &w0 = fw[ks & 1][2 * WM], &w1 = fw[ks & 1][2 * WM + 1], &x = fe[ks];
-      asm volatile("s_nop 1\n\tv_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(a0) : "v"(w0), "v"(x));
-      asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(a1) : "v"(w1), "v"(x));
+      asm volatile("s_nop 1");
+#pragma unroll
+      for (int i = 0; i < 4; i++)
+#pragma unroll
+        for (int j = 0; j < 2; j++) {
+          f32x4 &c = acce[i][j];
+          const bf16x8 &w = fw[ks & 1][i], &x = fe[ks >> 1][j];
+          asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(c) : "v"(w), "v"(x));
+        }
     }
   };
   // every wave's reads so far have arrived, and so has what it has waited for
@@ -285,9 +307,7 @@ __device__ __forceinline__ void gemm256_wave(const Gemm256Params &p, unsigned ch
 #pragma unroll
   for (int ti = 0; ti < 4; ti++) read_w(0, 0, ti);
 #pragma unroll
-  for (int ks = 0; ks < 2; ks++)
-#pragma unroll
-    for (int tj = 0; tj < XF; tj++) read_x(ks, 0, tj);
+  for (int tj = 0; tj < XF; tj++) read_x(0, 0, tj);
   // one slice; `ahead`: how many of the slices t+1 .. t+kSlots exist
   auto slice = [&](auto ahead_c, int t, int slot, int slot_next) {
     constexpr int ahead = decltype(ahead_c)::value;
@@ -333,24 +353,36 @@ __device__ __forceinline__ void gemm256_wave(const Gemm256Params &p, unsigned ch
   if (RES && NTJ > 0) E4::load_residual(p, mw, nw, lane, res[0]);
   slice(K0{}, t, slot, 0);
   // (the accumulators are final here: left to itself the compiler sinks the last products into the epilogue's slabs,
-  // and their operands are spilled on the way)
+  // and their operands are spilled on the way; the first of these also waits for the last product)
 #pragma unroll
-  for (int ti = 0; ti < 4; ti++)
+  for (int ti = 0; ti < 8; ti++)
 #pragma unroll
-    for (int tj = 0; tj < NTJ; tj++) asm volatile("" : "+a"(acc[ti][tj]));
-  if (EXT) asm volatile("s_nop 15\n\ts_nop 7" : "+v"(acce[0]), "+v"(acce[1]));   // (their products are asm: no one else pads)
+    for (int tj = 0; tj < 2 * NTJ; tj++) {
+      if (ti == 0 && tj == 0) asm volatile("s_nop 15" : "+a"(acc[0][0]));
+      else asm volatile("" : "+a"(acc[ti][tj]));
+    }
+  if (EXT)
+#pragma unroll
+    for (int i = 0; i < 4; i++) asm volatile("s_nop 15" : "+v"(acce[i][0]), "+v"(acce[i][1]));   // (their products are asm: no one else pads)
   __syncthreads();             // every wave is done with the stages: they become the epilogue's staging area
 
   // ---- epilogue, one 32-token slab at a time
   unsigned char *const ebuf[2] = {smem + wave * kEpiWave, smem + (4 + wave) * kEpiWave};
   static_assert(8 * kEpiWave <= kGemmLds, "two staged slabs per wave");
   auto stage = [&](int tj) {
-    if (tj < NTJ) {
-      const f32x16 *const slab[4] = {&acc[0][tj], &acc[1][tj], &acc[2][tj], &acc[3][tj]};
-      E4::stage(ebuf[tj & 1], slab, lane);
-    } else if (EXT) {
-      const f32x16 *const slab[2] = {&acce[0], &acce[1]};
-      E2::stage(ebuf[tj & 1], slab, lane);
+#pragma unroll
+    for (int j = 0; j < 2; j++) {
+      if (tj < NTJ) {
+        const f32x4 *tile[8];
+#pragma unroll
+        for (int i = 0; i < 8; i++) tile[i] = &acc[i][2 * tj + j];
+        E4::stage(ebuf[tj & 1], tile, j, lane);
+      } else if (EXT) {
+        const f32x4 *tile[4];
+#pragma unroll
+        for (int i = 0; i < 4; i++) tile[i] = &acce[i][j];
+        E2::stage(ebuf[tj & 1], tile, j, lane);
+      }
     }
   };
   stage(0);
