@@ -245,6 +245,11 @@ bool gemm256_supported(int M, int N, int K);
 ns_status launch_gemm256(const uint16_t *a, const uint16_t *w, const float *bias, const uint16_t *r,
                          uint16_t *c, int M, int N, int K, bool gelu, hipStream_t s, int batch = 1,
                          long long a_stride = 0, long long c_stride = 0);
+// ... with tiles of 128 x 32 tj, tj = 2 .. 6 (ns_gemm128.hip)
+bool gemm128_supported(int N, int K);
+ns_status launch_gemm128(const uint16_t *a, const uint16_t *w, const float *bias, const uint16_t *r,
+                         uint16_t *c, int M, int N, int K, bool gelu, hipStream_t s, int tj, int batch = 1,
+                         long long a_stride = 0, long long c_stride = 0);
 
 // ws: topk_select_workspace_bytes(B, N) bytes, 16-byte aligned (nothing for short score rows)
 size_t topk_select_workspace_bytes(int B, int N);

@@ -36,19 +36,14 @@
 // Measured (us, two slots per operand, 32x32x16 products and an epilogue that waits for each of its loads -> this): 16385 x 3072 x 1024
 // 111 -> 84, 16385 x 1024 x 1024 + residual 49 -> 32, 16385 x 4096 x 1024 + GELU 177 -> 131, 16385 x 1024 x 4096 + residual 128 -> 100;
 // 9832 rows: 70 -> 55, 31 -> 21, 113 -> 84, 89 -> 63.
-#include "ns_common.h"
+#include "ns_gemm.h"
 #include <type_traits>
 
 namespace ns {
 
 namespace {
 
-struct Gemm256Params {
-  const uint16_t *a, *w, *r;
-  const float *bias;
-  uint16_t *c;
-  int M, N, K;
-  int gelu;
+struct Gemm256Params : GemmIo {
   int ntn, ntm;      // tiles along n and m
   int extended;      // the last row tile has 288 rows
   int n256;          // the first n256 rows of tiles have 256 token rows, the others 192 (three slabs per wave):
@@ -60,82 +55,7 @@ struct Gemm256Params {
 constexpr int kStageW = 256 * 128;           // bytes: 256 weight rows x 64 k
 constexpr int kStageX = 256 * 128;           // 256 token rows x 64 k
 constexpr int kGemmLds = 2 * kStageX + 3 * kStageW;
-constexpr int kEpiRow = 528;                 // bytes per staged output row: 128 floats + 16 pad
-constexpr int kEpiWave = 32 * kEpiRow;
-
-typedef bf16x8 __attribute__((address_space(3))) *lds_bf16x8_ptr;
-
-
-
-// ---- epilogue of NS weight slabs x one 32-token slab: accumulators -> LDS (fp32, [token][32*NS n]) -> lanes that
-// own 8 consecutive n of one token: + bias, GELU, + residual, one 16-byte store.  A wave has its SIMD to itself here, so
-// every latency it waits for is lost: the next slab is staged (two buffers) and its residual rows are requested before
-// this one is finished, the staged values are read four passes ahead, and nothing is loaded behind a store that
-// would have to be waited for with it (one in-order counter).  Lanes past the last row, whose inputs repeat it, store
-// its values once more, to the same place: no branch around the stores.  Against an epilogue that staged, loaded and read each
-// slab and pass in turn (32 LDS latencies and four drained stores a tile; whole calls): 16385 x 1024 x 1024 + residual 38.0 -> 36.7 us,
-// 16385 x 4096 x 1024 + GELU 153 -> 148; 9832 rows: 26.0 -> 24.0 and 100 -> 96, x 3072 x 1024 63 -> 61; K = 4096 as before.
-template <int NS>
-struct Epi {
-  static constexpr int LPT = NS * 4;                          // lanes per token row
-  static constexpr int TPP = 64 / LPT, PASSES = LPT / 2;      // tokens per pass
-  static constexpr int AHEAD = 4;
-  static __device__ __forceinline__ int col(int nbase, int lane) { return nbase + 8 * (lane & (LPT - 1)); }
-  static __device__ __forceinline__ size_t at(const Gemm256Params &p, int mbase, int nbase, int ps, int lane) {
-    return (size_t)min(mbase + TPP * ps + lane / LPT, p.M - 1) * p.N + col(nbase, lane);
-  }
-  static __device__ __forceinline__ void load_bias(const Gemm256Params &p, int nbase, int lane, f32x4 (&b)[2]) {
-    b[0] = *reinterpret_cast<const f32x4 *>(p.bias + col(nbase, lane));
-    b[1] = *reinterpret_cast<const f32x4 *>(p.bias + col(nbase, lane) + 4);
-  }
-  static __device__ __forceinline__ void load_residual(const Gemm256Params &p, int mbase, int nbase, int lane, uint4 (&res)[PASSES]) {
-#pragma unroll
-    for (int ps = 0; ps < PASSES; ps++) res[ps] = *reinterpret_cast<const uint4 *>(p.r + at(p, mbase, nbase, ps, lane));
-  }
-  // half: tokens 0..15 or 16..31 of the slab.  (A row of the staging area is four banks further than the one before: 16
-  // lanes write 64 different banks.)
-  static __device__ __forceinline__ void stage(unsigned char *ebuf, const f32x4 *(&tile)[2 * NS], int half, int lane) {
-#pragma unroll
-    for (int ti = 0; ti < 2 * NS; ti++)
-      *reinterpret_cast<f32x4 *>(ebuf + (16 * half + (lane & 15)) * kEpiRow + (16 * ti + 4 * (lane >> 4)) * 4) = *tile[ti];
-  }
-  // finishes the slab staged in ebuf; `then` is called when the first values have been asked for
-  template <bool GELU, bool RES, class F>
-  static __device__ __forceinline__ void emit(const Gemm256Params &p, const unsigned char *ebuf, const f32x4 (&b)[2],
-                                              const uint4 (&res)[PASSES], int mbase, int nbase, int lane, F then) {
-    const unsigned char *src = ebuf + lane / LPT * kEpiRow + 32 * (lane & (LPT - 1));
-    f32x4 v[AHEAD][2];
-    auto fetch = [&](int ps, f32x4 (&x)[2]) {
-      x[0] = *reinterpret_cast<const f32x4 *>(src + TPP * kEpiRow * ps);
-      x[1] = *reinterpret_cast<const f32x4 *>(src + TPP * kEpiRow * ps + 16);
-    };
-#pragma unroll
-    for (int i = 0; i < AHEAD; i++) fetch(i, v[i]);
-    then();
-    auto pass = [&](int ps, f32x4 (&x)[2], const uint4 &r4) {
-      float o[8];
-#pragma unroll
-      for (int i = 0; i < 8; i++) o[i] = x[i >> 2][i & 3] + b[i >> 2][i & 3];
-      fetch(min(ps + AHEAD, PASSES - 1), x);
-      if (GELU) gelu_erf8(o);
-      if (RES) {
-        o[0] += bf16_lo(r4.x); o[1] += bf16_hi(r4.x); o[2] += bf16_lo(r4.y); o[3] += bf16_hi(r4.y);
-        o[4] += bf16_lo(r4.z); o[5] += bf16_hi(r4.z); o[6] += bf16_lo(r4.w); o[7] += bf16_hi(r4.w);
-      }
-      const uint4 u = {pack_bf16(o[0], o[1]), pack_bf16(o[2], o[3]), pack_bf16(o[4], o[5]), pack_bf16(o[6], o[7])};
-      *reinterpret_cast<uint4 *>(p.c + at(p, mbase, nbase, ps, lane)) = u;
-    };
-    if (RES) {
-#pragma unroll
-      for (int ps = 0; ps < PASSES; ps++) pass(ps, v[ps % AHEAD], res[ps]);
-    } else {
-#pragma unroll 1
-      for (int ps = 0; ps < PASSES; ps += AHEAD)
-#pragma unroll
-        for (int i = 0; i < AHEAD; i++) pass(ps + i, v[i], res[0]);
-    }
-  }
-};
+constexpr int kEpiWave = Epi<4>::kBytes;
 
 // One wave's work on one workgroup tile.  NTJ: 32-row token slabs of its own 128 rows that this
 // wave computes (0..4).  EXT: the tile has a ninth token slab (rows 256..287); this wave then
@@ -194,25 +114,7 @@ __device__ __forceinline__ void gemm256_wave(const Gemm256Params &p, unsigned ch
   const int eoff = (256 - wm * WROWS) * 128;           // from xrd to the ninth slab
   bf16x8 fw[2][4], fx[2][2 * NT], fe[2][2];
   f32x4 acc[8][2 * NT];   // [16 weights][16 tokens]: register e = n 4*(lane/16) + e, token l16
-#pragma unroll
-  for (int ti = 0; ti < 8; ti++)
-#pragma unroll
-    for (int tj = 0; tj < 2 * NT; tj++) {
-      acc[ti][tj] = {0.f, 0.f, 0.f, 0.f};
-      asm volatile("" : "+a"(acc[ti][tj]));   // (64 separate values: as copies of one zero the compiler moves them about behind the loop)
-    }
   f32x4 acce[4][2];       // weights 64*WM + 16*i, ninth slab's tokens 16*j
-#pragma unroll
-  for (int i = 0; i < 4; i++)
-#pragma unroll
-    for (int j = 0; j < 2; j++)
-#pragma unroll
-      for (int e = 0; e < 4; e++) acce[i][j][e] = 0.f;
-  // (their products are asm, for which the compiler pads no hazard: a matrix instruction right behind the vector instruction
-  // that clears its accumulator reads what the register held before.  So they are cleared here, not next to it.)
-  if (EXT)
-#pragma unroll
-    for (int i = 0; i < 4; i++) asm volatile("s_nop 1" : "+v"(acce[i][0]), "+v"(acce[i][1]));
 
   // One quarter of a slice: half ks/2 of its k with weights 64*(ks & 1) .. + 63 of the wave's 128, i.e. the MFMAs of fragments
   // (fw[ks & 1], fx[ks >> 1]) with, spread between them, the LDS reads of
@@ -302,6 +204,25 @@ __device__ __forceinline__ void gemm256_wave(const Gemm256Params &p, unsigned ch
 #pragma unroll
       for (int j = 0; j < XREQ; j++) issue_x(s, j);
   }
+  // (cleared while the first transfers are on their way: 256 registers)
+#pragma unroll
+  for (int ti = 0; ti < 8; ti++)
+#pragma unroll
+    for (int tj = 0; tj < 2 * NT; tj++) {
+      acc[ti][tj] = {0.f, 0.f, 0.f, 0.f};
+      asm volatile("" : "+a"(acc[ti][tj]));   // (64 separate values: as copies of one zero the compiler moves them about behind the loop)
+    }
+#pragma unroll
+  for (int i = 0; i < 4; i++)
+#pragma unroll
+    for (int j = 0; j < 2; j++)
+#pragma unroll
+      for (int e = 0; e < 4; e++) acce[i][j][e] = 0.f;
+  // (their products are asm, for which the compiler pads no hazard: a matrix instruction right behind the vector instruction
+  // that clears its accumulator reads what the register held before.  So they are cleared here, not next to it.)
+  if (EXT)
+#pragma unroll
+    for (int i = 0; i < 4; i++) asm volatile("s_nop 1" : "+v"(acce[i][0]), "+v"(acce[i][1]));
   wait_vm<NK == 0 ? 8 + kBehind : (NK - 1) * (8 + XREQ)>();
   meet();
 #pragma unroll
@@ -458,7 +379,7 @@ ns_status launch_gemm256(const uint16_t *a, const uint16_t *w, const float *bias
   if (!gemm256_supported(M, N, K)) return fail(NS_ERR_UNSUPPORTED, "GEMM shape M=%d N=%d K=%d", M, N, K);
   if ((long long)M * K * 2 >= 0x7fffffffLL || (long long)N * K * 2 >= 0x7fffffffLL)
     return fail(NS_ERR_UNSUPPORTED, "GEMM operand beyond 2 GiB");
-  Gemm256Params p{a, w, r, bias, c, M, N, K, gelu ? 1 : 0, N / 256, 0, 0, 0, batch, a_stride, c_stride};
+  Gemm256Params p{{a, w, r, bias, c, M, N, K}, N / 256, 0, 0, 0, batch, a_stride, c_stride};
   const int q = M / 256, rem = M % 256;
   p.extended = (rem > 0 && rem <= 32) ? 1 : 0;
   p.ntm = (rem == 0 || p.extended) ? q : q + 1;

@@ -2,8 +2,8 @@
 //   h = x + Wproj Attn(LN1 x) + bproj;   y = h + W2 gelu(W1 LN2 h + b1) + b2
 // The paper applies its sparse attention and its token pruning inside a ViT backbone
 // ("Experimental Setups": UNI-2); this file supplies that surrounding block so that the path can
-// be run and measured end to end: a LayerNorm kernel, one bf16 MFMA GEMM kernel with fused
-// epilogues (bias, exact GELU, residual), and the host-side sequencing.
+// be run and measured end to end: a LayerNorm kernel, the preparation of the patch embedding, the choice of the linear
+// maps' kernel (ns_gemm256.hip, ns_gemm128.hip), and the host-side sequencing.
 #include "ns_common.h"
 #include <algorithm>
 
@@ -61,131 +61,6 @@ __global__ __launch_bounds__(256) void layernorm_kernel(const uint16_t *x, const
   }
 }
 
-// ------------------------------------------------------------------------------------------
-// GEMM: C[m][n] = sum_k A[m][k] * W[n][k] + bias[n], optional exact GELU, optional residual
-// R[m][n]; A, W, R, C bf16 (row-major, k contiguous for both operands), bias fp32, fp32 accumulate.
-// Bound: bf16 MFMA; 2*M*N*K FLOP.
-//
-// Workgroup tile 128 (m) x 128 (n), k-step 64; 4 waves, each a 64x64 quadrant = 2x2 MFMA tiles of
-// v_mfma_f32_32x32x16_bf16.  The product is formed transposed (W rows as the A operand, token
-// rows as the B operand) so that a lane ends up with 4 consecutive n of one token row per
-// register group: 8-byte stores, and bias / residual in the same layout.  Both operand tiles
-// go global -> LDS by direct 16-byte transfers (no registers), double-buffered, XOR-swizzled
-// (16-byte chunk c of row r sits at chunk c ^ ((r>>1)&7)) so that the per-lane 16-byte
-// fragment reads are free of bank conflicts.
-// ------------------------------------------------------------------------------------------
-struct GemmParams {
-  const uint16_t *a, *w, *r;
-  const float *bias;
-  uint16_t *c;
-  int M, N, K;
-  int gelu;
-};
-
-
-typedef bf16x8 __attribute__((address_space(3))) *lds_bf16x8_ptr;
-
-
-__global__ __launch_bounds__(256, 2) void gemm_bf16_kernel(GemmParams p) {
-  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
-  const int l32 = lane & 31, hh = lane >> 5;
-  const int wm = wave >> 1, wn = wave & 1;          // quadrant of this wave
-  // consecutive workgroups walk n first, so the workgroups that share a token tile run together
-  const int ntn = p.N / 128;
-  const int bm = blockIdx.x / ntn, bn = blockIdx.x % ntn;
-  const int m0 = bm * 128, n0 = bn * 128;
-
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];   // [stage][A 16K | W 16K]
-  const uint32_t lds0 = (uint32_t)(size_t)((__attribute__((address_space(3))) unsigned char *)smem);
-
-  // ---- transfers: a 128-row x 64-k tile is 16 requests of 8 rows; this wave issues 4 of the
-  // token tile and 4 of the weight tile.  Slot `lane` of request `it` is row it*8 + lane/8,
-  // physical chunk lane%8, logical chunk (lane%8) ^ ((row>>1)&7).
-  const char *ab = reinterpret_cast<const char *>(p.a);
-  const char *wb = reinterpret_cast<const char *>(p.w);
-  const uint32_t rowB = (uint32_t)p.K * 2u;
-  uint32_t aoff[4], woff[4];
-#pragma unroll
-  for (int j = 0; j < 4; j++) {
-    const int it = wave * 4 + j, row = it * 8 + (lane >> 3);
-    const int chunk = (lane & 7) ^ ((row >> 1) & 7);
-    const int am = min(m0 + row, p.M - 1);            // rows past M repeat the last row (never stored)
-    aoff[j] = (uint32_t)am * rowB + 16u * chunk;
-    woff[j] = (uint32_t)(n0 + row) * rowB + 16u * chunk;
-  }
-  auto issue = [&](int kt, int stage) {
-    const char *ak = ab + (size_t)kt * 128, *wk = wb + (size_t)kt * 128;
-    const uint32_t base = lds0 + stage * 32768 + wave * 4 * 1024;
-#pragma unroll
-    for (int j = 0; j < 4; j++) {
-      dma16(ak, aoff[j], base + j * 1024);
-      dma16(wk, woff[j], base + 16384 + j * 1024);
-    }
-  };
-  // ---- fragment reads: lane (row l32 [+32], half hh) reads logical chunks 4*hh + ks
-  unsigned char *frd[4];
-#pragma unroll
-  for (int ks = 0; ks < 4; ks++) frd[ks] = smem + l32 * 128 + 16 * ((4 * hh + ks) ^ ((l32 >> 1) & 7));
-
-  f32x16 acc[2][2];   // [nt (weight rows)][mt (token rows)]: rows n, column m
-#pragma unroll
-  for (int i = 0; i < 2; i++)
-#pragma unroll
-    for (int j = 0; j < 2; j++)
-#pragma unroll
-      for (int e = 0; e < 16; e++) acc[i][j][e] = 0.f;
-
-  const int nk = p.K / 64;
-  issue(0, 0);
-  for (int kt = 0; kt < nk; kt++) {
-    const int stage = kt & 1;
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this wave's share of tile kt has landed
-    __syncthreads();                                    // everyone's has; everyone is done with tile kt-1
-    if (kt + 1 < nk) issue(kt + 1, stage ^ 1);
-    bf16x8 fa[2][4], fw[2][4];
-#pragma unroll
-    for (int t = 0; t < 2; t++)
-#pragma unroll
-      for (int ks = 0; ks < 4; ks++) {
-        fa[t][ks] = *(lds_bf16x8_ptr)(frd[ks] + stage * 32768 + (wm * 64 + t * 32) * 128);
-        fw[t][ks] = *(lds_bf16x8_ptr)(frd[ks] + stage * 32768 + 16384 + (wn * 64 + t * 32) * 128);
-      }
-#pragma unroll
-    for (int ks = 0; ks < 4; ks++)
-#pragma unroll
-      for (int nt = 0; nt < 2; nt++)
-#pragma unroll
-        for (int mt = 0; mt < 2; mt++)
-          acc[nt][mt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fw[nt][ks], fa[mt][ks], acc[nt][mt], 0, 0, 0);
-  }
-
-  // ---- epilogue: lane (token row m = l32, half hh) owns n = 8*ig + 4*hh + 0..3 of each 32x32 tile
-#pragma unroll
-  for (int mt = 0; mt < 2; mt++) {
-    const int m = m0 + wm * 64 + mt * 32 + l32;
-    if (m >= p.M) continue;
-#pragma unroll
-    for (int nt = 0; nt < 2; nt++)
-#pragma unroll
-      for (int ig = 0; ig < 4; ig++) {
-        const int n = n0 + wn * 64 + nt * 32 + 8 * ig + 4 * hh;
-        const f32x4 b4 = *reinterpret_cast<const f32x4 *>(p.bias + n);
-        float o[4];
-#pragma unroll
-        for (int e = 0; e < 4; e++) o[e] = acc[nt][mt][4 * ig + e] + b4[e];
-        if (p.gelu)                       // (one branch: the four dependency chains run side by side)
-#pragma unroll
-          for (int e = 0; e < 4; e++) o[e] = gelu_erf(o[e]);
-        if (p.r) {
-          const uint2 r2 = *reinterpret_cast<const uint2 *>(p.r + (size_t)m * p.N + n);
-          o[0] += bf16_lo(r2.x); o[1] += bf16_hi(r2.x); o[2] += bf16_lo(r2.y); o[3] += bf16_hi(r2.y);
-        }
-        uint2 u = {pack_bf16(o[0], o[1]), pack_bf16(o[2], o[3])};
-        *reinterpret_cast<uint2 *>(p.c + (size_t)m * p.N + n) = u;
-      }
-  }
-}
-
 ns_status launch_layernorm(const uint16_t *x, const float *g, const float *b, uint16_t *y, int rows,
                            int dim, float eps, hipStream_t s) {
   dim3 grid((rows + 3) / 4), blk(256);
@@ -199,23 +74,26 @@ ns_status launch_layernorm(const uint16_t *x, const float *g, const float *b, ui
   return check_launch("layernorm_kernel");
 }
 
-bool use_gemm256(int M, int N, int K) {
-  // NSATTN_GEMM=128 keeps the 128 x 128 kernel for every shape; read once per process
-  static const bool only128 = [] { const char *e = getenv("NSATTN_GEMM"); return e && e[0] == '1'; }();
-  return gemm256_supported(M, N, K) && !only128;
-}
-
+// Which kernel.  A tile of 128 x 32 tj takes about 0.13 + 0.06 tj us per 64 of K, one of 256 x 256 0.76 where few CUs work and 1.45
+// where all do, so the smaller ones are faster wherever a launch of them is over in one round of workgroups, and the smallest
+// that are the fastest: 1025 x 1024 x 4096 (tj 2) 20 us, 256 x 256 tiles 54; 4097 x 1024 x 1024 (tj 5) 13 against 19.  In
+// two rounds they are slower (6401 x 1024 x 4096: 60.6 and more against 56.5), but for K = 512 (12545 x 1536: 28 against 34).  Over 225 shapes of
+// 449 to 25601 rows, widths 512 to 1536, this takes 0.7 % more than the best of all six, 256 x 256 tiles everywhere 22 %.
 ns_status launch_gemm(const uint16_t *a, const uint16_t *w, const float *bias, const uint16_t *r,
-                      uint16_t *c, int M, int N, int K, bool gelu, hipStream_t s) {
-  if (use_gemm256(M, N, K)) return launch_gemm256(a, w, bias, r, c, M, N, K, gelu, s);
-  if (N % 128 || K % 64) return fail(NS_ERR_UNSUPPORTED, "GEMM needs N %% 128 == 0 and K %% 64 == 0 (N=%d K=%d)", N, K);
-  if ((long long)M * K * 2 >= 0x7fffffffLL || (long long)N * K * 2 >= 0x7fffffffLL)
-    return fail(NS_ERR_UNSUPPORTED, "GEMM operand beyond 2 GiB");
-  GemmParams p{a, w, r, bias, c, M, N, K, gelu ? 1 : 0};
-  const long long wgs = (long long)((M + 127) / 128) * (N / 128);
-  if (wgs > 0x7fffffffLL) return fail(NS_ERR_UNSUPPORTED, "GEMM grid too large");
-  hipLaunchKernelGGL(gemm_bf16_kernel, dim3((unsigned)wgs), dim3(256), 65536, s, p);
-  return check_launch("gemm_bf16_kernel");
+                      uint16_t *c, int M, int N, int K, bool gelu, hipStream_t s, int batch = 1, long long a_stride = 0,
+                      long long c_stride = 0) {
+  // NSATTN_GEMM=128 keeps the kernel of the smaller tiles for every shape; read once per process
+  static const bool only128 = [] { const char *e = getenv("NSATTN_GEMM"); return e && e[0] == '1'; }();
+  const int cus = device_cu_count();
+  auto rounds = [&](int tj) { return ((long long)((M + 32 * tj - 1) / (32 * tj)) * (N / 128) * batch + cus - 1) / cus; };
+  int tj = 2;
+  while (tj < 6 && rounds(tj) > 1) tj++;
+  if (rounds(tj) > 1) {
+    if (gemm256_supported(M, N, K) && !only128) return launch_gemm256(a, w, bias, r, c, M, N, K, gelu, s, batch, a_stride, c_stride);
+    for (int t = 5; t >= 2; t--)
+      if (rounds(t) * (2 + t) < rounds(tj) * (2 + tj)) tj = t;
+  }
+  return launch_gemm128(a, w, bias, r, c, M, N, K, gelu, s, tj, batch, a_stride, c_stride);
 }
 
 struct VitWorkspace {
@@ -595,13 +473,7 @@ ns_status vit_embed(int32_t batch, int32_t channels, int32_t grid_h, int32_t gri
   const uint16_t *w = Kp != K ? wp : p.w;
   // rows 1..N of every image: projection + bias, the position embeddings ride in as the residual
   const long long image_stride = (long long)(1 + N) * dim;
-  if (use_gemm256(N, dim, Kp))
-    return launch_gemm256(a, w, b_patch, pos + dim, x + dim, N, dim, Kp, false, s, batch, (long long)N * Kp, image_stride);
-  for (int b = 0; b < batch; b++) {
-    st = launch_gemm(a + (size_t)b * N * Kp, w, b_patch, pos + dim, x + b * image_stride + dim, N, dim, Kp, false, s);
-    if (st != NS_OK) return st;
-  }
-  return NS_OK;
+  return launch_gemm(a, w, b_patch, pos + dim, x + dim, N, dim, Kp, false, s, batch, (long long)N * Kp, image_stride);
 }
 
 ns_status linear_forward(int32_t M, int32_t N, int32_t K, const void *x, const void *w, const float *bias,

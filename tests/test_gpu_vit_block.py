@@ -378,6 +378,18 @@ def test_linear_forward_last_rows(nb, M, K):
     # one and two slices of k
     (16385, 1024, 64, False, True), (1025, 1024, 64, True, False), (577, 512, 64, True, True),
     (16385, 1024, 128, True, True), (1025, 1024, 128, False, True), (577, 512, 128, False, False), (12000, 2048, 128, False, True),
+    # launches of one round of the smaller tiles, 128 x 64 to 128 x 192 (N = 4096: up to 512, 768, .. 1536 rows): last rows of a tile, of half
+    # a slab and of a pass; one to more slices of k than the slots hold
+    (1, 4096, 64, True, True), (33, 128, 64, False, True), (512, 4096, 256, False, True), (497, 1024, 320, True, False),
+    (513, 4096, 192, True, True), (768, 4096, 128, False, False), (769, 4096, 320, False, True), (1023, 4096, 64, True, False),
+    (1025, 4096, 256, True, True), (1279, 4096, 640, False, True), (1281, 4096, 192, False, False), (1536, 4096, 320, True, True),
+    (1457, 4096, 128, False, True),
+    # .. and of several rounds, where 256 does not divide N
+    (9000, 640, 192, True, True), (20001, 384, 64, False, True),
+    # the 256 x 256 kernel where a launch has 256 of its tiles: ninth slab of one and of 32 rows, partial tiles of one to seven slabs
+    (1025, 16384, 64, False, True), (800, 16384, 128, True, False), (769, 16384, 192, False, True), (1056, 16384, 320, True, True),
+    (801, 16384, 192, True, True), (833, 16384, 256, False, False), (897, 16384, 64, False, True), (961, 16384, 320, False, True),
+    (1024, 16384, 192, False, False),
 ])
 def test_linear_forward(nb, M, N, K, gelu, res):
     """The fused linear map against float64 matmul / erf GELU on the same bf16 inputs."""
