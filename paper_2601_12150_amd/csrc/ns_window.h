@@ -158,6 +158,7 @@ __device__ __forceinline__ uint32_t screened(uint32_t x, int pass) {
 // bf16: v_mfma_f32_32x32x16_bf16, weights rounded to bf16 for the second product.
 struct StepBf16 {
   typedef uint16_t elem;
+  typedef StepBf16 Whole;
   static constexpr int kDepth = 2, kReq = 4, kHalf = 4096;     // slots, requests per 32 rows, bytes of 32 rows
   struct Q { bf16x8 f[4]; };
   typedef s16x4 __attribute__((address_space(3))) *tr_ptr;
@@ -389,10 +390,10 @@ struct StepBf16 {
 };
 
 // fp32 arithmetic: v_mfma_f32_32x32x2_f32 on rows of 64 floats (T = uint16_t: bf16 rows, converted
-// on the way into LDS).  An operand register holds one k index per half-wave: step s of the
+// on the way into LDS), for what StepF32 below cannot do.  An operand register holds one k index per half-wave: step s of the
 // logits pairs channels s and 32 + s, step e of the second product keys (e, hh = 0) and (e, hh = 1).
 template <typename T>
-struct StepF32 {
+struct StepF32Whole {
   typedef T elem;
   static constexpr int kDepth = 1, kReq = 8, kHalf = 8192;
   struct Q { float f[32]; };
@@ -432,14 +433,16 @@ struct StepF32 {
   }
   static __device__ __forceinline__ uint32_t place(int tok, int64_t) { return (uint32_t)tok; }
   __device__ __forceinline__ void issue_k(const char *base, int64_t rowB, const uint32_t (&at)[kReq], unsigned char *dst, uint32_t lds, int lane) const {
+    const int ln = opaque(lane);              // (chunk numbers: put together here, not kept)
 #pragma unroll
     for (int it = 0; it < kReq; it++)
-      request(base + (int64_t)at[it] * rowB, (lane & 15) ^ ((4 * it + rrow) & 15), dst + it * 1024, lds + it * 1024, lane);
+      request(base + (int64_t)at[it] * rowB, (ln & 15) ^ ((4 * it + (ln >> 4)) & 15), dst + it * 1024, lds + it * 1024, lane);
   }
   __device__ __forceinline__ void issue_v(const char *base, int64_t rowB, const uint32_t (&at)[kReq], unsigned char *dst, uint32_t lds, int lane) const {
+    const int ln = opaque(lane);
 #pragma unroll
     for (int it = 0; it < kReq; it++)
-      request(base + (int64_t)at[it] * rowB, (lane & 15) ^ (8 * (it & 1)), dst + it * 1024, lds + it * 1024, lane);
+      request(base + (int64_t)at[it] * rowB, (ln & 15) ^ (8 * (it & 1)), dst + it * 1024, lds + it * 1024, lane);
   }
   template <int NT>
   __device__ __forceinline__ void logits(const Q (&q)[NT], const unsigned char *slot, f32x16 (&s)[NT]) const {
@@ -469,6 +472,108 @@ struct StepF32 {
   static __device__ __forceinline__ void store4out(float *p, f32x4 v) { *reinterpret_cast<f32x4 *>(p) = v; }
   static __device__ __forceinline__ void store4out(uint16_t *p, f32x4 v) {
     *reinterpret_cast<u32x2 *>(p) = u32x2{pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3])};
+  }
+};
+
+// Eight floats as sums of up to three bf16 numbers each, the next the rounding of what those before leave: exact, all 24 bits.
+template <int P>
+__device__ __forceinline__ void split8(const float (&x)[8], bf16x8 (&p)[P]) {
+#pragma unroll
+  for (int e = 0; e < 8; e += 2) {
+    float a = x[e], b = x[e + 1];
+#pragma unroll
+    for (int i = 0; i < P; i++) {
+      const uint32_t u = pack_bf16(a, b);
+      const bf16x2 pk = __builtin_bit_cast(bf16x2, u);
+      p[i][e] = pk[0];
+      p[i][e + 1] = pk[1];
+      if (i + 1 < P) {
+        a -= bf16_lo(u);
+        b -= bf16_hi(u);
+      }
+    }
+  }
+}
+
+// fp32 precision from v_mfma_f32_32x32x16_bf16: each value in three bf16 parts (a row's of bf16 in one), and of the nine products
+// of parts the six that count, smallest first; the others are below 2^-25 of the whole, less than one rounding of the sum.
+// That is 192 cycles of the matrix pipe for 16 k where v_mfma_f32_32x32x2_f32 takes 512.  (64 queries a step would share K's and V's
+// parts, but the parts of 64 rows of Q leave too few registers: 30 are spilled.)  A value that is not finite has parts that are NaN: rows whose sums are not
+// finite are computed once more from whole values (walk_not_finite on Whole, half of the queries at a time).
+template <typename T>
+struct StepF32 : StepF32Whole<T> {
+  typedef StepF32Whole<T> Whole;
+  static constexpr int KP = sizeof(T) == 4 ? 3 : 1;      // parts of a value of K or V
+  struct Q { bf16x8 f[4][3]; };                          // [channels 8 s .. of this half][part]
+  __device__ __forceinline__ void load_q(Q &q, const char *base, int64_t rowB, int tok, int lane, float mul) const {
+    const T *row = reinterpret_cast<const T *>(base + (int64_t)tok * rowB) + 32 * (lane >> 5);
+#pragma unroll
+    for (int s = 0; s < 4; s++) {
+      float x[8];
+#pragma unroll
+      for (int c = 0; c < 2; c++) {
+        const f32x4 v = Whole::load4(row + 8 * s + 4 * c);
+#pragma unroll
+        for (int e = 0; e < 4; e++) x[4 * c + e] = v[e] * mul;
+      }
+      split8(x, q.f[s]);
+    }
+  }
+  // c += a b of values in PA and PB parts
+  template <int PA, int PB>
+  static __device__ __forceinline__ f32x16 product(const bf16x8 (&a)[PA], const bf16x8 (&b)[PB], f32x16 c) {
+#pragma unroll
+    for (int order = 2; order >= 0; order--)
+#pragma unroll
+      for (int i = 0; i < PA; i++)
+        if (order - i >= 0 && order - i < PB) c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], b[order - i], c, 0, 0, 0);
+    return c;
+  }
+  template <int NT>
+  __device__ __forceinline__ void logits(const Q (&q)[NT], const unsigned char *slot, f32x16 (&s)[NT]) const {
+#pragma unroll
+    for (int nt = 0; nt < NT; nt++) s[nt] = f32x16{0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    const uint32_t kx = (uint32_t)opaque((int)this->kx);     // (eight addresses otherwise live through the walk)
+#pragma unroll
+    for (int t = 0; t < 4; t++) {
+      float x[8];
+#pragma unroll
+      for (int c = 0; c < 2; c++) {
+        const f32x4 k4 = *reinterpret_cast<const f32x4 *>(slot + this->kbase + (kx ^ (16 * (2 * t + c))));
+#pragma unroll
+        for (int e = 0; e < 4; e++) x[4 * c + e] = k4[e];
+      }
+      bf16x8 k[KP];
+      split8(x, k);
+#pragma unroll
+      for (int nt = 0; nt < NT; nt++) s[nt] = product(k, q[nt].f[t], s[nt]);
+      __builtin_amdgcn_sched_barrier(0);      // (the parts of one k-step at a time: the registers do not hold more)
+    }
+  }
+  template <int NT, bool LO>
+  __device__ __forceinline__ void weigh(const f32x16 (&w)[NT], const unsigned char *slot, f32x16 (&o)[NT][2], int) const {
+#pragma unroll
+    for (int sp = 0; sp < 2; sp++) {
+      bf16x8 pw[NT][3];
+#pragma unroll
+      for (int nt = 0; nt < NT; nt++) {
+        float x[8];
+#pragma unroll
+        for (int e = 0; e < 8; e++) x[e] = w[nt][8 * sp + e];
+        split8(x, pw[nt]);
+      }
+#pragma unroll
+      for (int dt = 0; dt < 2; dt++) {
+        float x[8];
+#pragma unroll
+        for (int e = 0; e < 8; e++) x[e] = *reinterpret_cast<const float *>(slot + this->vrd[dt] + (16 * sp + 8 * (e >> 2) + (e & 3)) * 256);
+        bf16x8 v[KP];
+        split8(x, v);
+#pragma unroll
+        for (int nt = 0; nt < NT; nt++) o[nt][dt] = product(v, pw[nt], o[nt][dt]);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
   }
 };
 
@@ -699,15 +804,16 @@ __device__ __forceinline__ void walk_keys(const S &st, WaveAcc<S, NT> &a, const 
   constexpr int rpr = 32 / R;                 // rows per request
   uint32_t at[R];                             // where the rows of this lane's requests stand
   auto tokens = [&](int i) {
+    const int rrow = R > 4 ? opaque(st.rrow) : st.rrow;      // (fp32: eight lane numbers otherwise live through the walk)
     if (RING) {
       // (lane l of each half turns the token of key l into its row's place)
       const uint32_t t = S::place(fix_token(i, lane & 31, ring[(i & 3) * 64 + (lane & 31)]), rowB);
 #pragma unroll
-      for (int it = 0; it < R; it++) at[it] = __shfl(t, it * rpr + st.rrow);
+      for (int it = 0; it < R; it++) at[it] = __shfl(t, it * rpr + rrow);
     } else {
       const uint32_t t = S::place(key_token(i), rowB);
 #pragma unroll
-      for (int it = 0; it < R; it++) at[it] = __shfl(t, it * rpr + st.rrow);
+      for (int it = 0; it < R; it++) at[it] = __shfl(t, it * rpr + rrow);
     }
   };
   auto issue_k = [&](int slot) { const int o = slot * S::kHalf; st.issue_k(kb, rowB, at, wsm + o, lds + o, lane); };
@@ -848,6 +954,20 @@ __device__ __forceinline__ void walk_not_finite(const S &st, WaveAcc<S, NT> &a, 
       }
 }
 
+// ... of a step that works on parts: the queries of half nt (lane l32: token tok), from whole values
+template <class S, bool RING, bool LO, int NT, class... Args>
+__device__ __forceinline__ void whole_rows(const S &st, WaveAcc<S, NT> &a, int nt, const char *qb, const char *kb, const char *vb,
+                                           int64_t rowB, int tok, float scale, unsigned char *wsm, int n, float c, int lane, Args &&...args) {
+  typedef typename S::Whole W;
+  WaveAcc<W, 1> b;
+  static_cast<const W &>(st).load_q(b.q[0], qb, rowB, tok, lane, scale);
+  walk_not_finite<W, 1, RING, LO>(st, b, kb, vb, rowB, wsm, n, c, lane, args...);
+  a.o[nt][0] = b.o[0][0];
+  a.o[nt][1] = b.o[0][1];
+  a.m[nt] = b.m[0];
+  a.l[nt] = b.l[0];
+}
+
 // a query tile's walk: pipelined where there are two slots
 template <class S, int NT, bool RING, bool FIXED, class... Args>
 __device__ __forceinline__ void window_walk(const S &st, WaveAcc<S, NT> &a, Args &&...args) {
@@ -963,7 +1083,8 @@ __device__ __forceinline__ void global_rows_chunk(const GlobalRows &p, int heads
       });
     if (!a.exceeds(careful ? INFINITY : kLargeSum)) break;
     if (careful) {
-      if (WITH_V) walk_not_finite<S, 1, false, kBf16>(st, a, kb, vb, rowB, wsm, n, c, lane, key_token, no_entry, as_is, hide);
+      if constexpr (WITH_V && kBf16) walk_not_finite<S, 1, false, true>(st, a, kb, vb, rowB, wsm, n, c, lane, key_token, no_entry, as_is, hide);
+      else if constexpr (WITH_V) whole_rows<S, false, false>(st, a, 0, qb, kb, vb, rowB, min(g, G - 1), p.scale, wsm, n, c, lane, key_token, no_entry, as_is, hide);
       break;
     }
     a.clear();
@@ -1172,9 +1293,9 @@ __device__ __forceinline__ void window_attention(const WindowParams &p, unsigned
   auto key_token = [&](int i) { return w.key(g, key0(i) + l32); };
   auto key_entry = [&](int i) { return w.key_entry(g, key0(i) + l32); };
   auto fix_token = [&](int i, int row, int t) { return key0(i) + row < g.n_global ? key0(i) + row : t; };
-  auto hide = [&](int i, int nt, f32x16 &s) {
+  auto hide_of = [&](int i, int nt, bool first, f32x16 &s) {
     if (MASK) {
-      if (nt == 0) {
+      if (first) {
         codes[l32] = w.key_code(g, key0(i) + l32, inv_block);
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
       }
@@ -1191,11 +1312,19 @@ __device__ __forceinline__ void window_attention(const WindowParams &p, unsigned
       for (int e = 0; e < 16; e++) s[e] = jb + 8 * (e >> 2) + (e & 3) < w.nkeys ? s[e] : -INFINITY;
     }
   };
+  auto hide = [&](int i, int nt, f32x16 &s) { hide_of(i, nt, nt == 0, s); };
   for (bool careful = MASK && part != 0;; careful = true) {
     window_walk<S, NT, LISTS, MASK>(st, a, kb, vb, rowB, wsm, n, c, careful, lane, key_token, key_entry, fix_token, hide);
     if (!a.exceeds(careful ? INFINITY : kLargeSum)) break;
     if (careful) {
-      walk_not_finite<S, NT, LISTS, false>(st, a, kb, vb, rowB, wsm, n, c, lane, key_token, key_entry, fix_token, hide);
+      if constexpr (kBf16) {
+        walk_not_finite<S, NT, LISTS, false>(st, a, kb, vb, rowB, wsm, n, c, lane, key_token, key_entry, fix_token, hide);
+      } else {
+#pragma unroll
+        for (int nt = 0; nt < NT; nt++)
+          whole_rows<S, LISTS, false>(st, a, nt, qb, kb, vb, rowB, w.query(g, 32 * nt + l32), p.r.scale, wsm, n, c, lane, key_token,
+                                      key_entry, fix_token, [&](int i, int, f32x16 &s) { hide_of(i, nt, true, s); });
+      }
       break;
     }
     a.clear();

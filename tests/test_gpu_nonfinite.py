@@ -172,3 +172,23 @@ def test_weights_beyond_the_first_steps_reference(nb, monkeypatch, dtype, split,
         assert np.abs(got - ref).max() <= 1e-3
     else:
         assert_attn_close(got, ref, dtype, "second walk")
+
+
+@pytest.mark.parametrize("split", ["1", "2", "4"])
+@pytest.mark.parametrize("gh,gw,block,G", [(21, 26, 3, 2), (20, 27, 8, 1)])
+def test_keys_that_are_not_finite_in_fp32(nb, monkeypatch, gh, gw, block, G, split):
+    """A key with -inf where every query is positive counts for nothing; one with +inf makes the rows NaN whose query is positive
+    there.  (The fp32 products work on parts of a value, and those of an infinite one are NaN.)"""
+    force(monkeypatch, "f32", split)
+    N = gh * gw
+    q, k, v = synth.small_case(7 + N, 1, 2, 64, gh, gw, "f32", n_global=G)
+    q[:, :, :, 7] = np.abs(q[:, :, :, 7]) + np.float32(0.1)
+    k[0, 1, G + N // 2, 7] = -np.inf
+    k[0, 1, G + N - 1, 7] = -np.inf
+    k[0, 0, G + N // 3, 9] = np.inf
+    print("keys not finite: grid %dx%d block %d G=%d split %s" % (gh, gw, block, G, split), flush=True)
+    out = nb.ns_attn_forward(*(to_dev(a, "f32") for a in (q, k, v)), gh, gw, block, 0.125, n_global=G)
+    torch.cuda.synchronize()
+    ref = oracle.ns_attn(q, k, v, gh, gw, block, 0.125, n_global=G)
+    assert np.isfinite(ref[0, 1]).all() and not np.isfinite(ref[0, 0]).all() and np.isfinite(ref[0, 0]).any()
+    assert_same_values(to_np(out), ref, "f32", "keys not finite")
