@@ -156,14 +156,18 @@ __global__ __launch_bounds__(kCombineThreads) void cls_combine_kernel(const floa
   cls_combine_body<T, WITH_V>(blockIdx.x, blockIdx.y, partials, nchunks, H, G, out, osb, osh, ost, lse);
 }
 
-// Workgroup `blk` of image b scores blockDim.x patches (thread = patch).  H counts the global rows
-// of an image (heads x global tokens): the score is the mean over all of them.  lse given
+// Workgroup `blk` of image b scores 256 patches: thread = (patch, group of rows), the groups added in order.  H counts the global
+// rows of an image (heads x global tokens): the score is the mean over all of them.  lse given
 // directly, or recomputed per row from the (max, sum) of the partial records.
+// Bound: latency, of the records and then of a thread's share of the logits, which come from other XCDs' L2s: hence four groups and up to
+// eight loads on their way.  (A thread per patch that went through all rows: 80 rows, 2 x 10000 patches, 12.3 us the launch, this 7.7.)
+constexpr int kScoreThreads = 1024, kScorePatches = 256;
 __device__ __forceinline__ void cls_scores_body(int blk, int b, const float *logits, const float *lse,
                                                 const float *partials, int nchunks, int H, int T_, int G,
                                                 float *scores) {
-  __shared__ float s_lse[1024];
-  const int tid = threadIdx.x, nthreads = blockDim.x;
+  __shared__ float s_lse[1024], s_part[kScoreThreads / kScorePatches][kScorePatches];
+  const int tid = threadIdx.x;
+  constexpr int nthreads = kScoreThreads, kGroups = kScoreThreads / kScorePatches;
   if (lse) {
     for (int h = tid; h < H; h += nthreads) s_lse[h] = lse[(size_t)b * H + h];
   } else {
@@ -195,26 +199,28 @@ __device__ __forceinline__ void cls_scores_body(int blk, int b, const float *log
     }
   }
   __syncthreads();
-  const int N = T_ - G;
-  const int j = blk * nthreads + tid;
-  if (j >= N) return;
+  const int N = T_ - G, g = tid / kScorePatches, lj = tid % kScorePatches, j = blk * kScorePatches + lj;
+  const float *row = logits + (size_t)b * H * T_ + G + min(j, N - 1);
   float acc = 0.f;
-  for (int h = 0; h < H; h++) {
-    const float x = logits[((size_t)b * H + h) * T_ + G + j];
-    acc += __builtin_amdgcn_exp2f((x - s_lse[h]) * kLog2e);
-  }
+#pragma unroll 8
+  for (int h = g; h < H; h += kGroups) acc += __builtin_amdgcn_exp2f((row[(size_t)h * T_] - s_lse[h]) * kLog2e);
+  s_part[g][lj] = acc;
+  __syncthreads();
+  if (g != 0 || j >= N) return;
+#pragma unroll
+  for (int i = 1; i < kGroups; i++) acc += s_part[i][lj];
   scores[(size_t)b * N + j] = acc / (float)H;
 }
 
-// grid (ceil(N/256), B), 256 threads
-__global__ __launch_bounds__(256) void cls_scores_kernel(const float *logits, const float *lse,
+// grid (ceil(N/256), B)
+__global__ __launch_bounds__(kScoreThreads) void cls_scores_kernel(const float *logits, const float *lse,
                                                          const float *partials, int nchunks, int H,
                                                          int T_, int G, float *scores) {
   cls_scores_body(blockIdx.x, blockIdx.y, logits, lse, partials, nchunks, H, T_, G, scores);
 }
 
-// Both in one launch, grid (H + ceil(N/1024), B), 1024 threads: the first H workgroups of an image
-// merge the records of one global row each (output row and log-sum-exp), the others score 1024
+// Both in one launch, grid (H + ceil(N/256), B), 1024 threads: the first H workgroups of an image
+// merge the records of one global row each (output row and log-sum-exp), the others score 256
 // patches each, with the log-sum-exps they derive from the records themselves.
 template <typename T>
 __global__ __launch_bounds__(kCombineThreads) void cls_combine_scores_kernel(const float *partials, int nchunks,
@@ -300,7 +306,8 @@ ns_status launch_cls_combine_scores(const ns_attn_desc &d, const float *partials
                                     const float *logits, float *scores, hipStream_t s, int nchunks) {
   const int nch = nchunks > 0 ? nchunks : cls_num_chunks(d.tokens);
   const int N = d.tokens - d.n_global;
-  dim3 grid(d.heads * d.n_global + (N + kCombineThreads - 1) / kCombineThreads, d.batch), blk(kCombineThreads);
+  static_assert(kCombineThreads == kScoreThreads, "one launch");
+  dim3 grid(d.heads * d.n_global + (N + kScorePatches - 1) / kScorePatches, d.batch), blk(kCombineThreads);
   if (d.dtype == NS_F32)
     hipLaunchKernelGGL((cls_combine_scores_kernel<float>), grid, blk, 0, s, partials, nch, d.heads, d.n_global,
                        static_cast<float *>(out), d.out_stride_b, d.out_stride_h, d.out_stride_t, lse, logits,
@@ -315,7 +322,7 @@ ns_status launch_cls_combine_scores(const ns_attn_desc &d, const float *partials
 ns_status launch_cls_scores(int B, int H, int T, int G, const float *logits, const float *lse,
                             const float *partials, int nchunks, float *scores, hipStream_t s) {
   const int N = T - G;
-  dim3 grid((N + 255) / 256, B), blk(256);
+  dim3 grid((N + kScorePatches - 1) / kScorePatches, B), blk(kScoreThreads);
   hipLaunchKernelGGL(cls_scores_kernel, grid, blk, 0, s, logits, lse, partials, nchunks, H * G, T, G,
                      scores);
   return check_launch("cls_scores_kernel");
