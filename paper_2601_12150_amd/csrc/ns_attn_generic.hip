@@ -6,7 +6,9 @@
 //
 // One workgroup per tile of 32 queries, the tile's keys shared out over its four waves; products of fp32 values as six products of
 // their bf16 parts on the matrix pipe (StepF32 in ns_window.h); the global rows' chunks ride in the same launch.
-// Bound: taking the parts on the vector ALU, about 400 of a step's 640 vector instructions.  Against v_mfma_f32_32x32x2_f32, which runs at the
+// Bound: at small sizes the chain of a wave's few steps, at large ones the transfers (a step of 32 keys and queries moves 16 KB into
+// LDS: 9.3 TB/s on 64x64, four images); taking the parts is about 400 of a step's 580 vector instructions and stands between the products.
+// Against v_mfma_f32_32x32x2_f32, which runs at the
 // vector ALU's fp32 peak, us a call, 16 heads: 64x64 with 8x8 blocks, four images, 362 -> 270, one image 104 -> 80, 28x28 with 7x7 blocks 31.7
 // -> 26, four images 75 -> 59; error of the rows against 64 bits 3.5e-7 -> 2.8e-7, with logits of +-60 1.3e-6 -> 0.98e-6.
 #include "ns_window.h"

@@ -475,24 +475,27 @@ struct StepF32Whole {
   }
 };
 
-// Eight floats as sums of up to three bf16 numbers each, the next the rounding of what those before leave: exact, all 24 bits.
+// Values e and e + 1 of eight as sums of up to three bf16 numbers each, the next the rounding of what those before leave: exact,
+// all 24 bits.
+template <int P>
+__device__ __forceinline__ void split_pair(const float (&x)[8], bf16x8 (&p)[P], int e) {
+  float a = x[e], b = x[e + 1];
+#pragma unroll
+  for (int i = 0; i < P; i++) {
+    const uint32_t u = pack_bf16(a, b);
+    const bf16x2 pk = __builtin_bit_cast(bf16x2, u);
+    p[i][e] = pk[0];
+    p[i][e + 1] = pk[1];
+    if (i + 1 < P) {
+      a -= bf16_lo(u);
+      b -= bf16_hi(u);
+    }
+  }
+}
 template <int P>
 __device__ __forceinline__ void split8(const float (&x)[8], bf16x8 (&p)[P]) {
 #pragma unroll
-  for (int e = 0; e < 8; e += 2) {
-    float a = x[e], b = x[e + 1];
-#pragma unroll
-    for (int i = 0; i < P; i++) {
-      const uint32_t u = pack_bf16(a, b);
-      const bf16x2 pk = __builtin_bit_cast(bf16x2, u);
-      p[i][e] = pk[0];
-      p[i][e + 1] = pk[1];
-      if (i + 1 < P) {
-        a -= bf16_lo(u);
-        b -= bf16_hi(u);
-      }
-    }
-  }
+  for (int e = 0; e < 8; e += 2) split_pair(x, p, e);
 }
 
 // fp32 precision from v_mfma_f32_32x32x16_bf16: each value in three bf16 parts (a row's of bf16 in one), and of the nine products
@@ -519,61 +522,72 @@ struct StepF32 : StepF32Whole<T> {
       split8(x, q.f[s]);
     }
   }
-  // c += a b of values in PA and PB parts
-  template <int PA, int PB>
-  static __device__ __forceinline__ f32x16 product(const bf16x8 (&a)[PA], const bf16x8 (&b)[PB], f32x16 c) {
+  // c += a b of values in KP and 3 parts.  between(m): what is to stand behind product m of kProducts; the fences keep it there,
+  // since the scheduler would put the vector instructions first and the products, which then wait for each other, behind them
+  // (28x28, 7x7 blocks 24.3 -> 23.7 us a call, 16x16 14.8 -> 14.1; large grids, bound by their transfers, as before).
+  static constexpr int kProducts = KP == 3 ? 6 : 3;
+  template <class F>
+  static __device__ __forceinline__ void product(const bf16x8 (&a)[KP], const bf16x8 (&b)[3], f32x16 &c, F between) {
+    int m = 0;
 #pragma unroll
     for (int order = 2; order >= 0; order--)
 #pragma unroll
-      for (int i = 0; i < PA; i++)
-        if (order - i >= 0 && order - i < PB) c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], b[order - i], c, 0, 0, 0);
-    return c;
+      for (int i = 0; i < KP; i++)
+        if (order - i >= 0) {
+          c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], b[order - i], c, 0, 0, 0);
+          between(m++);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+  }
+  // pairs [from, to) of the four of x that stand behind product m
+  template <int P>
+  static __device__ __forceinline__ void split_behind(int m, const float (&x)[8], bf16x8 (&p)[P], int from, int to) {
+#pragma unroll
+    for (int i = 0; i < to - from; i++)
+      if (i * kProducts / (to - from) == m) split_pair(x, p, 2 * (from + i));
   }
   template <int NT>
   __device__ __forceinline__ void logits(const Q (&q)[NT], const unsigned char *slot, f32x16 (&s)[NT]) const {
-#pragma unroll
-    for (int nt = 0; nt < NT; nt++) s[nt] = f32x16{0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    static_assert(NT == 1, "32 queries");
     const uint32_t kx = (uint32_t)opaque((int)this->kx);     // (eight addresses otherwise live through the walk)
+    float x[4][8];
 #pragma unroll
-    for (int t = 0; t < 4; t++) {
-      float x[8];
+    for (int c = 0; c < 8; c++) {
+      const f32x4 k4 = *reinterpret_cast<const f32x4 *>(slot + this->kbase + (kx ^ (16 * c)));
 #pragma unroll
-      for (int c = 0; c < 2; c++) {
-        const f32x4 k4 = *reinterpret_cast<const f32x4 *>(slot + this->kbase + (kx ^ (16 * (2 * t + c))));
-#pragma unroll
-        for (int e = 0; e < 4; e++) x[4 * c + e] = k4[e];
-      }
-      bf16x8 k[KP];
-      split8(x, k);
-#pragma unroll
-      for (int nt = 0; nt < NT; nt++) s[nt] = product(k, q[nt].f[t], s[nt]);
-      __builtin_amdgcn_sched_barrier(0);      // (the parts of one k-step at a time: the registers do not hold more)
+      for (int e = 0; e < 4; e++) x[c >> 1][4 * (c & 1) + e] = k4[e];
     }
+    s[0] = f32x16{0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    bf16x8 k[2][KP];
+    split8(x[0], k[0]);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int t = 0; t < 4; t++)
+      product(k[t & 1], q[0].f[t], s[0], [&](int m) {
+        if (t < 3) split_behind(m, x[t < 3 ? t + 1 : 3], k[(t + 1) & 1], 0, 4);
+      });
   }
   template <int NT, bool LO>
   __device__ __forceinline__ void weigh(const f32x16 (&w)[NT], const unsigned char *slot, f32x16 (&o)[NT][2], int) const {
+    static_assert(NT == 1, "32 queries");
+    float x[4][8], y[2][8];                   // V: [2 sp + dt]; weights: [sp]
 #pragma unroll
-    for (int sp = 0; sp < 2; sp++) {
-      bf16x8 pw[NT][3];
+    for (int g = 0; g < 4; g++)
 #pragma unroll
-      for (int nt = 0; nt < NT; nt++) {
-        float x[8];
+      for (int e = 0; e < 8; e++)
+        x[g][e] = *reinterpret_cast<const float *>(slot + this->vrd[g & 1] + (16 * (g >> 1) + 8 * (e >> 2) + (e & 3)) * 256);
 #pragma unroll
-        for (int e = 0; e < 8; e++) x[e] = w[nt][8 * sp + e];
-        split8(x, pw[nt]);
-      }
+    for (int e = 0; e < 16; e++) y[e >> 3][e & 7] = w[0][e];
+    bf16x8 pw[2][3], v[2][KP];
+    split8(y[0], pw[0]);
+    split8(x[0], v[0]);
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int dt = 0; dt < 2; dt++) {
-        float x[8];
-#pragma unroll
-        for (int e = 0; e < 8; e++) x[e] = *reinterpret_cast<const float *>(slot + this->vrd[dt] + (16 * sp + 8 * (e >> 2) + (e & 3)) * 256);
-        bf16x8 v[KP];
-        split8(x, v);
-#pragma unroll
-        for (int nt = 0; nt < NT; nt++) o[nt][dt] = product(v, pw[nt], o[nt][dt]);
-        __builtin_amdgcn_sched_barrier(0);
-      }
-    }
+    for (int g = 0; g < 4; g++)
+      product(v[g & 1], pw[g >> 1], o[0][g & 1], [&](int m) {
+        if (g < 3) split_behind(m, x[g < 3 ? g + 1 : 3], v[(g + 1) & 1], 0, 4);
+        if (g < 2) split_behind(m, y[1], pw[1], 2 * g, 2 * g + 2);
+      });
   }
 };
 
