@@ -239,17 +239,30 @@ ns_status launch_cls_combine_scores(const ns_attn_desc &d, const float *partials
 ns_status launch_cls_scores(int B, int H, int T, int G, const float *logits, const float *lse,
                             const float *partials, int nchunks, float *scores, hipStream_t s);
 
+// Where the rows of a product's first operand are patches of 8, 16, 32 pixels a side and it is read from the pixels themselves: a patch's row
+// of pixels is then whole 16-byte pieces, and 64 columns of the matrix are whole rows of pixels.  The launch also writes the row in
+// front of every image's patches.
+struct PixelRows {
+  int grid_w, lside, lchunks;           // patches in a row; log2 of a patch's side and of its 16-byte pieces a row
+  int images;
+  uint32_t row_bytes;                   // of the image
+  size_t plane_bytes;                   // of a channel
+  const uint16_t *cls, *pos;
+  uint16_t *x;
+  long long image_stride;               // of x, in elements
+};
+
 // linear map with fused epilogue, 256 x 256 workgroup tiles (ns_gemm256.hip); batch: so many of them with the
 // same weights, bias and residual in one launch, rows and results at the given distances in elements
 bool gemm256_supported(int M, int N, int K);
 ns_status launch_gemm256(const uint16_t *a, const uint16_t *w, const float *bias, const uint16_t *r,
                          uint16_t *c, int M, int N, int K, bool gelu, hipStream_t s, int batch = 1,
-                         long long a_stride = 0, long long c_stride = 0);
+                         long long a_stride = 0, long long c_stride = 0, const PixelRows *pixels = nullptr);
 // ... with tiles of 128 x 32 tj, tj = 2 .. 6 (ns_gemm128.hip)
 bool gemm128_supported(int N, int K);
 ns_status launch_gemm128(const uint16_t *a, const uint16_t *w, const float *bias, const uint16_t *r,
                          uint16_t *c, int M, int N, int K, bool gelu, hipStream_t s, int tj, int batch = 1,
-                         long long a_stride = 0, long long c_stride = 0);
+                         long long a_stride = 0, long long c_stride = 0, const PixelRows *pixels = nullptr);
 
 // ws: topk_select_workspace_bytes(B, N) bytes, 16-byte aligned (nothing for short score rows)
 size_t topk_select_workspace_bytes(int B, int N);

@@ -14,6 +14,26 @@ struct GemmIo {
 
 typedef bf16x8 __attribute__((address_space(3))) *lds_bf16x8_ptr;
 
+// Rows that are patches of an image, read from its pixels: byte offset of 16-byte chunk `chunk` (of the eight of a slice of 64
+// columns) of patch m, and of slice kt.
+__device__ __forceinline__ uint32_t pixel_chunk(const PixelRows &p, int m, uint32_t chunk) {
+  const int r = div_small(m, 1.f / (float)p.grid_w), c = m - r * p.grid_w;
+  return (((uint32_t)r << p.lside) + (chunk >> p.lchunks)) * p.row_bytes + ((uint32_t)c << (p.lside + 1)) +
+         16u * (chunk & ((1u << p.lchunks) - 1u));
+}
+__device__ __forceinline__ size_t pixel_slice(const PixelRows &p, int kt) {
+  const int ls = 2 * p.lside - 6;              // log2 of a channel's slices; a slice is 8 >> lchunks rows of pixels
+  return (size_t)(kt >> ls) * p.plane_bytes + (size_t)((kt & ((1 << ls) - 1)) << (3 - p.lchunks)) * p.row_bytes;
+}
+// x[b, 0, :] = cls + pos, the row in front of an image's patches: workgroup `wg` of those that do this
+__device__ __forceinline__ void cls_rows(const PixelRows &p, int wg, int dim, int tid) {
+  const long long t = (long long)wg * 256 + tid;
+  if (t >= (long long)p.images * dim) return;
+  const int b = (int)(t / dim), d = (int)(t - (long long)b * dim);
+  const float v = bf16_lo((uint32_t)p.cls[d]) + bf16_lo((uint32_t)p.pos[d]);
+  p.x[b * p.image_stride + d] = (uint16_t)(pack_bf16(v, 0.f) & 0xffffu);
+}
+
 // ---- epilogue of NS slabs of 32 weights x TOK tokens: accumulators -> LDS (fp32, [token][32*NS n]) -> lanes that
 // own 8 consecutive n of one token: + bias, GELU, + residual, one 16-byte store.  A wave has its SIMD to itself here, so
 // every latency it waits for is lost: the next slab is staged (two buffers) and its residual rows are requested before

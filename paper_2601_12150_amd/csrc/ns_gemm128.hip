@@ -24,18 +24,24 @@ struct Gemm128Params : GemmIo {
   int per_xcd;       // workgroups per XCD
   int batch;         // products of the same w, bias and r: a and c of the next one follow at these distances
   long long a_stride, c_stride;   // in elements
+  PixelRows pix;
 };
 
 constexpr int kSlots = 4;
 template <int TJ> constexpr int stage_bytes() { return TJ * 4096 + 16384; }   // 32 TJ token rows, 128 weight rows, 64 k each
 
-template <int TJ, bool GELU, bool RES>
+// PIX: the token rows are patches, read from their pixels
+template <int TJ, bool GELU, bool RES, bool PIX = false>
 __global__ __launch_bounds__(256, 2) void gemm128_bf16_kernel(Gemm128Params p) {
   constexpr int kX = TJ * 4096, kStage = stage_bytes<TJ>(), kReq = 4 + TJ;
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int l16 = lane & 15, wm = wave >> 1, wn = wave & 1;
   // workgroups are dealt round-robin to the 8 XCDs; each XCD gets a contiguous run of tiles, n fastest, so that the tiles that
   // share token rows meet in one L2
+  if (PIX && (int)blockIdx.x >= 8 * p.per_xcd) {
+    cls_rows(p.pix, (int)blockIdx.x - 8 * p.per_xcd, p.N, tid);
+    return;
+  }
   const int id = (int)(blockIdx.x & 7) * p.per_xcd + (int)(blockIdx.x >> 3), per = p.ntn * p.ntm;
   if (id >= per * p.batch) return;
   const int z = __builtin_amdgcn_readfirstlane(id / per), t0 = id - z * per;
@@ -55,12 +61,14 @@ __global__ __launch_bounds__(256, 2) void gemm128_bf16_kernel(Gemm128Params p) {
 #pragma unroll
   for (int j = 0; j < 2; j++) woff[j] = (uint32_t)(n0 + wave * 32 + drow) * rowB + dchunk(j);
 #pragma unroll
-  for (int j = 0; j < TJ; j++)
-    xoff[j] = (uint32_t)min(m0 + (wave * TJ + j) * 8 + drow, p.M - 1) * rowB + dchunk(wave * TJ + j);   // rows past M repeat the last row
+  for (int j = 0; j < TJ; j++) {
+    const int m = min(m0 + (wave * TJ + j) * 8 + drow, p.M - 1);     // rows past M repeat the last row
+    xoff[j] = PIX ? pixel_chunk(p.pix, m, dchunk(wave * TJ + j) >> 4) : (uint32_t)m * rowB + dchunk(wave * TJ + j);
+  }
   auto issue = [&](int kt, int j) {
     const uint32_t dst = lds0 + (uint32_t)(kt & (kSlots - 1)) * kStage;
     if (j < 4) dma16(wb + (size_t)kt * 128 + (size_t)j * 8 * rowB, woff[j & 1], dst + kX + (wave * 4 + j) * 1024);
-    else dma16(ab + (size_t)kt * 128, xoff[j - 4], dst + (wave * TJ + j - 4) * 1024);
+    else dma16(ab + (PIX ? pixel_slice(p.pix, kt) : (size_t)kt * 128), xoff[j - 4], dst + (wave * TJ + j - 4) * 1024);
   };
 
   // ---- fragments of half a slice (32 k): lane (row l16, quarter lane/16) reads logical chunk 4*h + lane/16
@@ -173,24 +181,29 @@ bool gemm128_supported(int N, int K) { return N % 128 == 0 && K % 64 == 0 && K >
 
 ns_status launch_gemm128(const uint16_t *a, const uint16_t *w, const float *bias, const uint16_t *r,
                          uint16_t *c, int M, int N, int K, bool gelu, hipStream_t s, int tj, int batch,
-                         long long a_stride, long long c_stride) {
+                         long long a_stride, long long c_stride, const PixelRows *pixels) {
   if (!gemm128_supported(N, K)) return fail(NS_ERR_UNSUPPORTED, "GEMM needs N %% 128 == 0 and K %% 64 == 0 (N=%d K=%d)", N, K);
   if ((long long)M * K * 2 >= 0x7fffffffLL || (long long)N * K * 2 >= 0x7fffffffLL)
     return fail(NS_ERR_UNSUPPORTED, "GEMM operand beyond 2 GiB");
-  Gemm128Params p{{a, w, r, bias, c, M, N, K}, N / 128, (M + 32 * tj - 1) / (32 * tj), 0, batch, a_stride, c_stride};
+  Gemm128Params p{{a, w, r, bias, c, M, N, K}, N / 128, (M + 32 * tj - 1) / (32 * tj), 0, batch, a_stride, c_stride, {}};
+  if (pixels) p.pix = *pixels;
   const long long tiles = (long long)p.ntn * p.ntm * batch, wgs = (tiles + 7) / 8 * 8;
-  if (wgs > 0x7fffffffLL) return fail(NS_ERR_UNSUPPORTED, "GEMM grid too large");
+  const long long cls = pixels ? ((long long)batch * N + 255) / 256 : 0;
+  if (wgs + cls > 0x7fffffffLL) return fail(NS_ERR_UNSUPPORTED, "GEMM grid too large");
   p.per_xcd = (int)(wgs / 8);
   typedef void (*kern_t)(Gemm128Params);
 #define NS_KERNS(TJ) \
   {gemm128_bf16_kernel<TJ, false, false>, gemm128_bf16_kernel<TJ, false, true>, gemm128_bf16_kernel<TJ, true, false>, gemm128_bf16_kernel<TJ, true, true>}
   static const kern_t kerns[5][4] = {NS_KERNS(2), NS_KERNS(3), NS_KERNS(4), NS_KERNS(5), NS_KERNS(6)};
 #undef NS_KERNS
-  const kern_t kern = kerns[tj - 2][(gelu ? 2 : 0) + (r ? 1 : 0)];
+  static const kern_t pixel_kerns[5] = {gemm128_bf16_kernel<2, false, true, true>, gemm128_bf16_kernel<3, false, true, true>,
+                                        gemm128_bf16_kernel<4, false, true, true>, gemm128_bf16_kernel<5, false, true, true>,
+                                        gemm128_bf16_kernel<6, false, true, true>};
+  const kern_t kern = pixels ? pixel_kerns[tj - 2] : kerns[tj - 2][(gelu ? 2 : 0) + (r ? 1 : 0)];
   const int lds = kSlots * (tj * 4096 + 16384);
   const ns_status rs = reserve_lds_once(reinterpret_cast<const void *>(kern), lds);
   if (rs != NS_OK) return rs;
-  hipLaunchKernelGGL(kern, dim3((unsigned)wgs), dim3(256), lds, s, p);
+  hipLaunchKernelGGL(kern, dim3((unsigned)(wgs + cls)), dim3(256), lds, s, p);
   return check_launch("gemm128_bf16_kernel");
 }
 

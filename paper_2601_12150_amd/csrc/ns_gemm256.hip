@@ -50,6 +50,7 @@ struct Gemm256Params : GemmIo {
                      // the mix that fills the chip's rounds of workgroups best
   int batch;         // products of the same w, bias and r: a and c of the next one follow at these distances
   long long a_stride, c_stride;   // in elements
+  PixelRows pix;
 };
 
 constexpr int kStageW = 256 * 128;           // bytes: 256 weight rows x 64 k
@@ -62,7 +63,7 @@ constexpr int kEpiWave = Epi<4>::kBytes;
 // also computes that slab against weight slabs 2*WM and 2*WM+1 of its n half, and every wave
 // issues 9 instead of 8 token-row requests per k-slice.  NK: slices of k where there
 // are only one or two, which are all requested at the start, else 0.
-template <int NK, int NTJ, bool EXT, int WM, bool GELU, bool RES, int TM = 256>
+template <int NK, int NTJ, bool EXT, int WM, bool GELU, bool RES, bool PIX, int TM = 256>
 __device__ __forceinline__ void gemm256_wave(const Gemm256Params &p, unsigned char *smem, int m0, int n0,
                                              int wave, int lane) {
   static_assert(TM == 256 || (TM == 192 && !EXT && NTJ <= 3), "192-row tiles: three slabs per wave, no ninth slab");
@@ -95,12 +96,12 @@ __device__ __forceinline__ void gemm256_wave(const Gemm256Params &p, unsigned ch
 #pragma unroll
   for (int j = 0; j < XREQ; j++) {
     const int m = min(m0 + (xreq0 + j) * 8 + drow, p.M - 1);         // rows past M repeat the last row
-    xoff[j] = (uint32_t)m * rowB + dchunk(xreq0 + j);
+    xoff[j] = PIX ? pixel_chunk(p.pix, m, dchunk(xreq0 + j) >> 4) : (uint32_t)m * rowB + dchunk(xreq0 + j);
   }
   auto issue_w = [&](int kt, int slot, int j) {
     dma16(wb + (size_t)kt * 128 + (size_t)j * 8 * rowB, woff[j & 1], lds0 + kW + slot * kStageW + (wreq0 + j) * 1024);
   };
-  auto issue_x = [&](int kt, int j) { dma16(ab + (size_t)kt * 128, xoff[j], lds0 + (kt & 1) * kX + (xreq0 + j) * 1024); };
+  auto issue_x = [&](int kt, int j) { dma16(ab + (PIX ? pixel_slice(p.pix, kt) : (size_t)kt * 128), xoff[j], lds0 + (kt & 1) * kX + (xreq0 + j) * 1024); };
 
   // ---- fragment reads: lane (row l16 of a 16-row tile, quarter lane/16) reads logical chunk 4*h + lane/16 of
   // half h of the slice, i.e. physical chunk (4*h + lane/16) ^ (l16 >> 1) (tiles start at multiples of 16 rows)
@@ -317,13 +318,18 @@ __device__ __forceinline__ void gemm256_wave(const Gemm256Params &p, unsigned ch
   if (EXT) E2::template emit<GELU, RES>(p, ebuf[NTJ & 1], biase, rese, m0 + 256, ne, lane, []() {});
 }
 
-template <int NK, bool GELU, bool RES>
+// PIX: the token rows are patches, read from their pixels
+template <int NK, bool GELU, bool RES, bool PIX = false>
 __global__ __launch_bounds__(256) void gemm256_bf16_kernel(Gemm256Params p) {
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   // workgroups are dealt round-robin to the 8 XCDs; give each XCD a contiguous run of tiles (n
   // fastest) so that the tiles sharing token rows and the weight matrix meet in one L2
   const int total = p.ntn * p.ntm * p.batch;
   int bid = blockIdx.x;
+  if (PIX && bid >= total) {
+    cls_rows(p.pix, bid - total, p.N, tid);
+    return;
+  }
   const bool uniform = p.n256 == 0 || p.n256 == p.ntm;     // (a mix of tile heights keeps the launch order: tall tiles first)
   if (uniform && total % 8 == 0) bid = (bid & 7) * (total / 8) + (bid >> 3);
   int bm = bid / p.ntn;
@@ -345,25 +351,25 @@ __global__ __launch_bounds__(256) void gemm256_bf16_kernel(Gemm256Params p) {
   const int rows = min(p.M - (m0 + wm * wrows), wrows);   // may be <= 0
   const int ntj = __builtin_amdgcn_readfirstlane(rows <= 0 ? 0 : (rows + 31) / 32);
   if (ext) {   // the extended tile is full: 256 + (1..32) rows
-    if (wm) gemm256_wave<NK, 4, true, 1, GELU, RES>(p, smem, m0, n0, wave, lane);
-    else gemm256_wave<NK, 4, true, 0, GELU, RES>(p, smem, m0, n0, wave, lane);
+    if (wm) gemm256_wave<NK, 4, true, 1, GELU, RES, PIX>(p, smem, m0, n0, wave, lane);
+    else gemm256_wave<NK, 4, true, 0, GELU, RES, PIX>(p, smem, m0, n0, wave, lane);
     return;
   }
   if (tm == 192) {
     switch (ntj) {
-      case 3: gemm256_wave<NK, 3, false, 0, GELU, RES, 192>(p, smem, m0, n0, wave, lane); break;
-      case 2: gemm256_wave<NK, 2, false, 0, GELU, RES, 192>(p, smem, m0, n0, wave, lane); break;
-      case 1: gemm256_wave<NK, 1, false, 0, GELU, RES, 192>(p, smem, m0, n0, wave, lane); break;
-      default: gemm256_wave<NK, 0, false, 0, GELU, RES, 192>(p, smem, m0, n0, wave, lane); break;
+      case 3: gemm256_wave<NK, 3, false, 0, GELU, RES, PIX, 192>(p, smem, m0, n0, wave, lane); break;
+      case 2: gemm256_wave<NK, 2, false, 0, GELU, RES, PIX, 192>(p, smem, m0, n0, wave, lane); break;
+      case 1: gemm256_wave<NK, 1, false, 0, GELU, RES, PIX, 192>(p, smem, m0, n0, wave, lane); break;
+      default: gemm256_wave<NK, 0, false, 0, GELU, RES, PIX, 192>(p, smem, m0, n0, wave, lane); break;
     }
     return;
   }
   switch (ntj) {
-    case 4: gemm256_wave<NK, 4, false, 0, GELU, RES>(p, smem, m0, n0, wave, lane); break;
-    case 3: gemm256_wave<NK, 3, false, 0, GELU, RES>(p, smem, m0, n0, wave, lane); break;
-    case 2: gemm256_wave<NK, 2, false, 0, GELU, RES>(p, smem, m0, n0, wave, lane); break;
-    case 1: gemm256_wave<NK, 1, false, 0, GELU, RES>(p, smem, m0, n0, wave, lane); break;
-    default: gemm256_wave<NK, 0, false, 0, GELU, RES>(p, smem, m0, n0, wave, lane); break;
+    case 4: gemm256_wave<NK, 4, false, 0, GELU, RES, PIX>(p, smem, m0, n0, wave, lane); break;
+    case 3: gemm256_wave<NK, 3, false, 0, GELU, RES, PIX>(p, smem, m0, n0, wave, lane); break;
+    case 2: gemm256_wave<NK, 2, false, 0, GELU, RES, PIX>(p, smem, m0, n0, wave, lane); break;
+    case 1: gemm256_wave<NK, 1, false, 0, GELU, RES, PIX>(p, smem, m0, n0, wave, lane); break;
+    default: gemm256_wave<NK, 0, false, 0, GELU, RES, PIX>(p, smem, m0, n0, wave, lane); break;
   }
 }
 
@@ -375,11 +381,12 @@ bool gemm256_supported(int M, int N, int K) {
 
 ns_status launch_gemm256(const uint16_t *a, const uint16_t *w, const float *bias, const uint16_t *r,
                          uint16_t *c, int M, int N, int K, bool gelu, hipStream_t s, int batch,
-                         long long a_stride, long long c_stride) {
+                         long long a_stride, long long c_stride, const PixelRows *pixels) {
   if (!gemm256_supported(M, N, K)) return fail(NS_ERR_UNSUPPORTED, "GEMM shape M=%d N=%d K=%d", M, N, K);
   if ((long long)M * K * 2 >= 0x7fffffffLL || (long long)N * K * 2 >= 0x7fffffffLL)
     return fail(NS_ERR_UNSUPPORTED, "GEMM operand beyond 2 GiB");
-  Gemm256Params p{{a, w, r, bias, c, M, N, K}, N / 256, 0, 0, 0, batch, a_stride, c_stride};
+  Gemm256Params p{{a, w, r, bias, c, M, N, K}, N / 256, 0, 0, 0, batch, a_stride, c_stride, {}};
+  if (pixels) p.pix = *pixels;
   const int q = M / 256, rem = M % 256;
   p.extended = (rem > 0 && rem <= 32) ? 1 : 0;
   p.ntm = (rem == 0 || p.extended) ? q : q + 1;
@@ -421,7 +428,7 @@ ns_status launch_gemm256(const uint16_t *a, const uint16_t *w, const float *bias
     }
     if (best_b > 0) { p.n256 = best_a; p.ntm = best_a + best_b; p.extended = 0; }
   }
-  const long long wgs = (long long)p.ntm * p.ntn * batch;
+  const long long wgs = (long long)p.ntm * p.ntn * batch + (pixels ? ((long long)batch * N + 255) / 256 : 0);
   if (wgs > 0x7fffffffLL) return fail(NS_ERR_UNSUPPORTED, "GEMM grid too large");
   typedef void (*kern_t)(Gemm256Params);
   // K = 64 and 128: the pipeline is three slices deep, they have instantiations without it (16385 x 1024: 11.3 and
@@ -431,7 +438,7 @@ ns_status launch_gemm256(const uint16_t *a, const uint16_t *w, const float *bias
    gemm256_bf16_kernel<NK, true, true>}
   static const kern_t kerns[3][4] = {NS_KERNS(0), NS_KERNS(1), NS_KERNS(2)};
 #undef NS_KERNS
-  const kern_t kern = kerns[K >= 192 ? 0 : K / 64][(gelu ? 2 : 0) + (r ? 1 : 0)];
+  const kern_t kern = pixels ? gemm256_bf16_kernel<0, false, true, true> : kerns[K >= 192 ? 0 : K / 64][(gelu ? 2 : 0) + (r ? 1 : 0)];
   const ns_status rs = reserve_lds_once(reinterpret_cast<const void *>(kern), kGemmLds);
   if (rs != NS_OK) return rs;
   hipLaunchKernelGGL(kern, dim3((unsigned)wgs), dim3(256), kGemmLds, s, p);

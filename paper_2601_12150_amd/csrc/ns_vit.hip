@@ -81,7 +81,7 @@ ns_status launch_layernorm(const uint16_t *x, const float *g, const float *b, ui
 // 449 to 25601 rows, widths 512 to 1536, this takes 0.7 % more than the best of all six, 256 x 256 tiles everywhere 22 %.
 ns_status launch_gemm(const uint16_t *a, const uint16_t *w, const float *bias, const uint16_t *r,
                       uint16_t *c, int M, int N, int K, bool gelu, hipStream_t s, int batch = 1, long long a_stride = 0,
-                      long long c_stride = 0) {
+                      long long c_stride = 0, const PixelRows *pixels = nullptr) {
   // NSATTN_GEMM=128 keeps the kernel of the smaller tiles for every shape; read once per process
   static const bool only128 = [] { const char *e = getenv("NSATTN_GEMM"); return e && e[0] == '1'; }();
   const int cus = device_cu_count();
@@ -89,11 +89,11 @@ ns_status launch_gemm(const uint16_t *a, const uint16_t *w, const float *bias, c
   int tj = 2;
   while (tj < 6 && rounds(tj) > 1) tj++;
   if (rounds(tj) > 1) {
-    if (gemm256_supported(M, N, K) && !only128) return launch_gemm256(a, w, bias, r, c, M, N, K, gelu, s, batch, a_stride, c_stride);
+    if (gemm256_supported(M, N, K) && !only128) return launch_gemm256(a, w, bias, r, c, M, N, K, gelu, s, batch, a_stride, c_stride, pixels);
     for (int t = 5; t >= 2; t--)
       if (rounds(t) * (2 + t) < rounds(tj) * (2 + tj)) tj = t;
   }
-  return launch_gemm128(a, w, bias, r, c, M, N, K, gelu, s, tj, batch, a_stride, c_stride);
+  return launch_gemm128(a, w, bias, r, c, M, N, K, gelu, s, tj, batch, a_stride, c_stride, pixels);
 }
 
 struct VitWorkspace {
@@ -440,6 +440,17 @@ ns_status vit_embed(int32_t batch, int32_t channels, int32_t grid_h, int32_t gri
                                               align_up((size_t)batch * N * Kp * 2, 256));
   const uint16_t *pos = static_cast<const uint16_t *>(pos_embed);
   uint16_t *x = static_cast<uint16_t *>(x_out);
+  const long long image_stride = (long long)(1 + N) * dim;
+  // Patches of 8, 16 or 32 pixels a side: the product reads the pixels itself (us: 64x64 patches of 16 18.5 -> 12.2, 128x128
+  // 40 -> 28.7, two images of 200x180 236 -> 199).
+  const int lside = patch == 8 ? 3 : (patch == 16 ? 4 : (patch == 32 ? 5 : 0));
+  if (lside && K >= 192 && N < (1 << 21) && reinterpret_cast<uintptr_t>(pixels) % 16 == 0) {
+    const size_t row = (size_t)grid_w * patch * 2;
+    const PixelRows pix{grid_w, lside, lside - 3, batch, (uint32_t)row, row * grid_h * patch, static_cast<const uint16_t *>(cls_token),
+                        pos, x, image_stride};
+    return launch_gemm(static_cast<const uint16_t *>(pixels), static_cast<const uint16_t *>(w_patch), b_patch, pos + dim, x + dim, N, dim, Kp,
+                       false, s, batch, (long long)channels * grid_h * grid_w * patch * patch, image_stride, &pix);
+  }
   EmbedParams p{};
   p.pixels = static_cast<const uint16_t *>(pixels); p.w = static_cast<const uint16_t *>(w_patch);
   p.cls = static_cast<const uint16_t *>(cls_token); p.pos = pos;
@@ -474,7 +485,6 @@ ns_status vit_embed(int32_t batch, int32_t channels, int32_t grid_h, int32_t gri
   if (st != NS_OK) return st;
   const uint16_t *w = Kp != K ? wp : p.w;
   // rows 1..N of every image: projection + bias, the position embeddings ride in as the residual
-  const long long image_stride = (long long)(1 + N) * dim;
   return launch_gemm(a, w, b_patch, pos + dim, x + dim, N, dim, Kp, false, s, batch, (long long)N * Kp, image_stride);
 }
 

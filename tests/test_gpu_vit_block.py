@@ -250,6 +250,37 @@ def test_patch_embedding_matches_oracle(nb, B, ch, gh, gw, ps, dim):
                           "block on embedded tokens")
 
 
+@pytest.mark.parametrize("B,ch,gh,gw,ps,dim", [
+    (1, 3, 1, 1, 16, 128), (2, 3, 5, 7, 16, 384), (3, 1, 9, 13, 32, 512), (2, 3, 21, 34, 8, 512), (1, 4, 12, 11, 8, 256),
+    (2, 3, 37, 29, 32, 512), (1, 3, 101, 77, 16, 1024),     # (launches of several rounds: 256 x 256 tiles)
+    (4, 3, 64, 64, 16, 1024), (3, 3, 48, 43, 8, 2048),      # .. with a ninth slab: 2064 = 8 x 256 + 16
+])
+def test_patch_embedding_straight_from_the_pixels(nb, B, ch, gh, gw, ps, dim):
+    """Patches of 8, 16 and 32 pixels a side on 16-byte addresses are read by the product itself; pixels 8 bytes further on go by way of the
+    patch matrix.  Same columns in the same order: same bits, and both the oracle's tokens."""
+    rng = np.random.default_rng(gh * 1000 + gw)
+    gen = torch.Generator(device="cuda").manual_seed(gh * 1000 + gw)
+    n = B * ch * gh * gw * ps * ps
+    buf = torch.randn(n + 8, generator=gen, device="cuda").to(torch.bfloat16)
+    px = buf[:n].view(B, ch, gh * ps, gw * ps)
+    far = torch.empty_like(buf)
+    far[4:4 + n] = buf[:n]
+    far = far[4:4 + n].view(px.shape)
+    assert px.data_ptr() % 16 == 0 and far.data_ptr() % 16 == 8
+    w = (0.05 * torch.randn((dim, ch * ps * ps), generator=gen, device="cuda")).to(torch.bfloat16)
+    b = 0.1 * torch.randn(dim, generator=gen, device="cuda")
+    cls, pos = torch.randn(dim, generator=gen, device="cuda").to(torch.bfloat16), torch.randn((1 + gh * gw, dim), generator=gen, device="cuda").to(torch.bfloat16)
+    out, by_way = nb.vit_embed(px, w, b, cls, pos, ps), nb.vit_embed(far, w, b, cls, pos, ps)
+    torch.cuda.synchronize()
+    assert torch.equal(out, by_way)
+    f64 = lambda t: to_np(t).astype(np.float64)
+    rows = np.unique(np.concatenate([rng.integers(0, gh * gw, 40), [0, gh * gw - 1]]))     # the oracle on some rows
+    p = f64(px).reshape(B, ch, gh, ps, gw, ps).transpose(0, 2, 4, 1, 3, 5).reshape(B, gh * gw, -1)[:, rows]
+    ref = p @ f64(w).T + b.cpu().numpy().astype(np.float64) + f64(pos)[1 + rows]
+    assert_attn_close(f64(out)[:, 1 + rows], ref, "bf16", "from the pixels")
+    assert_attn_close(f64(out)[:, 0], np.repeat((f64(cls) + f64(pos)[0])[None], B, 0), "bf16", "first rows")
+
+
 def test_stack_without_pruning_equals_repeated_blocks(nb):
     B, g, block, heads, dim, mlp = 1, 16, 8, 8, 512, 512
     rng = np.random.default_rng(22)
