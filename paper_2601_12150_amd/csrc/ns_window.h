@@ -1398,17 +1398,19 @@ inline double mean_reach(int grid, int side, int block) {
 // to hide its latencies behind), every further one adds 0.65.
 struct WindowCost {
   double tiles, steps;     // tiles that exist, mean 32-key steps of a tile
+  bool fp32;               // steps of 32 queries on parts: longer ones, so that a start is 1.1 to 2 of them
   double of(int ks) const {
     const double per_cu = tiles * ks / 4.0 / device_cu_count();
-    return 0.65 * (std::max(per_cu, 1.0) + 0.65) * (std::max(steps / ks, 1.0) + (ks == 4 ? 4.2 : (ks == 2 ? 3.7 : 3.0)));
+    return 0.65 * (std::max(per_cu, 1.0) + 0.65) * (std::max(steps / ks, 1.0) + (fp32 ? (ks == 4 ? 1.95 : (ks == 2 ? 1.2 : 1.1)) : (ks == 4 ? 4.2 : (ks == 2 ? 3.7 : 3.0))));
   }
   // Waves per tile.  One wave per tile does the least work (no merge, one start), four fill the chip when there
   // are few tiles and shorten the walk when it is long.  (Measured with each forced over 88 grids of 14 to
   // 248 a side, 8 to 32 heads: the choice takes 0.7 % more than the best on average, 15 % more at worst - 20x33, 8x8 blocks, 16 heads,
   // two waves 15.1 us, four 13.1 -, 12 % with 24x24 blocks on 100x60.  Squares of several blocks take longer a step, for their
   // masks, than this says - 245x245, 2x2 blocks: 174 us, not 98 -, but by about the same factor for each split: of eight
-  // such grids in bf16 the choice is the best on seven and 3 % off on one, of seven in fp32 on five, 7 % off
-  // on one, and on 32x32 with 2x2 blocks two waves take 24.9 us where one or four take 20.3.)
+  // such grids in bf16 the choice is the best on seven and 3 % off on one.  fp32, 41 grids of 14 to 64 a side: 1.1 % more than the best, 11 % at
+  // worst - 23x27, 8x8 blocks, four images, two waves 56.3 us, four 50.6 -; with bf16's starts 6.6 %: 28x28, 7x7 blocks, two images 42.1 -> 34.6,
+  // 36x21 47.8 -> 35.8, 44x44, 8x8 blocks 87 -> 74.)
   int split() const { return of(4) <= of(2) && of(4) <= of(1) ? 4 : (of(2) <= of(1) ? 2 : 1); }
 };
 inline WindowCost window_cost(const ns_attn_desc &d, int qt) {
@@ -1418,7 +1420,7 @@ inline WindowCost window_cost(const ns_attn_desc &d, int qt) {
   auto runs = [&](int h, int w) { return std::ceil(full * h * w / qt); };
   const double per_image = (double)nh * nw * runs(side, side) + nw * runs(eh, side) + nh * runs(side, ew) + runs(eh, ew);
   return WindowCost{per_image * d.batch * d.heads,
-                    (full * mean_reach(d.grid_h, side, d.block) * mean_reach(d.grid_w, side, d.block) + d.n_global) / 32.0 + 0.5};
+                    (full * mean_reach(d.grid_h, side, d.block) * mean_reach(d.grid_w, side, d.block) + d.n_global) / 32.0 + 0.5, qt == 32};
 }
 
 // The geometry on the host; qt = queries per tile, rows_per_group = global rows that one global
