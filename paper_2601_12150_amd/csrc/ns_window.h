@@ -158,7 +158,7 @@ __device__ __forceinline__ uint32_t screened(uint32_t x, int pass) {
 // bf16: v_mfma_f32_32x32x16_bf16, weights rounded to bf16 for the second product.
 struct StepBf16 {
   typedef uint16_t elem;
-  typedef StepBf16 Whole;
+  static constexpr bool kParts = false;
   static constexpr int kDepth = 2, kReq = 4, kHalf = 4096;     // slots, requests per 32 rows, bytes of 32 rows
   struct Q { bf16x8 f[4]; };
   typedef s16x4 __attribute__((address_space(3))) *tr_ptr;
@@ -396,6 +396,7 @@ template <typename T>
 struct StepF32Whole {
   typedef T elem;
   static constexpr int kDepth = 1, kReq = 8, kHalf = 8192;
+  static constexpr bool kParts = false;
   struct Q { float f[32]; };
   uint32_t kbase, kx, vrd[2];
   int rrow;
@@ -475,8 +476,9 @@ struct StepF32Whole {
   }
 };
 
-// Values e and e + 1 of eight as sums of up to three bf16 numbers each, the next the rounding of what those before leave: exact,
-// all 24 bits.
+constexpr float kBf16Max = 0x1.fep127f;
+// Values e and e + 1 of eight as sums of up to three bf16 numbers each, the next the rounding of what those before leave: all 24
+// bits of a value between 2^-103, below which the last parts may be subnormal, and kBf16Max, which the first part must not exceed.
 template <int P>
 __device__ __forceinline__ void split_pair(const float (&x)[8], bf16x8 (&p)[P], int e) {
   float a = x[e], b = x[e + 1];
@@ -499,27 +501,58 @@ __device__ __forceinline__ void split8(const float (&x)[8], bf16x8 (&p)[P]) {
 }
 
 // fp32 precision from v_mfma_f32_32x32x16_bf16: each value in three bf16 parts (a row's of bf16 in one), and of the nine products
-// of parts the six that count, smallest first; the others are below 2^-25 of the whole, less than one rounding of the sum.
+// of parts the six that count, smallest first.  The three left out are together at most 2^-24 of the whole (2^-27.5 rms of random
+// values), as much as one rounding of the product; the error of the rows is smaller than with fp32 products, which round more often.
 // That is 192 cycles of the matrix pipe for 16 k where v_mfma_f32_32x32x2_f32 takes 512.  (64 queries a step would share K's and V's
-// parts, but the parts of 64 rows of Q leave too few registers: 30 are spilled.)  A value that is not finite has parts that are NaN: rows whose sums are not
-// finite are computed once more from whole values (walk_not_finite on Whole, half of the queries at a time).
+// parts, but the parts of 64 rows of Q leave too few registers: 30 are spilled.)
+// A value that is not finite, or that bf16 rounds to infinity, has parts that are NaN.  K: the logits of a step that has some are
+// formed once more, from whole values (walk_keys).  Q: load_q takes other parts.  V: rows whose sums are not finite are computed once
+// more from whole values (walk_not_finite on Whole, half of the queries at a time).
 template <typename T>
 struct StepF32 : StepF32Whole<T> {
   typedef StepF32Whole<T> Whole;
+  static constexpr bool kParts = true;
   static constexpr int KP = sizeof(T) == 4 ? 3 : 1;      // parts of a value of K or V
   struct Q { bf16x8 f[4][3]; };                          // [channels 8 s .. of this half][part]
   __device__ __forceinline__ void load_q(Q &q, const char *base, int64_t rowB, int tok, int lane, float mul) const {
     const T *row = reinterpret_cast<const T *>(base + (int64_t)tok * rowB) + 32 * (lane >> 5);
-#pragma unroll
-    for (int s = 0; s < 4; s++) {
-      float x[8];
+    float top = 0.f;
+    auto load8 = [&](const T *from, float (&x)[8]) {
 #pragma unroll
       for (int c = 0; c < 2; c++) {
-        const f32x4 v = Whole::load4(row + 8 * s + 4 * c);
+        const f32x4 v = Whole::load4(from + 4 * c);
 #pragma unroll
         for (int e = 0; e < 4; e++) x[4 * c + e] = v[e] * mul;
       }
+    };
+#pragma unroll
+    for (int s = 0; s < 4; s++) {
+      float x[8];
+      load8(row + 8 * s, x);
+#pragma unroll
+      for (int e = 0; e < 8; e++) top = max_abs(top, x[e]);
       split8(x, q.f[s]);
+    }
+    // Values whose first part would not be finite: the largest bf16 number in front, or, for one that is not finite itself, nothing
+    // but the last part, which is multiplied with a key's first part alone.
+    if (__builtin_expect(__any(!(top < kBf16Max)), 0)) {
+      row += opaque(0);
+#pragma unroll
+      for (int s = 0; s < 4; s++) {
+        float x[8];
+        load8(row + 8 * s, x);
+#pragma unroll
+        for (int e = 0; e < 8; e++) {
+          const float size = __builtin_fabsf(x[e]);
+          if (!(size < kBf16Max)) {
+            const float most = size < INFINITY ? __builtin_copysignf(kBf16Max, x[e]) : 0.f, rest = x[e] - most;
+            const __bf16 mid = (__bf16)(size < INFINITY ? rest : 0.f);
+            q.f[s][0][e] = (__bf16)most;
+            q.f[s][1][e] = mid;
+            q.f[s][2][e] = (__bf16)(rest - (float)mid);
+          }
+        }
+      }
     }
   }
   // c += a b of values in KP and 3 parts.  between(m): what is to stand behind product m of kProducts; the fences keep it there,
@@ -567,24 +600,47 @@ struct StepF32 : StepF32Whole<T> {
         if (t < 3) split_behind(m, x[t < 3 ? t + 1 : 3], k[(t + 1) & 1], 0, 4);
       });
   }
-  template <int NT, bool LO>
-  __device__ __forceinline__ void weigh(const f32x16 (&w)[NT], const unsigned char *slot, f32x16 (&o)[NT][2], int) const {
-    static_assert(NT == 1, "32 queries");
-    float x[4][8], y[2][8];                   // V: [2 sp + dt]; weights: [sp]
+  // The logits from whole values, with key l32's row read from memory: its slot may be the next step's already.
+  __device__ __forceinline__ void whole_logits(const Q &q, const char *row, int lane, f32x16 &s) const {
+    const T *k = reinterpret_cast<const T *>(row) + 32 * (lane >> 5);
+    s = f32x16{0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int c = 0; c < 8; c++) {
+      const f32x4 k4 = Whole::load4(k + 4 * c);
+#pragma unroll
+      for (int e = 0; e < 4; e += 2) {
+        uint32_t p[3];
+#pragma unroll
+        for (int i = 0; i < 3; i++) {         // (opaque: put together here, not kept through the walk)
+          const bf16x8 &f = q.f[c >> 1][i];
+          p[i] = (uint32_t)opaque(__builtin_bit_cast(int, bf16x2{f[4 * (c & 1) + e], f[4 * (c & 1) + e + 1]}));
+        }
+        s = __builtin_amdgcn_mfma_f32_32x32x2f32(k4[e], bf16_lo(p[0]) + (bf16_lo(p[1]) + bf16_lo(p[2])), s, 0, 0, 0);
+        s = __builtin_amdgcn_mfma_f32_32x32x2f32(k4[e + 1], bf16_hi(p[0]) + (bf16_hi(p[1]) + bf16_hi(p[2])), s, 0, 0, 0);
+      }
+    }
+  }
+  struct V { float x[4][8]; };                // [2 sp + dt]
+  __device__ __forceinline__ void load_v(V &v, const unsigned char *slot) const {
+    auto &x = v.x;
 #pragma unroll
     for (int g = 0; g < 4; g++)
 #pragma unroll
       for (int e = 0; e < 8; e++)
         x[g][e] = *reinterpret_cast<const float *>(slot + this->vrd[g & 1] + (16 * (g >> 1) + 8 * (e >> 2) + (e & 3)) * 256);
+  }
+  __device__ __forceinline__ void weigh(const f32x16 &w, const V &vv, f32x16 (&o)[2]) const {
+    const auto &x = vv.x;
+    float y[2][8];                            // weights: [sp]
 #pragma unroll
-    for (int e = 0; e < 16; e++) y[e >> 3][e & 7] = w[0][e];
+    for (int e = 0; e < 16; e++) y[e >> 3][e & 7] = w[e];
     bf16x8 pw[2][3], v[2][KP];
     split8(y[0], pw[0]);
     split8(x[0], v[0]);
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int g = 0; g < 4; g++)
-      product(v[g & 1], pw[g >> 1], o[0][g & 1], [&](int m) {
+      product(v[g & 1], pw[g >> 1], o[g & 1], [&](int m) {
         if (g < 3) split_behind(m, x[g < 3 ? g + 1 : 3], v[(g + 1) & 1], 0, 4);
         if (g < 2) split_behind(m, y[1], pw[1], 2 * g, 2 * g + 2);
       });
@@ -645,8 +701,8 @@ struct WaveAcc {
       for (int e = 0; e < 16; e++) { o[nt][0][e] *= alpha; o[nt][1][e] *= alpha; }
     }
   }
-  // logits -> weights
-  __device__ __forceinline__ void weights(f32x16 &s, int nt, float c) {
+  // logits -> weights, whose sum it gives back
+  __device__ __forceinline__ float weights(f32x16 &s, int nt, float c) {
     float l0 = 0.f, l1 = 0.f;
 #pragma unroll
     for (int e = 0; e < 16; e += 2) {
@@ -656,6 +712,7 @@ struct WaveAcc {
       l1 += s[e + 1];
     }
     l[nt] += l0 + l1;
+    return l0 + l1;
   }
 };
 
@@ -885,18 +942,43 @@ __device__ __forceinline__ void walk_keys(const S &st, WaveAcc<S, NT> &a, const 
       issue_k(slot);
       if (RING) request_tokens(i + D + 2);
     }
+    float before[NT], sum[NT];
 #pragma unroll
     for (int nt = 0; nt < NT; nt++) {
       if (careful || i == 0) a.reference(s[nt], nt, c);
-      a.weights(s[nt], nt, c);
+      before[nt] = a.l[nt];
+      sum[nt] = a.weights(s[nt], nt, c);
     }
+    // Parts: where a logit is NaN, which whole values may make an infinity, the step's once more.  (Asked of the sum of weights, behind
+    // V's reads: 28x28, 7x7 blocks 25.3 -> 25.4 us, 64x64, four images 269.8 -> 270.8; asked of the logits, which holds the next K back,
+    // 25.6 and 1 to 3 % more.  With one infinite key a head 27.3 and 272; whole walks for the rows that see it, 41.8 and 419.)
+    auto mend = [&]() {
+      if constexpr (S::kParts) {
+        if (!__builtin_expect(__any(sum[0] != sum[0]), 0)) return;
+        const int tok = RING ? fix_token(i, lane & 31, ring[(i & 3) * 64 + (lane & 31)]) : key_token(i);
+        st.whole_logits(a.q[0], kb + (int64_t)tok * rowB, lane, s[0]);
+        fix(i, 0, s[0]);                      // (stores more than are counted: a wait then waits for more, not for less)
+        a.l[0] = before[0];
+        if (careful || i == 0) a.reference(s[0], 0, c);
+        a.weights(s[0], 0, c);
+      }
+    };
+    if (!WITH_V) mend();
     if (WITH_V) {
       // V of step i.  Behind it: the next step (two slots), this step's stores, K of step i + D
       if (rem >= D) wait_vm<kNext + E + R + (D - 1) * TL>();
       else if (D == 2 && rem == 1) wait_vm<kNext + E>();
       else wait_vm<E>();
       screen(wsm + kV + slot * S::kHalf);
-      st.template weigh<NT, LO>(s, wsm + kV + slot * S::kHalf, a.o, lane);
+      if constexpr (S::kParts) {
+        typename S::V v;
+        st.load_v(v, wsm + kV + slot * S::kHalf);
+        __builtin_amdgcn_sched_barrier(0);
+        mend();
+        st.weigh(s[0], v, a.o[0]);
+      } else {
+        st.template weigh<NT, LO>(s, wsm + kV + slot * S::kHalf, a.o, lane);
+      }
       if constexpr (S::kDepth == 2 && NT == 2)
         if (slot == 0 && i == 0 && st.exact > 0)
 #pragma unroll

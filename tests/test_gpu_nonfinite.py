@@ -192,3 +192,52 @@ def test_keys_that_are_not_finite_in_fp32(nb, monkeypatch, gh, gw, block, G, spl
     ref = oracle.ns_attn(q, k, v, gh, gw, block, 0.125, n_global=G)
     assert np.isfinite(ref[0, 1]).all() and not np.isfinite(ref[0, 0]).all() and np.isfinite(ref[0, 0]).any()
     assert_same_values(to_np(out), ref, "f32", "keys not finite")
+
+
+@pytest.mark.parametrize("pruned", [False, True])
+@pytest.mark.parametrize("G", [1, 3, 40])
+@pytest.mark.parametrize("dtype,what", [("f32", "-inf"), ("f32", "large"), ("f32", "query"), ("bf16 in fp32", "-inf"), ("bf16 in fp32", "query")])
+def test_by_products_of_keys_that_are_not_finite_in_fp32(nb, monkeypatch, dtype, what, G, pruned):
+    """Logits, log-sum-exps and scores beside the rows, by every route.  A key whose logit is -inf has the weight 0 and is nobody else's
+    business.  large: finite values that bf16 rounds to infinity.  query: an infinite value in a global token's row, whose
+    logits are infinities of either sign (its log-sum-exp and the scores of its image are NaN).  bf16 rows are computed in
+    fp32 where the scale is negative.  A run of 40 such keys is a wave's whole first step."""
+    monkeypatch.delenv("NSATTN_KERNEL", raising=False)
+    dt, scale = (dtype, 0.125) if dtype == "f32" else ("bf16", -0.125)
+    gh, gw, block, H = 26, 27, 8, 2
+    rng = np.random.default_rng(G)
+    kept = np.flatnonzero(rng.random(gh * gw) < 0.8) if pruned else np.arange(gh * gw)
+    N = len(kept)
+    q, k, v = synth.small_case(900 + G, 2, H, 64, 1, N, dt, n_global=G)
+    q[:, :, :, 7] = np.maximum(np.abs(q[:, :, :, 7]), np.float32(0.125))
+    if what == "query":
+        q[0, 1, G - 1, 9] = np.inf
+    else:
+        bad = np.float32({"-inf": -np.inf, "large": -3.4e38}[what] * np.sign(scale))
+        k[0, 1, G + N // 2, 7] = bad                    # one head's
+        k[0, :, G + N // 3, 7] = bad                    # all heads'
+        k[1, 0, G + 96:G + 136, 7] = bad
+        k[1, 1, G + N - 1, 7] = bad                     # the last token stands in for keys past the end
+    coords = np.ascontiguousarray(np.broadcast_to(synth.raster_coords(gh, gw)[kept], (2, N))) if pruned else None
+    print("by-products: %s %s G=%d pruned %s" % (dtype, what, G, pruned), flush=True)
+    dq, dk, dv = (to_dev(a, dt) for a in (q, k, v))
+    dc = None if coords is None else torch.from_numpy(coords).cuda()
+    out, logits, lse = nb.ns_attn_forward(dq, dk, dv, gh, gw, block, scale, coords=dc, want_cls=True, n_global=G)
+    out2, logits2, lse2, scores = nb.ns_attn_forward_scores(dq, dk, dv, gh, gw, block, scale, coords=dc, n_global=G)
+    alone, later = nb.cls_scores(dq, dk, scale, n_global=G), nb.cls_scores_from_logits(logits, lse, n_global=G)
+    torch.cuda.synchronize()
+    with np.errstate(invalid="ignore"):
+        s = scale * np.einsum("bhgd,bhtd->bhgt", q[:, :, :G].astype(np.float64), k.astype(np.float64))
+        m = s.max(axis=-1, keepdims=True)
+        ref_lse = (m + np.log(np.exp(s - m).sum(axis=-1, keepdims=True)))[..., 0]
+        ref, ref_scores = oracle.ns_attn(q, k, v, gh, gw, block, scale, coords=coords, n_global=G), oracle.cls_scores(q, k, scale, n_global=G)
+    assert not np.isnan(s).any() and np.isfinite(ref_lse).all() == np.isfinite(ref_scores).all() == (what != "query")
+    assert not np.isfinite(s).all() or np.abs(s).max() > 1e36
+    assert_same_values(to_np(out), ref, dt, "rows")
+    # (the bounds that these values have where all keys are finite; 2^-20 of a logit where it is large)
+    np.testing.assert_allclose(to_np(logits).reshape(s.shape), s, rtol=2.0 ** -20, atol=2e-5)
+    np.testing.assert_allclose(to_np(lse).reshape(ref_lse.shape), ref_lse, rtol=0, atol=2e-5)
+    for name, got in (("with the attention", scores), ("by itself", alone), ("from the logits", later)):
+        np.testing.assert_allclose(to_np(got), ref_scores, rtol=5e-5, atol=1e-10, err_msg=name)
+    same = lambda a, b: torch.equal(torch.nan_to_num(a), torch.nan_to_num(b)) and torch.equal(a.isnan(), b.isnan())
+    assert same(out, out2) and same(logits, logits2) and same(lse, lse2)
