@@ -156,18 +156,20 @@ __global__ __launch_bounds__(kCombineThreads) void cls_combine_kernel(const floa
   cls_combine_body<T, WITH_V>(blockIdx.x, blockIdx.y, partials, nchunks, H, G, out, osb, osh, ost, lse);
 }
 
-// Workgroup `blk` of image b scores 256 patches: thread = (patch, group of rows), the groups added in order.  H counts the global
-// rows of an image (heads x global tokens): the score is the mean over all of them.  lse given
-// directly, or recomputed per row from the (max, sum) of the partial records.
+// Workgroup `blk` of image b scores THREADS / GROUPS patches: thread = (patch, group of rows).  H counts the global
+// rows of an image (heads x global tokens): the score is the mean over all of them, every fourth row summed by itself and the four sums
+// added in order, so that it does not depend on the launch.  lse given directly, or recomputed per row from the (max, sum) of the partial records.
 // Bound: latency, of the records and then of a thread's share of the logits, which come from other XCDs' L2s: hence four groups and up to
 // eight loads on their way.  (A thread per patch that went through all rows: 80 rows, 2 x 10000 patches, 12.3 us the launch, this 7.7.)
-constexpr int kScoreThreads = 1024, kScorePatches = 256;
+// Where that many threads are more than the chip holds at once, a thread takes a patch's rows alone.
+constexpr int kRowSums = 4;
+template <int THREADS, int GROUPS>
 __device__ __forceinline__ void cls_scores_body(int blk, int b, const float *logits, const float *lse,
                                                 const float *partials, int nchunks, int H, int T_, int G,
                                                 float *scores) {
-  __shared__ float s_lse[1024], s_part[kScoreThreads / kScorePatches][kScorePatches];
+  constexpr int nthreads = THREADS, kPatches = THREADS / GROUPS, kOwn = kRowSums / GROUPS;
+  __shared__ float s_lse[1024], s_part[GROUPS > 1 ? GROUPS : 1][GROUPS > 1 ? kPatches : 1];
   const int tid = threadIdx.x;
-  constexpr int nthreads = kScoreThreads, kGroups = kScoreThreads / kScorePatches;
   if (lse) {
     for (int h = tid; h < H; h += nthreads) s_lse[h] = lse[(size_t)b * H + h];
   } else {
@@ -199,30 +201,42 @@ __device__ __forceinline__ void cls_scores_body(int blk, int b, const float *log
     }
   }
   __syncthreads();
-  const int N = T_ - G, g = tid / kScorePatches, lj = tid % kScorePatches, j = blk * kScorePatches + lj;
+  const int N = T_ - G, g = tid / kPatches, lj = tid % kPatches, j = blk * kPatches + lj;
   const float *row = logits + (size_t)b * H * T_ + G + min(j, N - 1);
-  float acc = 0.f;
-#pragma unroll 8
-  for (int h = g; h < H; h += kGroups) acc += __builtin_amdgcn_exp2f((row[(size_t)h * T_] - s_lse[h]) * kLog2e);
-  s_part[g][lj] = acc;
-  __syncthreads();
-  if (g != 0 || j >= N) return;
+  auto weight = [&](int h) { return __builtin_amdgcn_exp2f((row[(size_t)h * T_] - s_lse[h]) * kLog2e); };
+  float acc[kOwn] = {};
+  int h0 = 0;
+#pragma unroll(8 / kOwn)
+  for (; h0 + kRowSums <= H; h0 += kRowSums)
 #pragma unroll
-  for (int i = 1; i < kGroups; i++) acc += s_part[i][lj];
-  scores[(size_t)b * N + j] = acc / (float)H;
+    for (int i = 0; i < kOwn; i++) acc[i] += weight(h0 + g + GROUPS * i);
+#pragma unroll
+  for (int i = 0; i < kOwn; i++)
+    if (h0 + g + GROUPS * i < H) acc[i] += weight(h0 + g + GROUPS * i);
+  static_assert(kOwn == 1 || GROUPS == 1, "sums in the order of their rows");
+  if (GROUPS > 1) {
+    s_part[g][lj] = acc[0];
+    __syncthreads();
+    if (g != 0) return;
+  }
+  if (j >= N) return;
+  float sum = acc[0];
+#pragma unroll
+  for (int i = 1; i < kRowSums; i++) sum += GROUPS > 1 ? s_part[i % GROUPS][lj] : acc[i % kOwn];
+  scores[(size_t)b * N + j] = sum / (float)H;
 }
 
-// grid (ceil(N/256), B)
-__global__ __launch_bounds__(kScoreThreads) void cls_scores_kernel(const float *logits, const float *lse,
-                                                         const float *partials, int nchunks, int H,
-                                                         int T_, int G, float *scores) {
-  cls_scores_body(blockIdx.x, blockIdx.y, logits, lse, partials, nchunks, H, T_, G, scores);
+// grid (ceil(N / (THREADS / GROUPS)), B)
+template <int THREADS, int GROUPS>
+__global__ __launch_bounds__(THREADS) void cls_scores_kernel(const float *logits, const float *lse, const float *partials, int nchunks,
+                                                             int H, int T_, int G, float *scores) {
+  cls_scores_body<THREADS, GROUPS>(blockIdx.x, blockIdx.y, logits, lse, partials, nchunks, H, T_, G, scores);
 }
 
-// Both in one launch, grid (H + ceil(N/256), B), 1024 threads: the first H workgroups of an image
-// merge the records of one global row each (output row and log-sum-exp), the others score 256
+// Both in one launch, grid (H + ceil(N / (1024 / GROUPS)), B), 1024 threads: the first H workgroups of an image
+// merge the records of one global row each (output row and log-sum-exp), the others score 1024 / GROUPS
 // patches each, with the log-sum-exps they derive from the records themselves.
-template <typename T>
+template <typename T, int GROUPS>
 __global__ __launch_bounds__(kCombineThreads) void cls_combine_scores_kernel(const float *partials, int nchunks,
                                                                              int heads, int G, T *out, int64_t osb,
                                                                              int64_t osh, int64_t ost, float *lse,
@@ -232,7 +246,7 @@ __global__ __launch_bounds__(kCombineThreads) void cls_combine_scores_kernel(con
   if ((int)blockIdx.x < H)
     cls_combine_body<T, true>(blockIdx.x, blockIdx.y, partials, nchunks, heads, G, out, osb, osh, ost, lse);
   else
-    cls_scores_body(blockIdx.x - H, blockIdx.y, logits, nullptr, partials, nchunks, H, T_, G, scores);
+    cls_scores_body<kCombineThreads, GROUPS>(blockIdx.x - H, blockIdx.y, logits, nullptr, partials, nchunks, H, T_, G, scores);
 }
 
 }  // namespace
@@ -302,29 +316,40 @@ ns_status launch_cls_combine(const ns_attn_desc &d, const float *partials, void 
   return check_launch("cls_combine_kernel");
 }
 
+// Four threads to a patch shorten a launch whose workgroups, of 1024 threads then, are all on the chip at once (two a CU).  More of them
+// take a second round, each of them deriving the log-sum-exps anew: a thread per patch, eight workgroups a CU, is faster from there on.
+// (cls_scores, 16 heads, four images, four threads to a patch against one: 32768 patches each, 512 workgroups, 53.4 us against 52.9; 33000
+// patches 55.9 against 53.0; one head, one image of 262144 27.5 against 21.3.  80 rows, 16384 patches, 64 workgroups 36.6 against 40.9.)
+static bool one_round_of_1024(long long wgs) { return wgs <= 2LL * device_cu_count(); }
+
 ns_status launch_cls_combine_scores(const ns_attn_desc &d, const float *partials, void *out, float *lse,
                                     const float *logits, float *scores, hipStream_t s, int nchunks) {
   const int nch = nchunks > 0 ? nchunks : cls_num_chunks(d.tokens);
-  const int N = d.tokens - d.n_global;
-  static_assert(kCombineThreads == kScoreThreads, "one launch");
-  dim3 grid(d.heads * d.n_global + (N + kScorePatches - 1) / kScorePatches, d.batch), blk(kCombineThreads);
-  if (d.dtype == NS_F32)
-    hipLaunchKernelGGL((cls_combine_scores_kernel<float>), grid, blk, 0, s, partials, nch, d.heads, d.n_global,
-                       static_cast<float *>(out), d.out_stride_b, d.out_stride_h, d.out_stride_t, lse, logits,
-                       d.tokens, scores);
-  else
-    hipLaunchKernelGGL((cls_combine_scores_kernel<uint16_t>), grid, blk, 0, s, partials, nch, d.heads, d.n_global,
-                       static_cast<uint16_t *>(out), d.out_stride_b, d.out_stride_h, d.out_stride_t, lse, logits,
-                       d.tokens, scores);
+  const int N = d.tokens - d.n_global, H = d.heads * d.n_global;
+  const bool four = one_round_of_1024((long long)(H + (N + 255) / 256) * d.batch);
+  const int patches = four ? kCombineThreads / 4 : kCombineThreads;
+  dim3 grid(H + (N + patches - 1) / patches, d.batch), blk(kCombineThreads);
+#define NS_LAUNCH(T, GROUPS)                                                                                                  \
+  hipLaunchKernelGGL((cls_combine_scores_kernel<T, GROUPS>), grid, blk, 0, s, partials, nch, d.heads, d.n_global,              \
+                     static_cast<T *>(out), d.out_stride_b, d.out_stride_h, d.out_stride_t, lse, logits, d.tokens, scores)
+  if (d.dtype == NS_F32) {
+    if (four) NS_LAUNCH(float, 4);
+    else NS_LAUNCH(float, 1);
+  } else {
+    if (four) NS_LAUNCH(uint16_t, 4);
+    else NS_LAUNCH(uint16_t, 1);
+  }
+#undef NS_LAUNCH
   return check_launch("cls_combine_scores_kernel");
 }
 
 ns_status launch_cls_scores(int B, int H, int T, int G, const float *logits, const float *lse,
                             const float *partials, int nchunks, float *scores, hipStream_t s) {
-  const int N = T - G;
-  dim3 grid((N + kScorePatches - 1) / kScorePatches, B), blk(kScoreThreads);
-  hipLaunchKernelGGL(cls_scores_kernel, grid, blk, 0, s, logits, lse, partials, nchunks, H * G, T, G,
-                     scores);
+  const dim3 grid((T - G + 255) / 256, B);
+  if (one_round_of_1024((long long)grid.x * B))
+    hipLaunchKernelGGL((cls_scores_kernel<1024, 4>), grid, dim3(1024), 0, s, logits, lse, partials, nchunks, H * G, T, G, scores);
+  else
+    hipLaunchKernelGGL((cls_scores_kernel<256, 1>), grid, dim3(256), 0, s, logits, lse, partials, nchunks, H * G, T, G, scores);
   return check_launch("cls_scores_kernel");
 }
 

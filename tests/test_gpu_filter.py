@@ -223,3 +223,36 @@ def test_indices_written_over_the_scores(nb):
     kept, _, _ = nb.topk_filter(buf, 9831, kept_idx=buf.view(torch.int32)[:, :9831])
     torch.cuda.synchronize()
     assert np.array_equal(kept.cpu().numpy(), oracle.topk(scores, 9831))
+
+
+@pytest.mark.parametrize("H,G,N", [(1, 1, 50001), (3, 1, 49920), (4, 1, 50000), (5, 3, 45000), (16, 1, 44801), (1, 7, 131073)])
+def test_scores_do_not_depend_on_the_launch(nb, H, G, N):
+    """Three images are more workgroups than the chip holds at once, one image (but the last) is not: other numbers of threads to a
+    patch, the same sums.  Exponentials and sums of at most 21 positive terms in fp32: 2^-20 of the result."""
+    gen = torch.Generator(device="cuda").manual_seed(N)
+    logits = torch.randn((3, H, G, G + N), generator=gen, device="cuda") * 2.0
+    lse = torch.logsumexp(logits.double(), dim=-1).float()
+    got = nb.cls_scores_from_logits(logits, lse, n_global=G)
+    alone = torch.cat([nb.cls_scores_from_logits(logits[b:b + 1], lse[b:b + 1], n_global=G) for b in range(3)])
+    ref = (logits.double() - lse.double()[..., None]).exp()[..., G:].mean(dim=(1, 2))
+    torch.cuda.synchronize()
+    assert torch.equal(got, alone)
+    np.testing.assert_allclose(got.double().cpu().numpy(), ref.cpu().numpy(), rtol=2.0 ** -19, atol=0)
+
+
+@pytest.mark.parametrize("H,G,B", [(2, 1, 60), (3, 2, 57)])
+def test_scores_with_the_attention_do_not_depend_on_the_launch(nb, monkeypatch, H, G, B):
+    """As above where the records are merged in the same launch."""
+    monkeypatch.setenv("NSATTN_KERNEL", "lists1")
+    g = 40
+    gen = torch.Generator(device="cuda").manual_seed(H)
+    q, k, v = (torch.randn((B, H, G + g * g, 64), generator=gen, device="cuda").to(torch.bfloat16) for _ in range(3))
+    out, logits, lse, scores = nb.ns_attn_forward_scores(q, k, v, g, g, 8, n_global=G)
+    torch.cuda.synchronize()
+    ref = torch.softmax(logits.double().reshape(B, H, G, -1), dim=-1)[..., G:].mean(dim=(1, 2))
+    np.testing.assert_allclose(scores.double().cpu().numpy(), ref.cpu().numpy(), rtol=2.0 ** -17, atol=0)
+    for b in (0, B - 1):
+        few = nb.ns_attn_forward_scores(*(t[b:b + 2] if b == 0 else t[b - 1:b + 1] for t in (q, k, v)), g, g, 8, n_global=G)
+        torch.cuda.synchronize()
+        at = 0 if b == 0 else 1
+        assert torch.equal(few[3][at], scores[b]) and torch.equal(few[0][at], out[b]) and torch.equal(few[2][at], lse[b])
