@@ -23,16 +23,22 @@ __global__ __launch_bounds__(256, 2) void attn_generic_kernel(WindowParams p) {
   window_attention<StepF32<T>, 1, LISTS, MASK, KS>(p, smem);
 }
 
-constexpr int kListThreads = 1024, kListWaves = kListThreads / 64, kListUnroll = 4;   // coordinates per thread and round
+constexpr int kListRound = 4096;      // coordinates per round
 
 // Pruned sequence: bucket the surviving patch tokens by block, preserving sequence order.
 // grid (nblocks, B); each workgroup scans the image's coordinate list for its own block, 4096
-// positions a round, the next round's on their way while one is counted and placed.  Bound: a chain of rounds; with 16 waves
-// instead of four a round's instructions take a quarter of the time (9831 of 16384 patches, 8x8 blocks: 9.1 -> 5.6 us the launch).
+// positions a round.  Bound: a chain of rounds; with 16 waves, and the next round's coordinates on their way while one is counted and
+// placed, instead of four a round's instructions take a quarter of the time (9831 of 16384 patches, 8x8 blocks: 9.1 -> 5.6 us the
+// launch).  That holds while all workgroups are on the chip at once, two of 16 waves a CU; beyond, where four waves fill it as well
+// and each step of the prefix sum is done by fewer, four are faster (whole calls, us, 16 waves and four: 512 blocks 22.1 and 23.3, 529
+// blocks 30.3 and 28.9, 1024 49.8 and 44.1, 16384 463 and 282).
+template <int kListThreads>
 __global__ __launch_bounds__(kListThreads) void block_lists_kernel(const int32_t *coords, int n_patch,
                                                           int n_global, int grid_h, int grid_w,
                                                           int block, int nbw, int nblocks, int cap,
                                                           int32_t *lists, int32_t *counts) {
+  constexpr int kListWaves = kListThreads / 64, kListUnroll = kListRound / kListThreads;   // coordinates per thread and round
+  static_assert(kListUnroll * kListWaves == 64, "one run per lane");
   const int blk = blockIdx.x, b = blockIdx.y;
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int R = blk / nbw, C = blk - R * nbw;
@@ -42,9 +48,14 @@ __global__ __launch_bounds__(kListThreads) void block_lists_kernel(const int32_t
   int32_t *lb = lists + ((size_t)b * nblocks + blk) * cap;
   int running = 0, flip = 0;
   uint32_t pc[kListUnroll];
+  auto load = [&](int base) {
 #pragma unroll
-  for (int i = 0; i < kListUnroll; i++) pc[i] = (uint32_t)cb[min(kListThreads * i + tid, n_patch - 1)];
-  for (int base = 0; base < n_patch; base += kListThreads * kListUnroll, flip ^= 1) {
+    for (int i = 0; i < kListUnroll; i++) pc[i] = (uint32_t)cb[min(base + kListThreads * i + tid, n_patch - 1)];
+  };
+  constexpr bool kAhead = kListUnroll <= 4;         // (16 of them ahead: 2 % more where the chip is full of workgroups)
+  if (kAhead) load(0);
+  for (int base = 0; base < n_patch; base += kListRound, flip ^= 1) {
+    if (!kAhead) load(base);
     unsigned long long bal[kListUnroll];
 #pragma unroll
     for (int i = 0; i < kListUnroll; i++) {
@@ -53,11 +64,9 @@ __global__ __launch_bounds__(kListThreads) void block_lists_kernel(const int32_t
       if (lane == 0) wcnt[flip][kListWaves * i + wave] = __popcll(bal[i]);
     }
     // the next round's coordinates, on their way while this one is counted and placed
-    if (base + kListThreads * kListUnroll < n_patch)
-#pragma unroll
-      for (int i = 0; i < kListUnroll; i++) pc[i] = (uint32_t)cb[min(base + kListThreads * (kListUnroll + i) + tid, n_patch - 1)];
+    if (kAhead && base + kListRound < n_patch) load(base + kListRound);
     __syncthreads();
-    // counts of the (group of 1024, wave) runs in sequence order: lane = run, prefix sum over the 64
+    // counts of the (group of kListThreads, wave) runs in sequence order: lane = run, prefix sum over the 64
     int pre = wcnt[flip][lane];
 #pragma unroll
     for (int s = 1; s < 64; s <<= 1) {
@@ -81,9 +90,10 @@ __global__ __launch_bounds__(kListThreads) void block_lists_kernel(const int32_t
 
 ns_status launch_block_lists(const ns_attn_desc &d, int32_t *lists, int32_t *counts, hipStream_t s) {
   const int nbh = (d.grid_h + d.block - 1) / d.block, nbw = (d.grid_w + d.block - 1) / d.block;
-  dim3 grid(nbh * nbw, d.batch);
-  static_assert(kListUnroll * kListWaves == 64, "one run per lane");
-  hipLaunchKernelGGL(block_lists_kernel, grid, dim3(kListThreads), 0, s, d.coords, d.tokens - d.n_global,
+  const dim3 grid(nbh * nbw, d.batch);
+  const bool wide = (long long)nbh * nbw * d.batch <= 2LL * device_cu_count();
+  const auto kern = wide ? block_lists_kernel<1024> : block_lists_kernel<256>;
+  hipLaunchKernelGGL(kern, grid, dim3(wide ? 1024 : 256), 0, s, d.coords, d.tokens - d.n_global,
                      d.n_global, d.grid_h, d.grid_w, d.block, nbw, nbh * nbw, d.block * d.block,
                      lists, counts);
   return check_launch("block_lists_kernel");

@@ -88,3 +88,20 @@ def test_global_row_in_a_launch_of_its_own(nb, monkeypatch, gh, gw, gain):
     np.testing.assert_allclose(to_np(logits).reshape(ref_logits.shape), ref_logits, rtol=0, atol=2e-5 * gain)
     np.testing.assert_allclose(to_np(lse).reshape(ref_lse.shape), ref_lse, rtol=0, atol=2e-5 * gain)
     np.testing.assert_allclose(to_np(scores), oracle.cls_scores(q, k, 0.125), rtol=5e-5 * gain, atol=1e-10)
+
+
+@pytest.mark.parametrize("g,block,B,n", [(64, 8, 8, 2457), (64, 8, 9, 2457), (92, 8, 1, 8193), (92, 2, 1, 5001), (72, 1, 1, 4097), (72, 1, 1, 4096)])
+def test_block_lists_of_few_and_of_many_blocks(nb, monkeypatch, g, block, B, n):
+    """Up to two blocks per CU (512) and more than that take other numbers of waves per block; one to three rounds of 4096 coordinates,
+    the last of one or of all; survivors in no order."""
+    monkeypatch.setenv("NSATTN_KERNEL", "lists")
+    rng = np.random.default_rng(n)
+    kept = np.stack([rng.permutation(g * g)[:n] for _ in range(B)])
+    q, k, v = synth.small_case(n, B, 1, 64, 1, n, "bf16")
+    coords = np.ascontiguousarray(synth.raster_coords(g, g)[kept])
+    out = nb.ns_attn_forward(*(to_dev(a, "bf16") for a in (q, k, v)), g, g, block, 0.125, coords=torch.from_numpy(coords).cuda())
+    torch.cuda.synchronize()
+    at = [0, B - 1] if B > 1 else [0]
+    rows = np.unique(np.concatenate([[0, 1, n], 1 + rng.integers(0, n, 500)]))
+    ref = oracle.ns_attn(q[at], k[at], v[at], g, g, block, 0.125, coords=np.ascontiguousarray(coords[at]), rows=rows)
+    assert_attn_close(to_np(out)[at][:, :, rows], ref, "bf16", "%d blocks" % (-(-g // block)) ** 2)
