@@ -170,8 +170,8 @@ struct EmbedParams {
   unsigned gather_wgs, pad_wgs;
 };
 
-// E: uint32_t for an even patch side and pixels on 4-byte addresses, else uint16_t
-template <typename E>
+// E: uint32_t for an even patch side and pixels on 4-byte addresses, else uint16_t; U: loads in flight
+template <typename E, int U>
 __global__ __launch_bounds__(256) void embed_prepare_kernel(EmbedParams p) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   const int tid = threadIdx.x;
@@ -213,7 +213,6 @@ __global__ __launch_bounds__(256) void embed_prepare_kernel(EmbedParams p) {
     const int patch = x / epp;
     unsigned char *dst = smem + patch * p.pitch + (x - patch * epp) * (int)sizeof(E);
     const uint16_t *src = img + (long long)x * PE;
-    constexpr int U = 12;               // loads in flight: all of a wave's for up to 16 pixels and three channels
     for (int r0 = wave; r0 < rows; r0 += 4 * U) {
       E v[U];
 #pragma unroll
@@ -457,13 +456,19 @@ ns_status vit_embed(int32_t batch, int32_t channels, int32_t grid_h, int32_t gri
   p.a = a; p.wp = wp; p.x = x;
   p.channels = channels; p.grid_h = grid_h; p.grid_w = grid_w; p.ps = patch; p.K = K; p.Kp = Kp; p.dim = dim; p.batch = batch;
   // Rows staged 32 bytes apart from a multiple of 128: the short runs of neighbouring patches then fall on different
-  // banks.  As many patches per workgroup as 64 lanes have pairs of pixels of an image row for - every load of a wave is then on
-  // its way at once, and many workgroups share a CU -, fewer where that leaves CUs without work, and what 64 KB hold.
-  // (100 x 100 patches of 14 pixels, this launch: up to 16 patches, eight loads at a time 13.4 us, this 10.5.)
+  // banks.  As many patches per workgroup as 64 lanes have elements of an image row for - every load of a wave is then on
+  // its way at once, and many workgroups share a CU -, or 16 where that is more and such a workgroup would read too little (8000
+  // bytes) while there are many of them (128 patches per CU); fewer where that leaves CUs without work, and what 64 KB hold.
+  // Loads at a time: those of the 4, 8, 12 with which a wave's share of the image rows takes the fewest turns of the loop and loads
+  // past the last row.  (Whole calls, us, with up to 16 patches and eight loads, with 64 lanes' worth and twelve, with this: one channel,
+  // 256x256 patches of 24 pixels 63, 83, 60; three channels, 128x128 of 18 on odd addresses 53, 63, 53; 100x100 of 14 30.6, 27.8, 27.8.  Over
+  // 305 shapes with patches of 1 to 56 pixels, one to twelve channels, this takes 1.7 % more than the best of six forms, those two 14 and 12 %.)
   p.pitch = 2 * Kp + 32;
-  const long long per_cu = (long long)batch * N / (2 * device_cu_count());
+  const long long patches = (long long)batch * N, per_cu = patches / (2 * device_cu_count());
   const bool pairs = patch % 2 == 0 && reinterpret_cast<uintptr_t>(pixels) % 4 == 0;
-  int per_wg = (int)std::min<long long>(std::max(1, 64 / (pairs ? patch / 2 : patch)), std::max<long long>(4, per_cu));
+  const int rows = channels * patch, lanes_worth = std::max(1, 64 / (pairs ? patch / 2 : patch));
+  const bool small = 64LL * (pairs ? 4 : 2) * rows < 8000 && patches > 128LL * device_cu_count();
+  int per_wg = (int)std::min<long long>(small ? std::max(lanes_worth, 16) : lanes_worth, std::max<long long>(4, per_cu));
   per_wg = std::max(1, std::min(per_wg, 65536 / p.pitch));
   p.segs = (grid_w + per_wg - 1) / per_wg;
   p.per_wg = (grid_w + p.segs - 1) / p.segs;
@@ -474,7 +479,12 @@ ns_status vit_embed(int32_t batch, int32_t channels, int32_t grid_h, int32_t gri
   if (wgs > 0x7fffffffLL) return fail(NS_ERR_UNSUPPORTED, "too many patches");
   p.gather_wgs = (unsigned)gather;
   p.pad_wgs = (unsigned)pads;
-  void (*const kern)(EmbedParams) = pairs ? embed_prepare_kernel<uint32_t> : embed_prepare_kernel<uint16_t>;
+  auto turns = [&](int u) { return (rows + 4 * u - 1) / (4 * u) * (u + 1); };
+  const int loads = turns(12) <= std::min(turns(8), turns(4)) ? 12 : (turns(8) <= turns(4) ? 8 : 4);
+  typedef void (*kern_t)(EmbedParams);
+  static const kern_t kerns[2][3] = {{embed_prepare_kernel<uint16_t, 4>, embed_prepare_kernel<uint16_t, 8>, embed_prepare_kernel<uint16_t, 12>},
+                                     {embed_prepare_kernel<uint32_t, 4>, embed_prepare_kernel<uint32_t, 8>, embed_prepare_kernel<uint32_t, 12>}};
+  const kern_t kern = kerns[pairs][loads / 4 - 1];
   const int lds = p.per_wg * p.pitch;
   if (lds > 65536) {                    // (one patch of more than 32752 values)
     st = reserve_lds_once(reinterpret_cast<const void *>(kern), 160 * 1024);

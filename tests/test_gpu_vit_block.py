@@ -250,6 +250,28 @@ def test_patch_embedding_matches_oracle(nb, B, ch, gh, gw, ps, dim):
                           "block on embedded tokens")
 
 
+@pytest.mark.parametrize("offset", [0, 1, 2])
+@pytest.mark.parametrize("B,ch,gh,gw,ps,dim", [
+    # four, eight and twelve loads at a time, in one turn of the loop and in several, the last of one row of pixels and of all
+    (1, 1, 5, 9, 3, 128), (2, 3, 33, 35, 12, 128), (1, 3, 21, 40, 22, 128), (1, 7, 9, 11, 13, 256), (1, 3, 12, 13, 18, 256), (1, 11, 6, 5, 3, 128),
+    # many patches of little each
+    (1, 1, 190, 181, 3, 128), (1, 1, 190, 181, 24, 128), (2, 2, 130, 129, 10, 128)])
+def test_patch_embedding_by_way_of_the_patch_matrix(nb, B, ch, gh, gw, ps, dim, offset):
+    """Pixels on 16-byte addresses, 2 and 4 bytes behind them: elements of two pixels where side and address are even, else of one."""
+    gen = torch.Generator(device="cuda").manual_seed(ps * 100 + offset)
+    n = B * ch * gh * gw * ps * ps
+    px = torch.randn(n + 8, generator=gen, device="cuda").to(torch.bfloat16)[offset:offset + n].view(B, ch, gh * ps, gw * ps)
+    w = (0.05 * torch.randn((dim, ch * ps * ps), generator=gen, device="cuda")).to(torch.bfloat16)
+    b = 0.1 * torch.randn(dim, generator=gen, device="cuda")
+    cls, pos = torch.randn(dim, generator=gen, device="cuda").to(torch.bfloat16), torch.randn((1 + gh * gw, dim), generator=gen, device="cuda").to(torch.bfloat16)
+    out = nb.vit_embed(px, w, b, cls, pos, ps)
+    rows = px.view(B, ch, gh, ps, gw, ps).permute(0, 2, 4, 1, 3, 5).reshape(B * gh * gw, -1).float()
+    ref = (rows @ w.float().T + b).view(B, gh * gw, dim) + pos[1:].float()
+    torch.cuda.synchronize()
+    assert_attn_close(to_np(out)[:, 1:], to_np(ref), "bf16", "by way of the matrix")
+    assert_attn_close(to_np(out)[:, 0], np.repeat(to_np(cls.float() + pos[0].float())[None], B, 0), "bf16", "first rows")
+
+
 @pytest.mark.parametrize("B,ch,gh,gw,ps,dim", [
     (1, 3, 1, 1, 16, 128), (2, 3, 5, 7, 16, 384), (3, 1, 9, 13, 32, 512), (2, 3, 21, 34, 8, 512), (1, 4, 12, 11, 8, 256),
     (2, 3, 37, 29, 32, 512), (1, 3, 101, 77, 16, 1024),     # (launches of several rounds: 256 x 256 tiles)
