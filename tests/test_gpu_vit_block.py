@@ -223,7 +223,7 @@ def test_stack_pruning_of_a_long_sequence(nb):
                                                # odd patch side and pixels (2-byte path); batches whose images have more than one
                                                # row of tiles; one patch that takes more than 64 KB
                                                (2, 3, 17, 19, 15, 256), (3, 1, 26, 31, 16, 512), (1, 3, 2, 3, 106, 128),
-                                               # batches whose images end in a ninth slab (784 = 3 x 256 + 16): 640, 64 and 128 columns
+                                               # batches whose images end in a quarter of a tile (784 = 12 x 64 + 16): 640, 64 and 128 columns
                                                (2, 3, 28, 28, 14, 256), (3, 1, 28, 28, 8, 256), (2, 2, 28, 28, 8, 512)])
 def test_patch_embedding_matches_oracle(nb, B, ch, gh, gw, ps, dim):
     """Tokenisation: 14-pixel patches (588 columns, padded to 640 inside) and 16-pixel patches (768),
@@ -272,14 +272,29 @@ def test_patch_embedding_by_way_of_the_patch_matrix(nb, B, ch, gh, gw, ps, dim, 
     assert_attn_close(to_np(out)[:, 0], np.repeat(to_np(cls.float() + pos[0].float())[None], B, 0), "bf16", "first rows")
 
 
-@pytest.mark.parametrize("B,ch,gh,gw,ps,dim", [
-    (1, 3, 1, 1, 16, 128), (2, 3, 5, 7, 16, 384), (3, 1, 9, 13, 32, 512), (2, 3, 21, 34, 8, 512), (1, 4, 12, 11, 8, 256),
-    (2, 3, 37, 29, 32, 512), (1, 3, 101, 77, 16, 1024),     # (launches of several rounds: 256 x 256 tiles)
-    (4, 3, 64, 64, 16, 1024), (3, 3, 48, 43, 8, 2048),      # .. with a ninth slab: 2064 = 8 x 256 + 16
+def gemm_tiles(M, N, batch):
+    """Half slabs (2 to 6) of the 128-column tiles that a launch of one round of them takes, 0: 256 x 256 tiles (the rule of launch_gemm
+    for N that 256 divides and M >= 256)."""
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    return next((tj for tj in range(2, 7) if -(-M // (32 * tj)) * (N // 128) * batch <= cus), 0)
+
+
+@pytest.mark.parametrize("B,ch,gh,gw,ps,dim,tiles", [
+    (1, 3, 1, 1, 16, 128, 2), (2, 3, 5, 7, 16, 384, 2), (3, 1, 9, 13, 32, 512, 2), (2, 3, 21, 34, 8, 512, 2), (1, 4, 12, 11, 8, 256, 2),
+    (2, 3, 37, 29, 32, 512, 2),
+    # larger tiles, with each patch side: whole ones, last rows of a tile and of half a slab, several images
+    (1, 3, 47, 61, 16, 1024, 3), (3, 3, 45, 47, 32, 384, 3), (4, 3, 33, 39, 8, 512, 3), (1, 3, 64, 64, 16, 1024, 4), (1, 4, 61, 59, 8, 1024, 4),
+    (1, 3, 53, 67, 32, 1024, 4), (2, 3, 69, 67, 8, 512, 5), (1, 3, 70, 70, 16, 1024, 5), (1, 3, 63, 75, 32, 1024, 5), (1, 3, 73, 79, 32, 1024, 6),
+    (2, 3, 75, 76, 16, 512, 6), (1, 3, 78, 72, 8, 1024, 6),
+    # launches of several rounds: 256 x 256 tiles
+    (1, 3, 101, 77, 16, 1024, 0), (1, 3, 83, 79, 32, 1024, 0),
+    (4, 3, 64, 64, 16, 1024, 0), (3, 3, 48, 43, 8, 2048, 0),      # .. with a ninth slab: 2064 = 8 x 256 + 16
+    (3, 1, 48, 43, 32, 2048, 0),
 ])
-def test_patch_embedding_straight_from_the_pixels(nb, B, ch, gh, gw, ps, dim):
+def test_patch_embedding_straight_from_the_pixels(nb, B, ch, gh, gw, ps, dim, tiles):
     """Patches of 8, 16 and 32 pixels a side on 16-byte addresses are read by the product itself; pixels 8 bytes further on go by way of the
     patch matrix.  Same columns in the same order: same bits, and both the oracle's tokens."""
+    assert gemm_tiles(gh * gw, dim, B) == tiles
     rng = np.random.default_rng(gh * 1000 + gw)
     gen = torch.Generator(device="cuda").manual_seed(gh * 1000 + gw)
     n = B * ch * gh * gw * ps * ps
