@@ -154,7 +154,7 @@ __device__ __forceinline__ void gemm256_wave(const Gemm256Params &p, unsigned ch
         if ((2 * reads <= groups ? 2 * r : r * groups / reads) == i) read(r);
       // (asm: with the builtin, whose result may lie elsewhere than its accumulator, the compiler rotates the 256 registers through
       // moves in every slice.  It pads no hazard for asm: nothing but these products and reads from LDS, which the compiler
-      // waits for, touches an operand inside the loop.)
+      // waits for, touches an operand inside the loop and in the slices behind it.  A test reads that off the built code.)
       if (mfmas > 0) {
         f32x4 &c = acc[4 * (ks & 1) + i / (2 * NT)][i % (2 * NT)];
         const bf16x8 &w = fw[ks & 1][i / (2 * NT)], &x = fx[ks >> 1][i % (2 * NT)];
@@ -394,7 +394,8 @@ ns_status launch_gemm256(const uint16_t *a, const uint16_t *w, const float *bias
   {
     // Rows of tiles: a of 256 token rows, then b of 192, a*256 + b*192 >= M.  Workgroups start in
     // launch order, a CU takes the next one when it is free: the mix with the shortest makespan
-    // (a 192-row tile costs 0.8 of a 256-row one).
+    // (a 192-row tile costs 0.8 of a 256-row one: 12288 rows against 16384, launches of whole rounds of the one or the other, K x N 1024 x 3072
+    // 69.2 and 86.4 us, 4096 x 1024 73.4 and 94.0, the most 0.84, 1024 x 1024, the least 0.72, 4096 x 4096).
     const int cus = device_cu_count();
     auto makespan = [&](long long na, long long nb) -> double {
       // na*ntn tiles of cost 1.0, then nb*ntn of cost 0.8, each given to the unit that is free first.
@@ -431,8 +432,8 @@ ns_status launch_gemm256(const uint16_t *a, const uint16_t *w, const float *bias
   const long long wgs = (long long)p.ntm * p.ntn * batch + (pixels ? ((long long)batch * N + 255) / 256 : 0);
   if (wgs > 0x7fffffffLL) return fail(NS_ERR_UNSUPPORTED, "GEMM grid too large");
   typedef void (*kern_t)(Gemm256Params);
-  // K = 64 and 128: the pipeline is three slices deep, they have instantiations without it (16385 x 1024: 11.3 and
-  // 12.6 us, with residual 14.6 and 16.1; the kernel of 128 x 128 tiles 19.4 and 22.5, 27.9 and 31.2)
+  // K = 64 and 128: the pipeline is three slices deep, they have instantiations without it (16385 x 1024: 10.8 and
+  // 12.0 us, with residual 12.8 and 14.2)
 #define NS_KERNS(NK)                                                                                                     \
   {gemm256_bf16_kernel<NK, false, false>, gemm256_bf16_kernel<NK, false, true>, gemm256_bf16_kernel<NK, true, false>,     \
    gemm256_bf16_kernel<NK, true, true>}
