@@ -507,7 +507,7 @@ __device__ __forceinline__ void split8(const float (&x)[8], bf16x8 (&p)[P]) {
 // parts, but the parts of 64 rows of Q leave too few registers: 30 are spilled.)
 // A value that is not finite, or that bf16 rounds to infinity, has parts that are NaN.  K: the logits of a step that has some are
 // formed once more, from whole values (walk_keys).  Q: load_q takes other parts.  V: rows whose sums are not finite are computed once
-// more from whole values (walk_not_finite on Whole, half of the queries at a time).
+// more from whole values (walk_not_finite on Whole).
 template <typename T>
 struct StepF32 : StepF32Whole<T> {
   typedef StepF32Whole<T> Whole;
@@ -1050,18 +1050,18 @@ __device__ __forceinline__ void walk_not_finite(const S &st, WaveAcc<S, NT> &a, 
       }
 }
 
-// ... of a step that works on parts: the queries of half nt (lane l32: token tok), from whole values
-template <class S, bool RING, bool LO, int NT, class... Args>
-__device__ __forceinline__ void whole_rows(const S &st, WaveAcc<S, NT> &a, int nt, const char *qb, const char *kb, const char *vb,
-                                           int64_t rowB, int tok, float scale, unsigned char *wsm, int n, float c, int lane, Args &&...args) {
+// ... of a step that works on parts: the queries (lane l32: token tok) from whole values
+template <class S, bool RING, class... Args>
+__device__ __forceinline__ void whole_rows(const S &st, WaveAcc<S, 1> &a, const char *qb, const char *kb, const char *vb, int64_t rowB,
+                                           int tok, float scale, unsigned char *wsm, int n, float c, int lane, Args &&...args) {
   typedef typename S::Whole W;
   WaveAcc<W, 1> b;
   static_cast<const W &>(st).load_q(b.q[0], qb, rowB, tok, lane, scale);
-  walk_not_finite<W, 1, RING, LO>(st, b, kb, vb, rowB, wsm, n, c, lane, args...);
-  a.o[nt][0] = b.o[0][0];
-  a.o[nt][1] = b.o[0][1];
-  a.m[nt] = b.m[0];
-  a.l[nt] = b.l[0];
+  walk_not_finite<W, 1, RING, false>(st, b, kb, vb, rowB, wsm, n, c, lane, args...);
+  a.o[0][0] = b.o[0][0];
+  a.o[0][1] = b.o[0][1];
+  a.m[0] = b.m[0];
+  a.l[0] = b.l[0];
 }
 
 // a query tile's walk: pipelined where there are two slots
@@ -1180,7 +1180,7 @@ __device__ __forceinline__ void global_rows_chunk(const GlobalRows &p, int heads
     if (!a.exceeds(careful ? INFINITY : kLargeSum)) break;
     if (careful) {
       if constexpr (WITH_V && kBf16) walk_not_finite<S, 1, false, true>(st, a, kb, vb, rowB, wsm, n, c, lane, key_token, no_entry, as_is, hide);
-      else if constexpr (WITH_V) whole_rows<S, false, false>(st, a, 0, qb, kb, vb, rowB, min(g, G - 1), p.scale, wsm, n, c, lane, key_token, no_entry, as_is, hide);
+      else if constexpr (WITH_V) whole_rows<S, false>(st, a, qb, kb, vb, rowB, min(g, G - 1), p.scale, wsm, n, c, lane, key_token, no_entry, as_is, hide);
       break;
     }
     a.clear();
@@ -1389,9 +1389,9 @@ __device__ __forceinline__ void window_attention(const WindowParams &p, unsigned
   auto key_token = [&](int i) { return w.key(g, key0(i) + l32); };
   auto key_entry = [&](int i) { return w.key_entry(g, key0(i) + l32); };
   auto fix_token = [&](int i, int row, int t) { return key0(i) + row < g.n_global ? key0(i) + row : t; };
-  auto hide_of = [&](int i, int nt, bool first, f32x16 &s) {
+  auto hide = [&](int i, int nt, f32x16 &s) {
     if (MASK) {
-      if (first) {
+      if (nt == 0) {
         codes[l32] = w.key_code(g, key0(i) + l32, inv_block);
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
       }
@@ -1408,7 +1408,6 @@ __device__ __forceinline__ void window_attention(const WindowParams &p, unsigned
       for (int e = 0; e < 16; e++) s[e] = jb + 8 * (e >> 2) + (e & 3) < w.nkeys ? s[e] : -INFINITY;
     }
   };
-  auto hide = [&](int i, int nt, f32x16 &s) { hide_of(i, nt, nt == 0, s); };
   for (bool careful = MASK && part != 0;; careful = true) {
     window_walk<S, NT, LISTS, MASK>(st, a, kb, vb, rowB, wsm, n, c, careful, lane, key_token, key_entry, fix_token, hide);
     if (!a.exceeds(careful ? INFINITY : kLargeSum)) break;
@@ -1416,10 +1415,7 @@ __device__ __forceinline__ void window_attention(const WindowParams &p, unsigned
       if constexpr (kBf16) {
         walk_not_finite<S, NT, LISTS, false>(st, a, kb, vb, rowB, wsm, n, c, lane, key_token, key_entry, fix_token, hide);
       } else {
-#pragma unroll
-        for (int nt = 0; nt < NT; nt++)
-          whole_rows<S, LISTS, false>(st, a, nt, qb, kb, vb, rowB, w.query(g, 32 * nt + l32), p.r.scale, wsm, n, c, lane, key_token,
-                                      key_entry, fix_token, [&](int i, int, f32x16 &s) { hide_of(i, nt, true, s); });
+        whole_rows<S, LISTS>(st, a, qb, kb, vb, rowB, w.query(g, l32), p.r.scale, wsm, n, c, lane, key_token, key_entry, fix_token, hide);
       }
       break;
     }
@@ -1492,7 +1488,9 @@ struct WindowCost {
   // masks, than this says - 245x245, 2x2 blocks: 174 us, not 98 -, but by about the same factor for each split: of eight
   // such grids in bf16 the choice is the best on seven and 3 % off on one.  fp32, 41 grids of 14 to 64 a side: 1.1 % more than the best, 11 % at
   // worst - 23x27, 8x8 blocks, four images, two waves 56.3 us, four 50.6 -; with bf16's starts 6.6 %: 28x28, 7x7 blocks, two images 42.1 -> 34.6,
-  // 36x21 47.8 -> 35.8, 44x44, 8x8 blocks 87 -> 74.)
+  // 36x21 47.8 -> 35.8, 44x44, 8x8 blocks 87 -> 74.  The other rows of the fp32 kernel take the same starts, against bf16's, of 14 to 18 grids:
+  // pruned ones 2.9 % more than the best against 3.7, bf16 rows 2.0 against 7.5, pruned bf16 rows 4.3 against 3.9; at worst 22 %, with either -
+  // 40x40, 16x16 blocks, 60 % left, two waves 61 us, four 51.)
   int split() const { return of(4) <= of(2) && of(4) <= of(1) ? 4 : (of(2) <= of(1) ? 2 : 1); }
 };
 inline WindowCost window_cost(const ns_attn_desc &d, int qt) {
