@@ -205,14 +205,18 @@ __device__ __forceinline__ void cls_scores_body(int blk, int b, const float *log
   const float *row = logits + (size_t)b * H * T_ + G + min(j, N - 1);
   auto weight = [&](int h) { return __builtin_amdgcn_exp2f((row[(size_t)h * T_] - s_lse[h]) * kLog2e); };
   float acc[kOwn] = {};
-  int h0 = 0;
-#pragma unroll(8 / kOwn)
-  for (; h0 + kRowSums <= H; h0 += kRowSums)
+  int h = g;
+  if (kOwn > 1)
+#pragma unroll 2
+    for (; h + kRowSums <= H; h += kRowSums)
 #pragma unroll
-    for (int i = 0; i < kOwn; i++) acc[i] += weight(h0 + g + GROUPS * i);
+      for (int i = 0; i < kOwn; i++) acc[i] += weight(h + i);
+#pragma unroll 8
+  for (int i = 0; h < H; h += GROUPS, i++) {
+    const float w = weight(h);
 #pragma unroll
-  for (int i = 0; i < kOwn; i++)
-    if (h0 + g + GROUPS * i < H) acc[i] += weight(h0 + g + GROUPS * i);
+    for (int j = 0; j < kOwn; j++) acc[j] += kOwn == 1 || i == j ? w : 0.f;
+  }
   static_assert(kOwn == 1 || GROUPS == 1, "sums in the order of their rows");
   if (GROUPS > 1) {
     s_part[g][lj] = acc[0];
