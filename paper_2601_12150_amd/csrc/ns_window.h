@@ -950,8 +950,8 @@ __device__ __forceinline__ void walk_keys(const S &st, WaveAcc<S, NT> &a, const 
       sum[nt] = a.weights(s[nt], nt, c);
     }
     // Parts: where a logit is NaN, which whole values may make an infinity, the step's once more.  (Asked of the sum of weights, behind
-    // V's reads: 28x28, 7x7 blocks 25.3 -> 25.4 us, 64x64, four images 269.8 -> 270.8; asked of the logits, which holds the next K back,
-    // 25.6 and 1 to 3 % more.  With one infinite key a head 27.3 and 272; whole walks for the rows that see it, 41.8 and 419.)
+    // V's reads: 28x28, 7x7 blocks 23.67 -> 23.86 us, 64x64, four images 267 -> 268; asked of the logits, which holds the next K back,
+    // 1 to 3 % more.  With one infinite key a head 27 and 269; a second walk on whole values for the rows that see it, 42 and 415.)
     auto mend = [&]() {
       if constexpr (S::kParts) {
         if (!__builtin_expect(__any(sum[0] != sum[0]), 0)) return;
