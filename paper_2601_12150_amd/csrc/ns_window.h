@@ -479,6 +479,7 @@ struct StepF32Whole {
 constexpr float kBf16Max = 0x1.fep127f;
 // Values e and e + 1 of eight as sums of up to three bf16 numbers each, the next the rounding of what those before leave: all 24
 // bits of a value between 2^-103, below which the last parts may be subnormal, and kBf16Max, which the first part must not exceed.
+// (Rows of values about 2^-112 are still as exact as others, of 2^-116 to 2e-6, of 2^-124 to 6e-4; with fp32 products 3e-7 throughout.)
 template <int P>
 __device__ __forceinline__ void split_pair(const float (&x)[8], bf16x8 (&p)[P], int e) {
   float a = x[e], b = x[e + 1];
